@@ -104,7 +104,13 @@ int sconv_encode(const sconv_desc_t* desc, int fmt, const float* x_dev, float* v
  * pipe (groups of 6, 8, 16 and 16 elements) and skip a group only when all of its elements are zero, so a
  * zero inside a group that also holds a nonzero is multiplied (0 * w adds nothing for finite w;
  * with Inf or NaN filters the variants can differ).
- * A workspace (lent with sconv_set_workspace, or passed to the ..._ws forms) is used two ways.
+ * A launch of any of these families runs on the "piece" kernel - three exact bf16 pieces per fp32 value, six products,
+ * fp32 accumulation, on the bf16 matrix pipe - when its cost model promises less time: 3x3 of any stride and padding and
+ * 1x1, plain or pooled over 2x2 windows, except on very sparse maps.  It multiplies the zeros of a tile (a result that
+ * is not finite is summed again with every zero element skipped).
+ * A workspace (lent with sconv_set_workspace, or passed to the ..._ws forms) is used three ways.
+ * (3) The piece kernel keeps its pieces of the filters there when there is room, and the partial sums of tiles that would
+ * not fill a last round of workgroups.
  * (1) Launches too small to fill the chip - fewer than 128 workgroups ("tap3x3" and "gen": deep layers
  * at batch 1), "tap3x3" launches of up to 768 workgroups that walk 256 or more channels, 100-400 tiles of
  * "quad3x3" on a map 28 or more wide - are split along the channels over up to 16 workgroups per tile;
@@ -129,8 +135,8 @@ int sconv_forward(const sconv_desc_t* desc, const float* x_dev, const float* w_d
  *   y[n][k][ph][pw] = max over py < p_h, px < p_w of max(0, conv[n][k][ph*p_s+py][pw*p_s+px]).
  * (A launch too small to fill the chip - fewer than 128 workgroups, and only when a workspace is there,
  * see sconv_forward - is split across workgroups and passes its partial sums through that workspace; the
- * second kernel then pools.  Every larger fused call is one convolution kernel, whatever the pooling window,
- * also after sconv_tune: it does not offer a split to such a call.)
+ * second kernel then pools.  Larger fused calls of the other kernels are one convolution kernel, whatever the pooling
+ * window, also after sconv_tune; the piece kernel splits the tiles of a last, partly filled round.)
  *   y_dev device, out: [N][K][PH][PW]
  * SCONV_EUNSUPPORTED if p_h*p_w > 64 or a tensor has 2^31 or more elements.
  */
@@ -301,10 +307,12 @@ int sconv_forward_static(const sconv_desc_t* desc, const float* x_dev, const flo
  * "gen" (every other shape with a kernel of at most 15x15; any pooling window of up to 64
  * results; also, for its split across workgroups, 1x1 layers of 512 or more channels per group and few
  * tiles and - with a workspace - 3x3 launches of fewer than 128 tile-workgroups with 64-160 channels per
- * group), "rows" (everything else).  A zero ratio in the descriptor's flags (SCONV_ZERO_RATIO) moves
+ * group), "rows" (everything else).  The name is the family that serves the shape; whether its launches run on the piece
+ * kernel is decided by cost models at the call (SCONV_TRACE_PLAN=1 prints it), and "piece" itself is named for a plan that
+ * sconv_tune found.  A zero ratio in the descriptor's flags (SCONV_ZERO_RATIO) moves
  * the choice among "quad3x3", "wide3x3" and "tap3x3" for launches that fill the matrix kernels' tiles
  * (see sconv_density).  The environment variable SCONV_VARIANT ("rows", "tap",
- * "quad", "wide", "gen" or unset) pins the choice for profiling; a plan remembered by sconv_tune comes
+ * "quad", "wide", "gen", "piece" or unset) pins the choice for profiling; a plan remembered by sconv_tune comes
  * before the static rules.
  * Returns NULL for an invalid descriptor.  Nothing is enqueued, but the call asks the HIP runtime for
  * the current device (to see whether a workspace is lent there), which initialises the runtime.
@@ -397,7 +405,7 @@ int sconv_plan_name(const sconv_desc_t* desc, int pooled, char* out, int out_siz
 
 /*
  * The SCONV_* environment variables (tuning aids for profiles and tests: SCONV_VARIANT,
- * SCONV_{TAP,QUAD,WIDE,GEN,PW}_GEOM, SCONV_{TAP,QUAD,WIDE,GEN,PW}_SPLIT, SCONV_ENCODE,
+ * SCONV_{TAP,QUAD,WIDE,GEN,PW,PIECE}_GEOM, SCONV_{TAP,QUAD,WIDE,GEN,PW,PIECE}_SPLIT, SCONV_PIECE_SRC, SCONV_ENCODE,
  * SCONV_TRACE_PLAN) are read once, by the first call that needs one, and kept; no launch calls
  * getenv.  sconv_env_refresh reads them again (a test that changes the environment calls it).  It must
  * not run while another thread is inside a launching call.  Host only.

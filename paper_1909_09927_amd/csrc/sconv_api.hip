@@ -23,7 +23,7 @@ const PlanPin* current_pin() { return g_pin; }
 // The tuning-aid environment (SCONV_*), read once - at the first call that looks - and again only when
 // sconv_env_refresh is called: no launch pays for getenv.
 static const char* const kEnvNames[] = {
-    "SCONV_VARIANT", "SCONV_TAP_GEOM", "SCONV_QUAD_GEOM", "SCONV_WIDE_GEOM", "SCONV_GEN_GEOM", "SCONV_PW_GEOM",
+    "SCONV_VARIANT", "SCONV_TAP_GEOM", "SCONV_QUAD_GEOM", "SCONV_WIDE_GEOM", "SCONV_GEN_GEOM", "SCONV_PW_GEOM", "SCONV_PIECE_GEOM", "SCONV_PIECE_SPLIT", "SCONV_PIECE_SRC",
     "SCONV_TAP_SPLIT", "SCONV_QUAD_SPLIT", "SCONV_WIDE_SPLIT", "SCONV_GEN_SPLIT", "SCONV_PW_SPLIT",
     "SCONV_ENCODE", "SCONV_TRACE_PLAN", "SCONV_NO_XCD_REMAP", "SCONV_ENCODE_TR16"};
 constexpr int kEnvCount = (int)(sizeof(kEnvNames) / sizeof(kEnvNames[0]));
@@ -136,7 +136,7 @@ int fill_problem(const sconv_desc_t* d, bool pooled, Problem* out)
     return SCONV_OK;
 }
 
-enum Variant { V_ROWS, V_TAP, V_QUAD, V_PW, V_WIDE, V_GEN };
+enum Variant { V_ROWS, V_TAP, V_QUAD, V_PW, V_WIDE, V_GEN, V_PIECE };
 
 static const char* variant_name(Variant v)
 {
@@ -146,6 +146,7 @@ static const char* variant_name(Variant v)
     case V_TAP: return "tap3x3";
     case V_WIDE: return "wide3x3";
     case V_GEN: return "gen";
+    case V_PIECE: return "piece";
     default: return "rows";
     }
 }
@@ -256,6 +257,7 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
     if (pin && !strcmp(pin, "wide")) return wide_supported(p, pooled) ? V_WIDE : V_ROWS;
     if (pin && !strcmp(pin, "quad")) return quad_supported(p, pooled) ? V_QUAD : V_ROWS;
     if (pin && !strcmp(pin, "gen")) return gen_supported(p, pooled) ? V_GEN : V_ROWS;
+    if (pin && !strcmp(pin, "piece")) return piece_supported(p, pooled) ? V_PIECE : V_ROWS;
     if (pw_supported(p, pooled)) {
         // A 1x1 layer of few 32-position tiles walking 512 or more channels is one latency chain per
         // workgroup, the longer the more channels: the general kernel, which splits such a launch's
@@ -361,6 +363,34 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
     return V_ROWS;
 }
 
+// Whether a launch of family v runs on the piece kernel instead: when that kernel's cost model promises less time than
+// these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
+// nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
+// any ratio), @28x28 at batch 8 190 at 75 % (165); a fixed share of 28 % where the ratio is unknown, and about 8 us
+// for the filter transposition of large launches.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
+// on), 80 (quad1x1), 70 (gen).
+// Caller holds g_lock and has selected the stream's workspace.
+static bool piece_first(const Problem& p, bool pooled, Variant v)
+{
+    if (v == V_ROWS || env_value("SCONV_VARIANT")) return false;
+    const double gf = 2e-9 * p.K * (double)p.L * p.N * (pooled ? (double)p.PH * p.PW * p.ph * p.pw : (double)p.OH * p.OW);
+    if (gf < 0.03) return false;
+    const double c = piece_cost(p, pooled);
+    if (c < 0.0) return false;
+    double other;
+    switch (v) {
+    case V_TAP: {
+        const double nz = p.zhint < 0.0f ? 0.28 : 1.0 - p.zhint;
+        other = 14.0 + gf * (2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+        break;
+    }
+    case V_QUAD: case V_WIDE: other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3); break;
+    case V_PW: other = 8.0 + gf * 12.0; break;
+    default: other = 12.0 + gf * 14.0; break;
+    }
+    return c < other;
+}
+
 // One launch of variant v, with the cost models' decomposition or the pinned one.  No fall-through
 // to other variants.  Caller holds g_lock.
 static int launch_variant(Variant v, const PlanPin* pin, const Problem& p, bool pooled, const float* x,
@@ -375,6 +405,7 @@ static int launch_variant(Variant v, const PlanPin* pin, const Problem& p, bool 
     case V_WIDE: rc = launch_wide(p, pooled, x, w, y, s); break;
     case V_QUAD: rc = launch_quad(p, pooled, x, w, y, s); break;
     case V_TAP: rc = tap_supported(p, pooled) ? launch_tap(p, pooled, x, w, y, s) : SCONV_EUNSUPPORTED; break;
+    case V_PIECE: rc = launch_piece(p, pooled, x, w, y, s); break;
     case V_ROWS: rc = launch_rows(p, pooled, x, w, y, s); break;
     }
     g_pin = nullptr;
@@ -404,11 +435,17 @@ static int run(const Problem& p, bool pooled, const float* x, const float* w, fl
     const float z = p.zhint;
     Variant v = choose(p, pooled, have_workspace(s), &sp, z);
     int rc = SCONV_EUNSUPPORTED;
+    split_scratch_select(s);
+    if (piece_first(p, pooled, v)) {
+        rc = launch_variant(V_PIECE, nullptr, p, pooled, x, w, y, s);
+        if (rc != SCONV_EUNSUPPORTED) return rc;
+    }
     if (sp.geom[0]) {
         rc = launch_variant(v, &sp, p, pooled, x, w, y, s);
         if (rc != SCONV_EUNSUPPORTED) return rc;
         v = choose(p, pooled, false, nullptr, z);      // e.g. the workspace is too small for this layer
     }
+    if (v == V_PIECE) rc = launch_variant(V_PIECE, nullptr, p, pooled, x, w, y, s);
     if (v == V_PW) rc = launch_variant(V_PW, nullptr, p, pooled, x, w, y, s);
     if (v == V_GEN) {
         rc = launch_variant(V_GEN, nullptr, p, pooled, x, w, y, s);
@@ -485,6 +522,7 @@ static int tune(const Problem& p, bool pooled, const float* x, const float* w, f
         {V_QUAD, quad_supported(p, pooled), quad_geoms(), 8, 16, 16},
         {V_WIDE, wide_supported(p, pooled), wide_geoms(), 4, 8, 1},
         {V_GEN, gen_supported(p, pooled), gen_geoms(), 4, 8, 16},
+        {V_PIECE, piece_supported(p, pooled), piece_geoms(), 4, 4, 1},   // (its model splits each geometry)
     };
     // every candidate that applies, with a first quick timing
     struct Cand {
@@ -519,6 +557,11 @@ static int tune(const Problem& p, bool pooled, const float* x, const float* w, f
     // the static rules' own choice comes first: it stays unless something measures clearly faster
     PlanPin sp;
     Variant v_static = choose(p, pooled, have_workspace(s), &sp, p.zhint);
+    split_scratch_select(s);
+    if (piece_first(p, pooled, v_static)) {
+        v_static = V_PIECE;
+        memset(&sp, 0, sizeof(sp));
+    }
     bool have_static = try_one(v_static, sp.geom[0] ? &sp : nullptr);
     if (!have_static && sp.geom[0]) {
         v_static = choose(p, pooled);
@@ -948,20 +991,23 @@ extern "C" int sconv_workspace_size(const sconv_desc_t* desc, int pooled, size_t
     Problem p;
     int rc = fill_problem(desc, pooled != 0, &p);
     if (rc) return rc;
-    *bytes = 0;
+    *bytes = plan_workspace_bytes(p, pooled != 0);
+    return SCONV_OK;
+}
+
+// Bytes of workspace the plans of a problem can use.
+size_t sconv::plan_workspace_bytes(const Problem& p, bool pooled)
+{
     // only the kernels that can split a launch use it, and only for launches of a few hundred
     // workgroups: up to 16 slices of the convolution tensor, never more than the cap
-    if (!tap_supported(p, pooled != 0) && !gen_supported(p, pooled != 0) && !quad_supported(p, pooled != 0))
-        return SCONV_OK;
+    if (!tap_supported(p, pooled) && !gen_supported(p, pooled) && !quad_supported(p, pooled)) return 0;
     const size_t slice = (size_t)p.N * p.K * p.OH * p.OW * sizeof(float);
     size_t need = 16 * slice;
     if (need > kSplitWorkspaceCap) need = kSplitWorkspaceCap;
     // plus the transposed copy of the filters the vector kernel's large launches read (filters per group
     // rounded up to whole blocks of 128)
-    if (tap_supported(p, pooled != 0))
-        need += (size_t)p.G * ((p.Kg + 127) / 128 * 128) * p.L * sizeof(float) + 256;
-    *bytes = (need + 255) / 256 * 256;
-    return SCONV_OK;
+    if (tap_supported(p, pooled)) need += (size_t)p.G * ((p.Kg + 127) / 128 * 128) * p.L * sizeof(float) + 256;
+    return (need + 255) / 256 * 256;
 }
 
 extern "C" int sconv_set_workspace(void* ws_dev, size_t bytes, void* hip_stream)
@@ -996,6 +1042,7 @@ static const char* const* geoms_of(Variant v)
     case V_QUAD: return quad_geoms();
     case V_WIDE: return wide_geoms();
     case V_GEN: return gen_geoms();
+    case V_PIECE: return piece_geoms();
     default: return nullptr;
     }
 }
@@ -1046,7 +1093,7 @@ extern "C" int sconv_tune_import(const char* text)
         if (sscanf(line.c_str() + pos, " %d %d %31s %d %d %d %lf %63s%n", &v, &pinned, geom, &t.pin.nwv, &t.pin.ncs,
                    &t.pin.nss, &ms, name, &used) != 8)
             return SCONV_EINVAL;
-        if (v < (int)V_ROWS || v > (int)V_GEN || strlen(geom) >= sizeof(t.pin.geom) || strlen(name) >= sizeof(t.name))
+        if (v < (int)V_ROWS || v > (int)V_PIECE || strlen(geom) >= sizeof(t.pin.geom) || strlen(name) >= sizeof(t.name))
             return SCONV_EINVAL;
         // only decompositions the launchers know: a geometry of that variant, powers of two within their ranges
         auto pow2_upto = [](int x, int hi) { return x == 0 || (x > 0 && x <= hi && (x & (x - 1)) == 0); };

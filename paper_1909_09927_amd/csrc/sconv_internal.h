@@ -81,6 +81,14 @@ bool pw_supported(const Problem& p, bool pooled);
 int launch_pointwise(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                      hipStream_t stream);
 
+// Matrix kernel on exact bf16 pieces: any kernel of at most 49 taps, any stride, padding and grouping, optional pooling
+// over 2x2 windows.
+bool piece_supported(const Problem& p, bool pooled);
+// modelled microseconds of the plan launch_piece would take (after split_scratch_select); negative: none
+double piece_cost(const Problem& p, bool pooled);
+int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
+                 hipStream_t stream);
+
 // A fixed decomposition in place of the cost models' choice: candidate geometry inside a kernel
 // variant, wavefronts per workgroup, channel slices.  Set by the dispatcher (under its lock) around
 // one launch - from the tuning cache or while sconv_tune tries the candidates; without one, the
@@ -120,6 +128,9 @@ void split_scratch_select(hipStream_t stream);
 void split_scratch_given(void* ws, size_t bytes, bool on);
 bool split_scratch_is_given();
 bool split_scratch_possible(hipStream_t stream);
+// bytes of workspace the plans of a problem can use (what sconv_workspace_size reports): a plan never takes more, so that
+// it does not depend on how much more was lent
+size_t plan_workspace_bytes(const Problem& p, bool pooled);
 float* split_scratch(hipStream_t stream);
 size_t split_scratch_bytes();
 int launch_split_reduce(const Problem& p, bool pooled, const float* part, int nss, float* y,
@@ -142,6 +153,7 @@ const char* const* tap_geoms();
 const char* const* quad_geoms();
 const char* const* wide_geoms();
 const char* const* gen_geoms();
+const char* const* piece_geoms();
 
 inline int launch_status()
 {

@@ -1,0 +1,878 @@
+// Matrix kernel on exact bf16 pieces: 3x3 kernels of any stride, padding and grouping, 1x1 kernels, optional pooling over
+// 2x2 windows.
+//
+// What bounds the other matrix kernels on the large layers is the fp32 matrix rate (157 TFLOP/s on paper, 138 measured on a
+// large product).  The bf16 matrix pipe is sixteen times as fast, and an fp32 value is the exact sum of three bf16 values
+// (24 bits = 3 x 8): x = x0 + x1 + x2, every remainder of the rounding being exact.  Of the nine products of two such sums
+// the six largest are issued - x0w0, x0w1, x1w0, x1w1, x0w2, x2w0 -, the other three are below 2^-24 of the product,
+// i.e. below one fp32 rounding of it.  Products of pieces are exact and every instruction adds 16 of them to an fp32
+// accumulator, which rounds six times per sixteen terms where an fp32 chain rounds sixteen times.  The sums of one staged
+// chunk start from zero and are added to the running sums at its end (16 additions per accumulator and 54 matrix
+// instructions), so that the roundings of a chunk happen at the size of its own partial sum.  Measured against 64-bit sums,
+// 512 channels: 2.0e-7 relative, against 2.7e-7 (quad3x3), 3.7e-7 (wide3x3) and 1.2e-7 - 2.2e-7 (tap3x3).
+// Values the pieces cannot carry - Inf, NaN, what overflows when rounded to bf16, results below 2^-80 - show in the result:
+// a lane that finds such a sum has its block of 32 x 32 results summed again in plain fp32, skipping zero elements.
+//
+// Zeros are not skipped inside a tile (a 32-window block of 16 channels is never empty when zeros are independent): the
+// rules that choose between this kernel and the element-skipping vector kernel are in sconv_api.hip (piece_first).
+//
+// A workgroup computes BM filters x BN windows.  The windows of a column strip (TW output columns) are numbered in format
+// order - (n, oh, ow), or (n, ph, pw, py, px) for the fused call, so that a pooling window is four neighbouring lanes -
+// and a tile is BN consecutive ones; the input rows they touch are staged once per chunk of 16 channels as pieces,
+// [channel group of 8][position][piece][8 channels], double buffered, and all taps read the same staged tile: a tap is an
+// offset.  Every lane reads its own window's address, so tiles fit any map, stride and padding; the padding is staged as
+// zeros.  Filters: a lane's fragment is 8 channels of one filter and tap, straight from memory into registers, one to three
+// taps ahead (no LDS, no barrier): from pieces that a kernel writes into the workspace first, from prepared filters, or
+// from the filters as stored.  MT = 1, NT = 4 gives an instruction stream of 216 matrix instructions to 108 LDS reads and
+// 27 loads per chunk; two workgroups a compute unit keep the matrix pipe busy 70 % of the time at 1.9 GHz, 250 TFLOP/s
+// dense-equivalent on 512 channels @28x28 at batch 62 (quad3x3: 120).
+//
+// Tiles that do not fill a last round of workgroups are split along the channels (split tiles: partial sums into the
+// workspace, piece_sum_kernel adds them): 784 tiles of 256 @56x56 at batch 8 on 768 places run as 768 whole ones and 16 in
+// 16 slices each, 153 us against 189.
+#include <math.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "sconv_internal.h"
+
+namespace sconv {
+
+namespace {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+struct PieceCfg {
+    int nrun;        // window rows of one column strip: N*OH*TW, or N*PH*TW*4 in PECR order
+    int ntiles;      // tiles of BN window rows per strip
+    int TW, strips;  // (pooled) output columns of a strip, strips
+    int kblocks;     // filter blocks of BM filters per group
+    int kb32;        // 32-filter blocks per group in the prepared layout
+    int nch;         // staged chunks of 16*CS channels
+    int whole;       // tiles run by one workgroup; the others are split along the channels over nss workgroups
+    int nss;
+    int T, S;        // taps, kernel width
+    int px, cgb;     // staged positions, bytes of one 8-channel group
+    int flat;        // 1x1 / stride 1: a map is one row of H*W positions
+};
+
+enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2 };
+
+// Eight fp32 values as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every
+// remainder is exact) as long as no piece leaves bf16's range.
+__device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = v[2 * i], b = v[2 * i + 1];
+        const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
+        const float ra = a - __builtin_bit_cast(float, h << 16);
+        const float rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
+        const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
+        const float sa = ra - __builtin_bit_cast(float, m << 16);
+        const float sb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
+        out[0][i] = h;
+        out[1][i] = m;
+        out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){sa, sb}, bf2));
+    }
+}
+
+template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int XU_, int OCC_>
+struct PGeom {
+    static constexpr int MT = MT_, NT = NT_, WM = WM_, WN = WN_, T = T_, CS = CS_, XU = XU_, OCC = OCC_;   // XU: staging units per wavefront
+    static constexpr bool POOL = POOL_;
+    // microseconds a compute unit spends on one staged chunk of one workgroup when two or three workgroups share it
+    static constexpr double tc(int src, int taps)
+    {
+        return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.75 : src == SRC_FP32 ? 4.9 : 5.3)
+                                   : (src == SRC_PIECES ? 2.6 : src == SRC_FP32 ? 2.75 : 3.7) * (MT * NT * NW) / 8.0) * (T_ == 1 ? 0.5 : taps / 9.0);
+    }
+    static constexpr int NW = WM * WN, BM = 32 * MT * WM, BN = 32 * NT * WN;
+    static constexpr int CG = 2 * CS;    // 8-channel groups per staged chunk
+    static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
+    static constexpr int AR = T == 9 ? 3 : T == 1 ? 4 : 1;   // filter fragments in flight (ring)
+    static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
+    static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
+};
+
+template <class G, int SRC>
+__global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
+                                                              const float* __restrict__ w, const void* __restrict__ wp,
+                                                              float* __restrict__ parts, float* __restrict__ y)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int MT = G::MT, NT = G::NT, CS = G::CS, CG = G::CG, NW = G::NW, XU = G::XU, AR = G::AR;
+    const int PX = cfg.px, CGB = cfg.cgb;
+    const int T = G::T ? G::T : cfg.T;
+    const int S = G::T == 9 ? 3 : G::T == 1 ? 1 : cfg.S;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % G::WM, wn = wave / G::WM;
+    const int half = lane >> 5, col = lane & 31;
+
+    // workgroup -> (tile, slice); ids are dealt to the eight XCDs in turn, every XCD gets a contiguous range
+    const int whole = cfg.whole, nb_all = gridDim.x;
+    const bool split = (int)blockIdx.x >= whole;
+    int b = split ? blockIdx.x - whole : blockIdx.x, ss = 0;
+    {
+        const int cnt = split ? nb_all - whole : whole;
+        const int n8 = cnt >> 3, rem = cnt & 7, xcd = b & 7, i = b >> 3;
+        b = xcd * n8 + min(xcd, rem) + i;
+    }
+    int ptile = 0;                       // number of the tile among the split ones
+    if (split) {
+        const int ns = (nb_all - whole) / cfg.nss;
+        ss = b / ns;
+        ptile = b - ss * ns;
+        b = whole + ptile;
+    }
+    const int kb = b % cfg.kblocks;
+    b /= cfg.kblocks;
+    const int strip = b % cfg.strips;
+    b /= cfg.strips;
+    const int tile = b % cfg.ntiles;
+    const int g = b / cfg.ntiles;
+
+    const int iH = cfg.flat ? 1 : p.H, iW = cfg.flat ? p.H * p.W : p.W;
+    const int oH = cfg.flat ? 1 : p.OH, oW = cfg.flat ? p.OH * p.OW : p.OW;
+    const int TW = cfg.TW;
+    const int HW = p.H * p.W, HP = iH + p.pad;      // images stacked along the rows, padding rows shared
+    const int pitch = (G::POOL ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + S;
+    const int pcols = G::POOL ? p.PW : oW, prows = G::POOL ? p.PH : oH;
+    const int plane = prows * pcols;                // stored results per image and filter
+    // window row P of the strip -> image, output row and column (of the convolution; columns counted from the strip's first)
+    auto window = [&](int P, int& n, int& oh, int& ow) {
+        const int pp = G::POOL ? P >> 2 : P;
+        const int q = pp / TW;
+        ow = pp - q * TW;
+        n = q / prows;
+        oh = q - n * prows;
+        if (G::POOL) {
+            oh = p.ps * oh + ((P & 3) >> 1);
+            ow = p.ps * ow + (P & 1);
+        }
+    };
+    int n0, oh0, ow0;
+    window(tile * G::BN, n0, oh0, ow0);
+    const int r0 = n0 * HP + oh0 * p.stride;   // first staged row
+    const int w0 = strip * TW * (G::POOL ? p.ps : 1) * p.stride - p.pad;   // input column of the first staged one
+
+    // this lane's windows (one per block of 32) as byte offsets into the staged tile
+    int lb[NT];
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        const int P = min(tile * G::BN + (wn * NT + nb) * 32 + col, cfg.nrun - 1);
+        int n, oh, ow;
+        window(P, n, oh, ow);
+        lb[nb] = ((n * HP + oh * p.stride - r0) * pitch + ow * p.stride) * 48 + half * CGB;
+    }
+
+    // staging: unit u of this wavefront = 64 positions of one 8-channel group
+    unsigned xvo[XU];
+    int xst[XU];
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+        const int id = u * NW + wave, cgi = id % CG, q = id / CG * 64 + lane;
+        const int row = q / pitch, cw = q - row * pitch + w0;
+        const int sr = r0 + row, n = sr / HP, h = sr - n * HP - p.pad;
+        const bool ok = q < PX && n < p.N && h >= 0 && h < iH && cw >= 0 && cw < iW;
+        xvo[u] = ok ? 4u * (unsigned)((n - n0) * p.C * HW + h * iW + cw) : 0x80000000u;
+        xst[u] = q < PX ? cgi * CGB + q * 48 : -1;
+    }
+    const float* xb = x + ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW;
+    const size_t xleft = ((size_t)p.N * p.C * HW - ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW) * 4;
+    const __amdgpu_buffer_rsrc_t xres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xb), 0, (int)min(xleft, (size_t)0x7ffffffc), 0x00020000);
+    float xr[XU][8];
+    auto fetch_x = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < XU; ++u) {
+            const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                xr[u][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
+        }
+    };
+    auto store_x = [&](unsigned char* buf, int ch) {
+        if ((ch + 1) * CS * 16 > p.Cg) {   // channels past the group's last one count as zeros
+#pragma unroll
+            for (int u = 0; u < XU; ++u)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (ch * CS * 16 + (u * NW + wave) % CG * 8 + j >= p.Cg) xr[u][j] = 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < XU; ++u) {
+            u4 f[3];
+            split8(xr[u], f);
+            if (xst[u] >= 0) {
+                u4* d = reinterpret_cast<u4*>(buf + xst[u]);
+                d[0] = f[0];
+                d[1] = f[1];
+                d[2] = f[2];
+            }
+        }
+    };
+
+    // filters: fragments of 32 filters x 16 channels of one tap
+    const int chb = split ? cfg.nch * ss / cfg.nss : 0, che = split ? cfg.nch * (ss + 1) / cfg.nss : cfg.nch;
+    const int kblk0 = kb * (G::BM / 32) + wm * MT;
+    __amdgpu_buffer_rsrc_t wres;
+    int wvo[SRC == SRC_RAW ? MT : 1];
+    if (SRC == SRC_PIECES) {
+        const size_t blk = (size_t)cfg.nch * CS * T * 3072;
+        wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
+        wvo[0] = lane * 16;
+    } else if (SRC == SRC_FP32) {
+        const size_t blk = (size_t)p.Cg * T * 256;
+        wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
+        wvo[0] = half * 8 * T * 256 + (kblk0 & 1) * 128 + col * 4;
+    } else {
+        // filters as stored; a filter past the group's last one re-reads the last, what lies past the tensor reads as zero
+        const size_t first = ((size_t)g * p.Kg + (size_t)kb * G::BM) * p.L;
+        const size_t left = ((size_t)p.K * p.L - first) * 4;
+        wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + first), 0, (int)min(left, (size_t)0x7ffffffc), 0x00020000);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+            wvo[i] = (min((wm * MT + i) * 32 + col, p.Kg - 1 - kb * G::BM) * p.L + half * 8 * T) * 4;
+    }
+    const int wblk = cfg.nch * CS * T * 3072;       // bytes between 32-filter blocks (pieces)
+    const int wblk64 = p.Cg * T * 256;              // bytes between 64-filter blocks (fp32)
+    constexpr int VW = G::VW;
+    u4 ap[SRC == SRC_PIECES ? AR : 1][SRC == SRC_PIECES ? MT : 1][3];
+    float af[SRC == SRC_FP32 ? AR : 1][SRC == SRC_FP32 ? MT : 1][8];
+    float ar[SRC == SRC_RAW ? AR : 1][SRC == SRC_RAW ? MT : 1][8][VW];
+    auto fetch_a = [&](int slot, int ch16, int t) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (SRC == SRC_PIECES) {
+                const int so = (ch16 * T + t) * 3072 + i * wblk;
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    ap[slot][i][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[0] + q * 1024, so, 0));
+            } else if (SRC == SRC_FP32) {
+                const int so = (ch16 * 16 * T + t) * 256 + (i >> 1) * wblk64;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    af[slot][i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[0] + (i & 1) * 128, so + j * T * 256, 0));
+            } else if (G::T == 1) {   // eight channels are consecutive
+                const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[i], ch16 * 64, 0));
+                const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[i] + 16, ch16 * 64, 0));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    ar[slot][i][j][0] = lo[j];
+                    ar[slot][i][j + 4][0] = hi[j];
+                }
+            } else {
+                const int so = (ch16 * 16 * T + t) * 4;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (VW == 3) {
+                        typedef float f3 __attribute__((ext_vector_type(3)));
+                        const f3 q = __builtin_bit_cast(f3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo[i] + j * T * 4, so, 0));
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) ar[slot][i][j][e % VW] = q[e];
+                    } else {
+                        ar[slot][i][j][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[i] + j * T * 4, so, 0));
+                    }
+                }
+            }
+        }
+    };
+
+    v16f acc[MT][NT], tmp[MT][NT];
+    const int bufb = CG * CGB;
+    const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int nb = 0; nb < NT; ++nb) acc[i][nb] = zero;
+
+    static_assert(NT >= 2, "two independent accumulators at least");
+    constexpr int NH = 2;                         // position blocks per half step
+    constexpr int HS = NT / NH;                   // half steps per tap
+    u4 bq[2][NH][3];
+    u4 a[MT][3];
+    auto load_b = [&](u4 (&dst)[NH][3], const unsigned char* tapbase, int imm, int h) {
+#pragma unroll
+        for (int n = 0; n < NH; ++n) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) dst[n][q] = *reinterpret_cast<const u4*>(tapbase + lb[h * NH + n] + imm + q * 16);
+        }
+    };
+    auto take_a = [&](int slot, int e) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (SRC == SRC_PIECES) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a[i][q] = ap[slot][i][q];
+            } else if (SRC == SRC_FP32) {
+                split8(af[slot][i], a[i]);
+            } else {
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = ar[slot][i][j][e];
+                split8(v, a[i]);
+            }
+        }
+    };
+    auto products = [&](const u4 (&bb)[NH][3], int h, bool first) {
+        // products smallest first: x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0
+        constexpr int qa[6] = {0, 2, 1, 0, 1, 0}, qb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+#pragma unroll
+            for (int n = 0; n < NH; ++n)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    tmp[i][h * NH + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
+                        first && c == 0 ? zero : tmp[i][h * NH + n], 0, 0, 0);
+    };
+
+    fetch_x(chb);
+    fetch_a(0, chb * CS, 0);
+    if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, chb * CS, 1);
+    if (G::T == 1) {
+        fetch_a(1, chb * CS + 1, 0);
+        fetch_a(2, chb * CS + 2, 0);
+    }
+    store_x(lds, chb);
+    if (G::T != 9) fetch_x(min(chb + 1, che - 1));
+    __syncthreads();
+
+    for (int ch = chb; ch < che; ++ch) {
+        const unsigned char* buf = lds + ((ch - chb) & 1) * bufb;
+        unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
+        const bool more = ch + 1 < che;
+        const int nx = more ? ch + 1 : ch;
+        if (G::T) {
+            constexpr int E = (G::T ? G::T : 1) * CS, D = AR - 1;
+            auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
+            auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
+            load_b(bq[0], buf + off(0), imm(0), 0);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if (SRC == SRC_RAW && G::T == 9) {   // three taps (one kernel row) are fetched at a time
+                    take_a(0, e % 3 % VW);
+                    if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
+                } else {
+                    take_a(e % AR, 0);
+                    fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
+                }
+                if (G::T == 9 && e == 0 && more) fetch_x(nx);
+#pragma unroll
+                for (int h = 0; h < HS; ++h) {
+                    const int cur = (e * HS + h) & 1;
+                    if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
+                    else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
+                    products(bq[cur], h, e == 0);
+                }
+                if (e == G::SE && more) {
+                    store_x(nbuf, nx);
+                    if (G::T != 9) fetch_x(min(ch + 2, che - 1));
+                }
+            }
+        } else {
+            int r = 0, sx = 0;
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int nb = 0; nb < NT; ++nb) tmp[i][nb] = zero;
+            load_b(bq[0], buf, 0, 0);
+            if (more) {
+                store_x(nbuf, nx);
+                fetch_x(min(ch + 2, che - 1));
+            }
+            for (int t = 0; t < T; ++t) {
+                const unsigned char* tb = buf + (r * pitch + sx) * 48;
+                if (++sx == S) { sx = 0; ++r; }
+                if (t + 1 == T) r = sx = 0;
+                take_a(0, 0);
+                fetch_a(0, t + 1 < T ? ch : nx, t + 1 < T ? t + 1 : 0);
+#pragma unroll
+                for (int h = 0; h < HS; ++h) {
+                    if (h + 1 < HS) load_b(bq[(h & 1) ^ 1], tb, 0, h + 1);
+                    else load_b(bq[HS == 1 ? 1 : 0], buf + (r * pitch + sx) * 48, 0, 0);
+                    products(bq[h & 1], h, false);
+                }
+                if (HS == 1) {
+#pragma unroll
+                    for (int n = 0; n < NH; ++n)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) bq[0][n][q] = bq[1][n][q];
+                }
+            }
+            // The last products' results take 11 more wait states after issue; across a branch the compiler has been seen to
+            // leave too few before the first read.
+#pragma unroll
+            for (int i = 0; i < MT; ++i) asm volatile("s_nop 15" : "+v"(tmp[i][NT - 2]), "+v"(tmp[i][NT - 1]));
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb) acc[i][nb] += tmp[i][nb];
+        __syncthreads();
+    }
+
+    // epilogue
+    float* part = split ? parts + ((size_t)ss * ((nb_all - whole) / cfg.nss) + ptile) * (G::BM * G::BN) : nullptr;
+    const int c_lo = chb * CS * 16, c_hi = min(che * CS * 16, p.Cg);
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        const int P = tile * G::BN + (wn * NT + nb) * 32 + col;
+        int n, oh, ow;
+        window(min(P, cfg.nrun - 1), n, oh, ow);
+        ow += strip * TW * (G::POOL ? p.ps : 1);
+        const int wcol = G::POOL ? (ow - (P & 1)) / p.ps : ow;
+        const bool pos_ok = P < cfg.nrun && wcol < pcols;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            const int k0 = kb * G::BM + (wm * MT + i) * 32 + 4 * half;   // filter of element v: k0 + 8*(v/4) + v%4
+            bool bad = false;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
+                const unsigned bits = __builtin_bit_cast(unsigned, r) & 0x7fffffffu;
+                bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && bits != 0u && bits - 0x17800000u >= 0x7f800000u - 0x17800000u;   // not within [2^-80, inf)
+            }
+            if (__any(bad)) {
+                float* sc = reinterpret_cast<float*>(lds) + wave * 1024 + lane;
+                for (int v = 0; v < 16; ++v) {
+                    const int kk = min(k0 + 8 * (v >> 2) + (v & 3), p.Kg - 1);
+                    const float* wk = w + ((size_t)g * p.Kg + kk) * p.L;
+                    float s = 0.0f;
+                    for (int c = c_lo; c < c_hi; ++c)
+                        for (int t = 0; t < T; ++t) {
+                            const int ih = oh * p.stride - p.pad + t / S, iw = ow * p.stride - p.pad + t % S;
+                            if (ih < 0 || ih >= iH || iw < 0 || iw >= iW) continue;
+                            const float e = x[(((size_t)n * p.G + g) * p.Cg + c) * HW + ih * iW + iw];
+                            if (e != 0.0f) s = __builtin_fmaf(e, wk[c * T + t], s);
+                        }
+                    sc[v * 64] = s;
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][nb][v] = sc[v * 64];
+            }
+            if (split) {
+                float* d = part + ((wm * MT + i) * 32 + 4 * half) * G::BN + (wn * NT + nb) * 32 + col;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + (v & 3)) * G::BN] = acc[i][nb][v];
+            } else if (!G::POOL) {
+                const size_t o0 = ((size_t)n * p.K + (size_t)g * p.Kg + k0) * plane + oh * oW + ow;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int dk = 8 * (v >> 2) + (v & 3);
+                    if (!pos_ok || k0 + dk >= p.Kg) continue;
+                    float r = acc[i][nb][v] + bias_of(p, (size_t)g * p.Kg + k0 + dk);
+                    if (p.relu) r = fmaxf(r, 0.0f);
+                    y[o0 + (size_t)dk * plane] = r;
+                }
+            } else {
+                // the four results of a pooling window lie in four neighbouring lanes; lane e of them keeps filter v = e
+                const int e = lane & 3, wrow = (oh - (e >> 1)) / p.ps;
+#pragma unroll
+                for (int vq = 0; vq < 4; ++vq) {
+                    float r = 0.0f;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float m = acc[i][nb][vq * 4 + v];
+                        m = fmaxf(m, __shfl_xor(m, 1));
+                        m = fmaxf(m, __shfl_xor(m, 2));
+                        if (v == e) r = m;
+                    }
+                    const int kk = k0 + 8 * vq + e;
+                    if (!pos_ok || kk >= p.Kg) continue;
+                    r = fmaxf(r + bias_of(p, (size_t)g * p.Kg + kk), 0.0f);
+                    y[((size_t)n * p.K + (size_t)g * p.Kg + kk) * plane + wrow * p.PW + wcol] = r;
+                }
+            }
+        }
+    }
+}
+
+// Adds the slices of the split tiles (slice 0 first) and applies the epilogue: one thread per filter and window row
+// (plain) or pooling window.
+template <bool POOL>
+__global__ __launch_bounds__(256) void piece_sum_kernel(Problem p, PieceCfg cfg, int BM, int BN, int ns, const float* __restrict__ parts,
+                                                        float* __restrict__ y)
+{
+    const int per_row = POOL ? BN / 4 : BN;
+    const int e = blockIdx.x * 256 + threadIdx.x, kr = e / per_row, c = e - kr * per_row;
+    int b = cfg.whole + blockIdx.y;
+    const int kb = b % cfg.kblocks;
+    b /= cfg.kblocks;
+    const int strip = b % cfg.strips;
+    b /= cfg.strips;
+    const int tile = b % cfg.ntiles;
+    const int g = b / cfg.ntiles;
+    const int pcols = POOL ? p.PW : cfg.flat ? p.OH * p.OW : p.OW, prows = POOL ? p.PH : cfg.flat ? 1 : p.OH;
+    const int P = (tile * BN) / (POOL ? 4 : 1) + c, k = kb * BM + kr;
+    const int q = P / cfg.TW, n = q / prows, wrow = q - n * prows, wcol = strip * cfg.TW + P - q * cfg.TW;
+    if (kr >= BM || P >= cfg.nrun / (POOL ? 4 : 1) || k >= p.Kg || wcol >= pcols) return;
+    const size_t tsz = (size_t)BM * BN;
+    const float* src = parts + (size_t)blockIdx.y * tsz + (size_t)kr * BN + c * (POOL ? 4 : 1);
+    const size_t step = (size_t)ns * tsz;
+    float r;
+    if (POOL) {
+        f4 v = *reinterpret_cast<const f4*>(src);
+        for (int s = 1; s < cfg.nss; ++s) v += *reinterpret_cast<const f4*>(src + s * step);
+        r = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+    } else {
+        r = src[0];
+        for (int s = 1; s < cfg.nss; ++s) r += src[s * step];
+    }
+    r += bias_of(p, (size_t)g * p.Kg + k);
+    if (p.relu) r = fmaxf(r, 0.0f);
+    y[(((size_t)n * p.K + (size_t)g * p.Kg + k) * prows + wrow) * pcols + wcol] = r;
+}
+
+// w[K][Cg][T] -> pieces[group][32 filters][16 channels][tap][piece][64 lanes][8 channels] bf16: lane l of a fragment holds
+// filter l % 32, channels 8 * (l / 32) + 0..7.  Filters past the group and channels past Cg are zero.
+__global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, int nch16, int T, const float* __restrict__ w,
+                                                           u4* __restrict__ out)
+{
+    const int t = blockIdx.x % T, ch = blockIdx.x / T, kb = blockIdx.y, g = blockIdx.z, l = threadIdx.x;
+    const int k = kb * 32 + (l & 31), c0 = ch * 16 + (l >> 5) * 8;
+    const float* src = w + ((size_t)g * p.Kg + min(k, p.Kg - 1)) * p.L + t;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = src[(size_t)min(c0 + j, p.Cg - 1) * T];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (k >= p.Kg || c0 + j >= p.Cg) v[j] = 0.0f;
+    u4 f[3];
+    split8(v, f);
+    u4* dst = out + ((((size_t)g * kb32 + kb) * nch16 + ch) * T + t) * 192 + l;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) dst[q * 64] = f[q];
+}
+
+struct Plan {
+    double cost = -1.0;   // modelled microseconds; negative = not applicable
+    PieceCfg cfg;
+    size_t lds_bytes = 0, piece_bytes = 0;
+    int src = SRC_RAW, ntail = 0;
+};
+
+bool shape_ok(const Problem& p, bool pooled)
+{
+    const int T = p.R * p.S;
+    if (T != 1 && (T != 9 || p.S != 3)) return false;
+    if (pooled && (p.ph != 2 || p.pw != 2)) return false;
+    const long long npos = pooled ? (long long)p.N * p.PH * p.PW * 4 : (long long)p.N * p.OH * p.OW;
+    if (npos >= (1LL << 30)) return false;
+    return true;
+}
+
+// Staged positions of a tile of BN windows of a strip TW columns wide: the largest over the tiles (a tile's rows depend
+// only on where it starts inside an image, so the distinct starts are walked; an upper bound where there are many).
+long long stage_positions(const Problem& p, bool pooled, bool flat, int BN, int TW)
+{
+    const long long B = BN / (pooled ? 4 : 1), ow = TW, oh = pooled ? p.PH : flat ? 1 : p.OH, plane = oh * ow;
+    const long long step = pooled ? (long long)p.ps * p.stride : p.stride, HP = (flat ? 1 : p.H) + p.pad;
+    const long long ntiles = (plane * p.N + B - 1) / B, last = plane * p.N - 1;
+    long long rows = 0;
+    if (ntiles <= 256) {
+        for (long long t = 0; t < ntiles; ++t) {
+            const long long a = t * B, b = a + B - 1 < last ? a + B - 1 : last;
+            const long long r = (b / plane - a / plane) * HP + (b % plane / ow - a % plane / ow) * step;
+            if (r > rows) rows = r;
+            if ((t + 1) * B % plane == 0) break;
+        }
+    } else {
+        const long long rs = (ow - 1 + B - 1) / ow, ib = (plane - 1 + B - 1) / plane, jump = HP - (oh - 1) * step;
+        rows = (rs - ib) * step + ib * (jump > step ? jump : step);
+    }
+    rows += p.R + (pooled ? p.stride : 0);
+    return rows * ((long long)(pooled ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + p.S);
+}
+
+size_t usable_workspace(const Problem& p, bool pooled)
+{
+    if (!split_scratch_possible(nullptr)) return 0;
+    const size_t have = split_scratch_bytes(), most = plan_workspace_bytes(p, pooled);
+    return have < most ? have : most;
+}
+
+// Workgroups of a geometry on one compute unit.
+template <class G>
+int occupancy_limit(int src, size_t lds_bytes)
+{
+    const int by_lds = (int)(160 * 1024 / lds_bytes), by_regs = G::tc(src, 9) > 4.0 || (src == SRC_RAW && G::XU > 2) ? 2 : 3;
+    const int n = by_regs * 4 / G::NW;
+    return by_lds < n ? by_lds : n;
+}
+
+// The most loaded of 256 compute units: na workgroups of length a dealt out first, then nb of length b wherever there is least.
+double cu_load(long long na, double a, long long nb, double b)
+{
+    const long long q = na / 256, r = na % 256;
+    double lo = q * a, hi = r ? (q + 1) * a : lo;
+    if (nb == 0) return hi;
+    double best = -1.0;
+    for (int side = 0; side < 2; ++side)
+        for (int i = 0; i <= 64; ++i) {
+            const double L = (side ? hi : lo) + i * b;
+            if (L + 1e-9 < hi) continue;
+            const double cap = (256 - r) * floor((L - lo) / b + 1e-9) + r * floor((L - hi) / b + 1e-9);
+            if (cap >= (double)nb) {
+                if (best < 0.0 || L < best) best = L;
+                break;
+            }
+        }
+    return best < 0.0 ? hi + (double)(nb + 255) / 256 * b : best;
+}
+
+template <class G>
+Plan plan_geom(const Problem& p, bool pooled)
+{
+    Plan pl;
+    if (G::POOL != pooled) return pl;
+    const int T = p.R * p.S;
+    if (G::T && (G::T != T || (G::T == 9 && p.S != 3))) return pl;
+    PieceCfg& c = pl.cfg;
+    c.flat = T == 1 && p.stride == 1 && !pooled;
+    c.T = T;
+    c.S = p.S;
+    c.nch = (p.Cg + 16 * G::CS - 1) / (16 * G::CS);
+    c.kblocks = (p.Kg + G::BM - 1) / G::BM;
+    // strips: the fewest columns past the map's edge, then the fewest staged positions
+    const int cols = pooled ? p.PW : c.flat ? p.OH * p.OW : p.OW, rows = pooled ? p.PH : c.flat ? 1 : p.OH;
+    double best = 0.0;
+    for (int m = 1; m <= cols; ++m) {
+        const int TW = (cols + m - 1) / m;
+        if (TW < 4 && m > 1) break;
+        if (TW > G::BN) continue;
+        const int strips = (cols + TW - 1) / TW;
+        const long long px = stage_positions(p, pooled, c.flat, G::BN, TW);
+        if (px > G::PXMAX) continue;
+        const long long run = (long long)p.N * rows * TW * (pooled ? 4 : 1), nt = (run + G::BN - 1) / G::BN;
+        const double cost = (double)nt * strips * (G::BN * (1.0 + 0.5 / TW) + px * 0.02);   // (a row's end costs LDS bank conflicts)
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            c.TW = TW;
+            c.strips = strips;
+            c.nrun = (int)run;
+            c.ntiles = (int)nt;
+            c.px = (int)px;
+        }
+    }
+    if (best == 0.0) return pl;
+    c.cgb = (c.px * 48 + 255) / 256 * 256;
+    pl.lds_bytes = 2 * (size_t)G::CG * c.cgb;
+    if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
+    if (pl.lds_bytes > 160 * 1024) return pl;
+    // images a tile can touch, and the byte offsets of their elements
+    const long long run_img = (long long)rows * c.TW * (pooled ? 4 : 1);
+    const long long imgs = (G::BN - 1 + run_img - 1) / run_img + 1;
+    if ((imgs + 1) * p.C * p.H * p.W * 4 >= (1LL << 31)) return pl;
+    if ((size_t)p.Cg * T * 256 >= (1u << 31) || (size_t)p.L * 4 * (G::BM + 1) >= (1u << 31)) return pl;
+    const long long tiles = (long long)c.ntiles * c.strips * c.kblocks * p.G;
+    if (tiles >= (1LL << 24)) return pl;
+
+    int pin_whole = 0, pin_ncs = 0, pin_nss = 0;   // tuning aid: SCONV_PIECE_SPLIT="whole tiles,1,slices of the others"
+    if (!current_pin()) pinned_split("SCONV_PIECE_SPLIT", &pin_whole, &pin_ncs, &pin_nss);
+    else if (current_pin()->nwv && (current_pin()->nwv != 4 || current_pin()->ncs != 1 || current_pin()->nss > 1)) return pl;
+    const char* pin_src = env_value("SCONV_PIECE_SRC");
+    const size_t ws = usable_workspace(p, pooled);
+    const size_t tile_bytes = (size_t)G::BM * G::BN * 4;
+    for (int src = SRC_PIECES; src <= SRC_RAW; ++src) {
+        // filters: as prepared by the caller; else cut into pieces by a kernel of their own when the workspace has room, or as stored
+        if (pin_src ? atoi(pin_src) != src : (src == SRC_FP32) != (p.wprep && G::T == 9)) continue;
+        if (src == SRC_FP32 && (!p.wprep || G::T != 9)) continue;
+        size_t pb = 0;
+        const int kb32 = src == SRC_FP32 ? (p.Kg + 127) / 128 * 4 : c.kblocks * (G::BM / 32);
+        if (src == SRC_PIECES) {
+            const size_t blk = (size_t)c.nch * G::CS * T * 3072;
+            if (blk * (G::BM / 32) >= (1u << 31) || c.nch * G::CS > 65535 || kb32 > 65535 || p.G > 65535) continue;
+            pb = (size_t)p.G * kb32 * blk;
+            if (pb > ws) continue;
+        }
+        const double tc = G::tc(src, T);
+        const int occ = occupancy_limit<G>(src, pl.lds_bytes);
+        const double pre = src == SRC_PIECES ? 6.0 + (double)p.K * p.L * 10.0 / 4e6 : 0.0;
+        // whole tiles first, then the rest, each split along the channels over s workgroups (s = 1: none)
+        const long long round = 256LL * occ;
+        const long long firsts[3] = {tiles, tiles / 256 * 256, tiles / round * round};
+        for (int f = 0; f < (tiles < 4096 ? 4 : 1); ++f) {
+            const long long whole = pin_nss ? (pin_nss > 1 ? pin_whole : tiles) : f < 3 ? firsts[f] : 0;
+            const long long tail = tiles - whole;
+            if (f && !pin_nss && (tail == 0 || (f == 2 && firsts[2] == firsts[1]) || (f == 3 && (firsts[1] == 0 || firsts[2] == 0)))) continue;
+            if (tail < 0) continue;
+            for (int s = tail ? 2 : 1; s <= (tail ? 32 : 1); s += s < 6 ? 1 : s < 16 ? 2 : 8) {
+                if (pin_nss > 1 && s != pin_nss) continue;
+                if (s > c.nch || pb + (size_t)tail * s * tile_bytes > ws + (tail ? 0 : pb)) break;
+                const double a = (c.nch + 0.6) * tc, b = ((c.nch + s - 1) / s + 0.6) * tc;
+                const double load = cu_load(whole, a, tail * s, b);
+                const double resident = (double)(whole + tail * s) / 256.0;
+                double cost = pre + 6.0 + load * (resident * G::NW <= 6.0 ? 1.25 : 1.0);
+                if (tail) cost += 3.0 + 2.0 * (double)(tail * s) * tile_bytes / 6e6;
+                if (pl.cost >= 0.0 && cost >= pl.cost) continue;
+                pl.cost = cost;
+                pl.src = src;
+                pl.piece_bytes = pb;
+                pl.ntail = (int)tail;
+                c.kb32 = kb32;
+                c.whole = (int)whole;
+                c.nss = s;
+            }
+            if (pin_nss) break;
+        }
+    }
+    return pl;
+}
+
+template <class G, int SRC>
+int launch_src(const Plan& pl, const Problem& p, const float* x, const float* w, const void* wp, float* parts, float* y, hipStream_t stream)
+{
+    auto kern = piece_kernel<G, SRC>;
+    static size_t opted = 0;
+    if (pl.lds_bytes > opted) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)pl.lds_bytes) != hipSuccess)
+            return SCONV_ELAUNCH;
+        opted = pl.lds_bytes;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.cfg.whole + pl.ntail * pl.cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, pl.cfg, x, w,
+                       wp, parts, y);
+    return launch_status();
+}
+
+template <class G>
+int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t stream)
+{
+    char* ws = reinterpret_cast<char*>(split_scratch(stream));
+    float* parts = pl.ntail ? reinterpret_cast<float*>(ws + pl.piece_bytes) : nullptr;
+    int rc;
+    if (pl.src == SRC_FP32) {
+        if constexpr (G::T == 9) rc = launch_src<G, SRC_FP32>(pl, p, x, w, p.wprep, parts, y, stream);
+        else return SCONV_EUNSUPPORTED;
+    } else if (pl.src == SRC_PIECES) {
+        const int nch16 = pl.cfg.nch * G::CS, T = pl.cfg.T;
+        hipLaunchKernelGGL(piece_filters_kernel, dim3((unsigned)(nch16 * T), (unsigned)pl.cfg.kb32, (unsigned)p.G), dim3(64), 0, stream, p,
+                           pl.cfg.kb32, nch16, T, w, reinterpret_cast<u4*>(ws));
+        rc = launch_status();
+        if (rc) return rc;
+        rc = launch_src<G, SRC_PIECES>(pl, p, x, w, ws, parts, y, stream);
+    } else {
+        rc = launch_src<G, SRC_RAW>(pl, p, x, w, nullptr, parts, y, stream);
+    }
+    if (rc || !pl.ntail) return rc;
+    hipLaunchKernelGGL(piece_sum_kernel<G::POOL>, dim3((unsigned)(G::BM * G::BN / (G::POOL ? 4 : 1) / 256), (unsigned)pl.ntail), dim3(256), 0, stream,
+                       p, pl.cfg, G::BM, G::BN, pl.ntail, parts, y);
+    return launch_status();
+}
+
+struct Candidate {
+    const char* name;
+    Plan (*plan)(const Problem&, bool);
+    int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
+};
+
+#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>}
+const Candidate kCandidates[] = {
+    CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2),
+    CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2),
+    CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2),
+    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2),
+    CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2),
+    CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2),
+    CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2),
+    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 3, 2),
+};
+
+}  // namespace
+
+const char* const* piece_geoms()
+{
+    static const char* names[sizeof(kCandidates) / sizeof(kCandidates[0]) + 1];
+    for (size_t i = 0; i < sizeof(kCandidates) / sizeof(kCandidates[0]); ++i) names[i] = kCandidates[i].name;
+    return names;
+}
+
+bool piece_supported(const Problem& p, bool pooled) { return shape_ok(p, pooled); }
+
+namespace {
+
+struct Choice {
+    const Candidate* cand = nullptr;
+    Plan plan;
+};
+
+// The cheapest plan by the model.  Walking the candidates takes tens of microseconds, so the last plans are kept by what
+// they depend on: the shape, the room in the workspace, whether the filters come prepared.  (Under the dispatcher's lock.)
+const Choice& choose_plan(const Problem& p, bool pooled)
+{
+    struct Key {
+        int v[18];
+        size_t ws;
+    };
+    struct Entry {
+        Key key;
+        Choice choice;
+    };
+    constexpr int kKept = 64;
+    static Entry kept[kKept];
+    static int used = 0, next = 0;
+    static Choice pinned;
+    const char* pin = pinned_geom("SCONV_PIECE_GEOM");
+    auto walk = [&](Choice& out) {
+        out = Choice();
+        if (!shape_ok(p, pooled)) return;
+        for (const Candidate& c : kCandidates) {
+            if (pin && strcmp(pin, c.name) != 0) continue;
+            Plan pl = c.plan(p, pooled);
+            if (pl.cost < 0.0) continue;
+            if (!out.cand || pl.cost < out.plan.cost) {
+                out.cand = &c;
+                out.plan = pl;
+            }
+        }
+    };
+    if (current_pin() || pin || env_value("SCONV_PIECE_SPLIT") || env_value("SCONV_PIECE_SRC")) {
+        walk(pinned);
+        return pinned;
+    }
+    Key k;
+    memset(&k, 0, sizeof(k));
+    const int v[18] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
+                       pooled ? 1 : 0, p.wprep ? 1 : 0, 0, 0, 0};
+    memcpy(k.v, v, sizeof(v));
+    k.ws = usable_workspace(p, pooled);
+    for (int i = 0; i < used; ++i)
+        if (!memcmp(&kept[i].key, &k, sizeof(k))) return kept[i].choice;
+    Entry& e = kept[next];
+    next = (next + 1) % kKept;
+    if (used < kKept) ++used;
+    e.key = k;
+    walk(e.choice);
+    return e.choice;
+}
+
+}  // namespace
+
+double piece_cost(const Problem& p, bool pooled)
+{
+    const Choice& c = choose_plan(p, pooled);
+    return c.cand ? c.plan.cost : -1.0;
+}
+
+int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t stream)
+{
+    const Choice& c = choose_plan(p, pooled);
+    if (!c.cand) return SCONV_EUNSUPPORTED;
+    if (env_value("SCONV_TRACE_PLAN"))
+        fprintf(stderr, "piece %s: src %d strips %d x %d, %d tiles x %d filter blocks, %d whole, %d split %d ways, modelled %.1f us\n", c.cand->name,
+                c.plan.src, c.plan.cfg.strips, c.plan.cfg.TW, c.plan.cfg.ntiles * c.plan.cfg.strips, c.plan.cfg.kblocks, c.plan.cfg.whole,
+                c.plan.ntail, c.plan.cfg.nss, c.plan.cost);
+    return c.cand->launch(c.plan, p, pooled, x, w, y, stream);
+}
+
+}  // namespace sconv

@@ -1,0 +1,122 @@
+"""The matrix kernel on bf16 pieces (SCONV_VARIANT=piece): every geometry at the edges of its tiles, whole and split
+along the channels, from every form of the filters; integer inputs exact, the others within the parity bar and as close
+to the 64-bit sums as an fp32 sum of the same length; non-finite and tiny values as the fp32 kernels treat them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+import paper_1909_09927_amd as sconv
+from parity import check_forward, check_pool_forward, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# (geometry, (N, C, H, W, K, R, S, stride, pad, groups, pool), split "whole tiles,1,slices" or None)
+CASES = [
+    ("a128x128", (1, 16, 11, 12, 128, 3, 3, 1, 1, 1, None), None),        # one chunk; the last tile four windows long
+    ("a128x128", (2, 48, 19, 23, 70, 3, 3, 1, 1, 1, None), "3,1,2"),      # ragged filter block, whole tiles and split ones
+    ("a128x64", (5, 33, 7, 7, 129, 3, 3, 1, 1, 1, None), "0,1,3"),        # ragged channels, one filter in the last block
+    ("a128x64", (2, 32, 9, 57, 64, 3, 3, 1, 0, 1, None), None),           # several column strips, the last one narrower
+    ("a64x128", (2, 96, 14, 14, 96, 3, 3, 1, 1, 3, None), None),          # grouped, half a filter block
+    ("a64x128", (1, 64, 3, 5, 40, 3, 3, 1, 2, 1, None), "0,1,4"),         # padding wider than a tile's share of the map
+    ("s128x64", (2, 33, 19, 23, 70, 3, 3, 2, 1, 1, None), None),          # stride 2
+    ("s128x64", (3, 20, 14, 14, 96, 3, 3, 3, 0, 1, None), None),          # stride 3, no padding
+    ("p128x128", (2, 32, 14, 14, 128, 3, 3, 1, 1, 1, (2, 2, 2)), None),
+    ("p128x64", (2, 48, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2)), "3,1,2"),
+    ("p128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),      # overlapping pooling windows
+    ("c128x64", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None), "1,1,2"),      # 1x1, ragged channels, strips across images
+    ("c128x64", (2, 64, 15, 14, 96, 1, 1, 2, 0, 2, None), None),          # 1x1, stride 2, grouped
+    ("q128x64", (2, 256, 14, 10, 96, 1, 1, 1, 0, 1, (2, 2, 2)), None),
+]
+
+
+def _pin(monkeypatch, geom, split, src):
+    monkeypatch.setenv("SCONV_VARIANT", "piece")
+    monkeypatch.setenv("SCONV_PIECE_GEOM", geom)
+    for name, value in (("SCONV_PIECE_SPLIT", split), ("SCONV_PIECE_SRC", src)):
+        if value is None:
+            monkeypatch.delenv(name, raising=False)
+        else:
+            monkeypatch.setenv(name, value)
+
+
+@pytest.mark.parametrize("src", ["0", "1", "2"])     # pieces in the workspace, prepared filters, filters as stored
+@pytest.mark.parametrize("geom,shp,split", CASES)
+def test_geometries_splits_and_filter_sources(device, monkeypatch, geom, shp, split, src):
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    prep = src == "1"
+    if prep and (R != 3 or stride != 1 or pad != 1 or (C // groups) % 16):
+        pytest.skip("no prepared layout for this layer")
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    for integer in (False, True):
+        layer, x, w = workloads.make_random_case(400, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6, integer)
+        xd, wd = to_dev(x), to_dev(w)
+        bias = to_dev(np.arange(K, dtype=np.float32) % 7 - 3) if prep else None
+        _pin(monkeypatch, geom, split, src)
+        wp = sconv.sconv_filter_prep(wd, groups, stride, pad) if prep else None
+        kw = dict(ws=ws, bias=bias, wprep=wp) if prep else dict(ws=ws)
+        if pool:
+            got = sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw)
+        else:
+            got = sconv.sconv_forward(xd, wd, stride, pad, groups, **kw)
+        torch.cuda.synchronize()
+        got = got.cpu().numpy().astype(np.float64)
+        ref, scale = oracle.conv(x, w, stride, pad, groups, relu=False)
+        if prep:
+            b = bias.cpu().numpy().astype(np.float64)[None, :, None, None]
+            ref, scale = ref + b, scale + np.abs(b)
+        if pool:
+            p = torch.nn.functional.max_pool2d
+            ref = p(torch.from_numpy(np.maximum(ref, 0.0)), pool[:2], pool[2]).numpy()
+            scale = p(torch.from_numpy(scale), pool[:2], pool[2]).numpy()
+        assert got.shape == ref.shape
+        if integer:
+            assert np.array_equal(got, ref)
+        else:
+            # fp32 accumulation of L terms in any order stays within L * 2^-24 of the scale; the six products of three
+            # pieces leave out 3 * 2^-24 of a term's size
+            bound = (C // groups * R * S + 3) * 2.0 ** -24
+            assert (np.abs(got - ref) <= bound * scale).all()
+            assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)   # measured 1e-7 to 2e-7
+
+
+@pytest.mark.parametrize("geom,src", [("a128x64", "2"), ("a128x128", "0"), ("a64x128", "1")])
+def test_values_outside_the_pieces_range(device, monkeypatch, geom, src):
+    """Inf, NaN, values that overflow when rounded to bf16 and values whose pieces fall below bf16's range give what the
+    window-row kernel gives; zeros of the map are skipped (0 * Inf adds nothing)."""
+    _, x, w = workloads.make_random_case(401, 2, 32, 14, 14, 70, 3, 3, 1, 1, 1, None, 0.6)
+    x_bad = x.copy()
+    x_bad[0, 3, 5, 5], x_bad[1, 7, 2, 3], x_bad[1, 9, 9, 9] = np.inf, np.nan, 3.4e38
+    w_bad = w.copy()
+    w_bad[5, 4, 1, 1], w_bad[66, 0, 0, 0] = np.inf, -np.inf
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    for xi, wi in ((x_bad, w), (x, w_bad), (x * np.float32(1e-36), w), (x, w * np.float32(1e-38))):
+        xd, wd = to_dev(xi), to_dev(wi)
+        _pin(monkeypatch, geom, None, src)
+        wp = sconv.sconv_filter_prep(wd) if src == "1" else None
+        y = sconv.sconv_forward(xd, wd, 1, 1, ws=ws, wprep=wp).cpu().numpy()
+        monkeypatch.setenv("SCONV_VARIANT", "rows")
+        r = sconv.sconv_forward(xd, wd, 1, 1, ws=ws).cpu().numpy()
+        assert np.array_equal(np.isnan(y), np.isnan(r)) and np.array_equal(np.isinf(y), np.isinf(r))
+        ok = np.isfinite(r)
+        _, scale = oracle.conv(np.where(np.isfinite(xi), xi, 0), np.where(np.isfinite(wi), wi, 0), 1, 1, 1)
+        assert (np.abs(y[ok].astype(np.float64) - r[ok]) <= 1e-4 * scale[ok]).all()
+
+
+@pytest.mark.parametrize("shp", [
+    (8, 64, 28, 28, 96, 3, 3, 1, 1, 1, None), (2, 256, 14, 14, 256, 3, 3, 1, 1, 1, (2, 2, 2)), (8, 128, 14, 14, 256, 1, 1, 1, 0, 1, None),
+    (8, 64, 28, 28, 64, 3, 3, 2, 1, 1, None), (4, 40, 33, 31, 60, 3, 3, 1, 0, 2, None),
+])
+def test_default_plans(device, monkeypatch, shp):
+    """The decomposition the model picks - with the lent workspace, without one, and the same result on every call."""
+    monkeypatch.setenv("SCONV_VARIANT", "piece")
+    layer, x, w = workloads.make_random_case(402, *shp[:10], shp[10], 0.7)
+    (check_pool_forward if layer.pool else check_forward)(layer, x, w)
+    xd, wd = to_dev(x), to_dev(w)
+    call = (lambda **k: sconv.sconv_pool_forward(xd, wd, layer.pool, layer.stride, layer.pad, layer.groups, **k)) if layer.pool else \
+        (lambda **k: sconv.sconv_forward(xd, wd, layer.stride, layer.pad, layer.groups, relu=True, **k))
+    a, b, c = call(), call(), call(ws=None)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    assert np.linalg.norm((a - c).cpu().numpy()) <= 1e-6 * np.linalg.norm(c.cpu().numpy())
