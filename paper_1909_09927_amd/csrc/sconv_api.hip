@@ -363,12 +363,14 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
     return V_ROWS;
 }
 
-// Whether a launch of family v runs on the piece kernel instead: when that kernel's cost model promises less time than
+// Whether a launch of family v runs on the piece kernels instead: when their cost model promises less time than
 // these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
 // any ratio), @28x28 at batch 8 190 at 75 % (165); a fixed share of 28 % where the ratio is unknown, and about 8 us
 // for the filter transposition of large launches.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
-// on), 80 (quad1x1), 70 (gen).
+// on), 80 (quad1x1), 75 (gen).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
+// splits it: without a workspace 41 us for 256 channels on the vector kernel (23 on the taps kernel), 8 + 0.029 per column on
+// gen (48 channels of 5x5 43 us against 13, 64 of 7x7 98 against 25), 0.27 per channel on wide3x3.
 // Caller holds g_lock and has selected the stream's workspace.
 static bool piece_first(const Problem& p, bool pooled, Variant v)
 {
@@ -377,18 +379,27 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     if (gf < 0.03) return false;
     const double c = piece_cost(p, pooled);
     if (c < 0.0) return false;
-    double other;
+    const bool can_split = split_scratch_possible(nullptr) && split_scratch_bytes() > 0;
+    double other, walk = 0.0;
     switch (v) {
     case V_TAP: {
         const double nz = p.zhint < 0.0f ? 0.28 : 1.0 - p.zhint;
         other = 14.0 + gf * (2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+        if (!can_split && !p.wprep) walk = 10.0 + p.Cg * (0.06 + 0.14 * nz);
         break;
     }
-    case V_QUAD: case V_WIDE: other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3); break;
+    case V_QUAD: other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3); break;
+    case V_WIDE:
+        other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3);
+        walk = 8.0 + 0.2 * p.Cg;
+        break;
     case V_PW: other = 8.0 + gf * 12.0; break;
-    default: other = 12.0 + gf * 14.0; break;
+    default:
+        other = 12.0 + gf * 13.0;
+        if (!can_split) walk = 8.0 + 0.029 * p.L;
+        break;
     }
-    return c < other;
+    return c < (other > walk ? other : walk);
 }
 
 // One launch of variant v, with the cost models' decomposition or the pinned one.  No fall-through

@@ -1,5 +1,5 @@
-// Matrix kernel on exact bf16 pieces: 3x3 kernels of any stride, padding and grouping, 1x1 kernels, optional pooling over
-// 2x2 windows.
+// Matrix kernels on exact bf16 pieces: 1x1, 3x3, 5x5 and 7x7 kernels of any stride, padding and grouping, optional pooling
+// over 2x2 windows.
 //
 // What bounds the other matrix kernels on the large layers is the fp32 matrix rate (157 TFLOP/s on paper, 138 measured on a
 // large product).  The bf16 matrix pipe is sixteen times as fast, and an fp32 value is the exact sum of three bf16 values
@@ -96,7 +96,7 @@ struct PGeom {
     static constexpr int NW = WM * WN, BM = 32 * MT * WM, BN = 32 * NT * WN;
     static constexpr int CG = 2 * CS;    // 8-channel groups per staged chunk
     static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
-    static constexpr int AR = T == 9 ? 3 : T == 1 ? 4 : 1;   // filter fragments in flight (ring)
+    static constexpr int AR = T == 9 ? 3 : 4;   // filter fragments in flight (ring)
     static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
 };
@@ -109,8 +109,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int MT = G::MT, NT = G::NT, CS = G::CS, CG = G::CG, NW = G::NW, XU = G::XU, AR = G::AR;
     const int PX = cfg.px, CGB = cfg.cgb;
-    const int T = G::T ? G::T : cfg.T;
-    const int S = G::T == 9 ? 3 : G::T == 1 ? 1 : cfg.S;
+    constexpr int T = G::T, S = T == 9 ? 3 : 1;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % G::WM, wn = wave / G::WM;
@@ -352,67 +351,31 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
         const bool more = ch + 1 < che;
         const int nx = more ? ch + 1 : ch;
-        if (G::T) {
-            constexpr int E = (G::T ? G::T : 1) * CS, D = AR - 1;
-            auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
-            auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
-            load_b(bq[0], buf + off(0), imm(0), 0);
+        constexpr int E = G::T * CS, D = AR - 1;
+        auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
+        auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
+        load_b(bq[0], buf + off(0), imm(0), 0);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (SRC == SRC_RAW && G::T == 9) {   // three taps (one kernel row) are fetched at a time
-                    take_a(0, e % 3 % VW);
-                    if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
-                } else {
-                    take_a(e % AR, 0);
-                    fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
-                }
-                if (G::T == 9 && e == 0 && more) fetch_x(nx);
-#pragma unroll
-                for (int h = 0; h < HS; ++h) {
-                    const int cur = (e * HS + h) & 1;
-                    if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
-                    else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
-                    products(bq[cur], h, e == 0);
-                }
-                if (e == G::SE && more) {
-                    store_x(nbuf, nx);
-                    if (G::T != 9) fetch_x(min(ch + 2, che - 1));
-                }
+        for (int e = 0; e < E; ++e) {
+            if (SRC == SRC_RAW && G::T == 9) {   // three taps (one kernel row) are fetched at a time
+                take_a(0, e % 3 % VW);
+                if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
+            } else {
+                take_a(e % AR, 0);
+                fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
             }
-        } else {
-            int r = 0, sx = 0;
+            if (G::T == 9 && e == 0 && more) fetch_x(nx);
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int nb = 0; nb < NT; ++nb) tmp[i][nb] = zero;
-            load_b(bq[0], buf, 0, 0);
-            if (more) {
+            for (int h = 0; h < HS; ++h) {
+                const int cur = (e * HS + h) & 1;
+                if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
+                else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
+                products(bq[cur], h, e == 0);
+            }
+            if (e == G::SE && more) {
                 store_x(nbuf, nx);
-                fetch_x(min(ch + 2, che - 1));
+                if (G::T != 9) fetch_x(min(ch + 2, che - 1));
             }
-            for (int t = 0; t < T; ++t) {
-                const unsigned char* tb = buf + (r * pitch + sx) * 48;
-                if (++sx == S) { sx = 0; ++r; }
-                if (t + 1 == T) r = sx = 0;
-                take_a(0, 0);
-                fetch_a(0, t + 1 < T ? ch : nx, t + 1 < T ? t + 1 : 0);
-#pragma unroll
-                for (int h = 0; h < HS; ++h) {
-                    if (h + 1 < HS) load_b(bq[(h & 1) ^ 1], tb, 0, h + 1);
-                    else load_b(bq[HS == 1 ? 1 : 0], buf + (r * pitch + sx) * 48, 0, 0);
-                    products(bq[h & 1], h, false);
-                }
-                if (HS == 1) {
-#pragma unroll
-                    for (int n = 0; n < NH; ++n)
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) bq[0][n][q] = bq[1][n][q];
-                }
-            }
-            // The last products' results take 11 more wait states after issue; across a branch the compiler has been seen to
-            // leave too few before the first read.
-#pragma unroll
-            for (int i = 0; i < MT; ++i) asm volatile("s_nop 15" : "+v"(tmp[i][NT - 2]), "+v"(tmp[i][NT - 1]));
         }
 #pragma unroll
         for (int i = 0; i < MT; ++i)
@@ -497,6 +460,255 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     }
 }
 
+// Taps dealt to the wavefronts of a workgroup: 5x5 and 7x7 kernels, and launches of 3x3 layers too small for the tiles above.
+template <int T_, int CS_, int NT_, bool POOL_, int XU_>
+struct TGeom {
+    static constexpr int T = T_, CS = CS_, NT = NT_, XU = XU_;
+    static constexpr bool POOL = POOL_;
+    static constexpr int S = T == 9 ? 3 : T == 25 ? 5 : 7;
+    static constexpr int NW = 8, BM = 32, BN = 32 * NT, CG = 2 * CS;
+    static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
+    static constexpr int E = T * CS;                  // fragments of 32 filters x 16 channels per chunk
+    static constexpr int FL = 16 * E, FS = FL | 1;    // floats of one filter per chunk, and their stride in LDS
+    static constexpr int FR = (FL + 63) / 64;         // loads of 64 lanes per filter and chunk; a wavefront takes BM / NW filters
+    static constexpr int FB = (BM * FS * 4 + 15) / 16 * 16;
+};
+
+// One workgroup computes 32 filters x 32 NT windows; its eight wavefronts share the staged chunk and take every eighth tap
+// each, their sums are added through LDS at the end.  A tile is then an eighth as long as one wavefront's walk over all taps,
+// and small enough that a layer of a few dozen tiles still spreads over the chip.  The filters as stored are read in runs of
+// 16 channels x T taps (a fragment straight from memory would touch 64 lines per load) and kept in LDS as fp32; a lane
+// cuts its eight values into pieces when it takes them.  Filters and map of the next chunk are on their way while a chunk is
+// multiplied.
+// Bound by the walk of one workgroup where there are few (2.0 us per chunk of 16 channels, 5x5 and 64 windows), by the matrix
+// pipe and the two barriers per chunk where there are many (55 % of the matrix rate at 5x5).  Against gen: 48 -> 128 5x5 @7x7 at
+// batch 32 13 us (43), 64 -> 256 5x5 @28x28 at batch 16 90 (136), 128 -> 512 7x7 @28x28 at batch 8 293 (513); against the vector
+// kernel without a workspace 256 -> 256 3x3 @14x14 at batch 1 23 (41).  More than one workgroup per compute unit needs 128
+// registers: with 64 accumulators the compiler spills and the kernel takes twice as long.  Relative error against 64-bit sums
+// 0.6e-7 to 1.1e-7, gen 0.8e-7 to 5.2e-7.
+template <class G>
+__global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
+                                                                   const float* __restrict__ w, float* __restrict__ parts,
+                                                                   float* __restrict__ y)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int T = G::T, S = G::S, CS = G::CS, CG = G::CG, NT = G::NT, NW = G::NW, XU = G::XU, E = G::E, FL = G::FL, FS = G::FS;
+    const int PX = cfg.px, CGB = cfg.cgb;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    float* fl = reinterpret_cast<float*>(lds);
+    unsigned char* buf = lds + G::FB;
+
+    // workgroup -> (tile, slice), as in piece_kernel
+    const int whole = cfg.whole, nb_all = gridDim.x;
+    const bool split = (int)blockIdx.x >= whole;
+    int b = split ? blockIdx.x - whole : blockIdx.x, ss = 0;
+    {
+        const int cnt = split ? nb_all - whole : whole;
+        const int n8 = cnt >> 3, rem = cnt & 7, xcd = b & 7, i = b >> 3;
+        b = xcd * n8 + min(xcd, rem) + i;
+    }
+    const int ns = split ? (nb_all - whole) / cfg.nss : 1;
+    int ptile = 0;
+    if (split) {
+        ss = b / ns;
+        ptile = b - ss * ns;
+        b = whole + ptile;
+    }
+    const int kb = b % cfg.kblocks;
+    b /= cfg.kblocks;
+    const int strip = b % cfg.strips;
+    b /= cfg.strips;
+    const int tile = b % cfg.ntiles;
+    const int g = b / cfg.ntiles;
+
+    const int TW = cfg.TW, HW = p.H * p.W, HP = p.H + p.pad;
+    const int pitch = (G::POOL ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + S;
+    const int pcols = G::POOL ? p.PW : p.OW, prows = G::POOL ? p.PH : p.OH;
+    const int plane = prows * pcols;
+    auto window = [&](int P, int& n, int& oh, int& ow) {   // as in piece_kernel
+        const int pp = G::POOL ? P >> 2 : P;
+        const int q = pp / TW;
+        ow = pp - q * TW;
+        n = q / prows;
+        oh = q - n * prows;
+        if (G::POOL) {
+            oh = p.ps * oh + ((P & 3) >> 1);
+            ow = p.ps * ow + (P & 1);
+        }
+    };
+    int n0, oh0, ow0;
+    window(tile * G::BN, n0, oh0, ow0);
+    const int r0 = n0 * HP + oh0 * p.stride;
+    const int w0 = strip * TW * (G::POOL ? p.ps : 1) * p.stride - p.pad;
+    int lb[NT];
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        int n, oh, ow;
+        window(min(tile * G::BN + nb * 32 + col, cfg.nrun - 1), n, oh, ow);
+        lb[nb] = ((n * HP + oh * p.stride - r0) * pitch + ow * p.stride) * 48 + half * CGB;
+    }
+
+    unsigned xvo[XU];
+    int xst[XU];
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+        const int id = u * NW + wave, cgi = id % CG, q = id / CG * 64 + lane;
+        const int row = q / pitch, cw = q - row * pitch + w0;
+        const int sr = r0 + row, n = sr / HP, h = sr - n * HP - p.pad;
+        const bool ok = q < PX && n < p.N && h >= 0 && h < p.H && cw >= 0 && cw < p.W;
+        xvo[u] = ok ? 4u * (unsigned)((n - n0) * p.C * HW + h * p.W + cw) : 0x80000000u;
+        xst[u] = q < PX ? cgi * CGB + q * 48 : -1;
+    }
+    const size_t xfirst = ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW;
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(x + xfirst), 0, (int)min(((size_t)p.N * p.C * HW - xfirst) * 4, (size_t)0x7ffffffc), 0x00020000);
+    // a filter past the group's last one re-reads the last, columns past the last re-read that one (their map elements are zeros)
+    const float* wb = w + ((size_t)g * p.Kg + (size_t)kb * G::BM) * p.L;
+    const int klast = p.Kg - 1 - kb * G::BM;
+    constexpr int KW = G::BM / NW;
+
+    float xr[XU][8], fr[KW][G::FR];
+    auto fetch = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < G::FR; ++u) {
+            const unsigned o = min(ch * FL + u * 64 + lane, p.L - 1);
+#pragma unroll
+            for (int k = 0; k < KW; ++k) fr[k][u] = wb[(size_t)min(wave * KW + k, klast) * p.L + o];
+        }
+#pragma unroll
+        for (int u = 0; u < XU; ++u) {
+            const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                xr[u][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
+        }
+    };
+    auto lay_out = [&](int ch) {
+#pragma unroll
+        for (int u = 0; u < G::FR; ++u) {
+            if (u * 64 + 64 > FL && lane >= FL - u * 64) continue;
+#pragma unroll
+            for (int k = 0; k < KW; ++k) fl[(wave * KW + k) * FS + u * 64 + lane] = fr[k][u];
+        }
+#pragma unroll
+        for (int u = 0; u < XU; ++u) {
+            const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
+            if (c0 + 8 > p.Cg) {   // channels past the group's last one count as zeros
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (c0 + j >= p.Cg) xr[u][j] = 0.0f;
+            }
+            u4 f[3];
+            split8(xr[u], f);
+            if (xst[u] >= 0) {
+                u4* d = reinterpret_cast<u4*>(buf + xst[u]);
+                d[0] = f[0];
+                d[1] = f[1];
+                d[2] = f[2];
+            }
+        }
+    };
+
+    // x0 w0 has sums of its own: one rounding per 16 terms at the size of the result, the other five at 2^-8 of it
+    v16f acc[NT], accl[NT];
+    const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) acc[nb] = accl[nb] = zero;
+    float av[8];
+    u4 bv[NT][3];
+    // fragment e of the chunk: channels 16 (e / T) and on, tap e % T
+    auto take = [&](int e) {
+        const int c = CS == 1 ? 0 : e / T, t = e - c * T, r = t / S;
+        const float* f = fl + col * FS + (c * 16 + half * 8) * T + t;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) av[j] = f[j * T];
+        const unsigned char* tb = buf + c * 2 * CGB + (r * pitch + t - r * S) * 48;
+#pragma unroll
+        for (int nb = 0; nb < NT; ++nb)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) bv[nb][q] = *reinterpret_cast<const u4*>(tb + lb[nb] + q * 16);
+    };
+
+    const int chb = split ? cfg.nch * ss / cfg.nss : 0, che = split ? cfg.nch * (ss + 1) / cfg.nss : cfg.nch;
+    fetch(chb);
+    for (int ch = chb; ch < che; ++ch) {
+        lay_out(ch);
+        __syncthreads();
+        if (ch + 1 < che) fetch(ch + 1);
+        take(wave);
+        for (int e = wave; e < E; e += NW) {
+            u4 a[3], bb[NT][3];
+            split8(av, a);
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) bb[nb][q] = bv[nb][q];
+            take(min(e + NW, E - 1));
+            constexpr int qa[6] = {0, 2, 1, 0, 1, 0}, qb[6] = {2, 0, 1, 1, 0, 0};   // smallest products first
+#pragma unroll
+            for (int c = 0; c < 6; ++c)
+#pragma unroll
+                for (int nb = 0; nb < NT; ++nb) {
+                    v16f& d = c == 5 ? acc[nb] : accl[nb];
+                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[qa[c]]), __builtin_bit_cast(bf8, bb[nb][qb[c]]), d,
+                                                                0, 0, 0);
+                }
+        }
+        __syncthreads();
+    }
+
+    // the wavefronts' sums, 32 windows at a time: element v of lane l = filter 8 (v / 4) + v % 4 + 4 (l / 32), window l % 32
+    const int c_lo = chb * CS * 16, c_hi = min(che * CS * 16, p.Cg);
+    float* part = split ? parts + ((size_t)ss * ns + ptile) * (G::BM * G::BN) : nullptr;
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        if (nb) __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) fl[(wave * 16 + v) * 64 + lane] = acc[nb][v] + accl[nb][v];
+        __syncthreads();
+        const int P = tile * G::BN + nb * 32 + col;
+        int n, oh, ow;
+        window(min(P, cfg.nrun - 1), n, oh, ow);
+        ow += strip * TW * (G::POOL ? p.ps : 1);
+        const int wcol = G::POOL ? (ow - (P & 1)) / p.ps : ow, wrow = G::POOL ? (oh - ((P & 3) >> 1)) / p.ps : oh;
+        const bool pos_ok = P < cfg.nrun && wcol < pcols;
+#pragma unroll
+        for (int i = 0; i < 16 / NW; ++i) {
+            const int v = i * NW + wave, kr = 8 * (v >> 2) + (v & 3) + 4 * half, k = kb * G::BM + kr;
+            float s = fl[v * 64 + lane];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) s += fl[(q * 16 + v) * 64 + lane];
+            const bool ok = pos_ok && k < p.Kg;
+            const unsigned bits = __builtin_bit_cast(unsigned, s) & 0x7fffffffu;
+            if (ok && bits != 0u && bits - 0x17800000u >= 0x7f800000u - 0x17800000u) {   // not within [2^-80, inf): see the top
+                const float* wk = w + ((size_t)g * p.Kg + k) * p.L;
+                s = 0.0f;
+                for (int c = c_lo; c < c_hi; ++c)
+                    for (int t = 0; t < T; ++t) {
+                        const int ih = oh * p.stride - p.pad + t / S, iw = ow * p.stride - p.pad + t % S;
+                        if (ih < 0 || ih >= p.H || iw < 0 || iw >= p.W) continue;
+                        const float e = x[(((size_t)n * p.G + g) * p.Cg + c) * HW + ih * p.W + iw];
+                        if (e != 0.0f) s = __builtin_fmaf(e, wk[c * T + t], s);
+                    }
+            }
+            if (split) {
+                part[kr * G::BN + nb * 32 + col] = s;
+                continue;
+            }
+            if (G::POOL) {   // the four results of a pooling window lie in four neighbouring lanes
+                s = fmaxf(s, __shfl_xor(s, 1));
+                s = fmaxf(s, __shfl_xor(s, 2));
+            }
+            if (!ok || (G::POOL && (lane & 3))) continue;
+            s += bias_of(p, (size_t)g * p.Kg + k);
+            if (G::POOL || p.relu) s = fmaxf(s, 0.0f);
+            y[((size_t)n * p.K + (size_t)g * p.Kg + k) * plane + wrow * pcols + wcol] = s;
+        }
+    }
+}
+
 // Adds the slices of the split tiles (slice 0 first) and applies the epilogue: one thread per filter and window row
 // (plain) or pooling window.
 template <bool POOL>
@@ -564,7 +776,7 @@ struct Plan {
 bool shape_ok(const Problem& p, bool pooled)
 {
     const int T = p.R * p.S;
-    if (T != 1 && (T != 9 || p.S != 3)) return false;
+    if (p.R != p.S || (T != 1 && T != 9 && T != 25 && T != 49)) return false;
     if (pooled && (p.ph != 2 || p.pw != 2)) return false;
     const long long npos = pooled ? (long long)p.N * p.PH * p.PW * 4 : (long long)p.N * p.OH * p.OW;
     if (npos >= (1LL << 30)) return false;
@@ -630,31 +842,21 @@ double cu_load(long long na, double a, long long nb, double b)
     return best < 0.0 ? hi + (double)(nb + 255) / 256 * b : best;
 }
 
-template <class G>
-Plan plan_geom(const Problem& p, bool pooled)
+// Column strips of a tile of BN windows: the fewest columns past the map's edge, then the fewest staged positions.  False
+// where no strip's staged positions fit.
+bool choose_strips(const Problem& p, bool pooled, int BN, int PXMAX, PieceCfg& c)
 {
-    Plan pl;
-    if (G::POOL != pooled) return pl;
-    const int T = p.R * p.S;
-    if (G::T && (G::T != T || (G::T == 9 && p.S != 3))) return pl;
-    PieceCfg& c = pl.cfg;
-    c.flat = T == 1 && p.stride == 1 && !pooled;
-    c.T = T;
-    c.S = p.S;
-    c.nch = (p.Cg + 16 * G::CS - 1) / (16 * G::CS);
-    c.kblocks = (p.Kg + G::BM - 1) / G::BM;
-    // strips: the fewest columns past the map's edge, then the fewest staged positions
     const int cols = pooled ? p.PW : c.flat ? p.OH * p.OW : p.OW, rows = pooled ? p.PH : c.flat ? 1 : p.OH;
     double best = 0.0;
     for (int m = 1; m <= cols; ++m) {
         const int TW = (cols + m - 1) / m;
         if (TW < 4 && m > 1) break;
-        if (TW > G::BN) continue;
+        if (TW > BN) continue;
         const int strips = (cols + TW - 1) / TW;
-        const long long px = stage_positions(p, pooled, c.flat, G::BN, TW);
-        if (px > G::PXMAX) continue;
-        const long long run = (long long)p.N * rows * TW * (pooled ? 4 : 1), nt = (run + G::BN - 1) / G::BN;
-        const double cost = (double)nt * strips * (G::BN * (1.0 + 0.5 / TW) + px * 0.02);   // (a row's end costs LDS bank conflicts)
+        const long long px = stage_positions(p, pooled, c.flat, BN, TW);
+        if (px > PXMAX) continue;
+        const long long run = (long long)p.N * rows * TW * (pooled ? 4 : 1), nt = (run + BN - 1) / BN;
+        const double cost = (double)nt * strips * (BN * (1.0 + 0.5 / TW) + px * 0.02);   // (a row's end costs LDS bank conflicts)
         if (best == 0.0 || cost < best) {
             best = cost;
             c.TW = TW;
@@ -664,22 +866,80 @@ Plan plan_geom(const Problem& p, bool pooled)
             c.px = (int)px;
         }
     }
-    if (best == 0.0) return pl;
+    return best != 0.0;
+}
+
+// A plan remembered by sconv_tune names a geometry and leaves the split to the model; any other decomposition is not this
+// kernel's.
+bool pin_allows()
+{
+    const PlanPin* pin = current_pin();
+    return !pin || !pin->nwv || (pin->nwv == 4 && pin->ncs == 1 && pin->nss <= 1);
+}
+
+// The cheapest split of a geometry's tiles, kept in pl when it beats what is there: whole tiles first, then the rest, each
+// split along the channels over s workgroups (s = 1: none).  tc: microseconds of a chunk, times lone where the compute units
+// hold a single workgroup; fixed: those of the launch.
+void consider(Plan& pl, long long tiles, long long round, int NW, double tc, double lone, double fixed, int src, size_t pb, int kb32, size_t ws,
+              size_t tile_bytes)
+{
+    PieceCfg& c = pl.cfg;
+    int pin_whole = 0, pin_ncs = 0, pin_nss = 0;   // tuning aid: SCONV_PIECE_SPLIT="whole tiles,1,slices of the others"
+    if (!current_pin()) pinned_split("SCONV_PIECE_SPLIT", &pin_whole, &pin_ncs, &pin_nss);
+    const long long firsts[3] = {tiles, tiles / 256 * 256, tiles / round * round};
+    for (int f = 0; f < (tiles < 4096 ? 4 : 1); ++f) {
+        const long long whole = pin_nss ? (pin_nss > 1 ? pin_whole : tiles) : f < 3 ? firsts[f] : 0;
+        const long long tail = tiles - whole;
+        if (f && !pin_nss && (tail == 0 || (f == 2 && firsts[2] == firsts[1]) || (f == 3 && (firsts[1] == 0 || firsts[2] == 0)))) continue;
+        if (tail < 0) continue;
+        for (int s = tail ? 2 : 1; s <= (tail ? 32 : 1); s += s < 6 ? 1 : s < 16 ? 2 : 8) {
+            if (pin_nss > 1 && s != pin_nss) continue;
+            if (s > c.nch || pb + (size_t)tail * s * tile_bytes > ws + (tail ? 0 : pb)) break;
+            const double a = (c.nch + 0.6) * tc, b = ((c.nch + s - 1) / s + 0.6) * tc;
+            const double load = cu_load(whole, a, tail * s, b);
+            const double resident = (double)(whole + tail * s) / 256.0;
+            double cost = fixed + load * (resident * NW <= (lone > 1.0 ? 6.0 : 8.0) ? lone : 1.0);
+            if (tail) cost += 3.0 + 2.0 * (double)(tail * s) * tile_bytes / 6e6;
+            if (pl.cost >= 0.0 && cost >= pl.cost) continue;
+            pl.cost = cost;
+            pl.src = src;
+            pl.piece_bytes = pb;
+            pl.ntail = (int)tail;
+            c.kb32 = kb32;
+            c.whole = (int)whole;
+            c.nss = s;
+        }
+        if (pin_nss) break;
+    }
+}
+
+template <class G>
+Plan plan_geom(const Problem& p, bool pooled)
+{
+    Plan pl;
+    if (G::POOL != pooled) return pl;
+    const int T = p.R * p.S;
+    if (G::T != T || p.R != p.S) return pl;
+    PieceCfg& c = pl.cfg;
+    c.flat = T == 1 && p.stride == 1 && !pooled;
+    c.T = T;
+    c.S = p.S;
+    c.nch = (p.Cg + 16 * G::CS - 1) / (16 * G::CS);
+    c.kblocks = (p.Kg + G::BM - 1) / G::BM;
+    if (!choose_strips(p, pooled, G::BN, G::PXMAX, c)) return pl;
     c.cgb = (c.px * 48 + 255) / 256 * 256;
     pl.lds_bytes = 2 * (size_t)G::CG * c.cgb;
     if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
     if (pl.lds_bytes > 160 * 1024) return pl;
     // images a tile can touch, and the byte offsets of their elements
-    const long long run_img = (long long)rows * c.TW * (pooled ? 4 : 1);
+    const long long run_img = (long long)(pooled ? p.PH : c.flat ? 1 : p.OH) * c.TW * (pooled ? 4 : 1);
     const long long imgs = (G::BN - 1 + run_img - 1) / run_img + 1;
     if ((imgs + 1) * p.C * p.H * p.W * 4 >= (1LL << 31)) return pl;
     if ((size_t)p.Cg * T * 256 >= (1u << 31) || (size_t)p.L * 4 * (G::BM + 1) >= (1u << 31)) return pl;
     const long long tiles = (long long)c.ntiles * c.strips * c.kblocks * p.G;
     if (tiles >= (1LL << 24)) return pl;
 
-    int pin_whole = 0, pin_ncs = 0, pin_nss = 0;   // tuning aid: SCONV_PIECE_SPLIT="whole tiles,1,slices of the others"
-    if (!current_pin()) pinned_split("SCONV_PIECE_SPLIT", &pin_whole, &pin_ncs, &pin_nss);
-    else if (current_pin()->nwv && (current_pin()->nwv != 4 || current_pin()->ncs != 1 || current_pin()->nss > 1)) return pl;
+    if (!pin_allows()) return pl;
     const char* pin_src = env_value("SCONV_PIECE_SRC");
     const size_t ws = usable_workspace(p, pooled);
     const size_t tile_bytes = (size_t)G::BM * G::BN * 4;
@@ -698,33 +958,7 @@ Plan plan_geom(const Problem& p, bool pooled)
         const double tc = G::tc(src, T);
         const int occ = occupancy_limit<G>(src, pl.lds_bytes);
         const double pre = src == SRC_PIECES ? 6.0 + (double)p.K * p.L * 10.0 / 4e6 : 0.0;
-        // whole tiles first, then the rest, each split along the channels over s workgroups (s = 1: none)
-        const long long round = 256LL * occ;
-        const long long firsts[3] = {tiles, tiles / 256 * 256, tiles / round * round};
-        for (int f = 0; f < (tiles < 4096 ? 4 : 1); ++f) {
-            const long long whole = pin_nss ? (pin_nss > 1 ? pin_whole : tiles) : f < 3 ? firsts[f] : 0;
-            const long long tail = tiles - whole;
-            if (f && !pin_nss && (tail == 0 || (f == 2 && firsts[2] == firsts[1]) || (f == 3 && (firsts[1] == 0 || firsts[2] == 0)))) continue;
-            if (tail < 0) continue;
-            for (int s = tail ? 2 : 1; s <= (tail ? 32 : 1); s += s < 6 ? 1 : s < 16 ? 2 : 8) {
-                if (pin_nss > 1 && s != pin_nss) continue;
-                if (s > c.nch || pb + (size_t)tail * s * tile_bytes > ws + (tail ? 0 : pb)) break;
-                const double a = (c.nch + 0.6) * tc, b = ((c.nch + s - 1) / s + 0.6) * tc;
-                const double load = cu_load(whole, a, tail * s, b);
-                const double resident = (double)(whole + tail * s) / 256.0;
-                double cost = pre + 6.0 + load * (resident * G::NW <= 6.0 ? 1.25 : 1.0);
-                if (tail) cost += 3.0 + 2.0 * (double)(tail * s) * tile_bytes / 6e6;
-                if (pl.cost >= 0.0 && cost >= pl.cost) continue;
-                pl.cost = cost;
-                pl.src = src;
-                pl.piece_bytes = pb;
-                pl.ntail = (int)tail;
-                c.kb32 = kb32;
-                c.whole = (int)whole;
-                c.nss = s;
-            }
-            if (pin_nss) break;
-        }
+        consider(pl, tiles, 256LL * occ, G::NW, tc, 1.25, 6.0 + pre, src, pb, kb32, ws, tile_bytes);
     }
     return pl;
 }
@@ -770,6 +1004,53 @@ int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, c
     return launch_status();
 }
 
+template <class G>
+Plan plan_taps(const Problem& p, bool pooled)
+{
+    Plan pl;
+    if (G::POOL != pooled || p.R != p.S || p.S != G::S || p.wprep) return pl;
+    PieceCfg& c = pl.cfg;
+    c = PieceCfg();
+    c.nch = (p.Cg + 16 * G::CS - 1) / (16 * G::CS);
+    c.kblocks = (p.Kg + G::BM - 1) / G::BM;
+    if (!choose_strips(p, pooled, G::BN, G::PXMAX, c)) return pl;
+    c.cgb = (c.px * 48 + 255) / 256 * 256;
+    pl.lds_bytes = G::FB + (size_t)G::CG * c.cgb;
+    if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
+    if (pl.lds_bytes > 160 * 1024) return pl;
+    const long long run_img = (long long)(pooled ? p.PH : p.OH) * c.TW * (pooled ? 4 : 1);
+    const long long imgs = (G::BN - 1 + run_img - 1) / run_img + 1;
+    if ((imgs + 1) * p.C * p.H * p.W * 4 >= (1LL << 31)) return pl;
+    if (((size_t)p.L + G::FL) * 4 * (G::BM + 1) >= (1u << 31)) return pl;
+    const long long tiles = (long long)c.ntiles * c.strips * c.kblocks * p.G;
+    if (tiles >= (1LL << 24) || !pin_allows()) return pl;
+    if (env_value("SCONV_PIECE_SRC") && atoi(env_value("SCONV_PIECE_SRC")) != SRC_RAW) return pl;
+    // a chunk: the matrix instructions of its busiest SIMD (32 clocks each), and barriers and staging that nothing hides (one
+    // workgroup per compute unit).  Measured: 2.0 us with few workgroups and 2.6 with all (5x5, 64 windows), 3.9 and 5.9 (7x7)
+    const double tc = (((G::E + 3) / 4) * G::NT * 6 * 32 / 2000.0 / 0.75 + 0.8) * (G::T == 49 ? 1.2 : 1.0);
+    consider(pl, tiles, 256LL, G::NW, tc, 0.75, 7.0, SRC_RAW, 0, 0, usable_workspace(p, pooled), (size_t)G::BM * G::BN * 4);
+    return pl;
+}
+
+template <class G>
+int launch_taps(const Plan& pl, const Problem& p, bool, const float* x, const float* w, float* y, hipStream_t stream)
+{
+    auto kern = piece_taps_kernel<G>;
+    static size_t opted = 0;
+    if (pl.lds_bytes > opted) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes) != hipSuccess)
+            return SCONV_ELAUNCH;
+        opted = pl.lds_bytes;
+    }
+    float* parts = pl.ntail ? split_scratch(stream) : nullptr;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.cfg.whole + pl.ntail * pl.cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, pl.cfg, x, w, parts, y);
+    const int rc = launch_status();
+    if (rc || !pl.ntail) return rc;
+    hipLaunchKernelGGL(piece_sum_kernel<G::POOL>, dim3((unsigned)(G::BM * G::BN / (G::POOL ? 4 : 1) / 256), (unsigned)pl.ntail), dim3(256), 0, stream,
+                       p, pl.cfg, G::BM, G::BN, pl.ntail, parts, y);
+    return launch_status();
+}
+
 struct Candidate {
     const char* name;
     Plan (*plan)(const Problem&, bool);
@@ -777,6 +1058,7 @@ struct Candidate {
 };
 
 #define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>}
+#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, launch_taps<TGeom<__VA_ARGS__>>}
 const Candidate kCandidates[] = {
     CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2),
     CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2),
@@ -786,6 +1068,14 @@ const Candidate kCandidates[] = {
     CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2),
     CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2),
     CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 3, 2),
+    // taps, 16-channel groups per chunk, window blocks, pooled, staging units
+    TAPS("t3x64", 9, 2, 2, false, 2),
+    TAPS("t5x64", 25, 1, 2, false, 1),
+    TAPS("t5x128", 25, 1, 4, false, 2),
+    TAPS("t7x64", 49, 1, 2, false, 2),
+    TAPS("t7x96", 49, 1, 3, false, 2),
+    TAPS("tp5x128", 25, 1, 4, true, 2),
+    TAPS("tp7x96", 49, 1, 3, true, 2),
 };
 
 }  // namespace

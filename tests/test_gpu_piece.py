@@ -28,6 +28,18 @@ CASES = [
     ("c128x64", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None), "1,1,2"),      # 1x1, ragged channels, strips across images
     ("c128x64", (2, 64, 15, 14, 96, 1, 1, 2, 0, 2, None), None),          # 1x1, stride 2, grouped
     ("q128x64", (2, 256, 14, 10, 96, 1, 1, 1, 0, 1, (2, 2, 2)), None),
+    # taps dealt to the wavefronts
+    ("t3x64", (1, 33, 7, 7, 33, 3, 3, 1, 1, 1, None), None),              # one channel in the second chunk, one filter in the second block
+    ("t3x64", (2, 64, 9, 13, 40, 3, 3, 2, 1, 2, None), "1,1,2"),
+    ("t5x64", (3, 16, 7, 7, 32, 5, 5, 1, 2, 1, None), None),              # one chunk, the last tile 19 windows long
+    ("t5x64", (1, 3, 33, 29, 20, 5, 5, 2, 0, 1, None), None),             # fewer channels than half a lane's eight, no padding
+    ("t5x64", (2, 50, 8, 12, 70, 5, 5, 1, 2, 2, None), "2,1,2"),
+    ("t5x128", (2, 40, 12, 31, 33, 5, 5, 1, 2, 1, None), "0,1,3"),
+    ("t7x64", (1, 24, 13, 6, 33, 7, 7, 1, 3, 1, None), None),
+    ("t7x96", (2, 17, 21, 18, 31, 7, 7, 2, 3, 1, None), "1,1,2"),
+    ("tp5x128", (2, 48, 13, 15, 33, 5, 5, 1, 2, 1, (2, 2, 2)), "1,1,3"),
+    ("tp5x128", (1, 16, 11, 9, 32, 5, 5, 1, 0, 1, (2, 2, 1)), None),
+    ("tp7x96", (1, 20, 14, 14, 40, 7, 7, 1, 3, 1, (2, 2, 2)), None),
 ]
 
 
@@ -48,6 +60,8 @@ def test_geometries_splits_and_filter_sources(device, monkeypatch, geom, shp, sp
     prep = src == "1"
     if prep and (R != 3 or stride != 1 or pad != 1 or (C // groups) % 16):
         pytest.skip("no prepared layout for this layer")
+    if geom[0] == "t" and src != "2":
+        pytest.skip("reads the filters as stored")
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
     for integer in (False, True):
         layer, x, w = workloads.make_random_case(400, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6, integer)
@@ -81,7 +95,7 @@ def test_geometries_splits_and_filter_sources(device, monkeypatch, geom, shp, sp
             assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)   # measured 1e-7 to 2e-7
 
 
-@pytest.mark.parametrize("geom,src", [("a128x64", "2"), ("a128x128", "0"), ("a64x128", "1")])
+@pytest.mark.parametrize("geom,src", [("a128x64", "2"), ("a128x128", "0"), ("a64x128", "1"), ("t3x64", "2")])
 def test_values_outside_the_pieces_range(device, monkeypatch, geom, src):
     """Inf, NaN, values that overflow when rounded to bf16 and values whose pieces fall below bf16's range give what the
     window-row kernel gives; zeros of the map are skipped (0 * Inf adds nothing)."""
