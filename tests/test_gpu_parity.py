@@ -89,6 +89,19 @@ def test_encode_both_kernels_bit_exact(device, monkeypatch, shp, which):
     check_encode(layer, x, w.shape, sconv.FMT_PECR)
 
 
+@pytest.mark.parametrize("shp", [
+    # 1, 16, 17 and 33 rows to a run; runs cut into tiles of 11, 14 and 16 rows; row lengths that are and are not whole sets of four
+    (1, 12, 46, 45, 8, 3, 3, 1, 0, 1, (2, 2, 2)), (1, 7, 48, 56, 8, 3, 3, 1, 1, 1, (3, 3, 2)), (2, 33, 64, 33, 8, 3, 3, 1, 1, 1, (2, 2, 1)),
+    (1, 8, 64, 64, 8, 5, 5, 2, 2, 2, (2, 2, 2)), (1, 6, 64, 49, 8, 3, 3, 3, 1, 1, (3, 1, 1)), (2, 90, 50, 61, 8, 1, 1, 1, 0, 1, (2, 2, 2)),
+    (1, 5, 700, 3, 8, 3, 3, 1, 0, 1, (2, 1, 1)),
+])
+def test_encode_tiles_inside_output_rows(device, monkeypatch, shp):
+    monkeypatch.setenv("SCONV_ENCODE", "tile")
+    layer, x, w = _mk(124, shp)
+    check_encode(layer, x, w.shape, sconv.FMT_ECR)
+    check_encode(layer, x, w.shape, sconv.FMT_PECR)
+
+
 @pytest.mark.parametrize("shp", ENCODE_LARGE)
 def test_encode_large_maps_bit_exact(device, shp):
     layer, x, w = _mk(123, shp)
