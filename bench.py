@@ -41,7 +41,8 @@ import workloads  # noqa: E402
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TF = 157.3  # 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flop x 2.4 GHz
 FP32_MFMA_PEAK_TF = 157.3    # dense fp32 matrix instructions, published
-MFMA_VARIANTS = ("quad3x3", "quad1x1", "wide3x3", "gen")
+MFMA_VARIANTS = ("quad3x3", "quad1x1", "wide3x3", "gen", "piece")
+PIECE_PEAK_TF = 2500.0 / 6   # piece kernel: six bf16 matrix products (dense peak, published) per fp32 one
 # HBM/fabric bytes per launch from rocprofv3 counter runs (FETCH_SIZE x 2 KiB + WRITE_SIZE x 1 KiB, scaled
 # by the copy calibration), keyed by (plan name, layer, batch): a figure from profiles/, not something this
 # run measures - the line names its source, and prints null when the plan that ran is not in the table.
@@ -321,7 +322,7 @@ def layer_record(dl: DeviceLayer, work: dict, ms: float) -> dict:
     # any test (geometry names ending in d, "dense") issue everything - the dense fallback on the matrix pipe
     g = SKIP_GRANULE.get(dl.variant, 1)
     geom = dl.plan.split("/")[1] if "/" in dl.plan else ""
-    dense_form = dl.variant in MFMA_VARIANTS and (geom == "dense" or (geom.endswith("d") and geom != "kept"))
+    dense_form = dl.variant == "piece" or dl.variant in MFMA_VARIANTS and (geom == "dense" or (geom.endswith("d") and geom != "kept"))
     z = work["zero_ratio"]
     skipped = 0.0 if dense_form else (z if g == 1 else z ** g)
     issued = work["dense_flops"] * (1.0 - skipped) if g > 1 or dense_form else work["nz_flops"]
@@ -474,9 +475,10 @@ def run_headline(args) -> None:
     else:
         ach = wk["nz_flops"] / t / 1e12
         if r["variant"] in MFMA_VARIANTS:
-            # products go through the fp32 matrix pipe; algorithmic flops = nonzero multiply-adds
-            roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": FP32_MFMA_PEAK_TF, "unit": "TFLOP/s",
-                    "frac": round(ach / FP32_MFMA_PEAK_TF, 4), "traffic": None,
+            # products go through the matrix pipe (fp32, or bf16 pieces); algorithmic flops = nonzero multiply-adds
+            peak = PIECE_PEAK_TF if r["variant"] == "piece" else FP32_MFMA_PEAK_TF
+            roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": round(peak, 1), "unit": "TFLOP/s",
+                    "frac": round(ach / peak, 4), "traffic": None,
                     "issued_dense_equiv_TFLOPs": round(wk["dense_flops"] / t / 1e12, 2)}
         else:
             roof = {"bound": "alu", "achieved": round(ach, 2), "peak": FP32_VECTOR_PEAK_TF, "unit": "TFLOP/s",

@@ -28,7 +28,7 @@ __device__ __forceinline__ bool wide_rows(int L, const float* values, const int3
 }
 
 // The end of a row: what is left in the ring (at most 63 pairs), then zeros, 16 bytes a lane where rows allow it - at 60 %
-// zeros they are most of what the kernel stores (1x1, 256 @60x60 at batch 8: 43.9 -> 29.7 us, 4.0 TB/s of stores).
+// zeros they are most of what the kernel stores (1x1, 256 @60x60 at batch 8: 43.9 -> 29.7 us, 2.0 TB/s of stores).
 __device__ __forceinline__ void finish_row(float* vrow, int32_t* irow, const float* rv, const int32_t* ri, int cnt, int flushed,
                                            int L, int lane, bool wide)
 {
