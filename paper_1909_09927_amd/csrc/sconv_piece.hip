@@ -10,8 +10,12 @@
 // chunk start from zero and are added to the running sums at its end (16 additions per accumulator and 54 matrix
 // instructions), so that the roundings of a chunk happen at the size of its own partial sum.  Measured against 64-bit sums,
 // 512 channels: 2.0e-7 relative, against 2.7e-7 (quad3x3), 3.7e-7 (wide3x3) and 1.2e-7 - 2.2e-7 (tap3x3).
-// Values the pieces cannot carry - Inf, NaN, what overflows when rounded to bf16, results below 2^-80 - show in the result:
-// a lane that finds such a sum has its block of 32 x 32 results summed again in plain fp32, skipping zero elements.
+// Both operands are multiplied by 2^24 before they are cut: the last bit of the smallest fp32 subnormal, 2^-149, becomes 2^-125,
+// so every piece of every value is a normal bf16 number or zero, and the products that fall below fp32's range are those below
+// 2^-174 - far under an fp32 sum's own smallest step.  The sums are multiplied by 2^-48 at the end.  What is left out of range is
+// too large - elements of 2^104 and more, sums of 2^80 and more, Inf, NaN - and shows in the result as Inf or NaN (an element
+// that becomes Inf leaves remainders of -Inf or NaN, which no other operand turns back into a finite sum): a lane that finds
+// such a sum has its block of 32 x 32 results summed again in plain fp32, skipping zero elements.
 //
 // Zeros are not skipped inside a tile (a 32-window block of 16 channels is never empty when zeros are independent): the
 // rules that choose between this kernel and the element-skipping vector kernel are in sconv_api.hip (piece_first).
@@ -64,13 +68,18 @@ struct PieceCfg {
 
 enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2 };
 
-// Eight fp32 values as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every
-// remainder is exact) as long as no piece leaves bf16's range.
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
+
+// Whether a scaled sum is Inf or NaN.
+__device__ __forceinline__ bool not_finite(float r) { return (__builtin_bit_cast(unsigned, r) & 0x7fffffffu) >= 0x7f800000u; }
+
+// Eight fp32 values times 2^24 as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every
+// remainder is exact) for all values below 2^104.
 __device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = v[2 * i], b = v[2 * i + 1];
+        const float a = v[2 * i] * kUp, b = v[2 * i + 1] * kUp;
         const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
         const float ra = a - __builtin_bit_cast(float, h << 16);
         const float rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
@@ -402,8 +411,8 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
-                const unsigned bits = __builtin_bit_cast(unsigned, r) & 0x7fffffffu;
-                bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && bits != 0u && bits - 0x17800000u >= 0x7f800000u - 0x17800000u;   // not within [2^-80, inf)
+                bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && not_finite(r);
+                acc[i][nb][v] = r * kDown;
             }
             if (__any(bad)) {
                 float* sc = reinterpret_cast<float*>(lds) + wave * 1024 + lane;
@@ -681,8 +690,9 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
 #pragma unroll
             for (int q = 1; q < NW; ++q) s += fl[(q * 16 + v) * 64 + lane];
             const bool ok = pos_ok && k < p.Kg;
-            const unsigned bits = __builtin_bit_cast(unsigned, s) & 0x7fffffffu;
-            if (ok && bits != 0u && bits - 0x17800000u >= 0x7f800000u - 0x17800000u) {   // not within [2^-80, inf): see the top
+            const bool again = ok && not_finite(s);
+            s *= kDown;
+            if (again) {   // out of the pieces' range: see the top
                 const float* wk = w + ((size_t)g * p.Kg + k) * p.L;
                 s = 0.0f;
                 for (int c = c_lo; c < c_hi; ++c)
@@ -745,7 +755,7 @@ __global__ __launch_bounds__(256) void piece_sum_kernel(Problem p, PieceCfg cfg,
     y[(((size_t)n * p.K + (size_t)g * p.Kg + k) * prows + wrow) * pcols + wcol] = r;
 }
 
-// w[K][Cg][T] -> pieces[group][32 filters][16 channels][tap][piece][64 lanes][8 channels] bf16: lane l of a fragment holds
+// w[K][Cg][T] times 2^24 -> pieces[group][32 filters][16 channels][tap][piece][64 lanes][8 channels] bf16: lane l of a fragment holds
 // filter l % 32, channels 8 * (l / 32) + 0..7.  Filters past the group and channels past Cg are zero.
 __global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, int nch16, int T, const float* __restrict__ w,
                                                            u4* __restrict__ out)

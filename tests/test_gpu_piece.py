@@ -118,6 +118,38 @@ def test_values_outside_the_pieces_range(device, monkeypatch, geom, src):
         assert (np.abs(y[ok].astype(np.float64) - r[ok]) <= 1e-4 * scale[ok]).all()
 
 
+@pytest.mark.parametrize("xe,we", [(-134, 0), (-124, 50), (-120, 45), (-140, 70), (0, -134), (45, -126), (-60, -60), (90, -60), (105, -70), (-70, 105),
+                                   (-14, -118)])
+@pytest.mark.parametrize("geom,src,shp", [
+    ("a128x64", "2", (2, 32, 14, 14, 70, 3, 3, 1, 1, 1, None)), ("a128x128", "0", (2, 32, 14, 14, 70, 3, 3, 1, 1, 1, None)),
+    ("a64x128", "1", (2, 32, 14, 14, 70, 3, 3, 1, 1, 1, None)), ("c128x64", "0", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None)),
+    ("c128x64", "2", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None)), ("p128x64", "0", (2, 32, 14, 14, 70, 3, 3, 1, 1, 1, (2, 2, 2))),
+    ("t3x64", "2", (2, 32, 14, 14, 70, 3, 3, 1, 1, 1, None)), ("tp5x128", "2", (1, 20, 14, 14, 40, 5, 5, 1, 2, 1, (2, 2, 2))),
+])
+def test_operands_of_any_size(device, monkeypatch, geom, src, shp, xe, we):
+    """Maps and filters scaled by powers of two down into fp32's subnormals (a few bits left: the operands are what the call is
+    given) and up to where the pieces overflow: as close to the 64-bit sums as ordinary operands are."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(403, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6)
+    x, w = np.ldexp(x, xe), np.ldexp(w, we)
+    xd, wd = to_dev(x), to_dev(w)
+    _pin(monkeypatch, geom, None, src)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd)) if src == "1" else dict(ws=ws)
+    got = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, **kw))
+    got = got.cpu().numpy().astype(np.float64)
+    ref, scale = oracle.conv(x, w, stride, pad, groups, relu=False)
+    if pool:
+        p = torch.nn.functional.max_pool2d
+        ref = p(torch.from_numpy(np.maximum(ref, 0.0)), pool[:2], pool[2]).numpy()
+        scale = p(torch.from_numpy(scale), pool[:2], pool[2]).numpy()
+    # the bound of the test above; results and partial sums below fp32's range round to multiples of 2^-149
+    bound = (C // groups * R * S + 3) * 2.0 ** -24
+    assert np.isfinite(got).all() and (np.abs(got - ref) <= bound * scale + 4 * 2.0 ** -149).all()
+    if np.median(scale) > 2.0 ** -120:
+        assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("shp", [
     (8, 64, 28, 28, 96, 3, 3, 1, 1, 1, None), (2, 256, 14, 14, 256, 3, 3, 1, 1, 1, (2, 2, 2)), (8, 128, 14, 14, 256, 1, 1, 1, 0, 1, None),
     (8, 64, 28, 28, 64, 3, 3, 2, 1, 1, None), (4, 40, 33, 31, 60, 3, 3, 1, 0, 2, None),
