@@ -92,6 +92,15 @@ __device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
     }
 }
 
+// Filters read as stored: a lane's reads are at raw_base (its filter's row, its half of a fragment's 16 channels) plus raw_step,
+// bytes from the block's first filter, all of it in the vector offset, which the buffer's bounds check covers (a scalar offset it
+// may not).  Past the row's last channel lies the next filter, or the tensor's end, from where on reads give zero: either is
+// multiplied by zeros of the map.  No read straddles the end: a 3x3 channel's taps are read by whole rows of three, a 1x1 filter by four
+// channels where their number is a multiple of four, else one by one and never past the row's last.
+__host__ __device__ constexpr int raw_base(int row, int L, int T, int half) { return (row * L + half * 8 * T) * 4; }
+__host__ __device__ constexpr int raw_step(int ch16, int T, int j, int t) { return (ch16 * 16 * T + t) * 4 + j * T * 4; }
+__host__ __device__ constexpr int raw_last(int base, int L, int half) { return base + (L - 1 - half * 8) * 4; }   // 1x1: the row's last channel
+
 template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int XU_, int OCC_>
 struct PGeom {
     static constexpr int MT = MT_, NT = NT_, WM = WM_, WN = WN_, T = T_, CS = CS_, XU = XU_, OCC = OCC_;   // XU: staging units per wavefront
@@ -242,13 +251,13 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
         wvo[0] = half * 8 * T * 256 + (kblk0 & 1) * 128 + col * 4;
     } else {
-        // filters as stored; a filter past the group's last one re-reads the last, what lies past the tensor reads as zero
+        // filters as stored; a filter past the group's last one re-reads the last
         const size_t first = ((size_t)g * p.Kg + (size_t)kb * G::BM) * p.L;
         const size_t left = ((size_t)p.K * p.L - first) * 4;
         wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + first), 0, (int)min(left, (size_t)0x7ffffffc), 0x00020000);
 #pragma unroll
         for (int i = 0; i < MT; ++i)
-            wvo[i] = (min((wm * MT + i) * 32 + col, p.Kg - 1 - kb * G::BM) * p.L + half * 8 * T) * 4;
+            wvo[i] = raw_base(min((wm * MT + i) * 32 + col, p.Kg - 1 - kb * G::BM), p.L, T, half);
     }
     const int wblk = cfg.nch * CS * T * 3072;       // bytes between 32-filter blocks (pieces)
     const int wblk64 = p.Cg * T * 256;              // bytes between 64-filter blocks (fp32)
@@ -270,25 +279,28 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                 for (int j = 0; j < 8; ++j)
                     af[slot][i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[0] + (i & 1) * 128, so + j * T * 256, 0));
             } else if (G::T == 1) {   // eight channels are consecutive
-                const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[i], ch16 * 64, 0));
-                const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[i] + 16, ch16 * 64, 0));
+                const int at = wvo[i] + raw_step(ch16, T, 0, 0);
+                if ((p.Cg & 3) == 0) {
+                    const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at, 0, 0));
+                    const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at + 16, 0, 0));
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    ar[slot][i][j][0] = lo[j];
-                    ar[slot][i][j + 4][0] = hi[j];
+                    for (int j = 0; j < 4; ++j) {
+                        ar[slot][i][j][0] = lo[j];
+                        ar[slot][i][j + 4][0] = hi[j];
+                    }
+                } else {
+                    const int last = raw_last(wvo[i], p.L, half);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        ar[slot][i][j][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, min(at + 4 * j, last), 0, 0));
                 }
             } else {
-                const int so = (ch16 * 16 * T + t) * 4;
+                typedef float f3 __attribute__((ext_vector_type(3)));
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    if (VW == 3) {
-                        typedef float f3 __attribute__((ext_vector_type(3)));
-                        const f3 q = __builtin_bit_cast(f3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo[i] + j * T * 4, so, 0));
+                    const f3 q = __builtin_bit_cast(f3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo[i] + raw_step(ch16, T, j, t), 0, 0));
 #pragma unroll
-                        for (int e = 0; e < 3; ++e) ar[slot][i][j][e % VW] = q[e];
-                    } else {
-                        ar[slot][i][j][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[i] + j * T * 4, so, 0));
-                    }
+                    for (int e = 0; e < 3; ++e) ar[slot][i][j][e % VW] = q[e];
                 }
             }
         }
@@ -1067,26 +1079,29 @@ struct Candidate {
     int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
 };
 
-#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>}
-#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, launch_taps<TGeom<__VA_ARGS__>>}
-const Candidate kCandidates[] = {
-    CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2),
-    CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2),
-    CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2),
-    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2),
-    CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2),
-    CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2),
-    CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2),
-    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 3, 2),
-    // taps, 16-channel groups per chunk, window blocks, pooled, staging units
-    TAPS("t3x64", 9, 2, 2, false, 2),
-    TAPS("t5x64", 25, 1, 2, false, 1),
-    TAPS("t5x128", 25, 1, 4, false, 2),
-    TAPS("t7x64", 49, 1, 2, false, 2),
-    TAPS("t7x96", 49, 1, 3, false, 2),
-    TAPS("tp5x128", 25, 1, 4, true, 2),
-    TAPS("tp7x96", 49, 1, 3, true, 2),
-};
+// The geometries, for the table below and for the test that walks their plans.
+#define PIECE_GEOMETRIES(CAND, TAPS) \
+    /* 32-filter and 32-window blocks of a wavefront, wavefronts along filters and windows, taps, 16-channel groups per chunk, pooled, */ \
+    /* staging units, wavefronts per SIMD */ \
+    CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2) \
+    CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2) \
+    CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2) \
+    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2) \
+    CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2) \
+    CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2) \
+    CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2) \
+    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 3, 2) \
+    /* taps, 16-channel groups per chunk, window blocks, pooled, staging units */ \
+    TAPS("t3x64", 9, 2, 2, false, 2) \
+    TAPS("t5x64", 25, 1, 2, false, 1) \
+    TAPS("t5x128", 25, 1, 4, false, 2) \
+    TAPS("t7x64", 49, 1, 2, false, 2) \
+    TAPS("t7x96", 49, 1, 3, false, 2) \
+    TAPS("tp5x128", 25, 1, 4, true, 2) \
+    TAPS("tp7x96", 49, 1, 3, true, 2)
+#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>},
+#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, launch_taps<TGeom<__VA_ARGS__>>},
+const Candidate kCandidates[] = {PIECE_GEOMETRIES(CAND, TAPS)};
 
 }  // namespace
 

@@ -27,6 +27,9 @@ CASES = [
     ("p128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),      # overlapping pooling windows
     ("c128x64", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None), "1,1,2"),      # 1x1, ragged channels, strips across images
     ("c128x64", (2, 64, 15, 14, 96, 1, 1, 2, 0, 2, None), None),          # 1x1, stride 2, grouped
+    ("c128x64", (2, 35, 9, 7, 129, 1, 1, 1, 0, 1, None), None),           # filters of 35 channels: read one by one, the last block one filter
+    ("c128x64", (1, 146, 15, 14, 258, 1, 1, 1, 0, 2, None), "1,1,2"),
+    ("c128x64", (1, 20, 9, 7, 129, 1, 1, 1, 0, 1, None), None),           # whole fragments past the last channel
     ("q128x64", (2, 256, 14, 10, 96, 1, 1, 1, 0, 1, (2, 2, 2)), None),
     # taps dealt to the wavefronts
     ("t3x64", (1, 33, 7, 7, 33, 3, 3, 1, 1, 1, None), None),              # one channel in the second chunk, one filter in the second block
