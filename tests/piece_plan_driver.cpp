@@ -57,7 +57,7 @@ static void raw_reads(const char* name)
                             const int base = raw_base(row < p.Kg - 1 - kb * G::BM ? row : p.Kg - 1 - kb * G::BM, p.L, G::T, half);
                             for (int t = 0; t < G::T; t += G::VW) {
                                 int at = base + raw_step(ch16, G::T, G::T == 1 ? 0 : j, t), bytes = 12;
-                                if (G::T == 1 && p.Cg % 4 == 0) {
+                                if (G::T == 1 && raw_wide(p.Cg, ch16)) {
                                     at += j / 4 * 16;
                                     bytes = 16;
                                 } else if (G::T == 1) {
@@ -69,7 +69,7 @@ static void raw_reads(const char* name)
                                 EXPECT(at >= 0 && (at + bytes <= left || at >= left), "%s C %d K %d G %d T %d: %d bytes at %d of %lld", name, p.C,
                                        p.K, p.G, G::T, bytes, at, left);
                                 if (ch16 * 16 + half * 8 + j < p.Cg)   // a channel that counts: its own element
-                                    EXPECT(at + (G::T == 1 && p.Cg % 4 == 0 ? j % 4 * 4 : 0) ==
+                                    EXPECT(at + (G::T == 1 && raw_wide(p.Cg, ch16) ? j % 4 * 4 : 0) ==
                                                ((row < p.Kg - 1 - kb * G::BM ? row : p.Kg - 1 - kb * G::BM) * p.L + (ch16 * 16 + half * 8 + j) * G::T + t) * 4,
                                            "%s", name);
                             }
