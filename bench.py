@@ -154,15 +154,16 @@ def flush_buffer():
 _workspaces = {}
 
 
-def lend_workspace() -> None:
+def lend_workspace() -> int:
     """The optional workspace of the library (sconv_set_workspace), lent once per stream: 64 MiB, the
-    most sconv_workspace_size ever asks for.  With it small launches are split across workgroups."""
+    most sconv_workspace_size ever asks for.  With it small launches are split across workgroups.  Returns its bytes."""
     import torch
     import paper_1909_09927_amd as sconv
     key = torch.cuda.current_stream().cuda_stream
     if key not in _workspaces:
         _workspaces[key] = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
         sconv.sconv_set_workspace(_workspaces[key])
+    return _workspaces[key].numel()
 
 
 class DeviceLayer:
@@ -214,8 +215,8 @@ class DeviceLayer:
                 sconv.sconv_tune(xs, ws, layer.stride, layer.pad, layer.groups, layer.pool, relu=True, out=y,
                                  flush=flush_buffer())
             self.tune_wall_s = time.perf_counter() - t0
-        self.variant = sconv.sconv_variant_name(d, bool(layer.pool))
-        self.plan = sconv.sconv_plan_name(d, bool(layer.pool))
+        self.plan = sconv.sconv_launch_name(d, bool(layer.pool), self.workspace.numel())
+        self.variant = self.plan.split("/")[0]
         self.i = 0
 
     def parity(self, seed: int) -> dict:
@@ -688,7 +689,7 @@ def run_split(args) -> None:
             t_fwd = _time(lambda: sconv.sconv_forward(xd, wd, L.stride, L.pad, L.groups, relu=True, out=y),
                           args.steps, args.warmup)
             rec = {"config": cfg["name"], "layer": L.name, "N": N,
-                   "variant": sconv.sconv_variant_name(desc, False),
+                   "variant": sconv.sconv_launch_name(desc, False, lend_workspace()).split("/")[0],
                    "forward_ms": round(t_fwd, 5), "encode_only_ms": round(t_enc, 5),
                    "format": "PECR" if L.pool else "ECR",
                    "encoded_MB": round(rows * (slots * 8 + 4) / 1e6, 1),
@@ -802,7 +803,7 @@ def run_chain(args) -> None:
         else:
             y = sconv.sconv_forward(cur, wd, layer.stride, layer.pad, layer.groups, relu=True, zero_ratio=z, **kw)
         d = sconv.desc_for(cur, wd, layer.stride, layer.pad, layer.groups, layer.pool, True, z, bool(kw))
-        recs.append({"layer": layer.name, "N": N, "plan": sconv.sconv_plan_name(d, bool(layer.pool)),
+        recs.append({"layer": layer.name, "N": N, "plan": sconv.sconv_launch_name(d, bool(layer.pool), lend_workspace()),
                      "input_zero_ratio": round(float((cur == 0).float().mean()), 4),
                      "dense_flops": 2.0 * N * layer.K * layer.OH * layer.OW * layer.Cg * 9})
         outs.append((cur, wd, y))

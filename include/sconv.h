@@ -307,9 +307,9 @@ int sconv_forward_static(const sconv_desc_t* desc, const float* x_dev, const flo
  * "gen" (every other shape with a kernel of at most 15x15; any pooling window of up to 64
  * results; also, for its split across workgroups, 1x1 layers of 512 or more channels per group and few
  * tiles and - with a workspace - 3x3 launches of fewer than 128 tile-workgroups with 64-160 channels per
- * group), "rows" (everything else).  The name is the family that serves the shape; whether its launches run on the piece
- * kernel is decided by cost models at the call (SCONV_TRACE_PLAN=1 prints it), and "piece" itself is named for a plan that
- * sconv_tune found.  A zero ratio in the descriptor's flags (SCONV_ZERO_RATIO) moves
+ * group), "rows" (everything else).  The name is the family that serves the shape; its launches run on the piece kernel
+ * where cost models promise less time, which depends on the call's workspace (sconv_launch_name tells), and "piece" itself is
+ * named here only for a plan that sconv_tune found.  A zero ratio in the descriptor's flags (SCONV_ZERO_RATIO) moves
  * the choice among "quad3x3", "wide3x3" and "tap3x3" for launches that fill the matrix kernels' tiles
  * (see sconv_density).  The environment variable SCONV_VARIANT ("rows", "tap",
  * "quad", "wide", "gen", "piece" or unset) pins the choice for profiling; a plan remembered by sconv_tune comes
@@ -396,12 +396,22 @@ int sconv_tune_import(const char* text);
  * geometry "-": the variant has one; "dense" and names ending in d: the form without zero tests), or
  * "variant/geometry/WxSxP" when P workgroups split a tile's channels, for a tuned descriptor
  * ("variant/model/kept" when tuning found nothing 3 % faster than the static choice, "tap3x3/model:geometry/WxS[xP]/kept"
- * for the vector kernel, whose static plan has a name);
+ * for the vector kernel and "piece/model:..." for the piece kernel, whose static plans have names);
  * "variant/model" for a descriptor that was not tuned ("tap3x3/model:geometry/WxS[xP]": the vector
- * kernel's cost model is asked what it would launch on the default stream, so a split shows).  Nothing is enqueued; asks the HIP runtime
+ * kernel's cost model is asked what it would launch on the default stream, so a split shows; a launch on the piece
+ * kernel instead shows in sconv_launch_name).  Nothing is enqueued; asks the HIP runtime
  * for the current device, as sconv_variant_name does.
  */
 int sconv_plan_name(const sconv_desc_t* desc, int pooled, char* out, int out_size);
+
+/*
+ * Writes the plan that a forward call with ws_bytes of workspace (0: none) launches into out, in the words of
+ * sconv_plan_name and for launches on the piece kernel: "piece/model:geometry/filters" with filters one of
+ * "pieces" (cut by a small kernel into the workspace first), "prepared" and "stored", and "/W+TxS" behind it when W tiles run
+ * whole and T more are split along the channels over S workgroups each.  (The two names above give the family that serves
+ * the shape, whichever kernel its launches run on.)  Nothing is enqueued.
+ */
+int sconv_launch_name(const sconv_desc_t* desc, int pooled, size_t ws_bytes, char* out, int out_size);
 
 /*
  * The SCONV_* environment variables (tuning aids for profiles and tests: SCONV_VARIANT,

@@ -64,6 +64,7 @@ def lib() -> ctypes.CDLL:
         L.sconv_tune_export.argtypes = [ctypes.c_char_p, ctypes.c_size_t, P(ctypes.c_size_t)]
         L.sconv_tune_import.argtypes = [ctypes.c_char_p]
         L.sconv_plan_name.argtypes = [P(Desc), ctypes.c_int, ctypes.c_char_p, ctypes.c_int]
+        L.sconv_launch_name.argtypes = [P(Desc), ctypes.c_int, ctypes.c_size_t, ctypes.c_char_p, ctypes.c_int]
         L.sconv_strerror.argtypes = [ctypes.c_int]
         L.sconv_strerror.restype = ctypes.c_char_p
         L.sconv_workspace_size.argtypes = [P(Desc), ctypes.c_int, P(ctypes.c_size_t)]
@@ -90,7 +91,7 @@ def lib() -> ctypes.CDLL:
                   "sconv_forward_ws", "sconv_pool_forward_ws", "sconv_forward_static", "sconv_forward_bias",
                   "sconv_pool_forward_bias", "sconv_pair_forward", "sconv_density", "sconv_filter_prep_size",
                   "sconv_filter_prep", "sconv_forward_prep", "sconv_pool_forward_prep", "sconv_tune_prep",
-                  "sconv_tune_export", "sconv_tune_import"):
+                  "sconv_tune_export", "sconv_tune_import", "sconv_launch_name"):
             getattr(L, f).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -152,6 +153,16 @@ def sconv_plan_name(desc: Desc, pooled: bool = False) -> str:
     rc = lib().sconv_plan_name(ctypes.byref(desc), 1 if pooled else 0, buf, len(buf))
     if rc:
         raise SconvError(rc, "sconv_plan_name")
+    return buf.value.decode()
+
+
+def sconv_launch_name(desc: Desc, pooled: bool = False, ws_bytes: int = 0) -> str:
+    """The plan a forward call with ws_bytes of workspace launches (the two names above give the family that serves the
+    shape: its launches may run on the piece kernels)."""
+    buf = ctypes.create_string_buffer(96)
+    rc = lib().sconv_launch_name(ctypes.byref(desc), 1 if pooled else 0, ws_bytes, buf, len(buf))
+    if rc:
+        raise SconvError(rc, "sconv_launch_name")
     return buf.value.decode()
 
 

@@ -402,6 +402,13 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     return c < (other > walk ? other : walk);
 }
 
+// The plan that the model of family v makes, by name, where the family has one; with the workspace that is selected.
+static bool describe_model(Variant v, const Problem& p, bool pooled, hipStream_t s, char* out, size_t out_size)
+{
+    if (v == V_TAP) return describe_tap(p, pooled, s, out, out_size);
+    return v == V_PIECE && describe_piece(p, pooled, out, out_size);
+}
+
 // One launch of variant v, with the cost models' decomposition or the pinned one.  No fall-through
 // to other variants.  Caller holds g_lock.
 static int launch_variant(Variant v, const PlanPin* pin, const Problem& p, bool pooled, const float* x,
@@ -433,6 +440,17 @@ static bool have_workspace(hipStream_t s)
     return split_workspace_lent(s, false);
 }
 
+// What the static rules and the piece kernels' model launch on stream s; *static_pin as for choose.  Leaves the stream's
+// workspace selected.
+static Variant decide(const Problem& p, bool pooled, hipStream_t s, PlanPin* static_pin)
+{
+    const Variant v = choose(p, pooled, have_workspace(s), static_pin, p.zhint);
+    split_scratch_select(s);
+    if (!piece_first(p, pooled, v)) return v;
+    memset(static_pin, 0, sizeof(*static_pin));
+    return V_PIECE;
+}
+
 static int run(const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t s)
 {
     // the launchers cache occupancy answers and attribute opt-ins in static variables: planning and
@@ -443,18 +461,12 @@ static int run(const Problem& p, bool pooled, const float* x, const float* w, fl
         if (rc != SCONV_EUNSUPPORTED) return rc;
     }
     PlanPin sp;
-    const float z = p.zhint;
-    Variant v = choose(p, pooled, have_workspace(s), &sp, z);
+    Variant v = decide(p, pooled, s, &sp);
     int rc = SCONV_EUNSUPPORTED;
-    split_scratch_select(s);
-    if (piece_first(p, pooled, v)) {
-        rc = launch_variant(V_PIECE, nullptr, p, pooled, x, w, y, s);
-        if (rc != SCONV_EUNSUPPORTED) return rc;
-    }
     if (sp.geom[0]) {
         rc = launch_variant(v, &sp, p, pooled, x, w, y, s);
         if (rc != SCONV_EUNSUPPORTED) return rc;
-        v = choose(p, pooled, false, nullptr, z);      // e.g. the workspace is too small for this layer
+        v = choose(p, pooled, false, nullptr, p.zhint);      // e.g. the workspace is too small for this layer
     }
     if (v == V_PIECE) rc = launch_variant(V_PIECE, nullptr, p, pooled, x, w, y, s);
     if (v == V_PW) rc = launch_variant(V_PW, nullptr, p, pooled, x, w, y, s);
@@ -567,12 +579,7 @@ static int tune(const Problem& p, bool pooled, const float* x, const float* w, f
     };
     // the static rules' own choice comes first: it stays unless something measures clearly faster
     PlanPin sp;
-    Variant v_static = choose(p, pooled, have_workspace(s), &sp, p.zhint);
-    split_scratch_select(s);
-    if (piece_first(p, pooled, v_static)) {
-        v_static = V_PIECE;
-        memset(&sp, 0, sizeof(sp));
-    }
+    Variant v_static = decide(p, pooled, s, &sp);
     bool have_static = try_one(v_static, sp.geom[0] ? &sp : nullptr);
     if (!have_static && sp.geom[0]) {
         v_static = choose(p, pooled);
@@ -648,10 +655,10 @@ static int tune(const Problem& p, bool pooled, const float* x, const float* w, f
         best.pin = c.pin;
         best.pinned = c.pinned;
         if (have_static && i == 0) {
-            // (the vector kernel's static plan by name, so that records show what was kept)
+            // (the vector and piece kernels' static plans by name, so that records show what was kept)
             char detail[32];
             split_scratch_select(s);
-            if (c.v == V_TAP && !c.pinned && describe_tap(p, pooled, s, detail, sizeof(detail)))
+            if (!c.pinned && describe_model(c.v, p, pooled, s, detail, sizeof(detail)))
                 snprintf(best.name, sizeof(best.name), "%s/model:%s/kept", variant_name(c.v), detail);
             else
                 snprintf(best.name, sizeof(best.name), "%s/model/kept", variant_name(c.v));
@@ -1143,6 +1150,33 @@ extern "C" int sconv_plan_name(const sconv_desc_t* desc, int pooled, char* out, 
     char detail[40];
     split_scratch_select(nullptr);   // the default stream's workspace, as for a launch there
     if (v == V_TAP && describe_tap(p, pooled != 0, nullptr, detail, sizeof(detail)))
+        snprintf(out, (size_t)out_size, "%s/model:%s", variant_name(v), detail);
+    else
+        snprintf(out, (size_t)out_size, "%s/model", variant_name(v));
+    return SCONV_OK;
+}
+
+extern "C" int sconv_launch_name(const sconv_desc_t* desc, int pooled, size_t ws_bytes, char* out, int out_size)
+{
+    if (!out || out_size <= 0) return SCONV_EINVAL;
+    Problem p;
+    int rc = fill_problem(desc, pooled != 0, &p);
+    if (rc) return rc;
+    mark_prepared_for_naming(desc, pooled != 0, &p);
+    std::lock_guard<std::mutex> lock(g_lock);
+    if (const Tuned* t = tuned_for(p, pooled != 0)) {
+        snprintf(out, (size_t)out_size, "%s", t->name);
+        return SCONV_OK;
+    }
+    // plan as for a call that brings this much workspace (nothing is launched: the address only has to be non-null)
+    split_scratch_given(ws_bytes ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, ws_bytes, true);
+    PlanPin sp;
+    Variant v = decide(p, pooled != 0, nullptr, &sp);
+    char detail[40];
+    const bool named = describe_model(v, p, pooled != 0, nullptr, detail, sizeof(detail));
+    split_scratch_given(nullptr, 0, false);
+    if (v == V_PIECE && !named) v = V_ROWS;   // pinned, and no plan: as at a launch
+    if (named)
         snprintf(out, (size_t)out_size, "%s/model:%s", variant_name(v), detail);
     else
         snprintf(out, (size_t)out_size, "%s/model", variant_name(v));

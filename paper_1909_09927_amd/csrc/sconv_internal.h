@@ -88,6 +88,8 @@ bool piece_supported(const Problem& p, bool pooled);
 double piece_cost(const Problem& p, bool pooled);
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                  hipStream_t stream);
+// that plan by name: "geometry/form of the filters", and "/whole tiles+split tiles x slices" where it has split ones
+bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size);
 
 // A fixed decomposition in place of the cost models' choice: candidate geometry inside a kernel
 // variant, wavefronts per workgroup, channel slices.  Set by the dispatcher (under its lock) around

@@ -1181,6 +1181,18 @@ double piece_cost(const Problem& p, bool pooled)
     return c.cand ? c.plan.cost : -1.0;
 }
 
+bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
+{
+    const Choice& c = choose_plan(p, pooled);
+    if (!c.cand) return false;
+    const char* const forms[] = {"pieces", "prepared", "stored"};
+    if (c.plan.ntail)
+        snprintf(out, out_size, "%s/%s/%d+%dx%d", c.cand->name, forms[c.plan.src], c.plan.cfg.whole, c.plan.ntail, c.plan.cfg.nss);
+    else
+        snprintf(out, out_size, "%s/%s", c.cand->name, forms[c.plan.src]);
+    return true;
+}
+
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t stream)
 {
     const Choice& c = choose_plan(p, pooled);

@@ -89,6 +89,7 @@ int main()
         EXPECT(sconv_density(&b, ffake, (unsigned long long*)fake, nullptr) == SCONV_EINVAL);
         EXPECT(sconv_variant_name(&b, 0) == nullptr);
         EXPECT(sconv_plan_name(&b, 0, name, sizeof(name)) == SCONV_EINVAL);
+        EXPECT(sconv_launch_name(&b, 0, 0, name, sizeof(name)) == SCONV_EINVAL);
         EXPECT(sconv_workspace_size(&b, 0, &bytes) == SCONV_EINVAL);
         EXPECT(sconv_filter_prep_size(&b, &bytes) == SCONV_EINVAL);
     }
@@ -130,6 +131,8 @@ int main()
                 EXPECT(sconv_plan_name(&q, pooled, name, sizeof(name)) == SCONV_OK && strlen(name) > 2);
                 EXPECT(sconv_plan_name(&q, pooled, name, 4) == SCONV_OK && strlen(name) <= 3);   // truncated, terminated
                 EXPECT(sconv_workspace_size(&q, pooled, &bytes) == SCONV_OK);
+                for (size_t ws : {size_t(0), bytes / 2, bytes})   // (the piece kernels' planner too)
+                    EXPECT(sconv_launch_name(&q, pooled, ws, name, sizeof(name)) == SCONV_OK && strlen(name) > 2);
                 EXPECT(sconv_filter_prep_size(&q, &bytes) == SCONV_OK);
             }
         }

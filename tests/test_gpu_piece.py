@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import conftest
 import oracle
 import workloads
 import paper_1909_09927_amd as sconv
@@ -169,3 +170,33 @@ def test_default_plans(device, monkeypatch, shp):
     torch.cuda.synchronize()
     assert torch.equal(a, b)
     assert np.linalg.norm((a - c).cpu().numpy()) <= 1e-6 * np.linalg.norm(c.cpu().numpy())
+
+
+@pytest.mark.parametrize("shp,ws,z", [
+    ((4, 128, 28, 28, 256, 3, 3, 1, 1, 1, None), False, None), ((4, 128, 28, 28, 256, 3, 3, 1, 1, 1, None), True, None),
+    ((8, 64, 28, 28, 64, 3, 3, 2, 1, 1, None), True, None), ((8, 512, 14, 14, 256, 1, 1, 1, 0, 1, (2, 2, 2)), True, None),
+    ((4, 256, 28, 28, 256, 3, 3, 1, 1, 1, None), True, 0.5), ((4, 256, 28, 28, 256, 3, 3, 1, 1, 1, None), True, 0.95),
+    ((1, 16, 28, 28, 32, 3, 3, 1, 1, 1, None), True, None), ((4, 48, 7, 7, 128, 5, 5, 1, 2, 1, None), False, None),
+])
+def test_launch_name_is_what_runs(device, monkeypatch, capfd, shp, ws, z):
+    """The piece kernel says on stderr what it launches (SCONV_TRACE_PLAN): that, or nothing, is what sconv_launch_name named."""
+    monkeypatch.setenv("SCONV_TRACE_PLAN", "1")
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(404, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.7)
+    xd, wd = to_dev(x), to_dev(w)
+    d = sconv.desc_for(xd, wd, stride, pad, groups, pool, True, z)
+    wsb = torch.empty(sconv.sconv_workspace_size(d, pool is not None), dtype=torch.uint8, device="cuda") if ws else None
+    sconv.sconv_env_refresh()
+    name = sconv.sconv_launch_name(d, pool is not None, wsb.numel() if ws else 0)
+    sconv.sconv_set_workspace(None)       # ws=None would take the lent one
+    try:
+        capfd.readouterr()
+        if pool:
+            sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, ws=wsb, zero_ratio=z)
+        else:
+            sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=wsb, zero_ratio=z)
+        torch.cuda.synchronize()
+    finally:
+        sconv.sconv_set_workspace(conftest._WORKSPACE)
+    said = [line.split()[1] for line in capfd.readouterr().err.splitlines() if line.startswith("piece ")]
+    assert said == ([name.split(":")[1].split("/")[0] + ":"] if name.startswith("piece/model:") else [])

@@ -137,6 +137,33 @@ def test_too_large_tensors_are_unsupported():
     assert L.sconv_forward(ctypes.byref(d), p, p, p, None) == sconv.SCONV_EUNSUPPORTED
 
 
+def test_launch_name_names_the_kernel_that_runs():
+    """sconv_variant_name gives the family that serves a shape; sconv_launch_name the kernel its launches run on, which
+    depends on the call's workspace."""
+    name = lambda *a, ws=0, pooled=False, **k: sconv.sconv_launch_name(sconv.make_desc(*a, **k), pooled, ws)
+    s2 = sconv.make_desc(32, 128, 56, 56, 128, 3, 3, 2, 1)
+    assert sconv.sconv_variant_name(s2) == "wide3x3" and sconv.sconv_plan_name(s2) == "wide3x3/model"
+    assert sconv.sconv_launch_name(s2) == "wide3x3/model"
+    assert sconv.sconv_launch_name(s2, False, sconv.sconv_workspace_size(s2)).startswith("piece/model:s128x64/pieces")
+    assert name(32, 896, 14, 14, 896, 3, 3, 1, 1, 7).startswith("piece/model:a128x64/stored")
+    # a small launch the vector kernel leaves to the tap-dealing kernel where there is no workspace to split it
+    d = sconv.make_desc(4, 128, 28, 28, 256, 3, 3, 1, 1, relu=True)
+    assert sconv.sconv_variant_name(d) == "tap3x3"
+    assert sconv.sconv_launch_name(d).startswith("piece/model:t3x64/stored")
+    # too small, and a shape the piece kernels have no plan for: the family, as the other two names have it
+    assert name(1, 16, 28, 28, 32, 3, 3, 1, 1).startswith("tap3x3/model:")
+    assert name(1, 16, 56, 56, 64, 17, 17, 1, 2) == "rows/model"
+    # the zero ratio decides
+    assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.5, ws=64 << 20).startswith("piece/model:")
+    assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.95, ws=64 << 20) == "quad3x3/model"
+    assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.5, ws=64 << 20, prepared=True).startswith("piece/model:a128x64/prepared")
+    buf = ctypes.create_string_buffer(8)
+    L = sconv.lib()
+    assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, buf, 6) == 0 and buf.value == b"wide3"
+    assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, None, 6) == sconv.SCONV_EINVAL
+    assert L.sconv_launch_name(ctypes.byref(sconv.Desc()), 0, 0, buf, 6) == sconv.SCONV_EINVAL
+
+
 def test_strerror_and_variant_name():
     assert sconv.strerror(0) == "success"
     assert "invalid" in sconv.strerror(sconv.SCONV_EINVAL)
