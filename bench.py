@@ -317,7 +317,8 @@ def time_layer(dl: DeviceLayer, iters: int, warmup: int) -> float:
 def layer_record(dl: DeviceLayer, work: dict, ms: float) -> dict:
     t = ms * 1e-3
     t_hbm = work["alg_bytes"] / (HBM_PEAK_GBS * 1e9)
-    t_valu = work["nz_flops"] / (FP32_VECTOR_PEAK_TF * 1e12)
+    # the pipe the plan runs on (the fp32 matrix and vector peaks are the same figure), as in the headline's roofline
+    t_pipe = work["nz_flops"] / ((PIECE_PEAK_TF if dl.variant == "piece" else FP32_VECTOR_PEAK_TF) * 1e12)
     # what the plan really issues: a kernel that tests groups of g elements multiplies every element of a
     # group that holds a nonzero (independent zeros: a share z^g of the groups is skipped); the forms without
     # any test (geometry names ending in d, "dense") issue everything - the dense fallback on the matrix pipe
@@ -346,8 +347,8 @@ def layer_record(dl: DeviceLayer, work: dict, ms: float) -> dict:
         "hbm_frac": round(work["alg_bytes"] / t / 1e9 / HBM_PEAK_GBS, 4),
         "valu_frac": round(work["nz_flops"] / t / 1e12 / FP32_VECTOR_PEAK_TF, 4),
         "frac_of_unpacked_fp32_peak": round(work["nz_flops"] / t / 1e12 / FP32_UNPACKED_PEAK_TF, 4),
-        "bound": "hbm" if t_hbm >= t_valu else ("mfma" if dl.variant in MFMA_VARIANTS else "alu"),
-        "bound_frac": round(max(t_hbm, t_valu) / t, 4),
+        "bound": "hbm" if t_hbm >= t_pipe else ("mfma" if dl.variant in MFMA_VARIANTS else "alu"),
+        "bound_frac": round(max(t_hbm, t_pipe) / t, 4),
     }
 
 

@@ -69,3 +69,16 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "one GPU" in (r.stderr + r.stdout)
+
+
+def test_layer_records_divide_by_the_peak_of_the_pipe_the_plan_runs_on():
+    """bench.py: a piece plan against a sixth of the bf16 matrix peak, as its roofline line has it; the others against 157.3."""
+    from types import SimpleNamespace
+    import bench
+    work = {"alg_bytes": 1e6, "nz_flops": 1e10, "dense_flops": 3e10, "zero_ratio": 0.7}
+    for variant, plan, peak in (("piece", "piece/model:a128x64/stored", 2500.0 / 6), ("quad3x3", "quad3x3/model", 157.3), ("tap3x3", "tap3x3/model", 157.3)):
+        dl = SimpleNamespace(layer=SimpleNamespace(name="x"), N=1, variant=variant, plan=plan)
+        r = bench.layer_record(dl, work, 0.1)
+        assert r["bound"] == ("alu" if variant == "tap3x3" else "mfma")
+        assert r["bound_frac"] == round(100.0 / peak, 4)       # 1e10 flops in 0.1 ms are 100 TFLOP/s
+        assert r["dense_fallback"] == (variant == "piece")
