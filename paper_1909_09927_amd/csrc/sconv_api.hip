@@ -366,8 +366,11 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
 // Whether a launch of family v runs on the piece kernels instead: when their cost model promises less time than
 // these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
-// any ratio), @28x28 at batch 8 190 at 75 % (165); a fixed share of 28 % where the ratio is unknown, and about 8 us
-// for the filter transposition of large launches.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
+// any ratio), @28x28 at batch 8 190 at 75 % (165) - and about 8 us for the filter transposition of large launches.  Where the ratio is
+// unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.6 (512
+// @28x28 at batch 8 with a workspace, vector / piece kernel: 331 / 208 us at 50 % zeros, 239 / 208 at 70, 172 / 207 at 85, 121 / 191 at
+// 95; 256 @56x56 304 / 162, 232 / 162, 182 / 160, 133 / 136).  Of 120 random layers and 21 of the benchmark's without a ratio, those of
+// this family that lost up to 1.6x from 85 % on stay; the others - short launches, and 256 @56x56 - keep the piece kernels.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
 // on), 80 (quad1x1), 75 (gen).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
 // splits it: without a workspace 41 us for 256 channels on the vector kernel (23 on the taps kernel), 8 + 0.029 per column on
 // gen (48 channels of 5x5 43 us against 13, 64 of 7x7 98 against 25), 0.27 per channel on wide3x3.
@@ -383,8 +386,8 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     double other, walk = 0.0;
     switch (v) {
     case V_TAP: {
-        const double nz = p.zhint < 0.0f ? 0.28 : 1.0 - p.zhint;
-        other = 14.0 + gf * (2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+        const double nz = p.zhint < 0.0f ? 0.1 : 1.0 - p.zhint;
+        other = 14.0 + gf * (p.zhint < 0.0f ? 4.6 : 2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
         if (!can_split && !p.wprep) walk = 10.0 + p.Cg * (0.06 + 0.14 * nz);
         break;
     }

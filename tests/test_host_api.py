@@ -146,8 +146,8 @@ def test_launch_name_names_the_kernel_that_runs():
     assert sconv.sconv_launch_name(s2) == "wide3x3/model"
     assert sconv.sconv_launch_name(s2, False, sconv.sconv_workspace_size(s2)).startswith("piece/model:s128x64/pieces")
     assert name(32, 896, 14, 14, 896, 3, 3, 1, 1, 7).startswith("piece/model:a128x64/stored")
-    # a small launch the vector kernel leaves to the tap-dealing kernel where there is no workspace to split it
-    d = sconv.make_desc(4, 128, 28, 28, 256, 3, 3, 1, 1, relu=True)
+    # a short launch that the vector kernel leaves to the tap-dealing kernel
+    d = sconv.make_desc(1, 256, 14, 14, 256, 3, 3, 1, 1, relu=True)
     assert sconv.sconv_variant_name(d) == "tap3x3"
     assert sconv.sconv_launch_name(d).startswith("piece/model:t3x64/stored")
     # too small, and a shape the piece kernels have no plan for: the family, as the other two names have it
@@ -162,6 +162,30 @@ def test_launch_name_names_the_kernel_that_runs():
     assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, buf, 6) == 0 and buf.value == b"wide3"
     assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, None, 6) == sconv.SCONV_EINVAL
     assert L.sconv_launch_name(ctypes.byref(sconv.Desc()), 0, 0, buf, 6) == sconv.SCONV_EINVAL
+
+
+@pytest.mark.parametrize("shp,pool,ws", [
+    ((8, 512, 28, 28, 512, 3, 3, 1, 1), None, True), ((8, 512, 28, 28, 512, 3, 3, 1, 1), None, False),
+    ((8, 512, 14, 14, 512, 3, 3, 1, 1), None, True), ((32, 512, 14, 14, 512, 3, 3, 1, 1), None, False),
+    ((32, 512, 7, 7, 512, 3, 3, 1, 1), None, True), ((8, 128, 56, 56, 128, 3, 3, 1, 1), None, True),
+    ((8, 512, 14, 14, 512, 3, 3, 1, 1), (2, 2, 2), True), ((8, 256, 28, 28, 256, 3, 3, 1, 1), (2, 2, 2), True),
+])
+def test_large_calls_without_a_ratio_keep_the_kernel_that_skips_elements(shp, pool, ws):
+    """On a sparse map (85 % zeros and more) the piece kernel takes 1.1-1.6x the vector kernel's time on these layers; without a
+    reported ratio the library cannot know, and a reported one of 50 % moves them."""
+    k = dict(groups=1, pool=pool, relu=True)
+    d = sconv.make_desc(*shp, **k)
+    bytes_ = sconv.sconv_workspace_size(d, pool is not None) if ws else 0
+    assert sconv.sconv_launch_name(d, pool is not None, bytes_).startswith("tap3x3/")
+    assert sconv.sconv_launch_name(sconv.make_desc(*shp, zero_ratio=0.5, **k), pool is not None, bytes_).startswith("piece/")
+
+
+@pytest.mark.parametrize("shp", [(1, 512, 7, 7, 512, 3, 3, 1, 1), (1, 256, 14, 14, 256, 3, 3, 1, 1)])
+def test_short_calls_without_a_ratio_run_on_the_piece_kernel(shp):
+    """A batch-1 layer: the vector kernel's time is the walk of its few workgroups at any ratio."""
+    d = sconv.make_desc(*shp, relu=True)
+    for ws in (0, sconv.sconv_workspace_size(d)):
+        assert sconv.sconv_launch_name(d, False, ws).startswith("piece/model:t3x64/")
 
 
 def test_strerror_and_variant_name():
