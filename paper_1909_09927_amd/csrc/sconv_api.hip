@@ -371,7 +371,10 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
 // @28x28 at batch 8 with a workspace, vector / piece kernel: 331 / 208 us at 50 % zeros, 239 / 208 at 70, 172 / 207 at 85, 121 / 191 at
 // 95; 256 @56x56 304 / 162, 232 / 162, 182 / 160, 133 / 136).  Of 120 random layers and 21 of the benchmark's without a ratio, those of
 // this family that lost up to 1.6x from 85 % on stay; the others - short launches, and 256 @56x56 - keep the piece kernels.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
-// on), 80 (quad1x1), 75 (gen).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
+// on), 75 (gen).  quad1x1: 6.6 + gf * 10.2, and what the piece kernel stores on top of its model at 0.15 us/MB, which 1x1 layers are too
+// short to hide (plain calls, quad1x1 / piece kernel: 512 -> 256 @28x28 at batch 16 43.9 / 35.3 us, 512 -> 2048 @7x7 at batch 32 51.1 /
+// 46.1, but 64 -> 256 @56x56 at batch 32 53.8 / 59.5, 1024 -> 256 @14x14 45.4 / 51.1, 256 -> 256 @28x28 at batch 8 17.0 / 18.6, 128 -> 256
+// 11.9 / 14.1).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
 // splits it: without a workspace 41 us for 256 channels on the vector kernel (23 on the taps kernel), 8 + 0.029 per column on
 // gen (48 channels of 5x5 43 us against 13, 64 of 7x7 98 against 25), 0.27 per channel on wide3x3.
 // Caller holds g_lock and has selected the stream's workspace.
@@ -380,7 +383,7 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     if (v == V_ROWS || env_value("SCONV_VARIANT")) return false;
     const double gf = 2e-9 * p.K * (double)p.L * p.N * (pooled ? (double)p.PH * p.PW * p.ph * p.pw : (double)p.OH * p.OW);
     if (gf < 0.03) return false;
-    const double c = piece_cost(p, pooled);
+    double c = piece_cost(p, pooled);
     if (c < 0.0) return false;
     const bool can_split = split_scratch_possible(nullptr) && split_scratch_bytes() > 0;
     double other, walk = 0.0;
@@ -396,7 +399,10 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
         other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3);
         walk = 8.0 + 0.2 * p.Cg;
         break;
-    case V_PW: other = 8.0 + gf * 12.0; break;
+    case V_PW:
+        other = 6.6 + gf * 10.2;
+        c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
+        break;
     default:
         other = 12.0 + gf * 13.0;
         if (!can_split) walk = 8.0 + 0.029 * p.L;

@@ -188,6 +188,16 @@ def test_short_calls_without_a_ratio_run_on_the_piece_kernel(shp):
         assert sconv.sconv_launch_name(d, False, ws).startswith("piece/model:t3x64/")
 
 
+@pytest.mark.parametrize("shp,piece", [
+    ((8, 64, 56, 56, 128, 1, 1), False), ((8, 128, 28, 28, 256, 1, 1), False), ((8, 256, 28, 28, 256, 1, 1), False),
+    ((32, 64, 56, 56, 256, 1, 1), False), ((32, 1024, 14, 14, 256, 1, 1), False), ((32, 256, 56, 56, 64, 1, 1), False),
+    ((16, 512, 28, 28, 256, 1, 1), True), ((32, 512, 28, 28, 128, 1, 1), True), ((32, 512, 7, 7, 2048, 1, 1), True),
+])
+def test_one_by_one_layers_run_on_the_faster_kernel(shp, piece):
+    """1x1 layers on both kernels: the piece kernel took 1.04-1.18x quad1x1's time on the first five and 0.8-0.9x on the last three."""
+    assert sconv.sconv_launch_name(sconv.make_desc(*shp, relu=True)).startswith("piece/model:" if piece else "quad1x1/model")
+
+
 def test_strerror_and_variant_name():
     assert sconv.strerror(0) == "success"
     assert "invalid" in sconv.strerror(sconv.SCONV_EINVAL)
