@@ -872,11 +872,9 @@ bool choose_strips(const Problem& p, bool pooled, int BN, int PXMAX, PieceCfg& c
 {
     const int cols = pooled ? p.PW : c.flat ? p.OH * p.OW : p.OW, rows = pooled ? p.PH : c.flat ? 1 : p.OH;
     double best = 0.0;
-    for (int m = 1; m <= cols; ++m) {
-        const int TW = (cols + m - 1) / m;
-        if (TW < 4 && m > 1) break;
-        if (TW > BN) continue;
+    for (int TW = cols < BN ? cols : BN; TW >= (cols < 4 ? cols : 4); --TW) {
         const int strips = (cols + TW - 1) / TW;
+        if ((cols + strips - 1) / strips != TW) continue;   // as many strips of fewer columns do
         const long long px = stage_positions(p, pooled, c.flat, BN, TW);
         if (px > PXMAX) continue;
         const long long run = (long long)p.N * rows * TW * (pooled ? 4 : 1), nt = (run + BN - 1) / BN;
@@ -1123,22 +1121,27 @@ struct Choice {
     Plan plan;
 };
 
-// The cheapest plan by the model.  Walking the candidates takes tens of microseconds, so the last plans are kept by what
-// they depend on: the shape, the room in the workspace, whether the filters come prepared.  (Under the dispatcher's lock.)
+// The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
+// kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, a geometry that
+// sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
+// dispatcher's lock; the reference lasts until the next call.)
 const Choice& choose_plan(const Problem& p, bool pooled)
 {
     struct Key {
-        int v[18];
         size_t ws;
+        int v[19];
+        PlanPin pin;
     };
-    struct Entry {
-        Key key;
-        Choice choice;
+    static_assert(sizeof(Key) == sizeof(size_t) + 19 * sizeof(int) + sizeof(PlanPin), "compared as bytes: no padding");
+    struct Set {
+        Key key[4];
+        Choice choice[4];
+        int used, next;
     };
-    constexpr int kKept = 64;
-    static Entry kept[kKept];
-    static int used = 0, next = 0;
+    constexpr size_t kSets = 512;
+    static Set kept[kSets];
     static Choice pinned;
+    const PlanPin* tuned = current_pin();
     const char* pin = pinned_geom("SCONV_PIECE_GEOM");
     auto walk = [&](Choice& out) {
         out = Choice();
@@ -1153,24 +1156,33 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             }
         }
     };
-    if (current_pin() || pin || env_value("SCONV_PIECE_SPLIT") || env_value("SCONV_PIECE_SRC")) {
+    if ((pin && !tuned) || env_value("SCONV_PIECE_SPLIT") || env_value("SCONV_PIECE_SRC")) {
         walk(pinned);
         return pinned;
     }
     Key k;
     memset(&k, 0, sizeof(k));
-    const int v[18] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
-                       pooled ? 1 : 0, p.wprep ? 1 : 0, 0, 0, 0};
+    const int v[19] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
+                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0};
     memcpy(k.v, v, sizeof(v));
     k.ws = usable_workspace(p, pooled);
-    for (int i = 0; i < used; ++i)
-        if (!memcmp(&kept[i].key, &k, sizeof(k))) return kept[i].choice;
-    Entry& e = kept[next];
-    next = (next + 1) % kKept;
-    if (used < kKept) ++used;
-    e.key = k;
-    walk(e.choice);
-    return e.choice;
+    if (tuned) {
+        snprintf(k.pin.geom, sizeof(k.pin.geom), "%s", tuned->geom);
+        k.pin.nwv = tuned->nwv;
+        k.pin.ncs = tuned->ncs;
+        k.pin.nss = tuned->nss;
+    }
+    unsigned long long h = 14695981039346656037ull;   // FNV-1a
+    for (size_t i = 0; i < sizeof(k); ++i) h = (h ^ reinterpret_cast<const unsigned char*>(&k)[i]) * 1099511628211ull;
+    Set& set = kept[(h ^ (h >> 32)) % kSets];
+    for (int i = 0; i < set.used; ++i)
+        if (!memcmp(&set.key[i], &k, sizeof(k))) return set.choice[i];
+    const int at = set.next;
+    set.next = (at + 1) % 4;
+    if (set.used < 4) ++set.used;
+    memcpy(&set.key[at], &k, sizeof(k));
+    walk(set.choice[at]);
+    return set.choice[at];
 }
 
 }  // namespace

@@ -1,6 +1,8 @@
 // The piece kernels' planner and index arithmetic, walked on the CPU under AddressSanitizer + UndefinedBehaviorSanitizer (built and
-// run by tests/test_host_sanitizers.py: the host side of sconv_piece.hip with everything else of the library, no device code, no GPU).
+// run by tests/test_host_sanitizers.py: the host side of the dispatcher and of sconv_piece.hip, included here, with everything else of the
+// library, no device code, no GPU).
 // Prints "ok" and exits 0 when every expectation holds.
+#include "sconv_api.hip"
 #include "sconv_piece.hip"
 
 #include <random>
@@ -83,8 +85,74 @@ static void taps_have_no_raw_reads(const char*)
 {
 }
 
+// The strips are the best of every number of strips of four or more columns.
+static void strips_are_the_best_of_all(int n)
+{
+    for (int i = 0; i < n; ++i) {
+        Problem p;
+        const int T = std::vector<int>{1, 9, 25, 49}[pick(0, 3)], BN = 64 * pick(1, 2), PXMAX = 64 * pick(1, 6);
+        const bool pooled = pick(0, 2) == 0;
+        if (!random_problem(T, pooled, &p)) continue;
+        PieceCfg c = {}, d = {};
+        c.flat = d.flat = T == 1 && p.stride == 1 && !pooled;
+        const bool found = choose_strips(p, pooled, BN, PXMAX, c);
+        const int cols = pooled ? p.PW : d.flat ? p.OH * p.OW : p.OW, rows = pooled ? p.PH : d.flat ? 1 : p.OH;
+        double best = 0.0;
+        for (int m = 1; m <= cols; ++m) {
+            const int TW = (cols + m - 1) / m, strips = (cols + TW - 1) / TW;
+            if (TW < 4 && m > 1) break;
+            const long long px = stage_positions(p, pooled, d.flat, BN, TW), run = (long long)p.N * rows * TW * (pooled ? 4 : 1);
+            if (TW > BN || px > PXMAX) continue;
+            const long long nt = (run + BN - 1) / BN;
+            const double cost = (double)nt * strips * (BN * (1.0 + 0.5 / TW) + px * 0.02);
+            if (best != 0.0 && cost >= best) continue;
+            best = cost;
+            d.TW = TW;
+            d.strips = strips;
+            d.nrun = (int)run;
+            d.ntiles = (int)nt;
+            d.px = (int)px;
+        }
+        EXPECT(found == (best != 0.0), "T %d %dx%d", T, p.OH, p.OW);
+        if (found) EXPECT(c.TW == d.TW && c.strips == d.strips && c.nrun == d.nrun && c.ntiles == d.ntiles && c.px == d.px, "T %d %dx%d", T, p.OH, p.OW);
+    }
+}
+
+// A network's plans are all kept: by shape, with a workspace and without, and with the geometry that tuning found.
+static void plans_are_kept()
+{
+    std::vector<Problem> net;
+    for (int i = 0; i < 100; ++i) {
+        sconv_desc_t d = {8, 64 + 32 * i, 56 >> i % 3, 56 >> i % 3, 128, i % 4 ? 1 : 3, i % 4 ? 1 : 3, 1, i % 4 ? 0 : 1, 1, 0, 0, 0, SCONV_RELU};
+        Problem p;
+        EXPECT(fill_problem(&d, false, &p) == SCONV_OK, "layer %d", i);
+        net.push_back(p);
+    }
+    PlanPin pins[2];
+    memset(pins, 0, sizeof(pins));
+    snprintf(pins[0].geom, sizeof(pins[0].geom), "c128x64");
+    snprintf(pins[1].geom, sizeof(pins[1].geom), "a128x64");
+    pins[0].nwv = pins[1].nwv = 4;
+    pins[0].ncs = pins[1].ncs = 1;
+    for (int pass = 0; pass < 2; ++pass)
+        for (size_t i = 0; i < net.size(); ++i)
+            for (const PlanPin* pin : {(const PlanPin*)nullptr, (const PlanPin*)&pins[0], (const PlanPin*)&pins[1]}) {
+                g_pin = pin;
+                split_scratch_given(i % 2 ? nullptr : reinterpret_cast<void*>(uintptr_t(256)), i % 2 ? 0 : size_t(64) << 20, true);
+                split_scratch_select(nullptr);
+                double& cost = const_cast<Choice&>(choose_plan(net[i], false)).plan.cost;
+                const double mark = 1e6 + i * 3.0 + (pin ? pin - pins + 1 : 0);   // (a plan that is walked again loses it)
+                if (pass) EXPECT(cost == mark, "layer %zu, geometry %s", i, pin ? pin->geom : "any");
+                cost = mark;
+            }
+    g_pin = nullptr;
+    split_scratch_given(nullptr, 0, false);
+}
+
 int main()
 {
+    strips_are_the_best_of_all(4000);
+    plans_are_kept();
 #define WALK_PIECE(NAME, ...) raw_reads<PGeom<__VA_ARGS__>>(NAME);
 #define WALK_TAPS(NAME, ...) taps_have_no_raw_reads<TGeom<__VA_ARGS__>>(NAME);
     PIECE_GEOMETRIES(WALK_PIECE, WALK_TAPS)
