@@ -112,7 +112,7 @@ def zero_ratio_flag(zero_ratio: Optional[float]) -> int:
 
 def make_desc(N, C, H, W, K, R, S, stride=1, pad=0, groups=1, pool: Optional[Tuple[int, int, int]] = None,
               relu: bool = False, zero_ratio: Optional[float] = None, prepared: bool = False) -> Desc:
-    """prepared: SCONV_PREPARED_FILTERS, read by the two naming calls only."""
+    """prepared: SCONV_PREPARED_FILTERS, read by the naming calls only."""
     ph, pw, ps = pool if pool is not None else (0, 0, 0)
     return Desc(N, C, H, W, K, R, S, stride, pad, groups, ph, pw, ps,
                 (SCONV_RELU if relu else 0) | (SCONV_PREPARED_FILTERS if prepared else 0) |

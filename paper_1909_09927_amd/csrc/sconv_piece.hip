@@ -115,6 +115,7 @@ struct PGeom {
     }
     static constexpr int NW = WM * WN, BM = 32 * MT * WM, BN = 32 * NT * WN;
     static constexpr int CG = 2 * CS;    // 8-channel groups per staged chunk
+    static_assert(XU * NW % CG == 0, "every 8-channel group has the same number of staging units");
     static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
     static constexpr int AR = T == 9 ? 3 : 4;   // filter fragments in flight (ring)
     static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
@@ -490,6 +491,7 @@ struct TGeom {
     static constexpr bool POOL = POOL_;
     static constexpr int S = T == 9 ? 3 : T == 25 ? 5 : 7;
     static constexpr int NW = 8, BM = 32, BN = 32 * NT, CG = 2 * CS;
+    static_assert(XU * NW % CG == 0, "as in PGeom");
     static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
     static constexpr int E = T * CS;                  // fragments of 32 filters x 16 channels per chunk
     static constexpr int FL = 16 * E, FS = FL | 1;    // floats of one filter per chunk, and their stride in LDS
@@ -1090,7 +1092,7 @@ struct Candidate {
     CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2) \
     CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2) \
     CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2) \
-    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 3, 2) \
+    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 2, 2) \
     /* taps, 16-channel groups per chunk, window blocks, pooled, staging units */ \
     TAPS("t3x64", 9, 2, 2, false, 2) \
     TAPS("t5x64", 25, 1, 2, false, 1) \
