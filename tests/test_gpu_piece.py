@@ -20,29 +20,36 @@ CASES = [
     ("a128x64", (5, 33, 7, 7, 129, 3, 3, 1, 1, 1, None), "0,1,3"),        # ragged channels, one filter in the last block
     ("a128x64", (2, 32, 9, 57, 64, 3, 3, 1, 0, 1, None), None),           # several column strips, the last one narrower
     ("a64x128", (2, 96, 14, 14, 96, 3, 3, 1, 1, 3, None), None),          # grouped, half a filter block
-    ("a64x128", (1, 64, 3, 5, 40, 3, 3, 1, 2, 1, None), "0,1,4"),         # padding wider than a tile's share of the map
+    ("a64x128", (4, 64, 3, 5, 40, 3, 3, 1, 2, 1, None), "0,1,2"),         # padding wider than a tile's share of the map
     ("s128x64", (2, 33, 19, 23, 70, 3, 3, 2, 1, 1, None), None),          # stride 2
     ("s128x64", (3, 20, 14, 14, 96, 3, 3, 3, 0, 1, None), None),          # stride 3, no padding
     ("p128x128", (2, 32, 14, 14, 128, 3, 3, 1, 1, 1, (2, 2, 2)), None),
     ("p128x64", (2, 48, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2)), "3,1,2"),
     ("p128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),      # overlapping pooling windows
+    ("p128x64", (1, 16, 14, 15, 64, 3, 3, 1, 1, 1, (2, 2, 3)), None),     # pooling windows with gaps
+    ("p128x64", (1, 20, 13, 12, 70, 3, 3, 1, 0, 1, (2, 2, 4)), None),
     ("c128x64", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None), "1,1,2"),      # 1x1, ragged channels, strips across images
-    ("c128x64", (2, 64, 15, 14, 96, 1, 1, 2, 0, 2, None), None),          # 1x1, stride 2, grouped
+    ("c128x64", (1, 64, 7, 7, 96, 1, 1, 2, 0, 2, None), None),            # 1x1, stride 2 (a tile's positions fit on small maps only), grouped
     ("c128x64", (2, 35, 9, 7, 129, 1, 1, 1, 0, 1, None), None),           # filters of 35 channels: read one by one, the last block one filter
     ("c128x64", (1, 146, 15, 14, 258, 1, 1, 1, 0, 2, None), "1,1,2"),
     ("c128x64", (1, 20, 9, 7, 129, 1, 1, 1, 0, 1, None), None),           # whole fragments past the last channel
-    ("q128x64", (2, 256, 14, 10, 96, 1, 1, 1, 0, 1, (2, 2, 2)), None),
+    ("q128x64", (2, 256, 14, 16, 96, 1, 1, 1, 0, 1, (2, 2, 2)), None),
+    ("q128x64", (3, 70, 6, 9, 129, 1, 1, 1, 0, 1, (2, 2, 2)), "2,1,2"),   # ragged channels, one filter in the last block, an odd column left out
+    ("q128x64", (1, 35, 5, 40, 64, 1, 1, 1, 0, 1, (2, 2, 2)), None),      # strips
     # taps dealt to the wavefronts
     ("t3x64", (1, 33, 7, 7, 33, 3, 3, 1, 1, 1, None), None),              # one channel in the second chunk, one filter in the second block
-    ("t3x64", (2, 64, 9, 13, 40, 3, 3, 2, 1, 2, None), "1,1,2"),
+    ("t3x64", (2, 128, 9, 13, 40, 3, 3, 2, 1, 2, None), "1,1,2"),
     ("t5x64", (3, 16, 7, 7, 32, 5, 5, 1, 2, 1, None), None),              # one chunk, the last tile 19 windows long
-    ("t5x64", (1, 3, 33, 29, 20, 5, 5, 2, 0, 1, None), None),             # fewer channels than half a lane's eight, no padding
+    ("t5x64", (1, 3, 13, 11, 20, 5, 5, 2, 0, 1, None), None),             # fewer channels than half a lane's eight, stride 2, no padding
+    ("t5x64", (1, 3, 33, 29, 20, 5, 5, 1, 0, 1, None), None),
     ("t5x64", (2, 50, 8, 12, 70, 5, 5, 1, 2, 2, None), "2,1,2"),
     ("t5x128", (2, 40, 12, 31, 33, 5, 5, 1, 2, 1, None), "0,1,3"),
     ("t7x64", (1, 24, 13, 6, 33, 7, 7, 1, 3, 1, None), None),
-    ("t7x96", (2, 17, 21, 18, 31, 7, 7, 2, 3, 1, None), "1,1,2"),
+    ("t7x96", (1, 17, 13, 14, 31, 7, 7, 2, 3, 1, None), "0,1,2"),         # stride 2
+    ("t7x96", (2, 17, 21, 18, 33, 7, 7, 1, 3, 1, None), "5,1,2"),
     ("tp5x128", (2, 48, 13, 15, 33, 5, 5, 1, 2, 1, (2, 2, 2)), "1,1,3"),
     ("tp5x128", (1, 16, 11, 9, 32, 5, 5, 1, 0, 1, (2, 2, 1)), None),
+    ("tp5x128", (1, 20, 17, 11, 40, 5, 5, 1, 2, 1, (2, 2, 4)), None),
     ("tp7x96", (1, 20, 14, 14, 40, 7, 7, 1, 3, 1, (2, 2, 2)), None),
 ]
 
@@ -57,12 +64,23 @@ def _pin(monkeypatch, geom, split, src):
             monkeypatch.setenv(name, value)
 
 
+def _assert_it_runs(desc, pool, ws, geom, split, src):
+    """The pinned geometry, split and form of the filters have a plan (without one the window-row kernel would run)."""
+    name = sconv.sconv_launch_name(desc, pool is not None, ws.numel() if ws is not None else 0)
+    want = f"piece/model:{geom}/{('pieces', 'prepared', 'stored')[int(src)]}"
+    if split is None:
+        assert name == want or name.startswith(want + "/")
+    else:
+        whole, _, slices = split.split(",")
+        assert name.startswith(f"{want}/{whole}+") and name.endswith(f"x{slices}")
+
+
 @pytest.mark.parametrize("src", ["0", "1", "2"])     # pieces in the workspace, prepared filters, filters as stored
 @pytest.mark.parametrize("geom,shp,split", CASES)
 def test_geometries_splits_and_filter_sources(device, monkeypatch, geom, shp, split, src):
     N, C, H, W, K, R, S, stride, pad, groups, pool = shp
     prep = src == "1"
-    if prep and (R != 3 or stride != 1 or pad != 1 or (C // groups) % 16):
+    if prep and (R != 3 or stride != 1 or pad != 1 or (C // groups) % 16 or pool and pool != (2, 2, 2)):
         pytest.skip("no prepared layout for this layer")
     if geom[0] == "t" and src != "2":
         pytest.skip("reads the filters as stored")
@@ -72,6 +90,7 @@ def test_geometries_splits_and_filter_sources(device, monkeypatch, geom, shp, sp
         xd, wd = to_dev(x), to_dev(w)
         bias = to_dev(np.arange(K, dtype=np.float32) % 7 - 3) if prep else None
         _pin(monkeypatch, geom, split, src)
+        _assert_it_runs(sconv.desc_for(xd, wd, stride, pad, groups, pool, True, None, prep), pool, ws, geom, split, src)
         wp = sconv.sconv_filter_prep(wd, groups, stride, pad) if prep else None
         kw = dict(ws=ws, bias=bias, wprep=wp) if prep else dict(ws=ws)
         if pool:
@@ -112,6 +131,7 @@ def test_values_outside_the_pieces_range(device, monkeypatch, geom, src):
     for xi, wi in ((x_bad, w), (x, w_bad), (x * np.float32(1e-36), w), (x, w * np.float32(1e-38))):
         xd, wd = to_dev(xi), to_dev(wi)
         _pin(monkeypatch, geom, None, src)
+        _assert_it_runs(sconv.desc_for(xd, wd, 1, 1, 1, None, True, None, src == "1"), None, ws, geom, None, src)
         wp = sconv.sconv_filter_prep(wd) if src == "1" else None
         y = sconv.sconv_forward(xd, wd, 1, 1, ws=ws, wprep=wp).cpu().numpy()
         monkeypatch.setenv("SCONV_VARIANT", "rows")
@@ -139,6 +159,7 @@ def test_operands_of_any_size(device, monkeypatch, geom, src, shp, xe, we):
     xd, wd = to_dev(x), to_dev(w)
     _pin(monkeypatch, geom, None, src)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    _assert_it_runs(sconv.desc_for(xd, wd, stride, pad, groups, pool, True, None, src == "1"), pool, ws, geom, None, src)
     kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd)) if src == "1" else dict(ws=ws)
     got = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, **kw))
     got = got.cpu().numpy().astype(np.float64)
@@ -200,3 +221,93 @@ def test_launch_name_is_what_runs(device, monkeypatch, capfd, shp, ws, z):
         sconv.sconv_set_workspace(conftest._WORKSPACE)
     said = [line.split()[1] for line in capfd.readouterr().err.splitlines() if line.startswith("piece ")]
     assert said == ([name.split(":")[1].split("/")[0] + ":"] if name.startswith("piece/model:") else [])
+
+
+def _off_by_one(a):
+    """The array on the device, 4 bytes past a 16-byte boundary."""
+    buf = torch.empty(a.size + 1, dtype=torch.float32, device="cuda")
+    view = buf[1:].view(*a.shape)
+    view.copy_(torch.from_numpy(np.ascontiguousarray(a)))
+    assert view.data_ptr() % 16 == 4 and view.is_contiguous()
+    return view
+
+
+@pytest.mark.parametrize("geom,src,shp", [
+    ("a128x64", "0", (2, 33, 14, 13, 70, 3, 3, 1, 1, 1, None)), ("a128x64", "2", (2, 33, 14, 13, 70, 3, 3, 1, 1, 1, None)),
+    ("p128x64", "2", (2, 33, 14, 13, 70, 3, 3, 1, 1, 1, (2, 2, 2))), ("c128x64", "2", (2, 100, 15, 14, 96, 1, 1, 1, 0, 1, None)),
+    ("c128x64", "2", (2, 35, 9, 7, 129, 1, 1, 1, 0, 1, None)), ("t5x64", "2", (1, 33, 7, 7, 33, 5, 5, 1, 2, 1, None)),
+])
+def test_operands_off_a_16_byte_boundary(device, monkeypatch, geom, src, shp):
+    """Maps, filters and results that are slices of something larger: the same bits as from aligned copies."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(405, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6)
+    _pin(monkeypatch, geom, None, src)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    _assert_it_runs(sconv.desc_for(to_dev(x), to_dev(w), stride, pad, groups, pool, True), pool, ws, geom, None, src)
+
+    def call(xd, wd, out=None):
+        if pool:
+            return sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, ws=ws, out=out)
+        return sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws, out=out)
+    aligned = call(to_dev(x), to_dev(w))
+    out = _off_by_one(np.full(tuple(aligned.shape), -1.0, np.float32))
+    call(_off_by_one(x), _off_by_one(w), out)
+    torch.cuda.synchronize()
+    assert torch.equal(aligned, out)
+
+
+@pytest.mark.parametrize("shp,forms", [
+    ((8, 64, 28, 28, 96, 3, 3, 2, 1, 1, None), ("s128x64/stored/0+25x4", "s128x64/pieces", "s128x64/stored")),
+    ((1, 512, 7, 7, 512, 3, 3, 1, 1, 1, None), ("t3x64/stored/0+16x16", "t3x64/stored/0+16x8", "t3x64/stored")),
+])
+def test_workspaces_of_any_size(device, monkeypatch, shp, forms):
+    """From what the plan can use down to nothing: pieces and partial sums go where they fit, the bytes behind the workspace
+    stay as they are, every result within the bar."""
+    monkeypatch.setenv("SCONV_VARIANT", "piece")
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(406, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6)
+    xd, wd = to_dev(x), to_dev(w)
+    d = sconv.desc_for(xd, wd, stride, pad, groups, pool, True)
+    full = sconv.sconv_workspace_size(d)
+    ref, scale = oracle.conv(x, w, stride, pad, groups, relu=True)
+    names = []
+    for size in (full, full // 2, full // 8, full // 64, 4096, 16):
+        buf = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        names.append(sconv.sconv_launch_name(d, False, size))
+        y = sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=buf[:size])
+        torch.cuda.synchronize()
+        assert (buf[size:] == 0xA5).all()
+        assert (np.abs(y.cpu().numpy().astype(np.float64) - ref) <= 1e-4 * scale).all()
+    assert {"piece/model:" + f for f in forms} <= set(names)
+
+
+@pytest.mark.parametrize("geom,split,src,shp", [
+    ("s128x64", "10,1,2", "0", (8, 64, 28, 28, 64, 3, 3, 2, 1, 1, None)), ("t3x64", "0,1,4", "2", (1, 256, 14, 14, 256, 3, 3, 1, 1, 1, None)),
+])
+def test_launches_captured_into_a_graph(device, monkeypatch, geom, split, src, shp):
+    """Pieces of the filters written and split tiles added inside the graph: every replay gives what an eager call gives on the
+    map and the filters as they are then."""
+    _pin(monkeypatch, geom, split, src)
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(407, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6)
+    xd, wd = to_dev(x), to_dev(w)
+    d = sconv.desc_for(xd, wd, stride, pad, groups, pool, True)
+    ws, ws2 = (torch.empty(sconv.sconv_workspace_size(d), dtype=torch.uint8, device="cuda") for _ in range(2))
+    _assert_it_runs(d, None, ws, geom, split, src)
+    st = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    out = sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        with torch.cuda.graph(graph, stream=st):
+            sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws, out=out)
+    torch.cuda.synchronize()
+    for rep in range(4):
+        _, xn, wn = workloads.make_random_case(408 + rep, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6)
+        xd.copy_(torch.from_numpy(xn))
+        wd.copy_(torch.from_numpy(wn))
+        out.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws2))
