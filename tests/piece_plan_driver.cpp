@@ -80,11 +80,6 @@ static void raw_reads(const char* name)
     }
 }
 
-template <class G>
-static void taps_have_no_raw_reads(const char*)
-{
-}
-
 // The strips are the best of every number of strips of four or more columns.
 static void strips_are_the_best_of_all(int n)
 {
@@ -149,12 +144,117 @@ static void plans_are_kept()
     split_scratch_given(nullptr, 0, false);
 }
 
+// The plans of one geometry: what a workgroup stages and reads in LDS, what it reads of the map and writes to the workspace, and which
+// results it computes, followed as the kernels compute it.
+template <class G>
+static void plans(const char* name, Plan (*plan)(const Problem&, bool), int CS, int PXMAX, int lds_other, int chunk_buffers)
+{
+    int walked = 0, split = 0, in_pieces = 0;
+    for (int tries = 0; tries < 4000 && walked < 60; ++tries) {
+        Problem p;
+        if (!random_problem(G::T, G::POOL, &p)) continue;
+        static const float some = 0.0f;
+        p.wprep = pick(0, 3) == 0 && tap_supported(p, G::POOL) && p.stride == 1 ? &some : nullptr;
+        // a third with the model's choice, the others with split tiles or with pieces of the filters where there is room
+        const int form = walked % 3;
+        char slices[16];
+        snprintf(slices, sizeof(slices), "%d,1,%d", pick(0, 2), pick(2, 5));
+        form == 1 ? setenv("SCONV_PIECE_SPLIT", slices, 1) : unsetenv("SCONV_PIECE_SPLIT");
+        form == 2 && G::BM != 32 ? setenv("SCONV_PIECE_SRC", "0", 1) : unsetenv("SCONV_PIECE_SRC");
+        EXPECT(sconv_env_refresh() == SCONV_OK, "%s", name);
+        const size_t room = form || pick(0, 1) ? plan_workspace_bytes(p, G::POOL) / (form ? 1 : (size_t)pick(1, 20)) : 0;
+        split_scratch_given(room ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, room, true);
+        split_scratch_select(nullptr);
+        const Plan pl = plan(p, G::POOL);
+        const size_t ws = usable_workspace(p, G::POOL);
+        split_scratch_given(nullptr, 0, false);
+        if (pl.cost < 0.0) continue;
+        ++walked;
+        const PieceCfg& c = pl.cfg;
+        const int T = G::T, S = p.S, iH = c.flat ? 1 : p.H, iW = c.flat ? p.H * p.W : p.W, HP = iH + p.pad;
+        const int prows = G::POOL ? p.PH : c.flat ? 1 : p.OH, pcols = G::POOL ? p.PW : c.flat ? p.OH * p.OW : p.OW;
+        const int pitch = (G::POOL ? (c.TW - 1) * p.ps + 1 : c.TW - 1) * p.stride + S;
+#define HOLDS(cond) EXPECT(cond, "%s N %d C %d %dx%d K %d G %d stride %d pad %d ps %d, %zu bytes", name, p.N, p.C, p.H, p.W, p.K, p.G, p.stride, p.pad, p.ps, ws)
+        // LDS, workspace, slices
+        HOLDS(c.px <= PXMAX && c.px * 48 <= c.cgb && pl.lds_bytes <= 160 * 1024);
+        HOLDS((size_t)lds_other + (size_t)chunk_buffers * 2 * CS * c.cgb <= pl.lds_bytes);
+        HOLDS(pl.piece_bytes + (size_t)pl.ntail * (pl.ntail ? c.nss : 0) * G::BM * G::BN * 4 <= ws);
+        HOLDS(c.whole + pl.ntail == c.ntiles * c.strips * c.kblocks * p.G && (!pl.ntail || (c.nss > 1 && c.nss <= c.nch)));
+        HOLDS(c.nch * 16 * CS >= p.Cg && c.kblocks * G::BM >= p.Kg && (c.nch - 1) * 16 * CS < p.Cg);
+        HOLDS((pl.src == SRC_FP32) <= (p.wprep != nullptr));
+        if (pl.src == SRC_PIECES) HOLDS(pl.piece_bytes == (size_t)p.G * c.kb32 * c.nch * CS * T * 3072 && c.kb32 * 32 >= c.kblocks * G::BM);
+        if (pl.src == SRC_FP32) HOLDS(c.kb32 * 32 >= c.kblocks * G::BM && p.Cg % (16 * CS) == 0);
+        split += pl.ntail > 0;
+        in_pieces += pl.src == SRC_PIECES;
+        std::vector<unsigned char> seen((size_t)p.N * prows * pcols, 0);
+        const bool all = (size_t)c.ntiles * c.strips * G::BN <= 40000;
+        for (int tile = 0; tile < c.ntiles; ++tile) {
+            const bool look = tile < 3 || tile >= c.ntiles - 2 || pick(0, c.ntiles / 4) == 0;
+            if (!look && !all) continue;
+            for (int strip = 0; strip < c.strips; ++strip) {
+                auto window = [&](int P, int& n, int& oh, int& ow) {
+                    const int pp = G::POOL ? P >> 2 : P, q = pp / c.TW;
+                    ow = pp - q * c.TW;
+                    n = q / prows;
+                    oh = q - n * prows;
+                    if (G::POOL) {
+                        oh = p.ps * oh + ((P & 3) >> 1);
+                        ow = p.ps * ow + (P & 1);
+                    }
+                };
+                int n0, oh0, ow0;
+                window(tile * G::BN, n0, oh0, ow0);
+                const int r0 = n0 * HP + oh0 * p.stride, first_col = strip * c.TW * (G::POOL ? p.ps : 1), w0 = first_col * p.stride - p.pad;
+                for (int i = 0; i < G::BN; ++i) {
+                    const int P = tile * G::BN + i;
+                    int n, oh, ow;
+                    window(P < c.nrun ? P : c.nrun - 1, n, oh, ow);
+                    const int at = (n * HP + oh * p.stride - r0) * pitch + ow * p.stride;
+                    const int col = ow + first_col, wcol = G::POOL ? (col - (P & 1)) / p.ps : col, wrow = G::POOL ? (oh - ((P & 3) >> 1)) / p.ps : oh;
+                    const bool counts = P < c.nrun && wcol < pcols;
+                    if (counts) {
+                        HOLDS(n < p.N && wrow < prows);
+                        if (n < p.N && wrow < prows) ++seen[((size_t)n * prows + wrow) * pcols + wcol];
+                    }
+                    for (int t = 0; look && t < T; ++t) {
+                        const int q = at + t / S * pitch + t % S;
+                        HOLDS(q >= 0 && q < c.px);
+                        // what is staged there
+                        const int sr = r0 + q / pitch, sn = sr / HP, h = sr - sn * HP - p.pad, cw = q % pitch + w0;
+                        const bool staged = sn < p.N && h >= 0 && h < iH && cw >= 0 && cw < iW;
+                        if (staged) {
+                            const long long o = (long long)(sn - n0) * p.C * p.H * p.W + h * iW + cw + (long long)(p.Cg - 1) * p.H * p.W;
+                            HOLDS(sn >= n0 && o * 4 < 0x7ffffffc && (n0 * p.C + (p.G - 1) * p.Cg) * (long long)(p.H * p.W) + o < (long long)p.N * p.C * p.H * p.W);
+                        }
+                        if (!counts) continue;
+                        const int ih = oh * p.stride - p.pad + t / S, iw = col * p.stride - p.pad + t % S;
+                        const bool inside = ih >= 0 && ih < iH && iw >= 0 && iw < iW;
+                        HOLDS(staged == inside && (!inside || (sn == n && h == ih && cw == iw)));
+                    }
+                }
+            }
+        }
+        for (size_t i = 0; all && i < seen.size(); ++i)
+            if (seen[i] != (G::POOL ? 4 : 1)) {
+                HOLDS(false);
+                break;
+            }
+    }
+    unsetenv("SCONV_PIECE_SPLIT");
+    unsetenv("SCONV_PIECE_SRC");
+    EXPECT(sconv_env_refresh() == SCONV_OK && walked >= 40 && split >= 10, "%s: %d plans, %d with split tiles", name, walked, split);
+    if (G::BM != 32) EXPECT(in_pieces >= 10, "%s: %d plans with pieces of the filters", name, in_pieces);
+}
+
 int main()
 {
     strips_are_the_best_of_all(4000);
     plans_are_kept();
-#define WALK_PIECE(NAME, ...) raw_reads<PGeom<__VA_ARGS__>>(NAME);
-#define WALK_TAPS(NAME, ...) taps_have_no_raw_reads<TGeom<__VA_ARGS__>>(NAME);
+#define WALK_PIECE(NAME, ...)                          \
+    raw_reads<PGeom<__VA_ARGS__>>(NAME);               \
+    plans<PGeom<__VA_ARGS__>>(NAME, plan_geom<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::CS, PGeom<__VA_ARGS__>::PXMAX, 0, 2);
+#define WALK_TAPS(NAME, ...) \
+    plans<TGeom<__VA_ARGS__>>(NAME, plan_taps<TGeom<__VA_ARGS__>>, TGeom<__VA_ARGS__>::CS, TGeom<__VA_ARGS__>::PXMAX, TGeom<__VA_ARGS__>::FB, 1);
     PIECE_GEOMETRIES(WALK_PIECE, WALK_TAPS)
     if (failures) {
         fprintf(stderr, "%d expectation(s) failed\n", failures);
