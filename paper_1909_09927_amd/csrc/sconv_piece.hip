@@ -101,7 +101,10 @@ __device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
 __host__ __device__ constexpr int raw_base(int row, int L, int T, int half) { return (row * L + half * 8 * T) * 4; }
 __host__ __device__ constexpr int raw_step(int ch16, int T, int j, int t) { return (ch16 * 16 * T + t) * 4 + j * T * 4; }
 __host__ __device__ constexpr int raw_last(int base, int L, int half) { return base + (L - 1 - half * 8) * 4; }   // 1x1: the row's last channel
-__host__ __device__ constexpr bool raw_wide(int Cg, int ch16) { return (Cg & 3) == 0 || ch16 * 16 + 16 <= Cg; }      // 1x1, a fragment of 16 channels
+// 1x1, a fragment of 16 channels: its first, out of every buffer's range where all of them lie past the row (they read as zeros
+// without a trip to memory); whether it is read by four channels
+__host__ __device__ constexpr int raw_fragment(int base, int Cg, int ch16) { return ch16 * 16 < Cg ? base + ch16 * 64 : (int)0x80000000u; }
+__host__ __device__ constexpr bool raw_wide(int Cg, int ch16) { return (Cg & 3) == 0 || ch16 * 16 + 16 <= Cg || ch16 * 16 >= Cg; }
 
 template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int XU_, int OCC_>
 struct PGeom {
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                 for (int j = 0; j < 8; ++j)
                     af[slot][i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[0] + (i & 1) * 128, so + j * T * 256, 0));
             } else if (G::T == 1) {   // eight channels are consecutive
-                const int at = wvo[i] + raw_step(ch16, T, 0, 0);
+                const int at = raw_fragment(wvo[i], p.Cg, ch16);
                 if (raw_wide(p.Cg, ch16)) {
                     const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at, 0, 0));
                     const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at + 16, 0, 0));

@@ -58,21 +58,22 @@ static void raw_reads(const char* name)
                         for (int j = 0; j < 8; ++j) {
                             const int base = raw_base(row < p.Kg - 1 - kb * G::BM ? row : p.Kg - 1 - kb * G::BM, p.L, G::T, half);
                             for (int t = 0; t < G::T; t += G::VW) {
-                                int at = base + raw_step(ch16, G::T, G::T == 1 ? 0 : j, t), bytes = 12;
+                                unsigned at = G::T == 1 ? raw_fragment(base, p.Cg, ch16) : base + raw_step(ch16, G::T, j, t);
+                                int bytes = 12;
                                 if (G::T == 1 && raw_wide(p.Cg, ch16)) {
                                     at += j / 4 * 16;
                                     bytes = 16;
                                 } else if (G::T == 1) {
-                                    const int last = raw_last(base, p.L, half);
+                                    const unsigned last = raw_last(base, p.L, half);
                                     at = at + 4 * j < last ? at + 4 * j : last;
                                     bytes = 4;
-                                    EXPECT(at >= 0 && at < left, "%s at %d of %lld", name, at, left);
+                                    EXPECT(at < left, "%s at %u of %lld", name, at, left);
                                 }
-                                EXPECT(at >= 0 && (at + bytes <= left || at >= left), "%s C %d K %d G %d T %d: %d bytes at %d of %lld", name, p.C,
+                                EXPECT(at + (long long)bytes <= left || at >= left, "%s C %d K %d G %d T %d: %d bytes at %u of %lld", name, p.C,
                                        p.K, p.G, G::T, bytes, at, left);
                                 if (ch16 * 16 + half * 8 + j < p.Cg)   // a channel that counts: its own element
                                     EXPECT(at + (G::T == 1 && raw_wide(p.Cg, ch16) ? j % 4 * 4 : 0) ==
-                                               ((row < p.Kg - 1 - kb * G::BM ? row : p.Kg - 1 - kb * G::BM) * p.L + (ch16 * 16 + half * 8 + j) * G::T + t) * 4,
+                                               (unsigned)((row < p.Kg - 1 - kb * G::BM ? row : p.Kg - 1 - kb * G::BM) * p.L + (ch16 * 16 + half * 8 + j) * G::T + t) * 4,
                                            "%s", name);
                             }
                         }
