@@ -8,8 +8,15 @@
 // i.e. below one fp32 rounding of it.  Products of pieces are exact and every instruction adds 16 of them to an fp32
 // accumulator, which rounds six times per sixteen terms where an fp32 chain rounds sixteen times.  The sums of one staged
 // chunk start from zero and are added to the running sums at its end (16 additions per accumulator and 54 matrix
-// instructions), so that the roundings of a chunk happen at the size of its own partial sum.  Measured against 64-bit sums,
-// 512 channels: 2.0e-7 relative, against 2.7e-7 (quad3x3), 3.7e-7 (wide3x3) and 1.2e-7 - 2.2e-7 (tap3x3).
+// instructions), so that the roundings of a chunk happen at the size of its own partial sum.  Where registers allow (PGeom::apart)
+// only x0w0 goes there, and the five small products have running sums of their own, whose roundings are 2^-8 of those: one rounding per sixteen
+// terms is left.  Measured against 64-bit sums, relative, 512 channels of 3x3 at 50 / 70 / 85 % zeros: 0.87e-7 / 0.80e-7 / 0.72e-7 with sums
+// apart, 1.86e-7 / 1.79e-7 / 1.60e-7 without; tap3x3 1.62e-7 / 1.33e-7 / 1.05e-7, quad3x3 2.24e-7 / 1.81e-7 / 1.40e-7, wide3x3 4.25e-7 /
+// 3.30e-7 / 2.35e-7.  The third set of accumulators takes a third workgroup off a compute unit: no loss where LDS or filters cut on the way
+// leave two anyway (128 -> 128 3x3 stride 2 @56x56 at batch 32 62.4 -> 55.8 us, 512 @28x28 at batch 8 with prepared filters 161 -> 159,
+// 1x1 512 -> 256 @28x28 at batch 16 32.9 -> 32.0), a quarter where three fit and the launch fills them (256 @56x56 149 -> 186).
+// The splitting is the one of G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations" (ARITH 2019).
 // Both operands are multiplied by 2^24 before they are cut: the last bit of the smallest fp32 subnormal, 2^-149, becomes 2^-125,
 // so every piece of every value is a normal bf16 number or zero, and the products that fall below fp32's range are those below
 // 2^-174 - far under an fp32 sum's own smallest step.  The sums are multiplied by 2^-48 at the end.  What is left out of range is
@@ -123,6 +130,8 @@ struct PGeom {
     static constexpr int AR = T == 9 ? 3 : 4;   // filter fragments in flight (ring)
     static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
+    // sums of their own for the five small products (see the top): where the third set of accumulators costs no time
+    static constexpr bool apart(int src) { return NT == 2 && (T == 1 || XU == 4 || src == SRC_FP32); }
 };
 
 template <class G, int SRC>
@@ -312,13 +321,17 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         }
     };
 
-    v16f acc[MT][NT], tmp[MT][NT];
+    constexpr bool APART = G::apart(SRC);
+    v16f acc[MT][NT], tmp[MT][NT], accl[APART ? MT : 1][APART ? NT : 1];
     const int bufb = CG * CGB;
     const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int nb = 0; nb < NT; ++nb) acc[i][nb] = zero;
+        for (int nb = 0; nb < NT; ++nb) {
+            acc[i][nb] = zero;
+            if (APART) accl[APART ? i : 0][APART ? nb : 0] = zero;
+        }
 
     static_assert(NT >= 2, "two independent accumulators at least");
     constexpr int NH = 2;                         // position blocks per half step
@@ -356,10 +369,11 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
 #pragma unroll
             for (int n = 0; n < NH; ++n)
 #pragma unroll
-                for (int i = 0; i < MT; ++i)
-                    tmp[i][h * NH + n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
-                        first && c == 0 ? zero : tmp[i][h * NH + n], 0, 0, 0);
+                for (int i = 0; i < MT; ++i) {
+                    v16f& d = APART && c < 5 ? accl[APART ? i : 0][APART ? h * NH + n : 0] : tmp[i][h * NH + n];
+                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
+                                                                first && c == (APART ? 5 : 0) ? zero : d, 0, 0, 0);
+                }
     };
 
     fetch_x(chb);
@@ -410,6 +424,12 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
             for (int nb = 0; nb < NT; ++nb) acc[i][nb] += tmp[i][nb];
         __syncthreads();
     }
+
+    if (APART)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb) acc[i][nb] += accl[APART ? i : 0][APART ? nb : 0];
 
     // epilogue
     float* part = split ? parts + ((size_t)ss * ((nb_all - whole) / cfg.nss) + ptile) * (G::BM * G::BN) : nullptr;
@@ -846,7 +866,7 @@ size_t usable_workspace(const Problem& p, bool pooled)
 template <class G>
 int occupancy_limit(int src, size_t lds_bytes)
 {
-    const int by_lds = (int)(160 * 1024 / lds_bytes), by_regs = G::tc(src, 9) > 4.0 || (src == SRC_RAW && G::XU > 2) ? 2 : 3;
+    const int by_lds = (int)(160 * 1024 / lds_bytes), by_regs = G::tc(src, 9) > 4.0 || G::apart(src) || (src == SRC_RAW && G::XU > 2) ? 2 : 3;
     const int n = by_regs * 4 / G::NW;
     return by_lds < n ? by_lds : n;
 }

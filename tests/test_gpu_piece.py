@@ -311,3 +311,34 @@ def test_launches_captured_into_a_graph(device, monkeypatch, geom, split, src, s
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws2))
+
+
+@pytest.mark.parametrize("shp,call,family", [
+    ((2, 512, 28, 28, 512, 3, 3, 1, 1, 1, None), "prepared", "tap"), ((2, 256, 28, 28, 256, 3, 3, 1, 1, 1, None), "prepared", "quad"),
+    ((2, 128, 56, 56, 128, 3, 3, 2, 1, 1, None), "ws", "wide"), ((2, 512, 28, 28, 256, 1, 1, 1, 0, 1, None), "ws", None),
+])
+@pytest.mark.parametrize("z", [0.5, 0.7])
+def test_no_further_from_64_bit_sums_than_the_kernel_it_replaces(device, monkeypatch, shp, call, family, z):
+    """The tiled geometries with sums of their own for the small products: relative error against the oracle's 64-bit sums, at
+    most a twentieth above that of the kernel that would run otherwise (its own sums round to other bits on another seed)."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(412, N, C, H, W, K, R, S, stride, pad, groups, pool, z)
+    xd, wd = to_dev(x), to_dev(w)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd)) if call == "prepared" else dict(ws=ws)
+    ref, _ = oracle.conv(x, w, stride, pad, groups, relu=False)
+
+    def error():
+        y = sconv.sconv_forward(xd, wd, stride, pad, groups, **kw).cpu().numpy().astype(np.float64)
+        return np.linalg.norm(y - ref) / np.linalg.norm(ref)
+    if family:
+        monkeypatch.setenv("SCONV_VARIANT", family)
+    assert not sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool), False, ws.numel()).startswith("piece")
+    other = error()
+    geom = "c128x64" if R == 1 else "s128x64" if stride == 2 else "a128x64"
+    _pin(monkeypatch, geom, None, "1" if call == "prepared" else "0")
+    _assert_it_runs(sconv.desc_for(xd, wd, stride, pad, groups, pool, False, None, call == "prepared"), pool, ws, geom, None,
+                    "1" if call == "prepared" else "0")
+    mine = error()
+    print(f"{mine:.3e} against {other:.3e}")
+    assert mine <= 1.05 * other
