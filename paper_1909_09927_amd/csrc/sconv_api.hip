@@ -363,6 +363,23 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
     return V_ROWS;
 }
 
+// Whether a piece kernel that takes a call over has to keep sums of its own for the small products.  Without them its error against
+// 64-bit sums is 1.7e-7 (1.5e-7 at 85 % zeros) at any number of channels, where the other kernels' grows with it: at 50 / 70 / 85 %
+// zeros quad3x3 and the vector kernel have 1.2 / 1.0 / 0.8 at 64 channels of 3x3, 1.6 / 1.3 / 1.0 at 128, 2.2 / 1.75 / 1.3 at 256; wide3x3 and
+// gen 1.6 / 1.3 / 1.0 at 64 and 2.1 / 1.7 / 1.2 at 128; the vector kernel's split launches less (512 channels 1.6 / 1.3 / 1.05).  With them
+// it is 0.5 - 0.9.
+bool piece_close(const Problem& p, bool pooled)
+{
+    const bool have_ws = split_scratch_possible(nullptr);
+    switch (choose(p, pooled, have_ws, nullptr, p.zhint)) {
+    case V_WIDE:
+    case V_GEN: return p.Cg < 128;
+    case V_QUAD: return p.Cg < 256;
+    case V_TAP: return p.Cg < 256 || (have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768);
+    default: return false;
+    }
+}
+
 // Whether a launch of family v runs on the piece kernels instead: when their cost model promises less time than
 // these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at

@@ -88,7 +88,9 @@ bool piece_supported(const Problem& p, bool pooled);
 double piece_cost(const Problem& p, bool pooled);
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                  hipStream_t stream);
-// that plan by name: "geometry/form of the filters", and "/whole tiles+split tiles x slices" where it has split ones
+// whether such a plan must keep the small products apart, so that no result is further from 64-bit sums than the other kernels'
+bool piece_close(const Problem& p, bool pooled);
+// the piece plan by name: "geometry/form of the filters", and "/whole tiles+split tiles x slices" where it has split ones
 bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size);
 
 // A fixed decomposition in place of the cost models' choice: candidate geometry inside a kernel

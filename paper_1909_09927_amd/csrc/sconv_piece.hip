@@ -110,10 +110,10 @@ __host__ __device__ constexpr int raw_step(int ch16, int T, int j, int t) { retu
 __host__ __device__ constexpr int raw_last(int base, int L, int half) { return base + (L - 1 - half * 8) * 4; }   // 1x1: the row's last channel
 // 1x1, a fragment of 16 channels: its first, out of every buffer's range where all of them lie past the row (they read as zeros
 // without a trip to memory); whether it is read by four channels
-__host__ __device__ constexpr int raw_fragment(int base, int Cg, int ch16) { return ch16 * 16 < Cg ? base + ch16 * 64 : (int)0x80000000u; }
+__host__ __device__ constexpr int raw_fragment(int base, int Cg, int ch16) { return ch16 * 16 < Cg ? base + raw_step(ch16, 1, 0, 0) : (int)0x80000000u; }
 __host__ __device__ constexpr bool raw_wide(int Cg, int ch16) { return (Cg & 3) == 0 || ch16 * 16 + 16 <= Cg || ch16 * 16 >= Cg; }
 
-template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int XU_, int OCC_>
+template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int XU_, int OCC_, bool APART_>
 struct PGeom {
     static constexpr int MT = MT_, NT = NT_, WM = WM_, WN = WN_, T = T_, CS = CS_, XU = XU_, OCC = OCC_;   // XU: staging units per wavefront
     static constexpr bool POOL = POOL_;
@@ -121,7 +121,7 @@ struct PGeom {
     static constexpr double tc(int src, int taps)
     {
         return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.75 : src == SRC_FP32 ? 4.9 : 5.3)
-                                   : (src == SRC_PIECES ? 2.6 : src == SRC_FP32 ? 2.75 : 3.7) * (MT * NT * NW) / 8.0) * (T_ == 1 ? 0.5 : taps / 9.0);
+                                   : (src == SRC_PIECES ? 2.6 : src == SRC_FP32 ? 2.75 : APART_ && T_ == 9 ? 3.45 : 3.7) * (MT * NT * NW) / 8.0) * (T_ == 1 ? 0.5 : taps / 9.0);
     }
     static constexpr int NW = WM * WN, BM = 32 * MT * WM, BN = 32 * NT * WN;
     static constexpr int CG = 2 * CS;    // 8-channel groups per staged chunk
@@ -130,8 +130,8 @@ struct PGeom {
     static constexpr int AR = T == 9 ? 3 : 4;   // filter fragments in flight (ring)
     static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
-    // sums of their own for the five small products (see the top): where the third set of accumulators costs no time
-    static constexpr bool apart(int src) { return NT == 2 && (T == 1 || XU == 4 || src == SRC_FP32); }
+    // sums of their own for the five small products (see the top)
+    static constexpr bool apart(int src) { return APART_ || (NT == 2 && src == SRC_FP32); }
 };
 
 template <class G, int SRC>
@@ -926,9 +926,10 @@ bool pin_allows()
 
 // The cheapest split of a geometry's tiles, kept in pl when it beats what is there: whole tiles first, then the rest, each
 // split along the channels over s workgroups (s = 1: none).  tc: microseconds of a chunk, times lone where the compute units
-// hold a single workgroup; fixed: those of the launch.
+// hold a single workgroup; fixed: those of the launch.  in_pairs: two workgroups on a compute unit, what is left of the longer
+// half runs alone.
 void consider(Plan& pl, long long tiles, long long round, int NW, double tc, double lone, double fixed, int src, size_t pb, int kb32, size_t ws,
-              size_t tile_bytes)
+              size_t tile_bytes, bool in_pairs)
 {
     PieceCfg& c = pl.cfg;
     int pin_whole = 0, pin_ncs = 0, pin_nss = 0;   // tuning aid: SCONV_PIECE_SPLIT="whole tiles,1,slices of the others"
@@ -943,7 +944,12 @@ void consider(Plan& pl, long long tiles, long long round, int NW, double tc, dou
             if (pin_nss > 1 && s != pin_nss) continue;
             if (s > c.nch || pb + (size_t)tail * s * tile_bytes > ws + (tail ? 0 : pb)) break;
             const double a = (c.nch + 0.6) * tc, b = ((c.nch + s - 1) / s + 0.6) * tc;
-            const double load = cu_load(whole, a, tail * s, b);
+            double load = cu_load(whole, a, tail * s, b);
+            if (in_pairs) {
+                const long long na = (whole + 255) / 256, nb = (tail * s + 255) / 256;
+                const double rest = na % 2 ? a - (double)nb * b : nb % 2 ? b : 0.0;
+                if (na + nb > 2 && rest > 0.0) load += (lone - 1.0) * rest;
+            }
             const double resident = (double)(whole + tail * s) / 256.0;
             double cost = fixed + load * (resident * NW <= (lone > 1.0 ? 6.0 : 8.0) ? lone : 1.0);
             if (tail) cost += 3.0 + 2.0 * (double)(tail * s) * tile_bytes / 6e6;
@@ -960,8 +966,9 @@ void consider(Plan& pl, long long tiles, long long round, int NW, double tc, dou
     }
 }
 
+// close: only forms with sums of their own for the small products.
 template <class G>
-Plan plan_geom(const Problem& p, bool pooled)
+Plan plan_geom(const Problem& p, bool pooled, bool close)
 {
     Plan pl;
     if (G::POOL != pooled) return pl;
@@ -994,6 +1001,7 @@ Plan plan_geom(const Problem& p, bool pooled)
         // filters: as prepared by the caller; else cut into pieces by a kernel of their own when the workspace has room, or as stored
         if (pin_src ? atoi(pin_src) != src : (src == SRC_FP32) != (p.wprep && G::T == 9)) continue;
         if (src == SRC_FP32 && (!p.wprep || G::T != 9)) continue;
+        if (close && !G::apart(src)) continue;
         size_t pb = 0;
         const int kb32 = src == SRC_FP32 ? (p.Kg + 127) / 128 * 4 : c.kblocks * (G::BM / 32);
         if (src == SRC_PIECES) {
@@ -1005,7 +1013,7 @@ Plan plan_geom(const Problem& p, bool pooled)
         const double tc = G::tc(src, T);
         const int occ = occupancy_limit<G>(src, pl.lds_bytes);
         const double pre = src == SRC_PIECES ? 6.0 + (double)p.K * p.L * 10.0 / 4e6 : 0.0;
-        consider(pl, tiles, 256LL * occ, G::NW, tc, 1.25, 6.0 + pre, src, pb, kb32, ws, tile_bytes);
+        consider(pl, tiles, 256LL * occ, G::NW, tc, 1.25, 6.0 + pre, src, pb, kb32, ws, tile_bytes, G::T == 9 && G::apart(src) && src != SRC_FP32);
     }
     return pl;
 }
@@ -1052,7 +1060,7 @@ int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, c
 }
 
 template <class G>
-Plan plan_taps(const Problem& p, bool pooled)
+Plan plan_taps(const Problem& p, bool pooled, bool)
 {
     Plan pl;
     if (G::POOL != pooled || p.R != p.S || p.S != G::S || p.wprep) return pl;
@@ -1075,7 +1083,7 @@ Plan plan_taps(const Problem& p, bool pooled)
     // a chunk: the matrix instructions of its busiest SIMD (32 clocks each), and barriers and staging that nothing hides (one
     // workgroup per compute unit).  Measured: 2.0 us with few workgroups and 2.6 with all (5x5, 64 windows), 3.9 and 5.9 (7x7)
     const double tc = (((G::E + 3) / 4) * G::NT * 6 * 32 / 2000.0 / 0.75 + 0.8) * (G::T == 49 ? 1.2 : 1.0);
-    consider(pl, tiles, 256LL, G::NW, tc, 0.75, 7.0, SRC_RAW, 0, 0, usable_workspace(p, pooled), (size_t)G::BM * G::BN * 4);
+    consider(pl, tiles, 256LL, G::NW, tc, 0.75, 7.0, SRC_RAW, 0, 0, usable_workspace(p, pooled), (size_t)G::BM * G::BN * 4, false);
     return pl;
 }
 
@@ -1100,22 +1108,24 @@ int launch_taps(const Plan& pl, const Problem& p, bool, const float* x, const fl
 
 struct Candidate {
     const char* name;
-    Plan (*plan)(const Problem&, bool);
+    Plan (*plan)(const Problem&, bool, bool);
     int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
 };
 
 // The geometries, for the table below and for the test that walks their plans.
 #define PIECE_GEOMETRIES(CAND, TAPS) \
     /* 32-filter and 32-window blocks of a wavefront, wavefronts along filters and windows, taps, 16-channel groups per chunk, pooled, */ \
-    /* staging units, wavefronts per SIMD */ \
-    CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2) \
-    CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2) \
-    CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2) \
-    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2) \
-    CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2) \
-    CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2) \
-    CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2) \
-    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 2, 2) \
+    /* staging units, wavefronts per SIMD, small products apart */ \
+    CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2, false) \
+    CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2, false) \
+    CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2, false) \
+    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2, true) \
+    CAND("b64x128", 1, 2, 2, 2, 9, 1, false, 3, 2, true) \
+    CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2, false) \
+    CAND("p128x64", 1, 2, 4, 1, 9, 1, true, 2, 2, false) \
+    CAND("u128x64", 1, 2, 4, 1, 9, 1, true, 2, 2, true) \
+    CAND("c128x64", 1, 2, 4, 1, 1, 4, false, 2, 2, true) \
+    CAND("q128x64", 1, 2, 4, 1, 1, 4, true, 2, 2, true) \
     /* taps, 16-channel groups per chunk, window blocks, pooled, staging units */ \
     TAPS("t3x64", 9, 2, 2, false, 2) \
     TAPS("t5x64", 25, 1, 2, false, 1) \
@@ -1147,8 +1157,8 @@ struct Choice {
 };
 
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
-// kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, a geometry that
-// sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
+// kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, whether small
+// products are kept apart, a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
 // dispatcher's lock; the reference lasts until the next call.)
 const Choice& choose_plan(const Problem& p, bool pooled)
 {
@@ -1168,12 +1178,13 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     static Choice pinned;
     const PlanPin* tuned = current_pin();
     const char* pin = pinned_geom("SCONV_PIECE_GEOM");
+    const bool close = !pin && piece_close(p, pooled);
     auto walk = [&](Choice& out) {
         out = Choice();
         if (!shape_ok(p, pooled)) return;
         for (const Candidate& c : kCandidates) {
             if (pin && strcmp(pin, c.name) != 0) continue;
-            Plan pl = c.plan(p, pooled);
+            Plan pl = c.plan(p, pooled, close);
             if (pl.cost < 0.0) continue;
             if (!out.cand || pl.cost < out.plan.cost) {
                 out.cand = &c;
@@ -1188,7 +1199,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     Key k;
     memset(&k, 0, sizeof(k));
     const int v[19] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
-                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0};
+                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0, close ? 1 : 0};
     memcpy(k.v, v, sizeof(v));
     k.ws = usable_workspace(p, pooled);
     if (tuned) {

@@ -148,7 +148,7 @@ static void plans_are_kept()
 // The plans of one geometry: what a workgroup stages and reads in LDS, what it reads of the map and writes to the workspace, and which
 // results it computes, followed as the kernels compute it.
 template <class G>
-static void plans(const char* name, Plan (*plan)(const Problem&, bool), int CS, int PXMAX, int lds_other, int chunk_buffers)
+static void plans(const char* name, Plan (*plan)(const Problem&, bool, bool), int CS, int PXMAX, int lds_other, int chunk_buffers)
 {
     int walked = 0, split = 0, in_pieces = 0;
     for (int tries = 0; tries < 4000 && walked < 60; ++tries) {
@@ -166,7 +166,7 @@ static void plans(const char* name, Plan (*plan)(const Problem&, bool), int CS, 
         const size_t room = form || pick(0, 1) ? plan_workspace_bytes(p, G::POOL) / (form ? 1 : (size_t)pick(1, 20)) : 0;
         split_scratch_given(room ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, room, true);
         split_scratch_select(nullptr);
-        const Plan pl = plan(p, G::POOL);
+        const Plan pl = plan(p, G::POOL, pick(0, 1) != 0);
         const size_t ws = usable_workspace(p, G::POOL);
         split_scratch_given(nullptr, 0, false);
         if (pl.cost < 0.0) continue;

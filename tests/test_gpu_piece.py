@@ -23,6 +23,10 @@ CASES = [
     ("a64x128", (4, 64, 3, 5, 40, 3, 3, 1, 2, 1, None), "0,1,2"),         # padding wider than a tile's share of the map
     ("s128x64", (2, 33, 19, 23, 70, 3, 3, 2, 1, 1, None), None),          # stride 2
     ("s128x64", (3, 20, 14, 14, 96, 3, 3, 3, 0, 1, None), None),          # stride 3, no padding
+    ("b64x128", (2, 96, 14, 14, 96, 3, 3, 1, 1, 3, None), None),          # as a64x128 and p128x64, small products apart
+    ("b64x128", (2, 48, 19, 23, 70, 3, 3, 1, 1, 1, None), "3,1,2"),
+    ("u128x64", (2, 48, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2)), "3,1,2"),
+    ("u128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),
     ("p128x128", (2, 32, 14, 14, 128, 3, 3, 1, 1, 1, (2, 2, 2)), None),
     ("p128x64", (2, 48, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2)), "3,1,2"),
     ("p128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),      # overlapping pooling windows
@@ -257,7 +261,8 @@ def test_operands_off_a_16_byte_boundary(device, monkeypatch, geom, src, shp):
 
 
 @pytest.mark.parametrize("shp,forms", [
-    ((8, 64, 28, 28, 96, 3, 3, 2, 1, 1, None), ("s128x64/stored/0+25x4", "s128x64/pieces", "s128x64/stored")),
+    ((8, 64, 28, 28, 96, 3, 3, 2, 1, 1, None), ("s128x64/stored/0+25x4", "s128x64/stored")),
+    ((16, 128, 56, 56, 128, 3, 3, 2, 1, 1, None), ("s128x64/pieces", "s128x64/stored")),
     ((1, 512, 7, 7, 512, 3, 3, 1, 1, 1, None), ("t3x64/stored/0+16x16", "t3x64/stored/0+16x8", "t3x64/stored")),
 ])
 def test_workspaces_of_any_size(device, monkeypatch, shp, forms):
@@ -313,32 +318,41 @@ def test_launches_captured_into_a_graph(device, monkeypatch, geom, split, src, s
         assert torch.equal(out, sconv.sconv_forward(xd, wd, stride, pad, groups, relu=True, ws=ws2))
 
 
-@pytest.mark.parametrize("shp,call,family", [
-    ((2, 512, 28, 28, 512, 3, 3, 1, 1, 1, None), "prepared", "tap"), ((2, 256, 28, 28, 256, 3, 3, 1, 1, 1, None), "prepared", "quad"),
-    ((2, 128, 56, 56, 128, 3, 3, 2, 1, 1, None), "ws", "wide"), ((2, 512, 28, 28, 256, 1, 1, 1, 0, 1, None), "ws", None),
+@pytest.mark.parametrize("shp,call,families", [
+    ((2, 512, 28, 28, 512, 3, 3, 1, 1, 1, None), "prepared", ("tap", "quad")), ((2, 256, 28, 28, 256, 3, 3, 1, 1, 1, None), "prepared", ("tap", "quad")),
+    ((2, 128, 56, 56, 128, 3, 3, 2, 1, 1, None), "ws", ("wide",)), ((2, 512, 28, 28, 256, 1, 1, 1, 0, 1, None), "ws", ("quad1x1",)),
+    ((8, 128, 56, 56, 128, 3, 3, 1, 1, 1, None), "ws", ("tap", "quad")), ((16, 64, 56, 56, 64, 3, 3, 1, 1, 1, None), "ws", ("tap", "quad")),
+    ((4, 256, 56, 56, 256, 3, 3, 1, 1, 1, None), "ws", ("tap", "quad")), ((16, 22, 33, 33, 256, 3, 3, 1, 1, 1, None), "ws", ("gen",)),
 ])
 @pytest.mark.parametrize("z", [0.5, 0.7])
-def test_no_further_from_64_bit_sums_than_the_kernel_it_replaces(device, monkeypatch, shp, call, family, z):
-    """The tiled geometries with sums of their own for the small products: relative error against the oracle's 64-bit sums, at
-    most a twentieth above that of the kernel that would run otherwise (its own sums round to other bits on another seed)."""
+def test_no_further_from_64_bit_sums_than_the_kernels_it_replaces(device, monkeypatch, shp, call, families, z):
+    """Relative error against the oracle's 64-bit sums of the plan that the model takes: at most a twentieth above that of the other
+    kernels (whose own moves by that much with the seed)."""
     N, C, H, W, K, R, S, stride, pad, groups, pool = shp
     _, x, w = workloads.make_random_case(412, N, C, H, W, K, R, S, stride, pad, groups, pool, z)
     xd, wd = to_dev(x), to_dev(w)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
     kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd)) if call == "prepared" else dict(ws=ws)
+    desc = sconv.desc_for(xd, wd, stride, pad, groups, pool, False, z, call == "prepared")
     ref, _ = oracle.conv(x, w, stride, pad, groups, relu=False)
 
     def error():
-        y = sconv.sconv_forward(xd, wd, stride, pad, groups, **kw).cpu().numpy().astype(np.float64)
+        y = sconv.sconv_forward(xd, wd, stride, pad, groups, zero_ratio=z, **kw).cpu().numpy().astype(np.float64)
         return np.linalg.norm(y - ref) / np.linalg.norm(ref)
-    if family:
-        monkeypatch.setenv("SCONV_VARIANT", family)
-    assert not sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool), False, ws.numel()).startswith("piece")
-    other = error()
-    geom = "c128x64" if R == 1 else "s128x64" if stride == 2 else "a128x64"
-    _pin(monkeypatch, geom, None, "1" if call == "prepared" else "0")
-    _assert_it_runs(sconv.desc_for(xd, wd, stride, pad, groups, pool, False, None, call == "prepared"), pool, ws, geom, None,
-                    "1" if call == "prepared" else "0")
+    monkeypatch.delenv("SCONV_VARIANT", raising=False)
+    name = sconv.sconv_launch_name(desc, False, ws.numel())
+    if not name.startswith("piece/"):      # (at these small batches: the one geometry that takes over at larger ones, pinned)
+        assert R == 1 or stride == 2
+        geom = "c128x64" if R == 1 else "s128x64"
+        _pin(monkeypatch, geom, None, "0")
+        _assert_it_runs(desc, pool, ws, geom, None, "0")
     mine = error()
-    print(f"{mine:.3e} against {other:.3e}")
-    assert mine <= 1.05 * other
+    for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_VARIANT"):
+        monkeypatch.delenv(name, raising=False)
+    for family in families:
+        if family != "quad1x1":
+            monkeypatch.setenv("SCONV_VARIANT", family)
+        assert not sconv.sconv_launch_name(desc, False, ws.numel()).startswith("piece")
+        other = error()
+        print(f"{family}: {mine:.3e} against {other:.3e}")
+        assert mine <= 1.05 * other

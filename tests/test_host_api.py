@@ -143,7 +143,7 @@ def test_launch_name_names_the_kernel_that_runs():
     name = lambda *a, ws=0, pooled=False, **k: sconv.sconv_launch_name(sconv.make_desc(*a, **k), pooled, ws)
     s2 = sconv.make_desc(32, 128, 56, 56, 128, 3, 3, 2, 1)
     assert sconv.sconv_variant_name(s2) == "wide3x3" and sconv.sconv_plan_name(s2) == "wide3x3/model"
-    assert sconv.sconv_launch_name(s2) == "wide3x3/model"
+    assert sconv.sconv_launch_name(s2).startswith("piece/model:s128x64/stored")
     assert sconv.sconv_launch_name(s2, False, sconv.sconv_workspace_size(s2)).startswith("piece/model:s128x64/pieces")
     assert name(32, 896, 14, 14, 896, 3, 3, 1, 1, 7).startswith("piece/model:a128x64/stored")
     # a short launch that the vector kernel leaves to the tap-dealing kernel
@@ -157,9 +157,15 @@ def test_launch_name_names_the_kernel_that_runs():
     assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.5, ws=64 << 20).startswith("piece/model:")
     assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.95, ws=64 << 20) == "quad3x3/model"
     assert name(8, 512, 28, 28, 512, 3, 3, 1, 1, zero_ratio=0.5, ws=64 << 20, prepared=True).startswith("piece/model:a128x64/prepared")
+    # on large launches of 256 channels any form, on others only those that keep the small products apart
+    assert name(8, 256, 56, 56, 256, 3, 3, 1, 1, zero_ratio=0.5, ws=64 << 20).startswith("piece/model:a128x64/pieces")
+    for z in (0.5, 0.7):
+        assert name(8, 128, 56, 56, 128, 3, 3, 1, 1, zero_ratio=z, ws=64 << 20).startswith("piece/model:s128x64/pieces")
+        assert name(32, 64, 56, 56, 64, 3, 3, 1, 1, zero_ratio=z, ws=64 << 20).startswith("piece/model:b64x128/")
+        assert name(8, 512, 14, 14, 512, 3, 3, 1, 1, pool=(2, 2, 2), zero_ratio=z, ws=64 << 20, pooled=True).startswith("piece/model:u128x64/")
     buf = ctypes.create_string_buffer(8)
     L = sconv.lib()
-    assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, buf, 6) == 0 and buf.value == b"wide3"
+    assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, buf, 6) == 0 and buf.value == b"piece"
     assert L.sconv_launch_name(ctypes.byref(s2), 0, 0, None, 6) == sconv.SCONV_EINVAL
     assert L.sconv_launch_name(ctypes.byref(sconv.Desc()), 0, 0, buf, 6) == sconv.SCONV_EINVAL
 
