@@ -48,6 +48,11 @@ PIECE_PEAK_TF = 2500.0 / 6   # piece kernel: six bf16 matrix products (dense pea
 # run measures - the line names its source, and prints null when the plan that ran is not in the table.
 MEASURED_TRAFFIC = {
     ("quad3x3/q32t7d/8x4", "vgg-256x56", 8): (54.8e6 + 25.9e6, "profiles/quad3x3_vgg-256x56_n8.txt"),
+    # the launches of a piece plan together: filters cut into pieces, the product kernel, the sum of its split tiles
+    **{(plan, "vgg-256x56", 8): (89.1e6 + 40.5e6, "profiles/piece_counters.txt")
+       for plan in ("piece/model:a128x64/pieces/768+16x16/kept", "piece/model:a128x64/pieces/768+16x16", "piece/a128x64/4x1")},
+    **{(plan, "vgg-512x28", 8): (275.4e6 + 40.8e6, "profiles/piece_counters.txt")
+       for plan in ("piece/model:s128x64/pieces/256+136x3/kept", "piece/model:s128x64/pieces/256+136x3", "piece/s128x64/4x1")},
 }
 # elements per zero test of the kernels that skip whole groups (1: every zero element is skipped)
 SKIP_GRANULE = {"rows": 1, "tap3x3": 1, "quad3x3": 6, "quad1x1": 32, "wide3x3": 16, "gen": 16}

@@ -105,8 +105,10 @@ int sconv_encode(const sconv_desc_t* desc, int fmt, const float* x_dev, float* v
  * zero inside a group that also holds a nonzero is multiplied (0 * w adds nothing for finite w;
  * with Inf or NaN filters the variants can differ).
  * A launch of any of these families runs on the "piece" kernel - three exact bf16 pieces per fp32 value, six products,
- * fp32 accumulation, on the bf16 matrix pipe - when its cost model promises less time: 1x1, 3x3, 5x5 and 7x7
- * of any stride and padding, plain or pooled over 2x2 windows, except on very sparse maps.  It multiplies the zeros of a tile (a result that
+ * fp32 accumulation, on the bf16 matrix pipe - when its cost model promises less time: 1x1, 3x3, 5x5 and 7x7,
+ * plain or pooled over 2x2 windows, where the input positions of its tiles fit (strided 3x3 mostly, strided 1x1, 5x5 and 7x7 on small
+ * maps only).  Its time does not depend on the zeros, the vector kernel's does: it takes 3x3 layers of that family over where a reported
+ * ratio makes it the faster one, and without one where it is no slower at 90 % zeros.  It multiplies the zeros of a tile (a result that
  * is not finite is summed again with every zero element skipped).
  * A workspace (lent with sconv_set_workspace, or passed to the ..._ws forms) is used three ways.
  * (3) The piece kernel keeps its pieces of the filters there when there is room, and the partial sums of tiles that would

@@ -81,7 +81,7 @@ bool pw_supported(const Problem& p, bool pooled);
 int launch_pointwise(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                      hipStream_t stream);
 
-// Matrix kernels on exact bf16 pieces: 1x1, 3x3, 5x5 and 7x7 kernels, any stride, padding and grouping, optional pooling over
+// Matrix kernels on exact bf16 pieces: 1x1, 3x3, 5x5 and 7x7 kernels of any grouping whose tiles' input fits, optional pooling over
 // 2x2 windows.
 bool piece_supported(const Problem& p, bool pooled);
 // modelled microseconds of the plan launch_piece would take (after split_scratch_select); negative: none

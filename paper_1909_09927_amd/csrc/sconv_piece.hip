@@ -1,5 +1,6 @@
-// Matrix kernels on exact bf16 pieces: 1x1, 3x3, 5x5 and 7x7 kernels of any stride, padding and grouping, optional pooling
-// over 2x2 windows.
+// Matrix kernels on exact bf16 pieces: 1x1, 3x3, 5x5 and 7x7 kernels, any grouping, optional pooling over 2x2 windows, of any stride and
+// padding as far as the input positions of a tile fit its staging (stage_positions): strided 3x3 on ordinary maps, strided 1x1, 5x5 and
+// 7x7, and strided or pooled 1x1 of widths that do not fill whole rows, only on small ones.
 //
 // What bounds the other matrix kernels on the large layers is the fp32 matrix rate (157 TFLOP/s on paper, 138 measured on a
 // large product).  The bf16 matrix pipe is sixteen times as fast, and an fp32 value is the exact sum of three bf16 values
@@ -35,7 +36,7 @@
 // zeros.  Filters: a lane's fragment is 8 channels of one filter and tap, straight from memory into registers, one to three
 // taps ahead (no LDS, no barrier): from pieces that a kernel writes into the workspace first, from prepared filters, or
 // from the filters as stored.  MT = 1, NT = 4 gives an instruction stream of 216 matrix instructions to 108 LDS reads and
-// 27 loads per chunk; two workgroups a compute unit keep the matrix pipe busy 70 % of the time at 1.9 GHz, 250 TFLOP/s
+// 27 loads per chunk; two workgroups a compute unit keep the matrix pipe busy 67 % of the time at 1.9 GHz, 220 - 240 TFLOP/s
 // dense-equivalent on 512 channels @28x28 at batch 62 (quad3x3: 120).
 //
 // Tiles that do not fill a last round of workgroups are split along the channels (split tiles: partial sums into the
@@ -117,7 +118,8 @@ template <int MT_, int NT_, int WM_, int WN_, int T_, int CS_, bool POOL_, int X
 struct PGeom {
     static constexpr int MT = MT_, NT = NT_, WM = WM_, WN = WN_, T = T_, CS = CS_, XU = XU_, OCC = OCC_;   // XU: staging units per wavefront
     static constexpr bool POOL = POOL_;
-    // microseconds a compute unit spends on one staged chunk of one workgroup when two or three workgroups share it
+    // microseconds a compute unit spends on one staged chunk of one workgroup when two or three workgroups share it (fitted to the
+    // launches of the benchmark layers; s128x64 on filters as stored: 512 @28x28 at batch 8 218 us)
     static constexpr double tc(int src, int taps)
     {
         return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.75 : src == SRC_FP32 ? 4.9 : 5.3)
@@ -529,7 +531,8 @@ struct TGeom {
 // cuts its eight values into pieces when it takes them.  Filters and map of the next chunk are on their way while a chunk is
 // multiplied.
 // Bound by the walk of one workgroup where there are few (2.0 us per chunk of 16 channels, 5x5 and 64 windows), by the matrix
-// pipe and the two barriers per chunk where there are many (55 % of the matrix rate at 5x5).  Against gen: 48 -> 128 5x5 @7x7 at
+// pipe and the two barriers per chunk where there are many (35 % of the busy compute
+// units' matrix clocks at 5x5).  Against gen: 48 -> 128 5x5 @7x7 at
 // batch 32 13 us (43), 64 -> 256 5x5 @28x28 at batch 16 90 (136), 128 -> 512 7x7 @28x28 at batch 8 293 (513); against the vector
 // kernel without a workspace 256 -> 256 3x3 @14x14 at batch 1 23 (41).  More than one workgroup per compute unit needs 128
 // registers: with 64 accumulators the compiler spills and the kernel takes twice as long.  Relative error against 64-bit sums
