@@ -384,7 +384,7 @@ bool piece_close(const Problem& p, bool pooled)
 // these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
 // any ratio), @28x28 at batch 8 190 at 75 % (165) - and about 8 us for the filter transposition of large launches.  Where the ratio is
-// unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.6 (512
+// unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.3 (512
 // @28x28 at batch 8 with a workspace, vector / piece kernel: 331 / 208 us at 50 % zeros, 239 / 208 at 70, 172 / 207 at 85, 121 / 191 at
 // 95; 256 @56x56 304 / 162, 232 / 162, 182 / 160, 133 / 136).  Of 120 random layers and 21 of the benchmark's without a ratio, those of
 // this family that lost up to 1.6x from 85 % on stay; the others - short launches, and 256 @56x56 - keep the piece kernels.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
@@ -407,7 +407,7 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     switch (v) {
     case V_TAP: {
         const double nz = p.zhint < 0.0f ? 0.1 : 1.0 - p.zhint;
-        other = 14.0 + gf * (p.zhint < 0.0f ? 4.6 : 2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+        other = 14.0 + gf * (p.zhint < 0.0f ? 4.3 : 2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
         if (!can_split && !p.wprep) walk = 10.0 + p.Cg * (0.06 + 0.14 * nz);
         break;
     }

@@ -15,7 +15,8 @@
 // apart, 1.86e-7 / 1.79e-7 / 1.60e-7 without; tap3x3 1.62e-7 / 1.33e-7 / 1.05e-7, quad3x3 2.24e-7 / 1.81e-7 / 1.40e-7, wide3x3 4.25e-7 /
 // 3.30e-7 / 2.35e-7.  The third set of accumulators takes a third workgroup off a compute unit: no loss where LDS or filters cut on the way
 // leave two anyway (128 -> 128 3x3 stride 2 @56x56 at batch 32 62.4 -> 55.8 us, 512 @28x28 at batch 8 with prepared filters 161 -> 159,
-// 1x1 512 -> 256 @28x28 at batch 16 32.9 -> 32.0), a quarter where three fit and the launch fills them (256 @56x56 149 -> 186).
+// 1x1 512 -> 256 @28x28 at batch 16 32.9 -> 32.0), nothing either with loads in their places (SPREAD), which leave two: 256 @56x56 150 (a128x64)
+// and 151 (b64x128) at batch 8.
 // The splitting is the one of G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
 // Higher-Precision Computations" (ARITH 2019).
 // Both operands are multiplied by 2^24 before they are cut: the last bit of the smallest fp32 subnormal, 2^-149, becomes 2^-125,
@@ -83,21 +84,25 @@ __device__ __forceinline__ bool not_finite(float r) { return (__builtin_bit_cast
 
 // Eight fp32 values times 2^24 as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every
 // remainder is exact) for all values below 2^104.
+__device__ __forceinline__ void split2(float a, float b, float up_a, float up_b, int i, u4 (&out)[3])
+{
+    a *= up_a;
+    b *= up_b;
+    const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
+    const float ra = a - __builtin_bit_cast(float, h << 16);
+    const float rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
+    const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
+    const float sa = ra - __builtin_bit_cast(float, m << 16);
+    const float sb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
+    out[0][i] = h;
+    out[1][i] = m;
+    out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){sa, sb}, bf2));
+}
+
 __device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
 {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float a = v[2 * i] * kUp, b = v[2 * i + 1] * kUp;
-        const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
-        const float ra = a - __builtin_bit_cast(float, h << 16);
-        const float rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
-        const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
-        const float sa = ra - __builtin_bit_cast(float, m << 16);
-        const float sb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
-        out[0][i] = h;
-        out[1][i] = m;
-        out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){sa, sb}, bf2));
-    }
+    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], kUp, kUp, i, out);
 }
 
 // Filters read as stored: a lane's reads are at raw_base (its filter's row, its half of a fragment's 16 channels) plus raw_step,
@@ -122,15 +127,17 @@ struct PGeom {
     // launches of the benchmark layers; s128x64 on filters as stored: 512 @28x28 at batch 8 218 us)
     static constexpr double tc(int src, int taps)
     {
-        return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.75 : src == SRC_FP32 ? 4.9 : 5.3)
-                                   : (src == SRC_PIECES ? 2.6 : src == SRC_FP32 ? 2.75 : APART_ && T_ == 9 ? 3.45 : 3.7) * (MT * NT * NW) / 8.0) * (T_ == 1 ? 0.5 : taps / 9.0);
+        const double wide = XU > 3 ? 0.12 : 0.0;   // (four staging units: 512 @28x28 at batch 8 158 us against 151 with three or two)
+        return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.7 : src == SRC_FP32 ? 4.9 : 5.3)
+                                   : (src == SRC_PIECES ? 2.48 + wide : src == SRC_FP32 ? 2.7 + wide : APART_ && T_ == 9 ? 3.45 : 3.7) * (MT * NT * NW) / 8.0) *
+               (T_ == 1 ? 0.5 : taps / 9.0);
     }
     static constexpr int NW = WM * WN, BM = 32 * MT * WM, BN = 32 * NT * WN;
     static constexpr int CG = 2 * CS;    // 8-channel groups per staged chunk
     static_assert(XU * NW % CG == 0, "every 8-channel group has the same number of staging units");
     static constexpr int PXMAX = XU * NW / CG * 64;   // staged positions
     static constexpr int AR = T == 9 ? 3 : 4;   // filter fragments in flight (ring)
-    static constexpr int SE = T == 9 ? 6 : CS > 1 ? CS - 2 : 0;   // tap after which the next chunk is laid out in LDS
+    static constexpr int SPARE = 1280;          // bytes of a chunk's LDS that lanes without a position write to (64 * 16 + 32)
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
     // sums of their own for the five small products (see the top)
     static constexpr bool apart(int src) { return APART_ || (NT == 2 && src == SRC_FP32); }
@@ -217,40 +224,33 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         const int sr = r0 + row, n = sr / HP, h = sr - n * HP - p.pad;
         const bool ok = q < PX && n < p.N && h >= 0 && h < iH && cw >= 0 && cw < iW;
         xvo[u] = ok ? 4u * (unsigned)((n - n0) * p.C * HW + h * iW + cw) : 0x80000000u;
-        xst[u] = q < PX ? cgi * CGB + q * 48 : -1;
+        xst[u] = q < PX ? cgi * CGB + q * 48 : CG * CGB + lane * 16;   // (lanes past the tile's positions write where nobody reads)
     }
     const float* xb = x + ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW;
     const size_t xleft = ((size_t)p.N * p.C * HW - ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW) * 4;
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xb), 0, (int)min(xleft, (size_t)0x7ffffffc), 0x00020000);
     float xr[XU][8];
-    auto fetch_x = [&](int ch) {
+    auto fetch_x = [&](int u, int ch) {
+        const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
 #pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                xr[u][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
-        }
+        for (int j = 0; j < 8; ++j)
+            xr[u][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
     };
-    auto store_x = [&](unsigned char* buf, int ch) {
-        if ((ch + 1) * CS * 16 > p.Cg) {   // channels past the group's last one count as zeros
-#pragma unroll
-            for (int u = 0; u < XU; ++u)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (ch * CS * 16 + (u * NW + wave) % CG * 8 + j >= p.Cg) xr[u][j] = 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            u4 f[3];
-            split8(xr[u], f);
-            if (xst[u] >= 0) {
-                u4* d = reinterpret_cast<u4*>(buf + xst[u]);
-                d[0] = f[0];
-                d[1] = f[1];
-                d[2] = f[2];
-            }
+    // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
+    // channels past the group's last one count as zeros
+    u4 xf[3];
+    auto stage = [&](int u, int part, unsigned char* buf, int ch, int after) {
+        if (part < 4) {
+            const int left = p.Cg - (ch * CS * 16 + (u * NW + wave) % CG * 8) - 2 * part;
+            split2(xr[u][2 * part], xr[u][2 * part + 1], left > 0 ? kUp : 0.0f, left > 1 ? kUp : 0.0f, part, xf);
+        } else if (part == 4) {
+            u4* d = reinterpret_cast<u4*>(buf + xst[u]);
+            d[0] = xf[0];
+            d[1] = xf[1];
+            d[2] = xf[2];
+        } else {
+            fetch_x(u, after);
         }
     };
 
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
 
     constexpr bool APART = G::apart(SRC);
     v16f acc[MT][NT], tmp[MT][NT], accl[APART ? MT : 1][APART ? NT : 1];
-    const int bufb = CG * CGB;
+    const int bufb = CG * CGB + G::SPARE;
     const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -363,62 +363,81 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
             }
         }
     };
-    auto products = [&](const u4 (&bb)[NH][3], int h, bool first) {
-        // products smallest first: x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0
+    // SPREAD: every load, cut and LDS write has its place between two matrix instructions; without the fences the compiler moves the
+    // loads down to their uses and waits there (b64x128 197 -> 153 us and s128x64 163 -> 158 on 512 @28x28 at batch 8, 256 @56x56 with a128x64
+    // 154 -> 150, 1x1 512 -> 256 @28x28 at batch 16 33.0 -> 31.2).  Not for 3x3 filters as stored, which are cut on the way: fenced, their
+    // registers spill (s128x64 107 -> 138 us on 896 channels in 7 groups @14x14).
+    constexpr bool SPREAD = SRC != SRC_RAW || G::T == 1;
+    // Matrix instruction m of a half step.  One chain: smallest products first (x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0); sums apart:
+    // x0 w0 first, so that its sums are ready when the others are still issued.
+    constexpr int NM = NH * MT * 6;
+    auto product = [&](const u4 (&bb)[NH][3], int h, int m, bool first) {
         constexpr int qa[6] = {0, 2, 1, 0, 1, 0}, qb[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-#pragma unroll
-            for (int n = 0; n < NH; ++n)
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    v16f& d = APART && c < 5 ? accl[APART ? i : 0][APART ? h * NH + n : 0] : tmp[i][h * NH + n];
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
-                                                                first && c == (APART ? 5 : 0) ? zero : d, 0, 0, 0);
-                }
+        const int c = APART && SPREAD ? (m / (NH * MT) + 5) % 6 : m / (NH * MT), n = m / MT % NH, i = m % MT;
+        v16f& d = APART && c < 5 ? accl[APART ? i : 0][APART ? h * NH + n : 0] : tmp[i][h * NH + n];
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
+                                                    first && c == (APART ? 5 : 0) ? zero : d, 0, 0, 0);
     };
 
-    fetch_x(chb);
+#pragma unroll
+    for (int u = 0; u < XU; ++u) fetch_x(u, chb);
     fetch_a(0, chb * CS, 0);
     if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, chb * CS, 1);
     if (G::T == 1) {
         fetch_a(1, chb * CS + 1, 0);
         fetch_a(2, chb * CS + 2, 0);
     }
-    store_x(lds, chb);
-    if (G::T != 9) fetch_x(min(chb + 1, che - 1));
+#pragma unroll
+    for (int u = 0; u < XU; ++u)
+#pragma unroll
+        for (int part = 0; part < (SPREAD ? 6 : 5); ++part) stage(u, part, lds, chb, min(chb + 1, che - 1));
     __syncthreads();
 
+    constexpr int E = G::T * CS, D = AR - 1;
+    constexpr int ITEMS = XU * 6, GAP = (E * HS - 1) * NM / ITEMS < 4 ? (E * HS - 1) * NM / ITEMS : 4;   // staging: a part every GAP instructions
+    static_assert(GAP >= 1, "the staging of a chunk fits its products");
     for (int ch = chb; ch < che; ++ch) {
         const unsigned char* buf = lds + ((ch - chb) & 1) * bufb;
         unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
-        const bool more = ch + 1 < che;
-        const int nx = more ? ch + 1 : ch;
-        constexpr int E = G::T * CS, D = AR - 1;
+        const int nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
         auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
         auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
+        auto next_b = [&](int e, int h, int cur) {
+            if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
+            else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
+        };
         load_b(bq[0], buf + off(0), imm(0), 0);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if (SRC == SRC_RAW && G::T == 9) {   // three taps (one kernel row) are fetched at a time
-                take_a(0, e % 3 % VW);
+            take_a(SRC == SRC_RAW && G::T == 9 ? 0 : e % AR, SRC == SRC_RAW && G::T == 9 ? e % 3 % VW : 0);
+            if (!SPREAD) {   // three taps (one kernel row) are fetched at a time
                 if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
-            } else {
-                take_a(e % AR, 0);
-                fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
+                if (e == 0 && ch + 1 < che)
+#pragma unroll
+                    for (int u = 0; u < XU; ++u) fetch_x(u, nx);
             }
-            if (G::T == 9 && e == 0 && more) fetch_x(nx);
 #pragma unroll
             for (int h = 0; h < HS; ++h) {
                 const int cur = (e * HS + h) & 1;
-                if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
-                else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
-                products(bq[cur], h, e == 0);
+                if (!SPREAD) next_b(e, h, cur);
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    product(bq[cur], h, m, e == 0);
+                    // between the matrix instructions, where the compiler would not put them: what the next ones need
+                    if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+                    if (SPREAD && m == 0) next_b(e, h, cur);
+                    if (SPREAD && m == 1 && h == 0)
+                        fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
+                    const int at = (e * HS + h) * NM + m - NM;
+                    if (SPREAD && at >= 0 && at % GAP == 0 && at / GAP < ITEMS) stage(at / GAP / 6, at / GAP % 6, nbuf, nx, nx2);
+                    if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            if (e == G::SE && more) {
-                store_x(nbuf, nx);
-                if (G::T != 9) fetch_x(min(ch + 2, che - 1));
-            }
+            if (!SPREAD && e == 6 && ch + 1 < che)
+#pragma unroll
+                for (int u = 0; u < XU; ++u)
+#pragma unroll
+                    for (int part = 0; part < 5; ++part) stage(u, part, nbuf, nx, nx2);
         }
 #pragma unroll
         for (int i = 0; i < MT; ++i)
@@ -869,7 +888,7 @@ size_t usable_workspace(const Problem& p, bool pooled)
 template <class G>
 int occupancy_limit(int src, size_t lds_bytes)
 {
-    const int by_lds = (int)(160 * 1024 / lds_bytes), by_regs = G::tc(src, 9) > 4.0 || G::apart(src) || (src == SRC_RAW && G::XU > 2) ? 2 : 3;
+    const int by_lds = (int)(160 * 1024 / lds_bytes), by_regs = G::tc(src, 9) > 4.0 || G::apart(src) || src != SRC_RAW || G::XU > 2 ? 2 : 3;
     const int n = by_regs * 4 / G::NW;
     return by_lds < n ? by_lds : n;
 }
@@ -985,7 +1004,7 @@ Plan plan_geom(const Problem& p, bool pooled, bool close)
     c.kblocks = (p.Kg + G::BM - 1) / G::BM;
     if (!choose_strips(p, pooled, G::BN, G::PXMAX, c)) return pl;
     c.cgb = (c.px * 48 + 255) / 256 * 256;
-    pl.lds_bytes = 2 * (size_t)G::CG * c.cgb;
+    pl.lds_bytes = 2 * ((size_t)G::CG * c.cgb + G::SPARE);
     if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
     if (pl.lds_bytes > 160 * 1024) return pl;
     // images a tile can touch, and the byte offsets of their elements
@@ -1016,7 +1035,7 @@ Plan plan_geom(const Problem& p, bool pooled, bool close)
         const double tc = G::tc(src, T);
         const int occ = occupancy_limit<G>(src, pl.lds_bytes);
         const double pre = src == SRC_PIECES ? 6.0 + (double)p.K * p.L * 10.0 / 4e6 : 0.0;
-        consider(pl, tiles, 256LL * occ, G::NW, tc, 1.25, 6.0 + pre, src, pb, kb32, ws, tile_bytes, G::T == 9 && G::apart(src) && src != SRC_FP32);
+        consider(pl, tiles, 256LL * occ, G::NW, tc, 1.25, 6.0 + pre, src, pb, kb32, ws, tile_bytes, G::T == 9 && src != SRC_FP32 && (src == SRC_PIECES || G::apart(src)));
     }
     return pl;
 }
@@ -1122,6 +1141,7 @@ struct Candidate {
     CAND("a128x128", 1, 4, 4, 1, 9, 1, false, 3, 2, false) \
     CAND("a128x64", 1, 2, 4, 1, 9, 1, false, 2, 2, false) \
     CAND("a64x128", 1, 2, 2, 2, 9, 1, false, 3, 2, false) \
+    CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 2, 2, true) /* as many positions as two units stage; more with four */ \
     CAND("s128x64", 1, 2, 4, 1, 9, 1, false, 4, 2, true) \
     CAND("b64x128", 1, 2, 2, 2, 9, 1, false, 3, 2, true) \
     CAND("p128x128", 1, 4, 4, 1, 9, 1, true, 3, 2, false) \
