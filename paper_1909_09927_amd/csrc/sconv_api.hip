@@ -363,25 +363,8 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
     return V_ROWS;
 }
 
-// Whether a piece kernel that takes a call over has to keep sums of its own for the small products.  Without them its error against
-// 64-bit sums is 1.7e-7 (1.5e-7 at 85 % zeros) at any number of channels, where the other kernels' grows with it: at 50 / 70 / 85 %
-// zeros quad3x3 and the vector kernel have 1.2 / 1.0 / 0.8 at 64 channels of 3x3, 1.6 / 1.3 / 1.0 at 128, 2.2 / 1.75 / 1.3 at 256; wide3x3 and
-// gen 1.6 / 1.3 / 1.0 at 64 and 2.1 / 1.7 / 1.2 at 128; the vector kernel's split launches less (512 channels 1.6 / 1.3 / 1.05).  With them
-// it is 0.5 - 0.9.
-bool piece_close(const Problem& p, bool pooled)
-{
-    const bool have_ws = split_scratch_possible(nullptr);
-    switch (choose(p, pooled, have_ws, nullptr, p.zhint)) {
-    case V_WIDE:
-    case V_GEN: return p.Cg < 128;
-    case V_QUAD: return p.Cg < 256;
-    case V_TAP: return p.Cg < 256 || (have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768);
-    default: return false;
-    }
-}
-
-// Whether a launch of family v runs on the piece kernels instead: when their cost model promises less time than
-// these fits of the family's measured times (us; gf = dense GFLOP).  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
+// What family v takes, by fits of its measured times (us; gf = dense GFLOP).  A launch runs on the piece kernels instead when their cost
+// model promises less.  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
 // any ratio), @28x28 at batch 8 190 at 75 % (165) - and about 8 us for the filter transposition of large launches.  Where the ratio is
 // unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.3 (512
@@ -395,13 +378,14 @@ bool piece_close(const Problem& p, bool pooled)
 // splits it: without a workspace 41 us for 256 channels on the vector kernel (23 on the taps kernel), 8 + 0.029 per column on
 // gen (48 channels of 5x5 43 us against 13, 64 of 7x7 98 against 25), 0.27 per channel on wide3x3.
 // Caller holds g_lock and has selected the stream's workspace.
-static bool piece_first(const Problem& p, bool pooled, Variant v)
+static double dense_gflop(const Problem& p, bool pooled)
 {
-    if (v == V_ROWS || env_value("SCONV_VARIANT")) return false;
-    const double gf = 2e-9 * p.K * (double)p.L * p.N * (pooled ? (double)p.PH * p.PW * p.ph * p.pw : (double)p.OH * p.OW);
-    if (gf < 0.03) return false;
-    double c = piece_cost(p, pooled);
-    if (c < 0.0) return false;
+    return 2e-9 * p.K * (double)p.L * p.N * (pooled ? (double)p.PH * p.PW * p.ph * p.pw : (double)p.OH * p.OW);
+}
+
+static double family_time(const Problem& p, bool pooled, Variant v)
+{
+    const double gf = dense_gflop(p, pooled);
     const bool can_split = split_scratch_possible(nullptr) && split_scratch_bytes() > 0;
     double other, walk = 0.0;
     switch (v) {
@@ -416,16 +400,45 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
         other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3);
         walk = 8.0 + 0.2 * p.Cg;
         break;
-    case V_PW:
-        other = 6.6 + gf * 10.2;
-        c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
-        break;
+    case V_PW: other = 6.6 + gf * 10.2; break;
     default:
         other = 12.0 + gf * 13.0;
         if (!can_split) walk = 8.0 + 0.029 * p.L;
         break;
     }
-    return c < (other > walk ? other : walk);
+    return other > walk ? other : walk;
+}
+
+// Whether a piece kernel that takes a call over has to keep sums of its own for the small products.  Without them its error against
+// 64-bit sums is 1.7e-7 (1.5e-7 at 85 % zeros) at any number of channels, where the other kernels' grows with it: at 50 / 70 / 85 %
+// zeros quad3x3 and the vector kernel have 1.2 / 1.0 / 0.8 at 64 channels of 3x3, 1.6 / 1.3 / 1.0 at 128, 2.2 / 1.75 / 1.3 at 256; wide3x3 and
+// gen 1.6 / 1.3 / 1.0 at 64 and 2.1 / 1.7 / 1.2 at 128; the vector kernel's split launches less (512 channels 1.6 / 1.3 / 1.05).  With them
+// it is 0.5 - 0.9.
+// *family_us: what the kernel it takes over from would take; negative: not known (a pinned variant), zero: no plan of
+// fewer products may take its place (the vector kernel without a ratio, and quad3x3 from 92 % zeros on, whose error falls with the products left).
+bool piece_close(const Problem& p, bool pooled, double* family_us)
+{
+    const bool have_ws = split_scratch_possible(nullptr);
+    const Variant v = choose(p, pooled, have_ws, nullptr, p.zhint);
+    const bool keeps = (v == V_TAP && p.zhint < 0.0f) || (v == V_QUAD && p.zhint >= 0.92f);
+    *family_us = v == V_ROWS || v == V_PIECE || env_value("SCONV_VARIANT") ? -1.0 : keeps ? 0.0 : family_time(p, pooled, v);
+    switch (v) {
+    case V_WIDE:
+    case V_GEN: return p.Cg < 128;
+    case V_QUAD: return p.Cg < 256;
+    case V_TAP: return p.Cg < 256 || (have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768);
+    default: return false;
+    }
+}
+
+static bool piece_first(const Problem& p, bool pooled, Variant v)
+{
+    if (v == V_ROWS || env_value("SCONV_VARIANT")) return false;
+    if (dense_gflop(p, pooled) < 0.03) return false;
+    double c = piece_cost(p, pooled);
+    if (c < 0.0) return false;
+    if (v == V_PW) c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
+    return c < family_time(p, pooled, v);
 }
 
 // The plan that the model of family v makes, by name, where the family has one; with the workspace that is selected.

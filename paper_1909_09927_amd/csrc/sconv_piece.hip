@@ -54,8 +54,11 @@ namespace sconv {
 
 namespace {
 
+
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -75,7 +78,9 @@ struct PieceCfg {
     int flat;        // 1x1 / stride 1: a map is one row of H*W positions
 };
 
-enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2 };
+// Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums),
+// the same with the running sums' rounding errors kept
+enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3, SRC_PAIRS_KEPT = 4 };
 
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
 
@@ -127,6 +132,7 @@ struct PGeom {
     // launches of the benchmark layers; s128x64 on filters as stored: 512 @28x28 at batch 8 218 us)
     static constexpr double tc(int src, int taps)
     {
+        if (src >= SRC_PAIRS) return src == SRC_PAIRS ? 1.72 : 1.82;
         const double wide = XU > 3 ? 0.12 : 0.0;   // (four staging units: 512 @28x28 at batch 8 158 us against 151 with three or two)
         return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.7 : src == SRC_FP32 ? 4.9 : 5.3)
                                    : (src == SRC_PIECES ? 2.48 + wide : src == SRC_FP32 ? 2.7 + wide : APART_ && T_ == 9 ? 3.45 : 3.7) * (MT * NT * NW) / 8.0) *
@@ -140,15 +146,260 @@ struct PGeom {
     static constexpr int SPARE = 1280;          // bytes of a chunk's LDS that lanes without a position write to (64 * 16 + 32)
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
     // sums of their own for the five small products (see the top)
-    static constexpr bool apart(int src) { return APART_ || (NT == 2 && src == SRC_FP32); }
+    static constexpr bool apart(int src) { return APART_ || (NT == 2 && (src == SRC_FP32 || src >= SRC_PAIRS)); }
+    static constexpr bool PAIRS = T == 9 && MT == 1 && NT == 2 && WM == 4 && XU == 2 && APART_ == POOL;   // has the form with pairs (a128x64, u128x64)
+    static constexpr int PAIR_BUF = 2 * 2 * PXMAX * 16 + 256;   // LDS of one chunk as pairs, and the ranges of the wavefronts
 };
 
-template <class G, int SRC>
+// Two fp32 values times up as pairs of fp16 values: v up = p0 + 2^-11 p1, but for the last bit of every fourth value.  (Multiplication
+// or subtraction and rounding to fp16 in one instruction each; up2 = 2^11 up.)
+__device__ __forceinline__ void pair2(float a, float b, float up_a, float up2_a, float up_b, float up2_b, int i, u4 (&out)[2])
+{
+    unsigned h, r;
+    const float a2 = a * up2_a, b2 = b * up2_b;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "=v"(h) : "v"(a), "s"(up_a));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "+v"(h) : "v"(b), "s"(up_b));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "s"(-2048.0f), "v"(a2));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(r) : "v"(h), "s"(-2048.0f), "v"(b2));
+    out[0][i] = h;
+    out[1][i] = r;
+}
+
+__device__ __forceinline__ unsigned wave_max(unsigned v)
+{
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr 1, 2, 4, 8
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast 15, 31
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The magnitudes of some values: the largest, and the smallest but zero as 2 * bits - 1 (2^32 - 1: all are zeros).
+struct Range {
+    float hi = 0.0f;
+    unsigned lo = 0xffffffffu;
+    __device__ __forceinline__ void add(float a, float b)
+    {
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(hi) : "v"(a), "v"(b));   // (fmaxf quiets its operands first)
+        lo = min(lo, min((__builtin_bit_cast(unsigned, a) << 1) - 1, (__builtin_bit_cast(unsigned, b) << 1) - 1));
+    }
+    __device__ __forceinline__ uint2 of_wave() const { return make_uint2(wave_max(__builtin_bit_cast(unsigned, hi)), ~wave_max(~lo)); }
+};
+
+// The exponent sigma of the power of two that takes the largest of a set of magnitudes to 2^13 .. 2^14 (115 at most, so that 2^11 times it
+// is finite).
+__host__ __device__ inline int pair_exponent(unsigned hi_bits)
+{
+    const int e = hi_bits ? (int)(hi_bits >> 23) : 127;   // (all zeros: as good as any)
+    const int sg = 140 - (e > 254 ? 254 : e);
+    return sg < 115 ? sg : 115;
+}
+// What pairs at that scale hold: magnitudes below `hi` (bits; none too large for fp16), and but for zeros none below `lo` (as in
+// Range): 2^-14 after scaling, under which p0 has fewer than 11 bits and the product left out weighs more; 2^(-14 - below) for filters,
+// down to which it is 2^(below - 22) of such a weight's products.
+struct PairLimits {
+    unsigned hi, lo;
+    __host__ __device__ PairLimits(int sigma, int below)
+    {
+        const int el = 113 - sigma - below;     // biased exponent of the smallest
+        hi = (unsigned)(142 - sigma) << 23;
+        if (hi > 0x7f800000u) hi = 0x7f800000u;
+        lo = ((unsigned)(el > 0 ? el : 1) << 24) - 1;   // (nor fp32's subnormals)
+    }
+    __host__ __device__ bool hold(unsigned hi_bits, unsigned lo_key) const { return hi_bits < hi && lo_key >= lo; }
+};
+__host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast(float, (unsigned)(e + 127) << 23); }
+
+// The sums of one tile from fp16 pairs: v = p0 + 2^-11 p1, three products p0q0, p0q1, p1q0 (the fourth is 2^-22 of the product) instead of
+// six, two thirds of the LDS and filter traffic.  Bound by the chip's power like the six products (1.9 - 2.1 GHz; a third LDS buffer with one
+// barrier a chunk, loads two taps ahead, a second set of map registers and a third fewer vector instructions all measured within 3 %), of
+// which three take two thirds of the time: 256 @56x56 at batch 8 151 -> 105 us, 512 @28x28 at batch 8 with prepared filters 160 -> 112, at
+// batch 62 955 -> 720 (1.0 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
+// The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
+// stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter a
+// weight 2^30 below, false is returned and the tile is summed from three pieces (as stored): about one of 4 x 10^7 normally distributed values.
+// The sums of a chunk start from zero (p0q0); the small products' run through, 2^11 times their size, and with KEPT take the rounding error of
+// every addition to the running sums along (4 % of the time; error at 512 channels 1.5e-7 -> 1.07e-7).
+// Filters: a ring of nine fragments, eight taps ahead, for which half the registers of three pieces would not do.
+template <class G, bool KEPT, class Fetch>
+__device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::NT], int pitch, int chb, int che, int wave, int lane,
+                                          unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], float& undo_x)
+{
+    constexpr int NT = G::NT, XU = G::XU, NW = G::NW, D = 8;
+    constexpr int PLANE = G::PXMAX * 16, CGB = 2 * PLANE, BUF = G::PAIR_BUF;
+    static_assert(G::T == 9 && G::MT == 1 && NT == 2 && G::CS == 1, "3x3, one block of filters by two of windows");
+    const int half = lane >> 5;
+    int lb[NT], xst[XU];
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) lb[nb] = pos[nb] * 16 + half * CGB;
+#pragma unroll
+    for (int u = 0; u < XU; ++u) xst[u] = (u * NW + wave) % 2 * CGB + ((u * NW + wave) / 2 * 64 + lane) * 16;
+
+    float xr[XU][8];
+    u4 ap[9][2];
+    auto fetch_a = [&](int ch, int t) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            ap[t][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16 + q * 1024, (ch * 9 + t) * 2048, 0));
+    };
+    // The scale.  In the rule every wavefront finds its share of the next chunk within the limits of the scale there is, and says so (one word
+    // each).  Where one does not, all exchange their ranges: a scale that holds the chunk, or none (false).
+    int sigma = 0;
+    PairLimits lim(0, 0);
+    Range rg;
+    auto say = [&](int parity) {
+        const bool out = __any(!lim.hold(__builtin_bit_cast(unsigned, rg.hi), rg.lo));
+        rg = Range();
+        *reinterpret_cast<unsigned*>(lds + parity * BUF + 2 * CGB + wave * 4) = out;
+    };
+    auto new_scale = [&](int parity, int& to) {
+        Range all;
+#pragma unroll
+        for (int u = 0; u < XU; ++u)
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) all.add(xr[u][j], xr[u][j + 1]);
+        const uint2 of = all.of_wave();
+        if (lane == 0) *reinterpret_cast<uint2*>(lds + parity * BUF + 2 * CGB + 64 + wave * 8) = of;
+        __syncthreads();
+        const u4* s = reinterpret_cast<const u4*>(lds + parity * BUF + 2 * CGB + 64);
+        const u4 a = s[0], b = s[1];
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(a[0], a[2]), max(b[0], b[2])));
+        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(a[1], a[3]), min(b[1], b[3])));
+        to = pair_exponent(hi);
+        lim = PairLimits(to, 0);
+        return lim.hold(hi, lo);
+    };
+    u4 xf[2];
+    // staging of one unit in six parts, as in piece_kernel; up: bits of 2^sigma
+    auto stage = [&](int u, int part, unsigned char* buf, int ch, int after, unsigned up) {
+        if (part < 4) {
+            const int left = p.Cg - (ch * 16 + (u * NW + wave) % 2 * 8) - 2 * part;
+            const unsigned ua = left > 0 ? up : 0, ub = left > 1 ? up : 0, ua2 = left > 0 ? up + (11u << 23) : 0, ub2 = left > 1 ? up + (11u << 23) : 0;
+            pair2(xr[u][2 * part], xr[u][2 * part + 1], __builtin_bit_cast(float, ua), __builtin_bit_cast(float, ua2), __builtin_bit_cast(float, ub),
+                  __builtin_bit_cast(float, ub2), part, xf);
+        } else if (part == 4) {
+            *reinterpret_cast<u4*>(buf + xst[u]) = xf[0];
+            *reinterpret_cast<u4*>(buf + xst[u] + PLANE) = xf[1];
+        } else {
+            fetch_x(xr[u], u, after);
+        }
+    };
+    auto range_of = [&](int u) {
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) rg.add(xr[u][j], xr[u][j + 1]);
+    };
+
+    const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    v16f tmp[NT], accl[NT];
+    float run[NT][16];
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        accl[nb] = zero;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) run[nb][v] = 0.0f;
+    }
+    u4 b0[3][NT], b1[2][NT];             // windows: p0 two taps ahead, p1 one
+    auto load_b = [&](u4& to, const unsigned char* buf, int e, int n, int q) {
+        to = *reinterpret_cast<const u4*>(buf + e / 3 * pitch * 16 + lb[n] + e % 3 * 16 + q * PLANE);
+    };
+    auto product = [&](int e, int m) {
+        const int c = m / NT, n = m % NT;      // p0q0, then p1q0 and p0q1
+        v16f& d = c ? accl[n] : tmp[n];
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, ap[e][c == 1 ? 1 : 0]), __builtin_bit_cast(h8, c == 2 ? b1[e & 1][n] : b0[e % 3][n]),
+                                                   e == 0 && !c ? zero : d, 0, 0, 0);
+    };
+
+#pragma unroll
+    for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb);
+#pragma unroll
+    for (int t = 0; t < D; ++t) fetch_a(chb, t);
+    if (!new_scale(0, sigma)) return false;
+#pragma unroll
+    for (int u = 0; u < XU; ++u)
+#pragma unroll
+        for (int part = 0; part < 6; ++part) stage(u, part, lds, chb, min(chb + 1, che - 1), (unsigned)(sigma + 127) << 23);
+#pragma unroll
+    for (int u = 0; u < XU; ++u) range_of(u);
+    say(1);
+    __syncthreads();
+
+    // a quarter of the chunk's sums to the running sums (times by: the step from the scale of the chunk before); with KEPT tmp becomes what
+    // the addition lost
+    float by = 1.0f;
+    auto fold = [&](int part) {
+#pragma unroll
+        for (int v = part % 2 * 8; v < part % 2 * 8 + 8; ++v) {
+            const float t = tmp[part / 2][v], a = run[part / 2][v], sum = __builtin_fmaf(a, by, t);
+            run[part / 2][v] = sum;
+            if (KEPT) tmp[part / 2][v] = t - __builtin_fmaf(-by, a, sum);
+        }
+    };
+    constexpr int NM = 3 * NT;               // matrix instructions of a tap
+    static_assert(XU == 2 && NT == 2, "the places of a chunk's work between its matrix instructions");
+    for (int ch = chb; ch < che; ++ch) {
+        const int par = (ch - chb) & 1, nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
+        const unsigned char* buf = lds + par * BUF;
+        unsigned char* nbuf = lds + (par ^ 1) * BUF;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) load_b(b0[0][n], buf, 0, n, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) load_b(b1[0][n], buf, 0, n, 1);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) load_b(b0[1][n], buf, 1, n, 0);
+        const u4 said = *reinterpret_cast<const u4*>(nbuf + 2 * CGB);
+        int next = sigma;
+        unsigned up = (unsigned)(sigma + 127) << 23;
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                product(e, m);
+                __builtin_amdgcn_sched_barrier(0);
+                if (m < NT && e < 7) load_b(b0[(e + 2) % 3][m], buf, e + 2, m, 0);
+                if (m >= NT && m < 2 * NT && e < 8) load_b(b1[(e + 1) & 1][m - NT], buf, e + 1, m - NT, 1);
+                if (m == NM - 1) fetch_a(e == 0 ? ch : nx, e == 0 ? 8 : e - 1);
+                const int at = e * NM + m - NM;
+                if (at >= 0 && at < XU * 6) stage(at / 6, at % 6, nbuf, nx, nx2, up);
+                if (e == 7 && m % 3 == 0) range_of(m / 3);
+                if (e == 8 && m == 0) say(par);
+                if (e == 8 && m >= 2) fold(m - 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (e == 0 && m == NM - 1 && __builtin_amdgcn_readfirstlane((int)(said[0] | said[1] | said[2] | said[3]))) {
+                    if (!new_scale(par ^ 1, next) || next > sigma + 60 || next < sigma - 60) return false;
+                    up = (unsigned)(next + 127) << 23;
+                }
+            }
+        }
+        if (KEPT)
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) accl[nb][v] = __builtin_fmaf(tmp[nb][v], 2048.0f, accl[nb][v]);
+        by = power_of_two(next - sigma);
+        if (next != sigma) {
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb) accl[nb] *= by;
+            sigma = next;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-11f;   // (the last chunk is staged twice, so its scale may have moved on)
+    undo_x = power_of_two(-sigma);
+    return true;
+}
+
+template <class G, int FORM>
 __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
                                                               const float* __restrict__ w, const void* __restrict__ wp,
                                                               float* __restrict__ parts, float* __restrict__ y)
 {
     extern __shared__ __align__(16) unsigned char lds[];
+    constexpr int SRC = FORM >= SRC_PAIRS ? SRC_RAW : FORM;   // (a tile that pairs cannot hold is summed from the filters as stored)
     constexpr int MT = G::MT, NT = G::NT, CS = G::CS, CG = G::CG, NW = G::NW, XU = G::XU, AR = G::AR;
     const int PX = cfg.px, CGB = cfg.cgb;
     constexpr int T = G::T, S = T == 9 ? 3 : 1;
@@ -204,14 +455,14 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     const int r0 = n0 * HP + oh0 * p.stride;   // first staged row
     const int w0 = strip * TW * (G::POOL ? p.ps : 1) * p.stride - p.pad;   // input column of the first staged one
 
-    // this lane's windows (one per block of 32) as byte offsets into the staged tile
-    int lb[NT];
+    // this lane's windows (one per block of 32) as positions of the staged tile
+    int pos[NT];
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb) {
         const int P = min(tile * G::BN + (wn * NT + nb) * 32 + col, cfg.nrun - 1);
         int n, oh, ow;
         window(P, n, oh, ow);
-        lb[nb] = ((n * HP + oh * p.stride - r0) * pitch + ow * p.stride) * 48 + half * CGB;
+        pos[nb] = (n * HP + oh * p.stride - r0) * pitch + ow * p.stride;
     }
 
     // staging: unit u of this wavefront = 64 positions of one 8-channel group
@@ -230,227 +481,249 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     const size_t xleft = ((size_t)p.N * p.C * HW - ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW) * 4;
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xb), 0, (int)min(xleft, (size_t)0x7ffffffc), 0x00020000);
-    float xr[XU][8];
-    auto fetch_x = [&](int u, int ch) {
+    auto fetch_x = [&](float (&to)[8], int u, int ch) {
         const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            xr[u][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
+            to[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
     };
-    // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
-    // channels past the group's last one count as zeros
-    u4 xf[3];
-    auto stage = [&](int u, int part, unsigned char* buf, int ch, int after) {
-        if (part < 4) {
-            const int left = p.Cg - (ch * CS * 16 + (u * NW + wave) % CG * 8) - 2 * part;
-            split2(xr[u][2 * part], xr[u][2 * part + 1], left > 0 ? kUp : 0.0f, left > 1 ? kUp : 0.0f, part, xf);
-        } else if (part == 4) {
-            u4* d = reinterpret_cast<u4*>(buf + xst[u]);
-            d[0] = xf[0];
-            d[1] = xf[1];
-            d[2] = xf[2];
-        } else {
-            fetch_x(u, after);
-        }
-    };
-
-    // filters: fragments of 32 filters x 16 channels of one tap
     const int chb = split ? cfg.nch * ss / cfg.nss : 0, che = split ? cfg.nch * (ss + 1) / cfg.nss : cfg.nch;
     const int kblk0 = kb * (G::BM / 32) + wm * MT;
-    __amdgpu_buffer_rsrc_t wres;
-    int wvo[SRC == SRC_RAW ? MT : 1];
-    if (SRC == SRC_PIECES) {
-        const size_t blk = (size_t)cfg.nch * CS * T * 3072;
-        wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
-        wvo[0] = lane * 16;
-    } else if (SRC == SRC_FP32) {
-        const size_t blk = (size_t)p.Cg * T * 256;
-        wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
-        wvo[0] = half * 8 * T * 256 + (kblk0 & 1) * 128 + col * 4;
-    } else {
-        // filters as stored; a filter past the group's last one re-reads the last
-        const size_t first = ((size_t)g * p.Kg + (size_t)kb * G::BM) * p.L;
-        const size_t left = ((size_t)p.K * p.L - first) * 4;
-        wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + first), 0, (int)min(left, (size_t)0x7ffffffc), 0x00020000);
+    v16f acc[MT][NT];
+
+    bool paired = false;
+    const float* undo = nullptr;         // what the sums of pairs are multiplied by, per filter
+    float undo_x = kDown;
+    if constexpr (FORM >= SRC_PAIRS) {
+        const size_t blk = (size_t)cfg.nch * T * 2048;
+        undo = reinterpret_cast<const float*>((const char*)wp + (size_t)p.G * cfg.kb32 * blk) + ((size_t)g * cfg.kb32 + kb * (G::BM / 32)) * 32;
+        paired = true;                   // (NaN: a filter that pairs cannot hold)
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-            wvo[i] = raw_base(min((wm * MT + i) * 32 + col, p.Kg - 1 - kb * G::BM), p.L, T, half);
+        for (int i = 0; i < G::BM; i += 64) paired &= !__any(undo[i + lane] != undo[i + lane]);
+        const __amdgpu_buffer_rsrc_t pres =
+            __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
+        if (paired) paired = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, undo_x);
+        undo += wm * MT * 32;
+        if (!paired) __syncthreads();    // (what pair_sums exchanged in LDS is overwritten)
     }
-    const int wblk = cfg.nch * CS * T * 3072;       // bytes between 32-filter blocks (pieces)
-    const int wblk64 = p.Cg * T * 256;              // bytes between 64-filter blocks (fp32)
-    constexpr int VW = G::VW;
-    u4 ap[SRC == SRC_PIECES ? AR : 1][SRC == SRC_PIECES ? MT : 1][3];
-    float af[SRC == SRC_FP32 ? AR : 1][SRC == SRC_FP32 ? MT : 1][8];
-    float ar[SRC == SRC_RAW ? AR : 1][SRC == SRC_RAW ? MT : 1][8][VW];
-    auto fetch_a = [&](int slot, int ch16, int t) {
+    if (!paired) {
+        // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
+        // channels past the group's last one count as zeros
+        float xr[XU][8];
+        u4 xf[3];
+        int lb[NT];   // windows as byte offsets into the staged tile
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (SRC == SRC_PIECES) {
-                const int so = (ch16 * T + t) * 3072 + i * wblk;
+        for (int nb = 0; nb < NT; ++nb) lb[nb] = pos[nb] * 48 + half * CGB;
+        auto stage = [&](int u, int part, unsigned char* buf, int ch, int after) {
+            if (part < 4) {
+                const int left = p.Cg - (ch * CS * 16 + (u * NW + wave) % CG * 8) - 2 * part;
+                split2(xr[u][2 * part], xr[u][2 * part + 1], left > 0 ? kUp : 0.0f, left > 1 ? kUp : 0.0f, part, xf);
+            } else if (part == 4) {
+                u4* d = reinterpret_cast<u4*>(buf + xst[u]);
+                d[0] = xf[0];
+                d[1] = xf[1];
+                d[2] = xf[2];
+            } else {
+                fetch_x(xr[u], u, after);
+            }
+        };
+
+        // filters: fragments of 32 filters x 16 channels of one tap
+        __amdgpu_buffer_rsrc_t wres;
+        int wvo[SRC == SRC_RAW ? MT : 1];
+        if (SRC == SRC_PIECES) {
+            const size_t blk = (size_t)cfg.nch * CS * T * 3072;
+            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
+            wvo[0] = lane * 16;
+        } else if (SRC == SRC_FP32) {
+            const size_t blk = (size_t)p.Cg * T * 256;
+            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
+            wvo[0] = half * 8 * T * 256 + (kblk0 & 1) * 128 + col * 4;
+        } else {
+            // filters as stored; a filter past the group's last one re-reads the last
+            const size_t first = ((size_t)g * p.Kg + (size_t)kb * G::BM) * p.L;
+            const size_t left = ((size_t)p.K * p.L - first) * 4;
+            wres = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w + first), 0, (int)min(left, (size_t)0x7ffffffc), 0x00020000);
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    ap[slot][i][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[0] + q * 1024, so, 0));
-            } else if (SRC == SRC_FP32) {
-                const int so = (ch16 * 16 * T + t) * 256 + (i >> 1) * wblk64;
+            for (int i = 0; i < MT; ++i)
+                wvo[i] = raw_base(min((wm * MT + i) * 32 + col, p.Kg - 1 - kb * G::BM), p.L, T, half);
+        }
+        const int wblk = cfg.nch * CS * T * 3072;       // bytes between 32-filter blocks (pieces)
+        const int wblk64 = p.Cg * T * 256;              // bytes between 64-filter blocks (fp32)
+        constexpr int VW = G::VW;
+        u4 ap[SRC == SRC_PIECES ? AR : 1][SRC == SRC_PIECES ? MT : 1][3];
+        float af[SRC == SRC_FP32 ? AR : 1][SRC == SRC_FP32 ? MT : 1][8];
+        float ar[SRC == SRC_RAW ? AR : 1][SRC == SRC_RAW ? MT : 1][8][VW];
+        auto fetch_a = [&](int slot, int ch16, int t) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    af[slot][i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[0] + (i & 1) * 128, so + j * T * 256, 0));
-            } else if (G::T == 1) {   // eight channels are consecutive
-                const int at = raw_fragment(wvo[i], p.Cg, ch16);
-                if (raw_wide(p.Cg, ch16)) {
-                    const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at, 0, 0));
-                    const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at + 16, 0, 0));
+            for (int i = 0; i < MT; ++i) {
+                if (SRC == SRC_PIECES) {
+                    const int so = (ch16 * T + t) * 3072 + i * wblk;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        ar[slot][i][j][0] = lo[j];
-                        ar[slot][i][j + 4][0] = hi[j];
-                    }
-                } else {
-                    const int last = raw_last(wvo[i], p.L, half);
+                    for (int q = 0; q < 3; ++q)
+                        ap[slot][i][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo[0] + q * 1024, so, 0));
+                } else if (SRC == SRC_FP32) {
+                    const int so = (ch16 * 16 * T + t) * 256 + (i >> 1) * wblk64;
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
-                        ar[slot][i][j][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, min(at + 4 * j, last), 0, 0));
-                }
-            } else {
-                typedef float f3 __attribute__((ext_vector_type(3)));
+                        af[slot][i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, wvo[0] + (i & 1) * 128, so + j * T * 256, 0));
+                } else if (G::T == 1) {   // eight channels are consecutive
+                    const int at = raw_fragment(wvo[i], p.Cg, ch16);
+                    if (raw_wide(p.Cg, ch16)) {
+                        const f4 lo = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at, 0, 0));
+                        const f4 hi = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(wres, at + 16, 0, 0));
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const f3 q = __builtin_bit_cast(f3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo[i] + raw_step(ch16, T, j, t), 0, 0));
+                        for (int j = 0; j < 4; ++j) {
+                            ar[slot][i][j][0] = lo[j];
+                            ar[slot][i][j + 4][0] = hi[j];
+                        }
+                    } else {
+                        const int last = raw_last(wvo[i], p.L, half);
 #pragma unroll
-                    for (int e = 0; e < 3; ++e) ar[slot][i][j][e % VW] = q[e];
+                        for (int j = 0; j < 8; ++j)
+                            ar[slot][i][j][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, min(at + 4 * j, last), 0, 0));
+                    }
+                } else {
+                    typedef float f3 __attribute__((ext_vector_type(3)));
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const f3 q = __builtin_bit_cast(f3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo[i] + raw_step(ch16, T, j, t), 0, 0));
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) ar[slot][i][j][e % VW] = q[e];
+                    }
                 }
             }
-        }
-    };
-
-    constexpr bool APART = G::apart(SRC);
-    v16f acc[MT][NT], tmp[MT][NT], accl[APART ? MT : 1][APART ? NT : 1];
-    const int bufb = CG * CGB + G::SPARE;
-    const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int nb = 0; nb < NT; ++nb) {
-            acc[i][nb] = zero;
-            if (APART) accl[APART ? i : 0][APART ? nb : 0] = zero;
-        }
-
-    static_assert(NT >= 2, "two independent accumulators at least");
-    constexpr int NH = 2;                         // position blocks per half step
-    constexpr int HS = NT / NH;                   // half steps per tap
-    u4 bq[2][NH][3];
-    u4 a[MT][3];
-    auto load_b = [&](u4 (&dst)[NH][3], const unsigned char* tapbase, int imm, int h) {
-#pragma unroll
-        for (int n = 0; n < NH; ++n) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) dst[n][q] = *reinterpret_cast<const u4*>(tapbase + lb[h * NH + n] + imm + q * 16);
-        }
-    };
-    auto take_a = [&](int slot, int e) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (SRC == SRC_PIECES) {
-#pragma unroll
-                for (int q = 0; q < 3; ++q) a[i][q] = ap[slot][i][q];
-            } else if (SRC == SRC_FP32) {
-                split8(af[slot][i], a[i]);
-            } else {
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = ar[slot][i][j][e];
-                split8(v, a[i]);
-            }
-        }
-    };
-    // SPREAD: every load, cut and LDS write has its place between two matrix instructions; without the fences the compiler moves the
-    // loads down to their uses and waits there (b64x128 197 -> 153 us and s128x64 163 -> 158 on 512 @28x28 at batch 8, 256 @56x56 with a128x64
-    // 154 -> 150, 1x1 512 -> 256 @28x28 at batch 16 33.0 -> 31.2).  Not for 3x3 filters as stored, which are cut on the way: fenced, their
-    // registers spill (s128x64 107 -> 138 us on 896 channels in 7 groups @14x14).
-    constexpr bool SPREAD = SRC != SRC_RAW || G::T == 1;
-    // Matrix instruction m of a half step.  One chain: smallest products first (x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0); sums apart:
-    // x0 w0 first, so that its sums are ready when the others are still issued.
-    constexpr int NM = NH * MT * 6;
-    auto product = [&](const u4 (&bb)[NH][3], int h, int m, bool first) {
-        constexpr int qa[6] = {0, 2, 1, 0, 1, 0}, qb[6] = {2, 0, 1, 1, 0, 0};
-        const int c = APART && SPREAD ? (m / (NH * MT) + 5) % 6 : m / (NH * MT), n = m / MT % NH, i = m % MT;
-        v16f& d = APART && c < 5 ? accl[APART ? i : 0][APART ? h * NH + n : 0] : tmp[i][h * NH + n];
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
-                                                    first && c == (APART ? 5 : 0) ? zero : d, 0, 0, 0);
-    };
-
-#pragma unroll
-    for (int u = 0; u < XU; ++u) fetch_x(u, chb);
-    fetch_a(0, chb * CS, 0);
-    if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, chb * CS, 1);
-    if (G::T == 1) {
-        fetch_a(1, chb * CS + 1, 0);
-        fetch_a(2, chb * CS + 2, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < XU; ++u)
-#pragma unroll
-        for (int part = 0; part < (SPREAD ? 6 : 5); ++part) stage(u, part, lds, chb, min(chb + 1, che - 1));
-    __syncthreads();
-
-    constexpr int E = G::T * CS, D = AR - 1;
-    constexpr int ITEMS = XU * 6, GAP = (E * HS - 1) * NM / ITEMS < 4 ? (E * HS - 1) * NM / ITEMS : 4;   // staging: a part every GAP instructions
-    static_assert(GAP >= 1, "the staging of a chunk fits its products");
-    for (int ch = chb; ch < che; ++ch) {
-        const unsigned char* buf = lds + ((ch - chb) & 1) * bufb;
-        unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
-        const int nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
-        auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
-        auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
-        auto next_b = [&](int e, int h, int cur) {
-            if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
-            else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
         };
-        load_b(bq[0], buf + off(0), imm(0), 0);
+
+        constexpr bool APART = G::apart(FORM);
+        v16f tmp[MT][NT], accl[APART ? MT : 1][APART ? NT : 1];
+        const int bufb = CG * CGB + G::SPARE;
+        const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            take_a(SRC == SRC_RAW && G::T == 9 ? 0 : e % AR, SRC == SRC_RAW && G::T == 9 ? e % 3 % VW : 0);
-            if (!SPREAD) {   // three taps (one kernel row) are fetched at a time
-                if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
-                if (e == 0 && ch + 1 < che)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-                    for (int u = 0; u < XU; ++u) fetch_x(u, nx);
+            for (int nb = 0; nb < NT; ++nb) {
+                acc[i][nb] = zero;
+                if (APART) accl[APART ? i : 0][APART ? nb : 0] = zero;
             }
+
+        static_assert(NT >= 2, "two independent accumulators at least");
+        constexpr int NH = 2;                         // position blocks per half step
+        constexpr int HS = NT / NH;                   // half steps per tap
+        u4 bq[2][NH][3];
+        u4 a[MT][3];
+        auto load_b = [&](u4 (&dst)[NH][3], const unsigned char* tapbase, int imm, int h) {
 #pragma unroll
-            for (int h = 0; h < HS; ++h) {
-                const int cur = (e * HS + h) & 1;
-                if (!SPREAD) next_b(e, h, cur);
+            for (int n = 0; n < NH; ++n) {
 #pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    product(bq[cur], h, m, e == 0);
-                    // between the matrix instructions, where the compiler would not put them: what the next ones need
-                    if (SPREAD) __builtin_amdgcn_sched_barrier(0);
-                    if (SPREAD && m == 0) next_b(e, h, cur);
-                    if (SPREAD && m == 1 && h == 0)
-                        fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
-                    const int at = (e * HS + h) * NM + m - NM;
-                    if (SPREAD && at >= 0 && at % GAP == 0 && at / GAP < ITEMS) stage(at / GAP / 6, at / GAP % 6, nbuf, nx, nx2);
-                    if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < 3; ++q) dst[n][q] = *reinterpret_cast<const u4*>(tapbase + lb[h * NH + n] + imm + q * 16);
+            }
+        };
+        auto take_a = [&](int slot, int e) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                if (SRC == SRC_PIECES) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[i][q] = ap[slot][i][q];
+                } else if (SRC == SRC_FP32) {
+                    split8(af[slot][i], a[i]);
+                } else {
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[j] = ar[slot][i][j][e];
+                    split8(v, a[i]);
                 }
             }
-            if (!SPREAD && e == 6 && ch + 1 < che)
+        };
+        // SPREAD: every load, cut and LDS write has its place between two matrix instructions; without the fences the compiler moves the
+        // loads down to their uses and waits there (b64x128 197 -> 153 us and s128x64 163 -> 158 on 512 @28x28 at batch 8, 256 @56x56 with a128x64
+        // 154 -> 150, 1x1 512 -> 256 @28x28 at batch 16 33.0 -> 31.2).  Not for 3x3 filters as stored, which are cut on the way: fenced, their
+        // registers spill (s128x64 107 -> 138 us on 896 channels in 7 groups @14x14).
+        constexpr bool SPREAD = SRC != SRC_RAW || G::T == 1;
+        // Matrix instruction m of a half step.  One chain: smallest products first (x2 w0, x0 w2, x1 w1, x1 w0, x0 w1, x0 w0); sums apart:
+        // x0 w0 first, so that its sums are ready when the others are still issued.
+        constexpr int NM = NH * MT * 6;
+        auto product = [&](const u4 (&bb)[NH][3], int h, int m, bool first) {
+            constexpr int qa[6] = {0, 2, 1, 0, 1, 0}, qb[6] = {2, 0, 1, 1, 0, 0};
+            const int c = APART && SPREAD ? (m / (NH * MT) + 5) % 6 : m / (NH * MT), n = m / MT % NH, i = m % MT;
+            v16f& d = APART && c < 5 ? accl[APART ? i : 0][APART ? h * NH + n : 0] : tmp[i][h * NH + n];
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][qa[c]]), __builtin_bit_cast(bf8, bb[n][qb[c]]),
+                                                        first && c == (APART ? 5 : 0) ? zero : d, 0, 0, 0);
+        };
+
 #pragma unroll
-                for (int u = 0; u < XU; ++u)
-#pragma unroll
-                    for (int part = 0; part < 5; ++part) stage(u, part, nbuf, nx, nx2);
+        for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb);
+        fetch_a(0, chb * CS, 0);
+        if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, chb * CS, 1);
+        if (G::T == 1) {
+            fetch_a(1, chb * CS + 1, 0);
+            fetch_a(2, chb * CS + 2, 0);
         }
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int u = 0; u < XU; ++u)
 #pragma unroll
-            for (int nb = 0; nb < NT; ++nb) acc[i][nb] += tmp[i][nb];
+            for (int part = 0; part < (SPREAD ? 6 : 5); ++part) stage(u, part, lds, chb, min(chb + 1, che - 1));
         __syncthreads();
-    }
 
-    if (APART)
+        constexpr int E = G::T * CS, D = AR - 1;
+        constexpr int ITEMS = XU * 6, GAP = (E * HS - 1) * NM / ITEMS < 4 ? (E * HS - 1) * NM / ITEMS : 4;   // staging: a part every GAP instructions
+        static_assert(GAP >= 1, "the staging of a chunk fits its products");
+        for (int ch = chb; ch < che; ++ch) {
+            const unsigned char* buf = lds + ((ch - chb) & 1) * bufb;
+            unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
+            const int nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
+            auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
+            auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
+            auto next_b = [&](int e, int h, int cur) {
+                if (h + 1 < HS) load_b(bq[cur ^ 1], buf + off(e), imm(e), h + 1);
+                else if (e + 1 < E) load_b(bq[cur ^ 1], buf + off(e + 1), imm(e + 1), 0);
+            };
+            load_b(bq[0], buf + off(0), imm(0), 0);
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+            for (int e = 0; e < E; ++e) {
+                take_a(SRC == SRC_RAW && G::T == 9 ? 0 : e % AR, SRC == SRC_RAW && G::T == 9 ? e % 3 % VW : 0);
+                if (!SPREAD) {   // three taps (one kernel row) are fetched at a time
+                    if (e % 3 == 2) fetch_a(0, e < 8 ? ch : nx, e < 8 ? e + 1 : 0);
+                    if (e == 0 && ch + 1 < che)
 #pragma unroll
-            for (int nb = 0; nb < NT; ++nb) acc[i][nb] += accl[APART ? i : 0][APART ? nb : 0];
+                        for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, nx);
+                }
+#pragma unroll
+                for (int h = 0; h < HS; ++h) {
+                    const int cur = (e * HS + h) & 1;
+                    if (!SPREAD) next_b(e, h, cur);
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        product(bq[cur], h, m, e == 0);
+                        // between the matrix instructions, where the compiler would not put them: what the next ones need
+                        if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+                        if (SPREAD && m == 0) next_b(e, h, cur);
+                        if (SPREAD && m == 1 && h == 0)
+                            fetch_a((e + D) % AR, (e + D < E ? ch : nx) * CS + (G::T == 9 ? 0 : (e + D) % E), G::T == 9 ? (e + D) % E : 0);
+                        const int at = (e * HS + h) * NM + m - NM;
+                        if (SPREAD && at >= 0 && at % GAP == 0 && at / GAP < ITEMS) stage(at / GAP / 6, at / GAP % 6, nbuf, nx, nx2);
+                        if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if (!SPREAD && e == 6 && ch + 1 < che)
+#pragma unroll
+                    for (int u = 0; u < XU; ++u)
+#pragma unroll
+                        for (int part = 0; part < 5; ++part) stage(u, part, nbuf, nx, nx2);
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int nb = 0; nb < NT; ++nb) acc[i][nb] += tmp[i][nb];
+            __syncthreads();
+        }
+
+        if (APART)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int nb = 0; nb < NT; ++nb) acc[i][nb] += accl[APART ? i : 0][APART ? nb : 0];
+    }
 
     // epilogue
     float* part = split ? parts + ((size_t)ss * ((nb_all - whole) / cfg.nss) + ptile) * (G::BM * G::BN) : nullptr;
@@ -471,7 +744,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
             for (int v = 0; v < 16; ++v) {
                 const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
                 bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && not_finite(r);
-                acc[i][nb][v] = r * kDown;
+                acc[i][nb][v] = r * (FORM >= SRC_PAIRS && paired ? undo_x * undo[i * 32 + 4 * half + 8 * (v >> 2) + (v & 3)] : kDown);
             }
             if (__any(bad)) {
                 float* sc = reinterpret_cast<float*>(lds) + wave * 1024 + lane;
@@ -837,6 +1110,57 @@ __global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, 
     for (int q = 0; q < 3; ++q) dst[q * 64] = f[q];
 }
 
+// w[K][Cg][9] -> pairs[group][32 filters][16 channels][tap][pair][64 lanes][8 channels] fp16, scaled per filter, and behind them the factor that
+// undoes the scale for every filter (NaN: not to be held in pairs).  Filters past the group and channels past Cg are zero.
+// A workgroup takes one filter through LDS: its range, then its pairs, 16 bytes a lane at a filter's place in the fragments; neighbouring
+// filters go to one XCD, whose L2 puts the lines together.  Bound by the two trips to memory: 512 x 512 x 9 9.5 us (11.4 with a wavefront per
+// filter; three pieces of it, by piece_filters_kernel, 14.7).
+__global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, int nch16, const float* __restrict__ w, u4* __restrict__ out)
+{
+    extern __shared__ float f[];
+    __shared__ uint2 part[4];
+    const int tid = threadIdx.x, g = blockIdx.y, L = p.L;
+    const int k = (blockIdx.x & 7) * (kb32 * 4) + (blockIdx.x >> 3);
+    const bool real = k < p.Kg;
+    Range rg;
+    if (real) {
+        const float* src = w + ((size_t)g * p.Kg + k) * L;
+        for (int o0 = tid; o0 < L; o0 += 16 * 256) {
+            float v[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = src[min(o0 + j * 256, L - 1)];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                f[min(o0 + j * 256, L - 1)] = v[j];
+                if (j & 1) rg.add(v[j - 1], v[j]);
+            }
+        }
+    }
+    const uint2 of = rg.of_wave();
+    if ((tid & 63) == 63) part[tid >> 6] = of;
+    __syncthreads();
+    const unsigned hi = __builtin_amdgcn_readfirstlane(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)));
+    const unsigned lo = __builtin_amdgcn_readfirstlane(min(min(part[0].y, part[1].y), min(part[2].y, part[3].y)));
+    const int sg = pair_exponent(hi);
+    const float up = power_of_two(sg), up2 = power_of_two(sg + 11);
+    u4* dst = out + ((size_t)g * kb32 + (k >> 5)) * nch16 * 9 * 128 + (k & 31);
+    for (int it = tid; it < nch16 * 18; it += 256) {
+        const int t = it % 9, hc = it / 9;          // 8 channels of one tap
+        u4 q[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = hc * 8 + 2 * i;
+            const float a = real && c < p.Cg ? f[c * 9 + t] : 0.0f, b = real && c + 1 < p.Cg ? f[c * 9 + 9 + t] : 0.0f;
+            pair2(a, b, up, up2, up, up2, i, q);
+        }
+        u4* d = dst + ((size_t)(hc >> 1) * 9 + t) * 128 + (hc & 1) * 32;
+        d[0] = q[0];
+        d[64] = q[1];
+    }
+    float* undo = reinterpret_cast<float*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
+    if (tid == 0) undo[k] = PairLimits(sg, 3).hold(hi, lo) ? power_of_two(-sg) : __builtin_nanf("");
+}
+
 struct Plan {
     double cost = -1.0;   // modelled microseconds; negative = not applicable
     PieceCfg cfg;
@@ -988,34 +1312,45 @@ void consider(Plan& pl, long long tiles, long long round, int NW, double tc, dou
     }
 }
 
-// close: only forms with sums of their own for the small products.
+// The tiles of a geometry, without a form of the filters (cost < 0); their number, 0 where it has none.
 template <class G>
-Plan plan_geom(const Problem& p, bool pooled, bool close)
+long long plan_tiles(const Problem& p, bool pooled, Plan& pl)
 {
-    Plan pl;
-    if (G::POOL != pooled) return pl;
+    if (G::POOL != pooled) return 0;
     const int T = p.R * p.S;
-    if (G::T != T || p.R != p.S) return pl;
+    if (G::T != T || p.R != p.S) return 0;
     PieceCfg& c = pl.cfg;
     c.flat = T == 1 && p.stride == 1 && !pooled;
     c.T = T;
     c.S = p.S;
     c.nch = (p.Cg + 16 * G::CS - 1) / (16 * G::CS);
     c.kblocks = (p.Kg + G::BM - 1) / G::BM;
-    if (!choose_strips(p, pooled, G::BN, G::PXMAX, c)) return pl;
+    if (!choose_strips(p, pooled, G::BN, G::PXMAX, c)) return 0;
     c.cgb = (c.px * 48 + 255) / 256 * 256;
     pl.lds_bytes = 2 * ((size_t)G::CG * c.cgb + G::SPARE);
     if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
-    if (pl.lds_bytes > 160 * 1024) return pl;
+    if (G::PAIRS && pl.lds_bytes < 2 * (size_t)G::PAIR_BUF) pl.lds_bytes = 2 * (size_t)G::PAIR_BUF;
+    if (pl.lds_bytes > 160 * 1024) return 0;
     // images a tile can touch, and the byte offsets of their elements
     const long long run_img = (long long)(pooled ? p.PH : c.flat ? 1 : p.OH) * c.TW * (pooled ? 4 : 1);
     const long long imgs = (G::BN - 1 + run_img - 1) / run_img + 1;
-    if ((imgs + 1) * p.C * p.H * p.W * 4 >= (1LL << 31)) return pl;
-    if ((size_t)p.Cg * T * 256 >= (1u << 31) || (size_t)p.L * 4 * (G::BM + 1) >= (1u << 31)) return pl;
+    if ((imgs + 1) * p.C * p.H * p.W * 4 >= (1LL << 31)) return 0;
+    if ((size_t)p.Cg * T * 256 >= (1u << 31) || (size_t)p.L * 4 * (G::BM + 1) >= (1u << 31)) return 0;
     const long long tiles = (long long)c.ntiles * c.strips * c.kblocks * p.G;
-    if (tiles >= (1LL << 24)) return pl;
+    if (tiles >= (1LL << 24)) return 0;
 
-    if (!pin_allows()) return pl;
+    return pin_allows() ? tiles : 0;
+}
+
+// close: only forms with sums of their own for the small products.
+template <class G>
+Plan plan_geom(const Problem& p, bool pooled, bool close)
+{
+    Plan pl;
+    const long long tiles = plan_tiles<G>(p, pooled, pl);
+    if (!tiles) return pl;
+    const PieceCfg& c = pl.cfg;
+    const int T = G::T;
     const char* pin_src = env_value("SCONV_PIECE_SRC");
     const size_t ws = usable_workspace(p, pooled);
     const size_t tile_bytes = (size_t)G::BM * G::BN * 4;
@@ -1040,10 +1375,32 @@ Plan plan_geom(const Problem& p, bool pooled, bool close)
     return pl;
 }
 
+// The form with pairs of geometries that have it (kept: with the running sums' rounding errors).
+template <class G>
+Plan plan_pairs(const Problem& p, bool pooled, bool kept)
+{
+    Plan pl;
+    if constexpr (G::PAIRS) {
+        const int src = kept ? SRC_PAIRS_KEPT : SRC_PAIRS;
+        const char* pin_src = env_value("SCONV_PIECE_SRC");
+        if (pin_src && atoi(pin_src) != src) return pl;
+        const long long tiles = plan_tiles<G>(p, pooled, pl);
+        if (!tiles) return pl;
+        const int kb32 = pl.cfg.kblocks * (G::BM / 32);
+        const size_t blk = (size_t)pl.cfg.nch * 9 * 2048, ws = usable_workspace(p, pooled);
+        const size_t pb = ((size_t)p.G * kb32 * (blk + 128) + 255) / 256 * 256;
+        if (blk * 4 >= (1u << 31) || p.G > 65535 || (size_t)p.L * 4 > 128 * 1024 || pb > ws) return pl;
+        consider(pl, tiles, 256LL * occupancy_limit<G>(src, pl.lds_bytes), G::NW, G::tc(src, 9), 1.25, 11.0 + 2e-6 * p.K * p.L, src, pb, kb32, ws,
+                 (size_t)G::BM * G::BN * 4, true);
+    }
+    return pl;
+}
+
 template <class G, int SRC>
 int launch_src(const Plan& pl, const Problem& p, const float* x, const float* w, const void* wp, float* parts, float* y, hipStream_t stream)
 {
     auto kern = piece_kernel<G, SRC>;
+    static_assert(SRC < SRC_PAIRS || G::PAIRS, "the forms with pairs are those of some geometries");
     static size_t opted = 0;
     if (pl.lds_bytes > opted) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1072,6 +1429,23 @@ int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, c
         rc = launch_status();
         if (rc) return rc;
         rc = launch_src<G, SRC_PIECES>(pl, p, x, w, ws, parts, y, stream);
+    } else if (pl.src >= SRC_PAIRS) {
+        if constexpr (G::PAIRS) {
+            const size_t row = (size_t)p.L * 4;
+            static size_t opted = 0;
+            if (row > opted) {
+                if (hipFuncSetAttribute(reinterpret_cast<const void*>(piece_pairs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)row) != hipSuccess)
+                    return SCONV_ELAUNCH;
+                opted = row;
+            }
+            hipLaunchKernelGGL(piece_pairs_kernel, dim3((unsigned)pl.cfg.kb32 * 32, (unsigned)p.G), dim3(256), row, stream, p, pl.cfg.kb32, pl.cfg.nch, w,
+                               reinterpret_cast<u4*>(ws));
+            rc = launch_status();
+            if (rc) return rc;
+            rc = pl.src == SRC_PAIRS ? launch_src<G, SRC_PAIRS>(pl, p, x, w, ws, parts, y, stream) : launch_src<G, SRC_PAIRS_KEPT>(pl, p, x, w, ws, parts, y, stream);
+        } else {
+            return SCONV_EUNSUPPORTED;
+        }
     } else {
         rc = launch_src<G, SRC_RAW>(pl, p, x, w, nullptr, parts, y, stream);
     }
@@ -1131,8 +1505,12 @@ int launch_taps(const Plan& pl, const Problem& p, bool, const float* x, const fl
 struct Candidate {
     const char* name;
     Plan (*plan)(const Problem&, bool, bool);
+    Plan (*pairs)(const Problem&, bool, bool);
     int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
+    bool (*apart)(int);
 };
+
+bool always_apart(int) { return true; }
 
 // The geometries, for the table below and for the test that walks their plans.
 #define PIECE_GEOMETRIES(CAND, TAPS) \
@@ -1157,8 +1535,8 @@ struct Candidate {
     TAPS("t7x96", 49, 1, 3, false, 2) \
     TAPS("tp5x128", 25, 1, 4, true, 2) \
     TAPS("tp7x96", 49, 1, 3, true, 2)
-#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>},
-#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, launch_taps<TGeom<__VA_ARGS__>>},
+#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, plan_pairs<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::apart},
+#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, nullptr, launch_taps<TGeom<__VA_ARGS__>>, always_apart},
 const Candidate kCandidates[] = {PIECE_GEOMETRIES(CAND, TAPS)};
 
 }  // namespace
@@ -1179,9 +1557,29 @@ struct Choice {
     Plan plan;
 };
 
+// Whether a plan keeps the small products' sums apart.
+bool apart_of(const Choice& c) { return c.cand->apart(c.plan.src); }
+
+// The form with pairs that may take the place of what a launch takes without them - the plan `three` (its sums apart or not), or its
+// family's kernel, `other` microseconds (negative: not known), where that is faster -, or -1.  Relative error against 64-bit sums (1e-7; the
+// same at 40 - 90 % zeros within a tenth): pairs 1.2 at 64 and 128 channels, 1.35 at 256, 1.5 at 512; kept 1.1 - 1.2 at any number.  Against three pieces in
+// one chain, 1.7 - 2.0, either is closer; against sums apart, 0.65 at 64 channels to 1.17 at 512 (less where tiles are split), kept ones from
+// 512 on while most tiles are whole; against the other families where piece_close has it that three pieces in one chain are no further off
+// than they, and from 512 channels on (vector kernel, split, 1.6 / 1.3 / 1.05 at 50 / 70 / 85 % zeros).
+// A call without a zero ratio whose family is the vector kernel's stays as it was (see piece_first).
+int pairs_for(const Problem& p, const Plan* three, bool apart, double other, bool close)
+{
+    if (other == 0.0) return -1;
+    if (three && (other < 0.0 || three->cost < other)) {
+        if (!apart) return p.Cg < 512 ? SRC_PAIRS : SRC_PAIRS_KEPT;
+        return p.Cg >= 512 && three->cfg.whole >= three->ntail ? SRC_PAIRS_KEPT : -1;
+    }
+    return !close || p.Cg >= 512 ? SRC_PAIRS_KEPT : -1;
+}
+
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
 // kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, whether small
-// products are kept apart, a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
+// products are kept apart, the zero ratio (by which the time of the launch's family is known), a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
 // dispatcher's lock; the reference lasts until the next call.)
 const Choice& choose_plan(const Problem& p, bool pooled)
 {
@@ -1201,7 +1599,9 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     static Choice pinned;
     const PlanPin* tuned = current_pin();
     const char* pin = pinned_geom("SCONV_PIECE_GEOM");
-    const bool close = !pin && piece_close(p, pooled);
+    double other = -1.0;
+    const bool close = piece_close(p, pooled, &other) && !pin;
+    if (pin) other = -1.0;
     auto walk = [&](Choice& out) {
         out = Choice();
         if (!shape_ok(p, pooled)) return;
@@ -1214,6 +1614,17 @@ const Choice& choose_plan(const Problem& p, bool pooled)
                 out.plan = pl;
             }
         }
+        // the same with pairs, where it is no further from 64-bit sums
+        const bool pinned_pairs = env_value("SCONV_PIECE_SRC") && atoi(env_value("SCONV_PIECE_SRC")) >= SRC_PAIRS;
+        const int form = pinned_pairs ? atoi(env_value("SCONV_PIECE_SRC")) : pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), other, close);
+        if (form < 0) return;
+        for (const Candidate& c : kCandidates) {
+            if (!c.pairs || (pin && strcmp(pin, c.name) != 0)) continue;
+            Plan pl = c.pairs(p, pooled, form == SRC_PAIRS_KEPT);
+            if (pl.cost < 0.0 || (out.cand && pl.cost >= out.plan.cost)) continue;
+            out.cand = &c;
+            out.plan = pl;
+        }
     };
     if ((pin && !tuned) || env_value("SCONV_PIECE_SPLIT") || env_value("SCONV_PIECE_SRC")) {
         walk(pinned);
@@ -1222,7 +1633,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     Key k;
     memset(&k, 0, sizeof(k));
     const int v[19] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
-                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0, close ? 1 : 0};
+                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0, close ? 1 : 0, (int)(p.zhint * 254.0f + 0.5f)};
     memcpy(k.v, v, sizeof(v));
     k.ws = usable_workspace(p, pooled);
     if (tuned) {
@@ -1256,7 +1667,8 @@ bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
 {
     const Choice& c = choose_plan(p, pooled);
     if (!c.cand) return false;
-    const char* const forms[] = {"pieces", "prepared", "stored"};
+    // (pairs are cut from the filters as stored in prepared calls too)
+    const char* const forms[] = {"pieces", "prepared", "stored", p.wprep ? "prepared-f16" : "pieces-f16", p.wprep ? "prepared-f16k" : "pieces-f16k"};
     if (c.plan.ntail)
         snprintf(out, out_size, "%s/%s/%d+%dx%d", c.cand->name, forms[c.plan.src], c.plan.cfg.whole, c.plan.ntail, c.plan.cfg.nss);
     else

@@ -356,3 +356,139 @@ def test_no_further_from_64_bit_sums_than_the_kernels_it_replaces(device, monkey
         other = error()
         print(f"{family}: {mine:.3e} against {other:.3e}")
         assert mine <= 1.05 * other
+
+
+PAIRS = [
+    ("a128x64", (1, 16, 11, 12, 128, 3, 3, 1, 1, 1, None), None),         # one chunk, the last tile four windows long
+    ("a128x64", (5, 33, 7, 7, 129, 3, 3, 1, 1, 1, None), "0,1,3"),        # ragged channels, one filter in the last block, a chunk per slice
+    ("a128x64", (2, 96, 9, 57, 192, 3, 3, 1, 0, 2, None), "2,1,2"),       # grouped, column strips, whole and split tiles
+    ("a128x64", (1, 64, 13, 21, 40, 3, 3, 1, 2, 1, None), "0,1,2"),       # padding 2, half a filter block
+    ("u128x64", (2, 48, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2)), "3,1,2"),
+    ("u128x64", (1, 16, 12, 9, 64, 3, 3, 1, 1, 1, (2, 2, 1)), None),
+]
+
+
+def _pairs_call(monkeypatch, geom, split, src, shp, x, w, relu=False):
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    xd, wd = to_dev(x), to_dev(w)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    _pin(monkeypatch, geom, split, src)
+    name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool, True), pool is not None, ws.numel())
+    assert name.startswith(f"piece/model:{geom}/pieces-f16{'k' if src == '4' else ''}")
+    y = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, ws=ws) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, relu, ws=ws))
+    return y.cpu().numpy().astype(np.float64)
+
+
+def _reference(shp, x, w):
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    ref, scale = oracle.conv(x, w, stride, pad, groups, relu=False)
+    if pool:
+        p = torch.nn.functional.max_pool2d
+        ref = p(torch.from_numpy(np.maximum(ref, 0.0)), pool[:2], pool[2]).numpy()
+        scale = p(torch.from_numpy(scale), pool[:2], pool[2]).numpy()
+    return ref, scale
+
+
+@pytest.mark.parametrize("src", ["3", "4"])     # pairs; pairs with the running sums' errors kept
+@pytest.mark.parametrize("geom,shp,split", PAIRS)
+def test_pairs(device, monkeypatch, geom, shp, split, src):
+    """Tile edges, remainders, splits: integers exact; the others within what fp32 sums of the same length may be off by, and within
+    5e-7 in all (measured 1e-7 to 1.5e-7)."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    for integer in (False, True):
+        _, x, w = workloads.make_random_case(420, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6, integer)
+        got = _pairs_call(monkeypatch, geom, split, src, shp, x, w)
+        ref, scale = _reference(shp, x, w)
+        if integer:
+            assert np.array_equal(got, ref)
+        else:
+            # as three pieces; of a pair's last bits the half ulp of either operand, and the fourth product, are left out: 2 * 2^-24 + 2^-22
+            assert (np.abs(got - ref) <= (C // groups * 9 + 6) * 2.0 ** -24 * scale).all()
+            assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("what", ["images", "channels up", "channels down", "late", "small among large", "subnormal", "huge", "small weights", "filters",
+                                  "weight range", "inf", "nan", "inf weight"])
+def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src):
+    """The scale of a pair follows the chunks; what no scale holds is summed from three pieces: as close as ever, element by element."""
+    shp = (6, 64, 6, 7, 140, 3, 3, 1, 1, 1, None)
+    _, x, w = workloads.make_random_case(421, *shp[:10], None, 0.6)
+    rng = np.random.default_rng(5)
+    if what == "images":               # several in one tile
+        x = np.ldexp(x, np.array([0, -40, 20, -70, 3, 0])[:, None, None, None])
+    elif what == "channels up":        # every chunk another scale
+        x = np.ldexp(x, (np.arange(64) // 16 * 9)[None, :, None, None])
+    elif what == "channels down":
+        x = np.ldexp(x, (np.arange(64) // 16 * -25)[None, :, None, None])
+    elif what == "late":               # the first chunks hold nothing
+        x[:, :40] = 0
+    elif what == "small among large":  # windows of values 2^-33 of their neighbours
+        x[:, :, :3] = np.ldexp(x[:, :, :3], -33)
+    elif what == "subnormal":
+        x = np.ldexp(x, -135)
+        w = np.ldexp(w, 60)
+    elif what == "huge":
+        x = np.ldexp(x, 110)
+        w = np.ldexp(w, -70)
+    elif what == "small weights":
+        w = np.ldexp(w, -135)
+        x = np.ldexp(x, 60)
+    elif what == "filters":            # neighbouring filters 2^-60 apart
+        w = np.ldexp(w, (np.arange(140) % 3 * -30)[:, None, None, None])
+    elif what == "weight range":       # a filter no pair holds
+        w = np.ldexp(w, np.where(rng.random(w.shape) < 0.5, -45, 0))
+    elif what == "inf":
+        x[2, 20, 3, 3] = np.inf
+    elif what == "nan":
+        x[2, 20, 3, 3] = np.nan
+    else:
+        w[77, 3, 1, 1] = -np.inf
+    x, w = x.astype(np.float32), w.astype(np.float32)
+    got = _pairs_call(monkeypatch, "a128x64", None, src, shp, x, w)
+    bad = ~np.isfinite(_pairs_rows(monkeypatch, shp, x, w))
+    xf, wf = np.where(np.isfinite(x), x, 0), np.where(np.isfinite(w), w, 0)
+    ref, scale = _reference(shp, xf, wf)
+    assert np.array_equal(~np.isfinite(got), bad) and bad.any() == (what in ("inf", "nan", "inf weight"))
+    assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[~bad].all()
+
+
+def _pairs_rows(monkeypatch, shp, x, w):
+    """The window-row kernel, which skips zeros of the map."""
+    for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
+        monkeypatch.delenv(name, raising=False)
+    monkeypatch.setenv("SCONV_VARIANT", "rows")
+    return sconv.sconv_forward(to_dev(x), to_dev(w), shp[7], shp[8], shp[9]).cpu().numpy()
+
+
+@pytest.mark.parametrize("shp,z,call,three", [
+    ((8, 256, 56, 56, 256, 3, 3, 1, 1, 1, None), 0.6, "ws", ("a128x64", "0")), ((8, 512, 28, 28, 512, 3, 3, 1, 1, 1, None), 0.5, "ws", ("s128x64", "0")),
+    ((8, 512, 28, 28, 512, 3, 3, 1, 1, 1, None), 0.75, "prepared", ("a128x64", "1")),
+    ((8, 640, 14, 14, 384, 3, 3, 1, 1, 1, None), 0.8, "ws", None), ((2, 320, 56, 56, 128, 3, 3, 1, 1, 1, None), 0.5, "ws", ("a128x128", "2")),
+])
+def test_pairs_are_no_further_from_64_bit_sums_than_what_they_replace(device, monkeypatch, shp, z, call, three):
+    """The plan the model takes against the one it would take without pairs (three pieces, or None: the vector kernel); seeds move either by
+    a twentieth."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(422, N, C, H, W, K, R, S, stride, pad, groups, pool, z)
+    xd, wd = to_dev(x), to_dev(w)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd)) if call == "prepared" else dict(ws=ws)
+    desc = sconv.desc_for(xd, wd, stride, pad, groups, pool, False, z, call == "prepared")
+    wn = wd.double().reshape(K, -1)
+    ref = torch.stack([wn @ torch.nn.functional.unfold(xd[n:n + 1].double(), 3, padding=pad)[0] for n in range(2)]).reshape(2, K, H, W)
+
+    def error():
+        y = sconv.sconv_forward(xd, wd, stride, pad, groups, zero_ratio=z, **kw)[:2].double()
+        return float((y - ref).norm() / ref.norm())
+    monkeypatch.delenv("SCONV_VARIANT", raising=False)
+    assert "-f16" in sconv.sconv_launch_name(desc, False, ws.numel())
+    mine = error()
+    if three:
+        _pin(monkeypatch, three[0], None, three[1])
+    else:
+        monkeypatch.setenv("SCONV_VARIANT", "tap")
+    assert "-f16" not in sconv.sconv_launch_name(desc, False, ws.numel())
+    other = error()
+    print(f"{mine:.3e} against {other:.3e}")
+    assert mine <= 1.05 * other
