@@ -434,3 +434,26 @@ def test_tuned_plans_travel_as_text():
         assert L.sconv_tune_import(None) == sconv.SCONV_EINVAL
     finally:
         sconv.sconv_tune_reset()
+
+
+def test_dims_of_a_call_are_the_librarys():
+    """The binding's own arithmetic, and the library's answer or refusal where it leaves a layer to it."""
+    import random
+    rng = random.Random(3)
+    pick = lambda *v: rng.choice(v)   # noqa: E731
+    refused = 0
+    for i in range(4000):
+        N, C, H, W, K, R, S = pick(1, 3, 32), pick(1, 6, 16, 512), pick(1, 5, 14, 56, 4000), pick(1, 7, 33, 4000), pick(1, 6, 64, 4096), pick(1, 2, 3, 7), pick(1, 3, 5)
+        stride, pad, groups = pick(1, 1, 1, 2, 2, 3, 0, -1, 2 ** 32 + 1), pick(0, 0, 0, 1, 1, 2, 3, -1), pick(1, 1, 1, 1, 2, 3, 0)
+        pool = pick(None, None, None, (2, 2, 2), (2, 2, 2), (3, 3, 2), (1, 1, 1), (0, 2, 2), (2, 2, 0), (9, 1, 1), (2, 2, 2 ** 32 + 2))
+        d = sconv.make_desc(N, C, H, W, K, R, S, stride, pad, groups, pool)
+        try:
+            want = sconv.sconv_output_dims(d)
+        except sconv.SconvError as e:
+            refused += 1
+            with pytest.raises(sconv.SconvError) as mine:
+                sconv._call_dims(d, N, C, H, W, K, R, S, stride, pad, groups, pool)
+            assert mine.value.code == e.code
+            continue
+        assert sconv._call_dims(d, N, C, H, W, K, R, S, stride, pad, groups, pool) == want
+    assert 500 < refused < 3500   # both sides are met
