@@ -16,9 +16,34 @@ namespace {
 
 constexpr int kEncodeBlock = 256;  // 4 wavefronts = 4 rows per workgroup
 
-__device__ __forceinline__ unsigned lanes_below(unsigned long long mask, int lane)
+// base + the number of lanes of mask below this one: two instructions
+__device__ __forceinline__ int rank_from(int base, unsigned long long mask)
 {
-    return __popcll(mask & ((1ull << lane) - 1ull));
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)base));
+}
+
+// A pair of the ring: the value's bits and its column.
+__device__ __forceinline__ uint2 pair_of(float v, int col) { return make_uint2(__builtin_bit_cast(unsigned, v), (unsigned)col); }
+
+// Bound by the instructions of this walk (a row per wavefront, 12 - 14 wavefronts a compute unit on the benchmark's layers), so: offsets carried
+// along instead of multiplied out, four groups of columns read before the first is ranked, two instructions for a rank.  512 @28x28 24.2 -> 21.3 us,
+// 256 @56x56 23.9 -> 22.5, 1x1 512 @14x14 at batch 4 20.5 -> 16.7, 256 @60x60 at batch 8 31.3 -> 29.5, stride 2 128 @64x64 14.5 -> 14.1.
+// 64 columns of a row: their nonzeros go into the row's ring, and a run of 64 pairs leaves it when there are as many.  (One LDS write and
+// one read for both halves of a pair.)
+__device__ __forceinline__ void take_columns(float v, int col, uint2* ring, float* vrow, int32_t* irow, int lane, int& cnt, int& flushed)
+{
+    const bool nz = v != 0.0f;  // +0, -0 dropped; denormals, negatives kept
+    const unsigned long long mask = __ballot(nz);
+    if (nz) ring[rank_from(cnt, mask) & 127] = pair_of(v, col);
+    cnt += __popcll(mask);
+    __builtin_amdgcn_wave_barrier();
+    if (cnt - flushed >= 64) {   // at most 127 pairs are pending: one run leaves
+        const uint2 q = ring[(flushed + lane) & 127];
+        vrow[flushed + lane] = __builtin_bit_cast(float, q.x);
+        irow[flushed + lane] = (int32_t)q.y;
+        flushed += 64;
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // Every row of both outputs starts on 16 bytes.
@@ -29,13 +54,13 @@ __device__ __forceinline__ bool wide_rows(int L, const float* values, const int3
 
 // The end of a row: what is left in the ring (at most 63 pairs), then zeros, 16 bytes a lane where rows allow it - at 60 %
 // zeros they are most of what the kernel stores (1x1, 256 @60x60 at batch 8: 43.9 -> 29.7 us, 2.0 TB/s of stores).
-__device__ __forceinline__ void finish_row(float* vrow, int32_t* irow, const float* rv, const int32_t* ri, int cnt, int flushed,
-                                           int L, int lane, bool wide)
+__device__ __forceinline__ void finish_row(float* vrow, int32_t* irow, const uint2* ring, int cnt, int flushed, int L, int lane, bool wide)
 {
     const int slot = flushed + lane;
     if (slot < L) {
-        vrow[slot] = slot < cnt ? rv[slot & 127] : 0.0f;
-        irow[slot] = slot < cnt ? ri[slot & 127] : 0;
+        const uint2 q = slot < cnt ? ring[slot & 127] : make_uint2(0u, 0u);
+        vrow[slot] = __builtin_bit_cast(float, q.x);
+        irow[slot] = (int32_t)q.y;
     }
     if (wide) {   // (flushed is a multiple of 64)
         for (int i = flushed + 64 + 4 * lane; i < L; i += 256) {
@@ -84,16 +109,19 @@ __global__ __launch_bounds__(kEncodeBlock) void encode_kernel(Problem p, int pec
     const int iw0 = ow * p.stride - p.pad;
     const float* xg = x + ((long long)n * p.C + (long long)g * p.Cg) * p.H * p.W;
 
-    // this lane's first column, split into (c, r, s); then steps of 64 columns with carries
+    // this lane's first column, split into (c, r, s), as an offset from the window's origin; then steps of 64 columns with carries
     const int RS = p.R * p.S;
-    int c = lane / RS;
-    int rs = lane - c * RS;
+    const int c = lane / RS;
+    const int rs = lane - c * RS;
     int r = rs / p.S;
     int s = rs - r * p.S;
     const int dc = 64 / RS;
     const int drs = 64 - dc * RS;
     const int dr = drs / p.S;
     const int ds = drs - dr * p.S;
+    long long off = ((long long)c * p.H + ih0 + r) * p.W + iw0 + s;
+    const long long step = ((long long)dc * p.H + dr) * p.W + ds;
+    const int carry_s = p.W - p.S, carry_r = (p.H - p.R) * p.W;
 
     float* vrow = values + row * p.L;
     int32_t* irow = index + row * p.L;
@@ -101,10 +129,8 @@ __global__ __launch_bounds__(kEncodeBlock) void encode_kernel(Problem p, int pec
     // The compacted (value, column) pairs pass through a 128-slot ring in LDS (one per wavefront)
     // and leave it 64 at a time, so every store to HBM is one whole run of 64 consecutive slots
     // of the row instead of a ragged piece per 64 columns.
-    __shared__ float ring_v[kEncodeBlock / 64][128];
-    __shared__ int32_t ring_i[kEncodeBlock / 64][128];
-    float* rv = ring_v[threadIdx.x >> 6];
-    int32_t* ri = ring_i[threadIdx.x >> 6];
+    __shared__ uint2 rings[kEncodeBlock / 64][128];
+    uint2* ring = rings[threadIdx.x >> 6];
 
     int cnt = 0;       // nonzeros found so far (wavefront-uniform)
     int flushed = 0;   // slots of the row already stored (a multiple of 64)
@@ -116,37 +142,19 @@ __global__ __launch_bounds__(kEncodeBlock) void encode_kernel(Problem p, int pec
             const int col = col0 + 64 * u + lane;
             v[u] = 0.0f;
             if (col < p.L) {
-                const int ih = ih0 + r, iw = iw0 + s;
-                if (ih >= 0 && ih < p.H && iw >= 0 && iw < p.W)
-                    v[u] = xg[((long long)c * p.H + ih) * p.W + iw];
+                if ((unsigned)(ih0 + r) < (unsigned)p.H && (unsigned)(iw0 + s) < (unsigned)p.W) v[u] = xg[off];
             }
+            off += step;
             s += ds;
-            if (s >= p.S) { s -= p.S; r += 1; }
+            if (s >= p.S) { s -= p.S; r += 1; off += carry_s; }
             r += dr;
-            if (r >= p.R) { r -= p.R; c += 1; }
-            c += dc;
+            if (r >= p.R) { r -= p.R; off += carry_r; }
         }
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const bool nz = v[u] != 0.0f;  // +0, -0 dropped; denormals, negatives kept
-            const unsigned long long mask = __ballot(nz);
-            if (nz) {
-                const int slot = (cnt + lanes_below(mask, lane)) & 127;
-                rv[slot] = v[u];
-                ri[slot] = col0 + 64 * u + lane;
-            }
-            cnt += __popcll(mask);
-            __builtin_amdgcn_wave_barrier();
-            if (cnt - flushed >= 64) {   // at most 127 pairs are pending: one run leaves
-                const int slot = (flushed + lane) & 127;
-                vrow[flushed + lane] = rv[slot];
-                irow[flushed + lane] = ri[slot];
-                flushed += 64;
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
+        for (int u = 0; u < UN; ++u)
+            if (col0 + 64 * u < p.L) take_columns(v[u], col0 + 64 * u + lane, ring, vrow, irow, lane, cnt, flushed);
     }
-    finish_row(vrow, irow, rv, ri, cnt, flushed, p.L, lane, wide_rows(p.L, values, index));
+    finish_row(vrow, irow, ring, cnt, flushed, p.L, lane, wide_rows(p.L, values, index));
     if (lane == 0) count[row] = (!pecr && cnt == 0) ? -1 : cnt;
 }
 
@@ -174,8 +182,7 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
 {
     __shared__ float stage[STAGE];          // [channel of the chunk][box row][box column]
     __shared__ int32_t box_off[STAGE];      // box element -> offset in a channel plane, -1 outside the map
-    __shared__ float ring_v[TR][128];
-    __shared__ int32_t ring_i[TR][128];
+    __shared__ uint2 rings[TR][128];
     __shared__ int s_ih0[TR], s_iw0[TR];
     constexpr int RPW = TR / (kTileBlock / 64);
 
@@ -221,7 +228,9 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
         const int ih = ih_min + bh, iw = iw_min + bw;
         box_off[pe] = (ih >= 0 && ih < p.H && iw >= 0 && iw < p.W) ? ih * p.W + iw : -1;
     }
-    const int CC = min(p.Cg, STAGE / plane);                 // channels per chunk
+    // channels per chunk: whole groups of 64 columns where there are as many (64 in each at 256 @56x56, where 85, 85, 85 and 1 fit), else as
+    // many as fit
+    const int CC = STAGE / plane >= 64 ? min(p.Cg, STAGE / plane / 64 * 64) : min(p.Cg, STAGE / plane);
     const unsigned magic = plane > 1 ? (unsigned)((1ull << 32) / (unsigned)plane) + 1u : 0u;
     const float* xg = x + ((long long)n * p.C + (long long)g * p.Cg) * HWp;
     __syncthreads();
@@ -236,6 +245,7 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
     const int drs = 64 - dc * RS;
     const int dr = drs / p.S;
     const int ds = drs - dr * p.S;
+    const int step = dc * plane + dr * BW + ds, carry_s = BW - p.S, carry_r = plane - p.R * BW;
 
     int cnt[RPW], flushed[RPW];
 #pragma unroll
@@ -269,35 +279,26 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
             const int rr = wave * RPW + j;
             if (rr >= nrows) continue;
             const int boff = (s_ih0[rr] - ih_min) * BW + (s_iw0[rr] - iw_min);
-            float* rv = ring_v[rr];
-            int32_t* ri = ring_i[rr];
+            uint2* ring = rings[rr];
             float* vrow = values + ((long long)ng * rows_per_ng + rl0 + rr) * p.L;
             int32_t* irow = index + ((long long)ng * rows_per_ng + rl0 + rr) * p.L;
-            int c = c_first, r = r_first, s = s_first;
-            for (int lc0 = 0; lc0 < ncols; lc0 += 64) {
-                const int lc = lc0 + lane;
-                const float v = lc < ncols ? stage[c * plane + boff + r * BW + s] : 0.0f;
-                const bool nz = v != 0.0f;  // +0, -0 dropped; denormals, negatives kept
-                const unsigned long long mask = __ballot(nz);
-                if (nz) {
-                    const int slot = (cnt[j] + lanes_below(mask, lane)) & 127;
-                    rv[slot] = v;
-                    ri[slot] = c0 * RS + lc;
+            int r = r_first, s = s_first, at = boff + c_first * plane + r * BW + s;
+            constexpr int UN = 4;   // column groups read together before any of them is ranked
+            for (int lc0 = 0; lc0 < ncols; lc0 += 64 * UN) {
+                float v[UN];
+#pragma unroll
+                for (int u = 0; u < UN; ++u) {
+                    if (lc0 + 64 * u >= ncols) break;
+                    v[u] = lc0 + 64 * u + lane < ncols ? stage[at] : 0.0f;
+                    at += step;
+                    s += ds;
+                    if (s >= p.S) { s -= p.S; r += 1; at += carry_s; }
+                    r += dr;
+                    if (r >= p.R) { r -= p.R; at += carry_r; }
                 }
-                cnt[j] += __popcll(mask);
-                __builtin_amdgcn_wave_barrier();
-                if (cnt[j] - flushed[j] >= 64) {
-                    const int slot = (flushed[j] + lane) & 127;
-                    vrow[flushed[j] + lane] = rv[slot];
-                    irow[flushed[j] + lane] = ri[slot];
-                    flushed[j] += 64;
-                    __builtin_amdgcn_wave_barrier();
-                }
-                s += ds;
-                if (s >= p.S) { s -= p.S; r += 1; }
-                r += dr;
-                if (r >= p.R) { r -= p.R; c += 1; }
-                c += dc;
+#pragma unroll
+                for (int u = 0; u < UN; ++u)
+                    if (lc0 + 64 * u < ncols) take_columns(v[u], c0 * RS + lc0 + 64 * u + lane, ring, vrow, irow, lane, cnt[j], flushed[j]);
             }
         }
         __syncthreads();   // the staged chunk is free again
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
         const long long row = (long long)ng * rows_per_ng + rl0 + rr;
         float* vrow = values + row * p.L;
         int32_t* irow = index + row * p.L;
-        finish_row(vrow, irow, ring_v[rr], ring_i[rr], cnt[j], flushed[j], p.L, lane, wide);
+        finish_row(vrow, irow, rings[rr], cnt[j], flushed[j], p.L, lane, wide);
         if (lane == 0) count[row] = (!pecr && cnt[j] == 0) ? -1 : cnt[j];
     }
 }
