@@ -1,4 +1,5 @@
 // Host side of libsconv: argument checks, size helpers, variant choice.  No device code here.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -388,14 +389,24 @@ static double family_time(const Problem& p, bool pooled, Variant v)
     const double gf = dense_gflop(p, pooled);
     const bool can_split = split_scratch_possible(nullptr) && split_scratch_bytes() > 0;
     double other, walk = 0.0;
+    // What the tiles of the vector kernel and of quad3x3 compute past the filters (64 to a block) and past the map's columns (7 to a tile; where
+    // they are more than a seventh another tile is taken).  The fits are of layers that fill them; without it 512 -> 80 @44x44 at batch 11, prepared
+    // filters, took 277 / 131 us at 60 / 90 % zeros on the vector kernel against 91, 96 -> 416 @44x44 at batch 5 123 / 71 against 52, 576 -> 448 in
+    // 4 groups @57x57 at batch 5 205 / 129 against 120.  Of 180 random layers at 60, 90 and 95 % zeros 40 move, 1.6 / 1.2 / 1.1 times as fast.  Not
+    // below 32 channels a group (64 -> 576 in 4 groups @38x38, pooled: 21.6 against 23.2 at 90 %), not without a workspace and a ratio (448 -> 92 in 4
+    // groups @41x41 57.6 against 66.4 at 95 %), on quad3x3 from half a block on (64 -> 192 in 4 groups @57x57 54 against 58).
+    const double spare_k = (double)((p.Kg + 63) / 64 * 64) / p.Kg;
+    const int cols = pooled ? p.PW * 2 : p.OW;
+    const bool fits_hold = p.Cg < 32 || (!can_split && !p.wprep && p.zhint < 0.0f);
+    const double spare = fits_hold ? 1.0 : spare_k * fmin(1.15, (double)((cols + 6) / 7 * 7) / cols);
     switch (v) {
     case V_TAP: {
         const double nz = p.zhint < 0.0f ? 0.1 : 1.0 - p.zhint;
-        other = 14.0 + gf * (p.zhint < 0.0f ? 4.3 : 2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+        other = 14.0 + gf * spare * (p.zhint < 0.0f ? 4.3 : 2.1 + 17.3 * nz) + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
         if (!can_split && !p.wprep) walk = 10.0 + p.Cg * (0.06 + 0.14 * nz);
         break;
     }
-    case V_QUAD: other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3); break;
+    case V_QUAD: other = 8.0 + gf * (spare_k >= 1.5 ? spare_k : 1.0) * (p.zhint >= 0.92f ? 5.0 : 8.3); break;
     case V_WIDE:
         other = 8.0 + gf * (p.zhint >= 0.92f ? 5.0 : 8.3);
         walk = 8.0 + 0.2 * p.Cg;
