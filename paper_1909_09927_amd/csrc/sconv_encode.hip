@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kTileBlock) void encode_tile_kernel(Problem p, int 
             float* vrow = values + ((long long)ng * rows_per_ng + rl0 + rr) * p.L;
             int32_t* irow = index + ((long long)ng * rows_per_ng + rl0 + rr) * p.L;
             int r = r_first, s = s_first, at = boff + c_first * plane + r * BW + s;
-            constexpr int UN = 4;   // column groups read together before any of them is ranked
+            constexpr int UN = 2;   // column groups read together before any of them is ranked
             for (int lc0 = 0; lc0 < ncols; lc0 += 64 * UN) {
                 float v[UN];
 #pragma unroll
