@@ -42,17 +42,25 @@ HBM_PEAK_GBS = 8000.0        # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TF = 157.3  # 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flop x 2.4 GHz
 FP32_MFMA_PEAK_TF = 157.3    # dense fp32 matrix instructions, published
 MFMA_VARIANTS = ("quad3x3", "quad1x1", "wide3x3", "gen", "piece")
-PIECE_PEAK_TF = 2500.0 / 6   # piece kernel: six bf16 matrix products (dense peak, published) per fp32 one
+
+
+def piece_peak_tf(plan: str) -> float:
+    """Piece kernel: the 16-bit matrix pipe's dense peak (published) over the products an fp32 one takes there - six of bf16 pieces, three of
+    fp16 pairs.  A tuned plan names its geometry only: the two that have the form with pairs are priced as if they ran it."""
+    pairs = "-f16" in plan or plan.startswith(("piece/a128x64/", "piece/u128x64/"))
+    return 2500.0 / (3 if pairs else 6)
+
+
 # HBM/fabric bytes per launch from rocprofv3 counter runs (FETCH_SIZE x 2 KiB + WRITE_SIZE x 1 KiB, scaled
 # by the copy calibration), keyed by (plan name, layer, batch): a figure from profiles/, not something this
 # run measures - the line names its source, and prints null when the plan that ran is not in the table.
 MEASURED_TRAFFIC = {
     ("quad3x3/q32t7d/8x4", "vgg-256x56", 8): (54.8e6 + 25.9e6, "profiles/quad3x3_vgg-256x56_n8.txt"),
     # the launches of a piece plan together: filters cut into pieces, the product kernel, the sum of its split tiles
-    **{(plan, "vgg-256x56", 8): (89.1e6 + 40.5e6, "profiles/piece_counters.txt")
-       for plan in ("piece/model:a128x64/pieces/768+16x16/kept", "piece/model:a128x64/pieces/768+16x16", "piece/a128x64/4x1")},
-    **{(plan, "vgg-512x28", 8): (275.4e6 + 40.8e6, "profiles/piece_counters.txt")
-       for plan in ("piece/model:s128x64/pieces/256+136x3/kept", "piece/model:s128x64/pieces/256+136x3", "piece/s128x64/4x1")},
+    **{(plan, "vgg-256x56", 8): (74.2e6 + 34.6e6, "profiles/piece_counters.txt")
+       for plan in ("piece/model:a128x64/pieces-f16/768+16x8/kept", "piece/model:a128x64/pieces-f16/768+16x8", "piece/a128x64/4x1")},
+    **{(plan, "vgg-512x28", 8): (151.4e6 + 40.4e6, "profiles/piece_counters.txt")
+       for plan in ("piece/model:a128x64/pieces-f16k/256+136x3/kept", "piece/model:a128x64/pieces-f16k/256+136x3", "piece/a128x64/4x1")},
 }
 # elements per zero test of the kernels that skip whole groups (1: every zero element is skipped)
 SKIP_GRANULE = {"rows": 1, "tap3x3": 1, "quad3x3": 6, "quad1x1": 32, "wide3x3": 16, "gen": 16}
@@ -323,7 +331,7 @@ def layer_record(dl: DeviceLayer, work: dict, ms: float) -> dict:
     t = ms * 1e-3
     t_hbm = work["alg_bytes"] / (HBM_PEAK_GBS * 1e9)
     # the pipe the plan runs on (the fp32 matrix and vector peaks are the same figure), as in the headline's roofline
-    t_pipe = work["nz_flops"] / ((PIECE_PEAK_TF if dl.variant == "piece" else FP32_VECTOR_PEAK_TF) * 1e12)
+    t_pipe = work["nz_flops"] / ((piece_peak_tf(dl.plan) if dl.variant == "piece" else FP32_VECTOR_PEAK_TF) * 1e12)
     # what the plan really issues: a kernel that tests groups of g elements multiplies every element of a
     # group that holds a nonzero (independent zeros: a share z^g of the groups is skipped); the forms without
     # any test (geometry names ending in d, "dense") issue everything - the dense fallback on the matrix pipe
@@ -483,7 +491,7 @@ def run_headline(args) -> None:
         ach = wk["nz_flops"] / t / 1e12
         if r["variant"] in MFMA_VARIANTS:
             # products go through the matrix pipe (fp32, or bf16 pieces); algorithmic flops = nonzero multiply-adds
-            peak = PIECE_PEAK_TF if r["variant"] == "piece" else FP32_MFMA_PEAK_TF
+            peak = piece_peak_tf(r["plan"]) if r["variant"] == "piece" else FP32_MFMA_PEAK_TF
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": round(peak, 1), "unit": "TFLOP/s",
                     "frac": round(ach / peak, 4), "traffic": None,
                     "issued_dense_equiv_TFLOPs": round(wk["dense_flops"] / t / 1e12, 2)}

@@ -26,6 +26,9 @@
 // that becomes Inf leaves remainders of -Inf or NaN, which no other operand turns back into a finite sum): a lane that finds
 // such a sum has its block of 32 x 32 results summed again in plain fp32, skipping zero elements.
 //
+// Where it is no further from 64-bit sums than what runs otherwise, a 3x3 launch with a workspace takes fp16 pairs and three products
+// instead (pair_sums, pairs_for).
+//
 // Zeros are not skipped inside a tile (a 32-window block of 16 channels is never empty when zeros are independent): the
 // rules that choose between this kernel and the element-skipping vector kernel are in sconv_api.hip (piece_first).
 //
