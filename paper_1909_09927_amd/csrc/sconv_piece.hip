@@ -708,11 +708,19 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                         if (SPREAD) __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                if (!SPREAD && e == 6 && ch + 1 < che)
+                if (!SPREAD && e == 6 && ch + 1 < che) {
+                    if ((nx + 1) * CS * 16 > p.Cg)   // (once, where `stage` would pick the scale of every channel)
 #pragma unroll
-                    for (int u = 0; u < XU; ++u)
+                        for (int u = 0; u < XU; ++u)
 #pragma unroll
-                        for (int part = 0; part < 5; ++part) stage(u, part, nbuf, nx, nx2);
+                            for (int j = 0; j < 8; ++j)
+                                if (nx * CS * 16 + (u * NW + wave) % CG * 8 + j >= p.Cg) xr[u][j] = 0.0f;
+#pragma unroll
+                    for (int u = 0; u < XU; ++u) {
+                        split8(xr[u], xf);
+                        stage(u, 4, nbuf, nx, nx2);
+                    }
+                }
             }
 #pragma unroll
             for (int i = 0; i < MT; ++i)
