@@ -87,6 +87,8 @@ enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3, SRC_PAIRS_KEPT 
 
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
 
+constexpr int kUnpaired = -0x40000000;   // in the place of a filter's exponent: no pairs of it
+
 // Whether a scaled sum is Inf or NaN.
 __device__ __forceinline__ bool not_finite(float r) { return (__builtin_bit_cast(unsigned, r) & 0x7fffffffu) >= 0x7f800000u; }
 
@@ -228,7 +230,7 @@ __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast
 // Filters: a ring of nine fragments, eight taps ahead, for which half the registers of three pieces would not do.
 template <class G, bool KEPT, class Fetch>
 __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::NT], int pitch, int chb, int che, int wave, int lane,
-                                          unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], float& undo_x)
+                                          unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], int& sigma)
 {
     constexpr int NT = G::NT, XU = G::XU, NW = G::NW, D = 8;
     constexpr int PLANE = G::PXMAX * 16, CGB = 2 * PLANE, BUF = G::PAIR_BUF;
@@ -249,7 +251,6 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     };
     // The scale.  In the rule every wavefront finds its share of the next chunk within the limits of the scale there is, and says so (one word
     // each).  Where one does not, all exchange their ranges: a scale that holds the chunk, or none (false).
-    int sigma = 0;
     PairLimits lim(0, 0);
     Range rg;
     auto say = [&](int parity) {
@@ -392,7 +393,6 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-11f;   // (the last chunk is staged twice, so its scale may have moved on)
-    undo_x = power_of_two(-sigma);
     return true;
 }
 
@@ -495,19 +495,30 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     v16f acc[MT][NT];
 
     bool paired = false;
-    const float* undo = nullptr;         // what the sums of pairs are multiplied by, per filter
-    float undo_x = kDown;
     if constexpr (FORM >= SRC_PAIRS) {
         const size_t blk = (size_t)cfg.nch * T * 2048;
-        undo = reinterpret_cast<const float*>((const char*)wp + (size_t)p.G * cfg.kb32 * blk) + ((size_t)g * cfg.kb32 + kb * (G::BM / 32)) * 32;
-        paired = true;                   // (NaN: a filter that pairs cannot hold)
+        // the filters' exponents (kUnpaired: a filter that pairs cannot hold)
+        const int* sg = reinterpret_cast<const int*>((const char*)wp + (size_t)p.G * cfg.kb32 * blk) + ((size_t)g * cfg.kb32 + kb * (G::BM / 32)) * 32;
+        paired = true;
 #pragma unroll
-        for (int i = 0; i < G::BM; i += 64) paired &= !__any(undo[i + lane] != undo[i + lane]);
+        for (int i = 0; i < G::BM; i += 64) paired &= !__any(sg[i + lane] == kUnpaired);
         const __amdgpu_buffer_rsrc_t pres =
             __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
-        if (paired) paired = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, undo_x);
-        undo += wm * MT * 32;
-        if (!paired) __syncthreads();    // (what pair_sums exchanged in LDS is overwritten)
+        int sigma = 0;
+        if (paired) paired = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, sigma);
+        // To the scale of sums of pieces, by the exponents' sum: map and filters both small (or large) make two factors whose product fp32
+        // does not hold, where the sum times both is an ordinary number.
+        if (paired) {
+            sg += wm * MT * 32 + 4 * half;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int e = 48 - sigma - sg[8 * (v >> 2) + (v & 3)];
+#pragma unroll
+                for (int nb = 0; nb < NT; ++nb) acc[0][nb][v] = __builtin_amdgcn_ldexpf(acc[0][nb][v], e);
+            }
+        } else {
+            __syncthreads();             // (what pair_sums exchanged in LDS is overwritten)
+        }
     }
     if (!paired) {
         // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
@@ -755,7 +766,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
             for (int v = 0; v < 16; ++v) {
                 const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
                 bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && not_finite(r);
-                acc[i][nb][v] = r * (FORM >= SRC_PAIRS && paired ? undo_x * undo[i * 32 + 4 * half + 8 * (v >> 2) + (v & 3)] : kDown);
+                acc[i][nb][v] = r * kDown;
             }
             if (__any(bad)) {
                 float* sc = reinterpret_cast<float*>(lds) + wave * 1024 + lane;
@@ -1137,8 +1148,8 @@ __global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, 
     for (int q = 0; q < 3; ++q) dst[q * 64] = f[q];
 }
 
-// w[K][Cg][9] -> pairs[group][32 filters][16 channels][tap][pair][64 lanes][8 channels] fp16, scaled per filter, and behind them the factor that
-// undoes the scale for every filter (NaN: not to be held in pairs).  Filters past the group and channels past Cg are zero.
+// w[K][Cg][9] -> pairs[group][32 filters][16 channels][tap][pair][64 lanes][8 channels] fp16, scaled per filter, and behind them the exponent of
+// every filter's scale (kUnpaired: not to be held in pairs).  Filters past the group and channels past Cg are zero.
 // A workgroup takes one filter through LDS: its range, then its pairs, 16 bytes a lane at a filter's place in the fragments; neighbouring
 // filters go to one XCD, whose L2 puts the lines together.  Bound by the two trips to memory: 512 x 512 x 9 9.5 us (11.4 with a wavefront per
 // filter; three pieces of it, by piece_filters_kernel, 14.7).
@@ -1184,8 +1195,8 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
         d[0] = q[0];
         d[64] = q[1];
     }
-    float* undo = reinterpret_cast<float*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
-    if (tid == 0) undo[k] = PairLimits(sg, 3).hold(hi, lo) ? power_of_two(-sg) : __builtin_nanf("");
+    int* exponents = reinterpret_cast<int*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
+    if (tid == 0) exponents[k] = PairLimits(sg, 3).hold(hi, lo) ? sg : kUnpaired;
 }
 
 struct Plan {

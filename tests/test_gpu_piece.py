@@ -453,6 +453,30 @@ def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src
     assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[~bad].all()
 
 
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("split,pool", [(None, None), ("0,1,2", None), (None, (2, 2, 2))])
+@pytest.mark.parametrize("up_x,up_w", [(-62, -62), (-76, -50), (-30, -96), (-99, -27), (55, 55), (104, 54), (54, 104)])
+def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch, up_x, up_w, split, pool, src):
+    """What undoes the two scales is far outside fp32's range where the results are ordinary numbers: sums of 2^-126 and more, windows of
+    zeros, and, where the large elements overflow, the windows that hold small ones against small weights."""
+    shp = (6, 64, 6, 7, 140, 3, 3, 1, 1, 1, pool)
+    _, x, w = workloads.make_random_case(423, *shp[:10], None, 0.6)
+    x, w = np.abs(x), w.copy()
+    x[2:4] = 0
+    if up_x + up_w > 128:      # images 4 and 5: every second channel 2^-24 of the others' elements, against weights 2^-24 of the others
+        x[4:, ::2] = 0
+        x[4:] = np.ldexp(x[4:], -24)
+        w[:, 1::2] = np.ldexp(w[:, 1::2], -24)
+        x, w = np.where(np.abs(x) < 2.0 ** -24.5, 0, x), np.where(np.abs(w) < 2.0 ** -28, 2.0 ** -28, w)
+    x, w = np.ldexp(x, up_x).astype(np.float32), np.ldexp(w, up_w).astype(np.float32)
+    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, src, shp, x, w)
+    ref, scale = _reference(shp, x, w)
+    assert np.abs(ref).max() > 2.0 ** -126 and not ref[2 if pool else 3, :, 0 if pool else 3].any()
+    fits = scale < 2.0 ** 126
+    assert fits.all() == (up_x + up_w < 128) and fits[4:].all()
+    assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[fits].all()
+
+
 def _pairs_rows(monkeypatch, shp, x, w):
     """The window-row kernel, which skips zeros of the map."""
     for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
