@@ -320,6 +320,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
 #pragma unroll
     for (int t = 0; t < D; ++t) fetch_a(chb, t);
     if (!new_scale(0, sigma)) return false;
+    const int first = sigma;             // (the running sums follow the scale: from 2^60 off the first one on their bits would not fit fp32's range)
 #pragma unroll
     for (int u = 0; u < XU; ++u)
 #pragma unroll
@@ -371,7 +372,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
                 if (e == 8 && m >= 2) fold(m - 2);
                 __builtin_amdgcn_sched_barrier(0);
                 if (e == 0 && m == NM - 1 && __builtin_amdgcn_readfirstlane((int)(said[0] | said[1] | said[2] | said[3]))) {
-                    if (!new_scale(par ^ 1, next) || next > sigma + 60 || next < sigma - 60) return false;
+                    if (!new_scale(par ^ 1, next) || next > first + 60 || next < first - 60) return false;
                     up = (unsigned)(next + 127) << 23;
                 }
             }

@@ -454,7 +454,7 @@ def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src
 
 
 @pytest.mark.parametrize("src", ["3", "4"])
-@pytest.mark.parametrize("split,pool", [(None, None), ("0,1,2", None), (None, (2, 2, 2))])
+@pytest.mark.parametrize("split,pool", [("0,1,1", None), ("0,1,2", None), ("0,1,1", (2, 2, 2)), ("0,1,2", (2, 2, 2))])
 @pytest.mark.parametrize("up_x,up_w", [(-62, -62), (-76, -50), (-30, -96), (-99, -27), (55, 55), (104, 54), (54, 104)])
 def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch, up_x, up_w, split, pool, src):
     """What undoes the two scales is far outside fp32's range where the results are ordinary numbers: sums of 2^-126 and more, windows of
@@ -475,6 +475,21 @@ def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch,
     fits = scale < 2.0 ** 126
     assert fits.all() == (up_x + up_w < 128) and fits[4:].all()
     assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[fits].all()
+
+
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("split", ["0,1,1", "0,1,2"])
+@pytest.mark.parametrize("step", [40, -40, 11, -11])
+def test_pairs_of_chunks_whose_scales_keep_moving(device, monkeypatch, step, split, src):
+    """Chunks that are each 2^step of the one before: windows that hold elements of the first one only keep their sums."""
+    shp = (6, 96, 6, 7, 140, 3, 3, 1, 1, 1, None)
+    _, x, w = workloads.make_random_case(424, *shp[:10], None, 0.6)
+    x[0, 16:] = 0
+    x[3, :80] = 0
+    x = np.ldexp(x, (np.arange(96) // 16 * step - 2.5 * step).astype(int)[None, :, None, None]).astype(np.float32)
+    got = _pairs_call(monkeypatch, "a128x64", split, src, shp, x, w)
+    ref, scale = _reference(shp, x, w)
+    assert (np.abs(got - ref) <= (96 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149).all()
 
 
 def _pairs_rows(monkeypatch, shp, x, w):
