@@ -156,16 +156,17 @@ struct PGeom {
     static constexpr int PAIR_BUF = 2 * 2 * PXMAX * 16 + 256;   // LDS of one chunk as pairs, and the ranges of the wavefronts
 };
 
-// Two fp32 values times up as pairs of fp16 values: v up = p0 + 2^-11 p1, but for the last bit of every fourth value.  (Multiplication
-// or subtraction and rounding to fp16 in one instruction each; up2 = 2^11 up.)
+// Two fp32 values times up as pairs of fp16 values: v up = p0 + 2^-12 p1, p0 of 11 bits, p1 of 11 and a sign - all but the last bit of every
+// fourth value, 2^-23 of it at most, for |v up| from 2^-14 (p1 down to 2^-24) to 2^15 (p1 up to 2^15).  (Multiplication or subtraction and
+// rounding to fp16 in one instruction each; up2 = 2^12 up.)
 __device__ __forceinline__ void pair2(float a, float b, float up_a, float up2_a, float up_b, float up2_b, int i, u4 (&out)[2])
 {
     unsigned h, r;
     const float a2 = a * up2_a, b2 = b * up2_b;
     asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "=v"(h) : "v"(a), "s"(up_a));
     asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "+v"(h) : "v"(b), "s"(up_b));
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "s"(-2048.0f), "v"(a2));
-    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(r) : "v"(h), "s"(-2048.0f), "v"(b2));
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "s"(-4096.0f), "v"(a2));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(r) : "v"(h), "s"(-4096.0f), "v"(b2));
     out[0][i] = h;
     out[1][i] = r;
 }
@@ -193,7 +194,7 @@ struct Range {
     __device__ __forceinline__ uint2 of_wave() const { return make_uint2(wave_max(__builtin_bit_cast(unsigned, hi)), ~wave_max(~lo)); }
 };
 
-// The exponent sigma of the power of two that takes the largest of a set of magnitudes to 2^13 .. 2^14 (115 at most, so that 2^11 times it
+// The exponent sigma of the power of two that takes the largest of a set of magnitudes to 2^13 .. 2^14 (115 at most, so that 2^12 times it
 // is finite).
 __host__ __device__ inline int pair_exponent(unsigned hi_bits)
 {
@@ -201,14 +202,13 @@ __host__ __device__ inline int pair_exponent(unsigned hi_bits)
     const int sg = 140 - (e > 254 ? 254 : e);
     return sg < 115 ? sg : 115;
 }
-// What pairs at that scale hold: magnitudes below `hi` (bits; none too large for fp16), and but for zeros none below `lo` (as in
-// Range): 2^-14 after scaling, under which p0 has fewer than 11 bits and the product left out weighs more; 2^(-14 - below) for filters,
-// down to which it is 2^(below - 22) of such a weight's products.
+// What pairs at that scale hold: magnitudes below `hi` (bits; 2^15 after scaling), and but for zeros none below `lo` (as in Range): 2^-14 after
+// scaling, under which p0 has fewer than 11 bits and the product left out weighs more than 2^-22.
 struct PairLimits {
     unsigned hi, lo;
-    __host__ __device__ PairLimits(int sigma, int below)
+    __host__ __device__ explicit PairLimits(int sigma)
     {
-        const int el = 113 - sigma - below;     // biased exponent of the smallest
+        const int el = 113 - sigma;     // biased exponent of the smallest
         hi = (unsigned)(142 - sigma) << 23;
         if (hi > 0x7f800000u) hi = 0x7f800000u;
         lo = ((unsigned)(el > 0 ? el : 1) << 24) - 1;   // (nor fp32's subnormals)
@@ -217,15 +217,16 @@ struct PairLimits {
 };
 __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast(float, (unsigned)(e + 127) << 23); }
 
-// The sums of one tile from fp16 pairs: v = p0 + 2^-11 p1, three products p0q0, p0q1, p1q0 (the fourth is 2^-22 of the product) instead of
+// The sums of one tile from fp16 pairs: v = p0 + 2^-12 p1, three products p0q0, p0q1, p1q0 (the fourth is 2^-22 of the product at most) instead of
 // six, two thirds of the LDS and filter traffic.  Bound by the chip's power like the six products (1.9 - 2.1 GHz; a third LDS buffer with one
 // barrier a chunk, loads two taps ahead, a second set of map registers and a third fewer vector instructions all measured within 3 %), of
 // which three take two thirds of the time: 256 @56x56 at batch 8 151 -> 105 us, 512 @28x28 at batch 8 with prepared filters 160 -> 112, at
 // batch 62 955 -> 720 (1.0 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
 // The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
-// stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter a
-// weight 2^30 below, false is returned and the tile is summed from three pieces (as stored): about one of 4 x 10^7 normally distributed values.
-// The sums of a chunk start from zero (p0q0); the small products' run through, 2^11 times their size, and with KEPT take the rounding error of
+// stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter such a
+// weight, false is returned and the tile is summed from three pieces (as stored): about one of 4 x 10^7 normally distributed values.  So every
+// single product is within 2^-21 of its value, whatever the others in its window.
+// The sums of a chunk start from zero (p0q0); the small products' run through, 2^12 times their size, and with KEPT take the rounding error of
 // every addition to the running sums along (4 % of the time; error at 512 channels 1.5e-7 -> 1.07e-7).
 // Filters: a ring of nine fragments, eight taps ahead, for which half the registers of three pieces would not do.
 template <class G, bool KEPT, class Fetch>
@@ -251,7 +252,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     };
     // The scale.  In the rule every wavefront finds its share of the next chunk within the limits of the scale there is, and says so (one word
     // each).  Where one does not, all exchange their ranges: a scale that holds the chunk, or none (false).
-    PairLimits lim(0, 0);
+    PairLimits lim(0);
     Range rg;
     auto say = [&](int parity) {
         const bool out = __any(!lim.hold(__builtin_bit_cast(unsigned, rg.hi), rg.lo));
@@ -272,7 +273,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
         const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(a[0], a[2]), max(b[0], b[2])));
         const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(a[1], a[3]), min(b[1], b[3])));
         to = pair_exponent(hi);
-        lim = PairLimits(to, 0);
+        lim = PairLimits(to);
         return lim.hold(hi, lo);
     };
     u4 xf[2];
@@ -280,7 +281,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     auto stage = [&](int u, int part, unsigned char* buf, int ch, int after, unsigned up) {
         if (part < 4) {
             const int left = p.Cg - (ch * 16 + (u * NW + wave) % 2 * 8) - 2 * part;
-            const unsigned ua = left > 0 ? up : 0, ub = left > 1 ? up : 0, ua2 = left > 0 ? up + (11u << 23) : 0, ub2 = left > 1 ? up + (11u << 23) : 0;
+            const unsigned ua = left > 0 ? up : 0, ub = left > 1 ? up : 0, ua2 = left > 0 ? up + (12u << 23) : 0, ub2 = left > 1 ? up + (12u << 23) : 0;
             pair2(xr[u][2 * part], xr[u][2 * part + 1], __builtin_bit_cast(float, ua), __builtin_bit_cast(float, ua2), __builtin_bit_cast(float, ub),
                   __builtin_bit_cast(float, ub2), part, xf);
         } else if (part == 4) {
@@ -381,7 +382,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
 #pragma unroll
             for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) accl[nb][v] = __builtin_fmaf(tmp[nb][v], 2048.0f, accl[nb][v]);
+                for (int v = 0; v < 16; ++v) accl[nb][v] = __builtin_fmaf(tmp[nb][v], 4096.0f, accl[nb][v]);
         by = power_of_two(next - sigma);
         if (next != sigma) {
 #pragma unroll
@@ -393,7 +394,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-11f;   // (the last chunk is staged twice, so its scale may have moved on)
+        for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-12f;   // (the last chunk is staged twice, so its scale may have moved on)
     return true;
 }
 
@@ -1181,7 +1182,7 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
     const unsigned hi = __builtin_amdgcn_readfirstlane(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)));
     const unsigned lo = __builtin_amdgcn_readfirstlane(min(min(part[0].y, part[1].y), min(part[2].y, part[3].y)));
     const int sg = pair_exponent(hi);
-    const float up = power_of_two(sg), up2 = power_of_two(sg + 11);
+    const float up = power_of_two(sg), up2 = power_of_two(sg + 12);
     u4* dst = out + ((size_t)g * kb32 + (k >> 5)) * nch16 * 9 * 128 + (k & 31);
     for (int it = tid; it < nch16 * 18; it += 256) {
         const int t = it % 9, hc = it / 9;          // 8 channels of one tap
@@ -1197,7 +1198,7 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
         d[64] = q[1];
     }
     int* exponents = reinterpret_cast<int*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
-    if (tid == 0) exponents[k] = PairLimits(sg, 3).hold(hi, lo) ? sg : kUnpaired;
+    if (tid == 0) exponents[k] = PairLimits(sg).hold(hi, lo) ? sg : kUnpaired;
 }
 
 struct Plan {

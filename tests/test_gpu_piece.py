@@ -492,6 +492,24 @@ def test_pairs_of_chunks_whose_scales_keep_moving(device, monkeypatch, step, spl
     assert (np.abs(got - ref) <= (96 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149).all()
 
 
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("spread_x,spread_w", [(0, 0), (26, 0), (0, 26), (26, 26), (0, 29), (29, 0)])
+def test_pairs_hold_every_single_product(device, monkeypatch, spread_x, spread_w, src):
+    """One nonzero element a window, so nothing averages: its product with any weight, over the range that pairs hold (26 octaves) and just
+    past it.  A value is held to 2^-23 of itself and the product left out is 2^-22; a fp32 rounding or two of the result besides."""
+    shp = (2, 32, 12, 15, 140, 3, 3, 1, 1, 1, None)
+    rng = np.random.default_rng(6)
+    x, w = np.zeros(shp[:4]), rng.uniform(1, 2, (140, 32, 3, 3)) * np.exp2(-rng.integers(0, spread_w + 1, (140, 32, 3, 3)))
+    at = np.ix_(range(2), range(1, 12, 3), range(1, 15, 3))
+    c = rng.integers(0, 32, (2, 4, 5))
+    x[at[0], c, at[1], at[2]] = rng.uniform(1, 2, c.shape) * np.exp2(-rng.integers(0, spread_x + 1, c.shape))
+    x, w = x.astype(np.float32), w.astype(np.float32)
+    got = _pairs_call(monkeypatch, "a128x64", None, src, shp, x, w)
+    ref, scale = _reference(shp, x, w)
+    assert (scale > 0).all()
+    assert (np.abs(got - ref) <= (2.0 ** -22 + 2 * 2.0 ** -23 + 2 * 2.0 ** -24) * scale).all()
+
+
 def _pairs_rows(monkeypatch, shp, x, w):
     """The window-row kernel, which skips zeros of the map."""
     for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
