@@ -81,8 +81,8 @@ struct PieceCfg {
     int flat;        // 1x1 / stride 1: a map is one row of H*W positions
 };
 
-// Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums),
-// the same with the running sums' rounding errors kept
+// Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums); the same
+// with the running sums' rounding errors kept
 enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3, SRC_PAIRS_KEPT = 4 };
 
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
@@ -224,14 +224,16 @@ __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast
 // batch 62 955 -> 720 (1.0 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
 // The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
 // stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter such a
-// weight, false is returned and the tile is summed from three pieces (as stored): about one of 4 x 10^7 normally distributed values.  So every
-// single product is within 2^-21 of its value, whatever the others in its window.
+// weight - about one of 4 x 10^7 normally distributed values -, the tile is summed from three pieces from there on: returned is the first chunk that
+// is not in the sums, `sigma` is their scale.  So every single product is within 2^-21 of its value, whatever the others in its window.  No map
+// and no filters take much longer than on pieces alone: 256 @56x56 at batch 32 347 us (pieces 493), with 64 elements of the map 2^-30 of its
+// largest 366, with every chunk or every block of filters out of range 535 and 517.
 // The sums of a chunk start from zero (p0q0); the small products' run through, 2^12 times their size, and with KEPT take the rounding error of
 // every addition to the running sums along (4 % of the time; error at 512 channels 1.5e-7 -> 1.07e-7).
 // Filters: a ring of nine fragments, eight taps ahead, for which half the registers of three pieces would not do.
 template <class G, bool KEPT, class Fetch>
-__device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::NT], int pitch, int chb, int che, int wave, int lane,
-                                          unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], int& sigma)
+__device__ __forceinline__ int pair_sums(const Problem& p, const int (&pos)[G::NT], int pitch, int chb, int che, int wave, int lane,
+                                         unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], int& sigma)
 {
     constexpr int NT = G::NT, XU = G::XU, NW = G::NW, D = 8;
     constexpr int PLANE = G::PXMAX * 16, CGB = 2 * PLANE, BUF = G::PAIR_BUF;
@@ -320,7 +322,7 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb);
 #pragma unroll
     for (int t = 0; t < D; ++t) fetch_a(chb, t);
-    if (!new_scale(0, sigma)) return false;
+    if (!new_scale(0, sigma)) return chb;
     const int first = sigma;             // (the running sums follow the scale: from 2^60 off the first one on their bits would not fit fp32's range)
 #pragma unroll
     for (int u = 0; u < XU; ++u)
@@ -344,7 +346,8 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     };
     constexpr int NM = 3 * NT;               // matrix instructions of a tap
     static_assert(XU == 2 && NT == 2, "the places of a chunk's work between its matrix instructions");
-    for (int ch = chb; ch < che; ++ch) {
+    int end = che;
+    for (int ch = chb; ch < end; ++ch) {
         const int par = (ch - chb) & 1, nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
         const unsigned char* buf = lds + par * BUF;
         unsigned char* nbuf = lds + (par ^ 1) * BUF;
@@ -373,7 +376,10 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
                 if (e == 8 && m >= 2) fold(m - 2);
                 __builtin_amdgcn_sched_barrier(0);
                 if (e == 0 && m == NM - 1 && __builtin_amdgcn_readfirstlane((int)(said[0] | said[1] | said[2] | said[3]))) {
-                    if (!new_scale(par ^ 1, next) || next > first + 60 || next < first - 60) return false;
+                    if (!new_scale(par ^ 1, next) || next > first + 60 || next < first - 60) {
+                        next = sigma;
+                        end = ch + 1;    // (what is staged of the next chunk is not read)
+                    }
                     up = (unsigned)(next + 127) << 23;
                 }
             }
@@ -395,16 +401,19 @@ __device__ __forceinline__ bool pair_sums(const Problem& p, const int (&pos)[G::
     for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-12f;   // (the last chunk is staged twice, so its scale may have moved on)
-    return true;
+    return end;
 }
 
-template <class G, int FORM>
+// Bytes of the pairs of all filters and their exponents; behind them the pieces.
+__host__ __device__ inline size_t pair_bytes(int G, int kb32, int nch16) { return ((size_t)G * kb32 * ((size_t)nch16 * 9 * 2048 + 128) + 255) / 256 * 256; }
+
+// FORM: SRC_PAIRS or SRC_PAIRS_KEPT (SRC: the filters' form where pairs do not do), or 0
+template <class G, int SRC, int FORM>
 __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
                                                               const float* __restrict__ w, const void* __restrict__ wp,
                                                               float* __restrict__ parts, float* __restrict__ y)
 {
     extern __shared__ __align__(16) unsigned char lds[];
-    constexpr int SRC = FORM >= SRC_PAIRS ? SRC_RAW : FORM;   // (a tile that pairs cannot hold is summed from the filters as stored)
     constexpr int MT = G::MT, NT = G::NT, CS = G::CS, CG = G::CG, NW = G::NW, XU = G::XU, AR = G::AR;
     const int PX = cfg.px, CGB = cfg.cgb;
     constexpr int T = G::T, S = T == 9 ? 3 : 1;
@@ -496,21 +505,21 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     const int kblk0 = kb * (G::BM / 32) + wm * MT;
     v16f acc[MT][NT];
 
-    bool paired = false;
+    int from = chb;                      // the chunks from here on are summed from pieces
     if constexpr (FORM >= SRC_PAIRS) {
         const size_t blk = (size_t)cfg.nch * T * 2048;
         // the filters' exponents (kUnpaired: a filter that pairs cannot hold)
         const int* sg = reinterpret_cast<const int*>((const char*)wp + (size_t)p.G * cfg.kb32 * blk) + ((size_t)g * cfg.kb32 + kb * (G::BM / 32)) * 32;
-        paired = true;
+        bool paired = true;
 #pragma unroll
         for (int i = 0; i < G::BM; i += 64) paired &= !__any(sg[i + lane] == kUnpaired);
         const __amdgpu_buffer_rsrc_t pres =
             __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
         int sigma = 0;
-        if (paired) paired = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, sigma);
+        if (paired) from = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, sigma);
         // To the scale of sums of pieces, by the exponents' sum: map and filters both small (or large) make two factors whose product fp32
         // does not hold, where the sum times both is an ordinary number.
-        if (paired) {
+        if (from > chb) {
             sg += wm * MT * 32 + 4 * half;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -519,10 +528,12 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                 for (int nb = 0; nb < NT; ++nb) acc[0][nb][v] = __builtin_amdgcn_ldexpf(acc[0][nb][v], e);
             }
         } else {
+            acc[0][0] = acc[0][1] = 0.0f;
             __syncthreads();             // (what pair_sums exchanged in LDS is overwritten)
         }
+        wp = SRC == SRC_FP32 ? (const void*)p.wprep : (const char*)wp + pair_bytes(p.G, cfg.kb32, cfg.nch);   // (unused as stored)
     }
-    if (!paired) {
+    if (FORM == 0 || from < che) {
         // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
         // channels past the group's last one count as zeros
         float xr[XU][8];
@@ -611,7 +622,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
             }
         };
 
-        constexpr bool APART = G::apart(FORM);
+        constexpr bool APART = G::apart(FORM ? FORM : SRC);
         v16f tmp[MT][NT], accl[APART ? MT : 1][APART ? NT : 1];
         const int bufb = CG * CGB + G::SPARE;
         const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
@@ -619,7 +630,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int nb = 0; nb < NT; ++nb) {
-                acc[i][nb] = zero;
+                if (FORM == 0) acc[i][nb] = zero;
                 if (APART) accl[APART ? i : 0][APART ? nb : 0] = zero;
             }
 
@@ -668,25 +679,25 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         };
 
 #pragma unroll
-        for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb);
-        fetch_a(0, chb * CS, 0);
-        if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, chb * CS, 1);
+        for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, from);
+        fetch_a(0, from * CS, 0);
+        if (G::T == 9 && SRC != SRC_RAW) fetch_a(1, from * CS, 1);
         if (G::T == 1) {
-            fetch_a(1, chb * CS + 1, 0);
-            fetch_a(2, chb * CS + 2, 0);
+            fetch_a(1, from * CS + 1, 0);
+            fetch_a(2, from * CS + 2, 0);
         }
 #pragma unroll
         for (int u = 0; u < XU; ++u)
 #pragma unroll
-            for (int part = 0; part < (SPREAD ? 6 : 5); ++part) stage(u, part, lds, chb, min(chb + 1, che - 1));
+            for (int part = 0; part < (SPREAD ? 6 : 5); ++part) stage(u, part, lds, from, min(from + 1, che - 1));
         __syncthreads();
 
         constexpr int E = G::T * CS, D = AR - 1;
         constexpr int ITEMS = XU * 6, GAP = (E * HS - 1) * NM / ITEMS < 4 ? (E * HS - 1) * NM / ITEMS : 4;   // staging: a part every GAP instructions
         static_assert(GAP >= 1, "the staging of a chunk fits its products");
-        for (int ch = chb; ch < che; ++ch) {
-            const unsigned char* buf = lds + ((ch - chb) & 1) * bufb;
-            unsigned char* nbuf = lds + ((ch + 1 - chb) & 1) * bufb;
+        for (int ch = from; ch < che; ++ch) {
+            const unsigned char* buf = lds + ((ch - from) & 1) * bufb;
+            unsigned char* nbuf = lds + ((ch + 1 - from) & 1) * bufb;
             const int nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
             auto off = [&](int e) { return G::T == 9 ? (e / 3) * pitch * 48 : e * 2 * CGB; };
             auto imm = [&](int e) { return G::T == 9 ? (e % 3) * 48 : 0; };
@@ -1152,10 +1163,13 @@ __global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, 
 
 // w[K][Cg][9] -> pairs[group][32 filters][16 channels][tap][pair][64 lanes][8 channels] fp16, scaled per filter, and behind them the exponent of
 // every filter's scale (kUnpaired: not to be held in pairs).  Filters past the group and channels past Cg are zero.
+// Where `pieces` is given, the three pieces there besides, as piece_filters_kernel writes them: what a launch reads where pairs do not do (from
+// the filters as stored it took a third longer: 256 @56x56 at batch 32 with eight weights of 1e-20 729 us, now 517).
 // A workgroup takes one filter through LDS: its range, then its pairs, 16 bytes a lane at a filter's place in the fragments; neighbouring
 // filters go to one XCD, whose L2 puts the lines together.  Bound by the two trips to memory: 512 x 512 x 9 9.5 us (11.4 with a wavefront per
 // filter; three pieces of it, by piece_filters_kernel, 14.7).
-__global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, int nch16, const float* __restrict__ w, u4* __restrict__ out)
+__global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, int nch16, const float* __restrict__ w, u4* __restrict__ out,
+                                                          u4* __restrict__ pieces)
 {
     extern __shared__ float f[];
     __shared__ uint2 part[4];
@@ -1183,19 +1197,28 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
     const unsigned lo = __builtin_amdgcn_readfirstlane(min(min(part[0].y, part[1].y), min(part[2].y, part[3].y)));
     const int sg = pair_exponent(hi);
     const float up = power_of_two(sg), up2 = power_of_two(sg + 12);
-    u4* dst = out + ((size_t)g * kb32 + (k >> 5)) * nch16 * 9 * 128 + (k & 31);
+    const size_t blk = ((size_t)g * kb32 + (k >> 5)) * nch16 * 9;
+    u4* dst = out + blk * 128 + (k & 31);
+    u4* dst3 = pieces + blk * 192 + (k & 31);
     for (int it = tid; it < nch16 * 18; it += 256) {
         const int t = it % 9, hc = it / 9;          // 8 channels of one tap
-        u4 q[2];
+        u4 q[2], q3[3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = hc * 8 + 2 * i;
             const float a = real && c < p.Cg ? f[c * 9 + t] : 0.0f, b = real && c + 1 < p.Cg ? f[c * 9 + 9 + t] : 0.0f;
             pair2(a, b, up, up2, up, up2, i, q);
+            if (pieces) split2(a, b, kUp, kUp, i, q3);
         }
-        u4* d = dst + ((size_t)(hc >> 1) * 9 + t) * 128 + (hc & 1) * 32;
+        const size_t at = (size_t)(hc >> 1) * 9 + t;
+        u4* d = dst + at * 128 + (hc & 1) * 32;
         d[0] = q[0];
         d[64] = q[1];
+        if (!pieces) continue;
+        d = dst3 + at * 192 + (hc & 1) * 32;
+        d[0] = q3[0];
+        d[64] = q3[1];
+        d[128] = q3[2];
     }
     int* exponents = reinterpret_cast<int*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
     if (tid == 0) exponents[k] = PairLimits(sg).hold(hi, lo) ? sg : kUnpaired;
@@ -1206,6 +1229,7 @@ struct Plan {
     PieceCfg cfg;
     size_t lds_bytes = 0, piece_bytes = 0;
     int src = SRC_RAW, ntail = 0;
+    int rest = SRC_RAW;   // with pairs: the filters' form where those do not do
 };
 
 bool shape_ok(const Problem& p, bool pooled)
@@ -1427,20 +1451,31 @@ Plan plan_pairs(const Problem& p, bool pooled, bool kept)
         const long long tiles = plan_tiles<G>(p, pooled, pl);
         if (!tiles) return pl;
         const int kb32 = pl.cfg.kblocks * (G::BM / 32);
-        const size_t blk = (size_t)pl.cfg.nch * 9 * 2048, ws = usable_workspace(p, pooled);
-        const size_t pb = ((size_t)p.G * kb32 * (blk + 128) + 255) / 256 * 256;
-        if (blk * 4 >= (1u << 31) || p.G > 65535 || (size_t)p.L * 4 > 128 * 1024 || pb > ws) return pl;
-        consider(pl, tiles, 256LL * occupancy_limit<G>(src, pl.lds_bytes), G::NW, G::tc(src, 9), 1.25, 11.0 + 2e-6 * p.K * p.L, src, pb, kb32, ws,
-                 (size_t)G::BM * G::BN * 4, true);
+        const size_t blk = (size_t)pl.cfg.nch * 9 * 3072, ws = usable_workspace(p, pooled);
+        if (blk * 4 >= (1u << 31) || p.G > 65535 || (size_t)p.L * 4 > 128 * 1024) return pl;
+        // What pairs do not hold is summed from the prepared filters, or from pieces written behind the pairs; from the filters as stored, which
+        // takes a third longer, where the pieces leave no room for the plan (a workspace of 16 MiB and 512 channels of 512 filters).
+        const size_t room[2] = {p.wprep ? 0 : (size_t)p.G * kb32 * blk, 0};
+        const int rest[2] = {p.wprep ? SRC_FP32 : SRC_PIECES, SRC_RAW};
+        const Plan empty = pl;
+        for (int i = 0; i < (p.wprep ? 1 : 2); ++i) {
+            Plan q = empty;
+            const size_t pb = pair_bytes(p.G, kb32, pl.cfg.nch) + room[i];
+            if (pb > ws) continue;
+            consider(q, tiles, 256LL * occupancy_limit<G>(src, q.lds_bytes), G::NW, G::tc(src, 9), 1.25, 11.0 + 2e-6 * p.K * p.L, src, pb, kb32, ws,
+                     (size_t)G::BM * G::BN * 4, true);
+            q.rest = rest[i];
+            if (q.cost >= 0.0 && (pl.cost < 0.0 || q.cost < 0.9 * pl.cost)) pl = q;
+        }
     }
     return pl;
 }
 
-template <class G, int SRC>
+template <class G, int SRC, int FORM = 0>
 int launch_src(const Plan& pl, const Problem& p, const float* x, const float* w, const void* wp, float* parts, float* y, hipStream_t stream)
 {
-    auto kern = piece_kernel<G, SRC>;
-    static_assert(SRC < SRC_PAIRS || G::PAIRS, "the forms with pairs are those of some geometries");
+    auto kern = piece_kernel<G, SRC, FORM>;
+    static_assert(FORM == 0 || G::PAIRS, "the forms with pairs are those of some geometries");
     static size_t opted = 0;
     if (pl.lds_bytes > opted) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1479,10 +1514,14 @@ int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, c
                 opted = row;
             }
             hipLaunchKernelGGL(piece_pairs_kernel, dim3((unsigned)pl.cfg.kb32 * 32, (unsigned)p.G), dim3(256), row, stream, p, pl.cfg.kb32, pl.cfg.nch, w,
-                               reinterpret_cast<u4*>(ws));
+                               reinterpret_cast<u4*>(ws), pl.rest == SRC_PIECES ? reinterpret_cast<u4*>(ws + pair_bytes(p.G, pl.cfg.kb32, pl.cfg.nch)) : nullptr);
             rc = launch_status();
             if (rc) return rc;
-            rc = pl.src == SRC_PAIRS ? launch_src<G, SRC_PAIRS>(pl, p, x, w, ws, parts, y, stream) : launch_src<G, SRC_PAIRS_KEPT>(pl, p, x, w, ws, parts, y, stream);
+            const bool kept = pl.src == SRC_PAIRS_KEPT;
+            auto launch = pl.rest == SRC_FP32 ? (kept ? launch_src<G, SRC_FP32, SRC_PAIRS_KEPT> : launch_src<G, SRC_FP32, SRC_PAIRS>)
+                          : pl.rest == SRC_PIECES ? (kept ? launch_src<G, SRC_PIECES, SRC_PAIRS_KEPT> : launch_src<G, SRC_PIECES, SRC_PAIRS>)
+                                                  : (kept ? launch_src<G, SRC_RAW, SRC_PAIRS_KEPT> : launch_src<G, SRC_RAW, SRC_PAIRS>);
+            rc = launch(pl, p, x, w, ws, parts, y, stream);
         } else {
             return SCONV_EUNSUPPORTED;
         }

@@ -368,14 +368,15 @@ PAIRS = [
 ]
 
 
-def _pairs_call(monkeypatch, geom, split, src, shp, x, w, relu=False):
+def _pairs_call(monkeypatch, geom, split, src, shp, x, w, relu=False, prepared=False):
     N, C, H, W, K, R, S, stride, pad, groups, pool = shp
     xd, wd = to_dev(x), to_dev(w)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
     _pin(monkeypatch, geom, split, src)
-    name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool, True), pool is not None, ws.numel())
-    assert name.startswith(f"piece/model:{geom}/pieces-f16{'k' if src == '4' else ''}")
-    y = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, ws=ws) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, relu, ws=ws))
+    kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd, groups)) if prepared else dict(ws=ws)
+    name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool, True, prepared=prepared), pool is not None, ws.numel())
+    assert name.startswith(f"piece/model:{geom}/{'prepared' if prepared else 'pieces'}-f16{'k' if src == '4' else ''}")
+    y = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, relu, **kw))
     return y.cpu().numpy().astype(np.float64)
 
 
@@ -508,6 +509,29 @@ def test_pairs_hold_every_single_product(device, monkeypatch, spread_x, spread_w
     ref, scale = _reference(shp, x, w)
     assert (scale > 0).all()
     assert (np.abs(got - ref) <= (2.0 ** -22 + 2 * 2.0 ** -23 + 2 * 2.0 ** -24) * scale).all()
+
+
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("split,pool", [("0,1,1", None), ("2,1,2", None), ("0,1,1", (2, 2, 2))])
+@pytest.mark.parametrize("what", [0, 1, 3, 5, "every", "filter", "filters"])
+def test_tiles_go_on_from_three_pieces(device, monkeypatch, what, split, pool, prepared, src):
+    """One element that pairs do not hold, in chunk `what` (or in every one): the chunks before it from pairs, it and those after it from
+    three pieces, of either form of the filters.  A filter that pairs do not hold: its whole block from pieces."""
+    shp = (4, 96, 6, 7, 140, 3, 3, 1, 1, 1, pool)
+    _, x, w = workloads.make_random_case(425, *shp[:10], None, 0.6)
+    x, w = x.copy(), w.copy()
+    if what == "filter":
+        w[77, 50, 1, 1] = 1e-20
+    elif what == "filters":
+        w[::9, 50, 1, 1] = 1e-40
+    else:
+        for c in range(96) if what == "every" else (16 * what + 3,):
+            x[1, c, 2, 3] = 2.0 ** -30
+    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, src, shp, x, w, prepared=prepared)
+    ref, scale = _reference(shp, x, w)
+    assert (np.abs(got - ref) <= (96 * 9 + 6) * 2.0 ** -24 * scale).all()
+    assert np.linalg.norm(got - ref) <= 2e-7 * np.linalg.norm(ref)
 
 
 def _pairs_rows(monkeypatch, shp, x, w):
