@@ -368,10 +368,12 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
 // model promises less.  The vector kernel: 14 + gf * (2.1 + 17.3 * share of
 // nonzeros) - 512 channels @14x14 at batch 8 with prepared filters 49 us at 85 % zeros, 67 at 70 % (piece kernel: 54 at
 // any ratio), @28x28 at batch 8 190 at 75 % (165) - and about 8 us for the filter transposition of large launches.  Where the ratio is
-// unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.3 (512
+// unknown a call must not lose to the vector kernel on a sparse map (see choose): the time that takes at 90 % zeros, 14 + gf * 4.6 (512
 // @28x28 at batch 8 with a workspace, vector / piece kernel: 331 / 208 us at 50 % zeros, 239 / 208 at 70, 172 / 207 at 85, 121 / 191 at
 // 95; 256 @56x56 304 / 162, 232 / 162, 182 / 160, 133 / 136).  Of 120 random layers and 21 of the benchmark's without a ratio, those of
-// this family that lost up to 1.6x from 85 % on stay; the others - short launches, and 256 @56x56 - keep the piece kernels.  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
+// this family that lost up to 1.6x from 85 % on stay; the others - short launches, and 256 @56x56 - keep the piece kernels.  (Where the
+// tiles leave more than 7 % empty, 4.3 times `spare`.  At 4.3 alone, 82 layers of 128 - 512 channels at batches of 8 - 32 leave the piece kernels, and
+// take 2.1 / 1.6 / 1.2 times as long on the vector kernel at 50 / 70 / 85 % zeros, 1.07 at 90, 0.96 at 95.)  The fp32 matrix kernels: 120 TFLOP/s (quad3x3, wide3x3; 200 from 92 % zeros
 // on), 75 (gen).  quad1x1: 6.6 + gf * 10.2, and what the piece kernel stores on top of its model at 0.15 us/MB, which 1x1 layers are too
 // short to hide (plain calls, quad1x1 / piece kernel: 512 -> 256 @28x28 at batch 16 43.9 / 35.3 us, 512 -> 2048 @7x7 at batch 32 51.1 /
 // 46.1, but 64 -> 256 @56x56 at batch 32 53.8 / 59.5, 1024 -> 256 @14x14 45.4 / 51.1, 256 -> 256 @28x28 at batch 8 17.0 / 18.6, 128 -> 256
@@ -449,7 +451,13 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     double c = piece_cost(p, pooled);
     if (c < 0.0) return false;
     if (v == V_PW) c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
-    return c < family_time(p, pooled, v);
+    if (c < family_time(p, pooled, v)) return true;
+    if (v != V_TAP || p.zhint >= 0.0f) return false;
+    // Without a ratio, on tiles that are full.  A plan with sums apart has to be ahead by 4 % there, on prepared filters by 2 %: what that leaves to the
+    // vector kernel is won and lost (512 @28x28 at batch 16, prepared, 243 against 284 us at 90 % zeros, 215 against 278 at 95, 413 against 299 at
+    // 70; 128 @56x56 at batch 8 52 against 48, 49 against 47, 73 against 50).
+    const double gf = dense_gflop(p, pooled);
+    return c * piece_margin(p, pooled) < 14.0 + 4.6 * gf + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
 }
 
 // The plan that the model of family v makes, by name, where the family has one; with the workspace that is selected.

@@ -86,6 +86,8 @@ int launch_pointwise(const Problem& p, bool pooled, const float* x, const float*
 bool piece_supported(const Problem& p, bool pooled);
 // modelled microseconds of the plan launch_piece would take (after split_scratch_select); negative: none
 double piece_cost(const Problem& p, bool pooled);
+// by how much such a plan has to be ahead of the vector kernel where the zero ratio is not known
+double piece_margin(const Problem& p, bool pooled);
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                  hipStream_t stream);
 // whether such a plan must keep the small products apart, so that no result is further from 64-bit sums than the other kernels'

@@ -1742,6 +1742,12 @@ double piece_cost(const Problem& p, bool pooled)
     return c.cand ? c.plan.cost : -1.0;
 }
 
+double piece_margin(const Problem& p, bool pooled)
+{
+    const Choice& c = choose_plan(p, pooled);
+    return !c.cand || !apart_of(c) || c.plan.src == SRC_RAW ? 1.0 : c.plan.src == SRC_FP32 ? 1.02 : 1.04;
+}
+
 bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
 {
     const Choice& c = choose_plan(p, pooled);

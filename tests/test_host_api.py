@@ -137,6 +137,14 @@ def test_too_large_tensors_are_unsupported():
     assert L.sconv_forward(ctypes.byref(d), p, p, p, None) == sconv.SCONV_EUNSUPPORTED
 
 
+@pytest.mark.parametrize("N,C,HW,K", [(8, 256, 56, 256), (12, 256, 56, 256), (8, 128, 112, 128), (16, 128, 56, 256), (12, 256, 28, 512), (16, 256, 28, 512),
+                                      (24, 256, 28, 512), (16, 512, 28, 512)])
+def test_large_layers_without_a_ratio_run_on_the_piece_kernel(N, C, HW, K):
+    """With a workspace: up to twice as fast there as on the vector kernel below 85 % zeros, level at 90."""
+    d = sconv.make_desc(N, C, HW, HW, K, 3, 3, 1, 1)
+    assert sconv.sconv_launch_name(d, False, sconv.sconv_workspace_size(d)).startswith("piece/")
+
+
 def test_launch_name_names_the_kernel_that_runs():
     """sconv_variant_name gives the family that serves a shape; sconv_launch_name the kernel its launches run on, which
     depends on the call's workspace."""
