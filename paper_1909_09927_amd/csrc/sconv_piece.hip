@@ -1658,7 +1658,8 @@ int pairs_for(const Problem& p, const Plan* three, bool apart, double other, boo
 
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
 // kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, whether small
-// products are kept apart, the zero ratio (by which the time of the launch's family is known), a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
+// products are kept apart, the zero ratio (by which the time of the launch's family is known), whether there is such a time (not with a pinned
+// variant) and pairs may stand against it, a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
 // dispatcher's lock; the reference lasts until the next call.)
 const Choice& choose_plan(const Problem& p, bool pooled)
 {
@@ -1712,7 +1713,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     Key k;
     memset(&k, 0, sizeof(k));
     const int v[19] = {p.N, p.C, p.H, p.W, p.K, p.R, p.S, p.stride, p.pad, p.G, pooled ? p.ph : 0, pooled ? p.pw : 0, pooled ? p.ps : 0,
-                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0, close ? 1 : 0, (int)(p.zhint * 254.0f + 0.5f)};
+                       pooled ? 1 : 0, p.wprep ? 1 : 0, tuned ? 1 : 0, close ? 1 : 0, (int)(p.zhint * 254.0f + 0.5f), other < 0.0 ? 0 : other == 0.0 ? 1 : 2};
     memcpy(k.v, v, sizeof(v));
     k.ws = usable_workspace(p, pooled);
     if (tuned) {

@@ -194,6 +194,20 @@ def test_large_calls_without_a_ratio_keep_the_kernel_that_skips_elements(shp, po
     assert sconv.sconv_launch_name(sconv.make_desc(*shp, zero_ratio=0.5, **k), pool is not None, bytes_).startswith("piece/")
 
 
+@pytest.mark.parametrize("pinned_first", [True, False])
+def test_a_pinned_variant_leaves_other_calls_plans_alone(monkeypatch, pinned_first):
+    """With the piece kernel pinned a layer takes pairs that it does not take on its own; either plan is kept for its own calls only."""
+    d = sconv.make_desc(17 + pinned_first, 512, 28, 28, 512, 3, 3, 1, 1)
+    ws = sconv.sconv_workspace_size(d)
+
+    def name(pinned):
+        monkeypatch.setenv("SCONV_VARIANT", "piece") if pinned else monkeypatch.delenv("SCONV_VARIANT", raising=False)
+        return sconv.sconv_launch_name(d, False, ws)
+    for pinned in (pinned_first, not pinned_first):
+        got = name(pinned)
+        assert got.startswith("piece/model:") and ("-f16" in got) == pinned
+
+
 @pytest.mark.parametrize("shp", [(1, 512, 7, 7, 512, 3, 3, 1, 1), (1, 256, 14, 14, 256, 3, 3, 1, 1)])
 def test_short_calls_without_a_ratio_run_on_the_piece_kernel(shp):
     """A batch-1 layer: the vector kernel's time is the walk of its few workgroups at any ratio."""
