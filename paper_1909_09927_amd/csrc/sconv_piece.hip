@@ -1659,7 +1659,7 @@ int pairs_for(const Problem& p, const Plan* three, bool apart, double other, boo
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
 // kept by what they depend on: the shape, the room in the workspace, whether the filters come prepared, whether small
 // products are kept apart, the zero ratio (by which the time of the launch's family is known), whether there is such a time (not with a pinned
-// variant) and pairs may stand against it, a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 512 sets of four, the oldest of a set goes.  (Under the
+// variant) and pairs may stand against it, a geometry that sconv_tune found.  Networks have up to a few hundred such keys: 256 sets of eight, the oldest of a set goes.  (Under the
 // dispatcher's lock; the reference lasts until the next call.)
 const Choice& choose_plan(const Problem& p, bool pooled)
 {
@@ -1670,11 +1670,11 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     };
     static_assert(sizeof(Key) == sizeof(size_t) + 19 * sizeof(int) + sizeof(PlanPin), "compared as bytes: no padding");
     struct Set {
-        Key key[4];
-        Choice choice[4];
+        Key key[8];
+        Choice choice[8];
         int used, next;
     };
-    constexpr size_t kSets = 512;
+    constexpr size_t kSets = 256;
     static Set kept[kSets];
     static Choice pinned;
     const PlanPin* tuned = current_pin();
@@ -1728,8 +1728,8 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     for (int i = 0; i < set.used; ++i)
         if (!memcmp(&set.key[i], &k, sizeof(k))) return set.choice[i];
     const int at = set.next;
-    set.next = (at + 1) % 4;
-    if (set.used < 4) ++set.used;
+    set.next = (at + 1) % 8;
+    if (set.used < 8) ++set.used;
     memcpy(&set.key[at], &k, sizeof(k));
     walk(set.choice[at]);
     return set.choice[at];
