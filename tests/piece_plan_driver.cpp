@@ -148,20 +148,23 @@ static void plans_are_kept()
 // The plans of one geometry: what a workgroup stages and reads in LDS, what it reads of the map and writes to the workspace, and which
 // results it computes, followed as the kernels compute it.
 template <class G>
-static void plans(const char* name, Plan (*plan)(const Problem&, bool, bool), int CS, int PXMAX, int lds_other, int chunk_buffers)
+static void plans(const char* name, Plan (*plan)(const Problem&, bool, bool), int CS, int PXMAX, int lds_other, int chunk_buffers, int pair_buffer = 0)
 {
-    int walked = 0, split = 0, in_pieces = 0;
-    for (int tries = 0; tries < 4000 && walked < 60; ++tries) {
+    const bool pairs = pair_buffer != 0;
+    int walked = 0, split = 0, in_pieces = 0, rests[3] = {0, 0, 0};
+    for (int tries = 0; tries < (pairs ? 40000 : 4000) && walked < 60; ++tries) {
         Problem p;
         if (!random_problem(G::T, G::POOL, &p)) continue;
         static const float some = 0.0f;
-        p.wprep = pick(0, 3) == 0 && tap_supported(p, G::POOL) && p.stride == 1 ? &some : nullptr;
+        const bool prepares = tap_supported(p, G::POOL) && p.stride == 1;
+        if (pairs && walked % 4 == 3 && !prepares) continue;
+        p.wprep = (pairs ? walked % 4 == 3 : pick(0, 3) == 0) && prepares ? &some : nullptr;
         // a third with the model's choice, the others with split tiles or with pieces of the filters where there is room
         const int form = walked % 3;
         char slices[16];
         snprintf(slices, sizeof(slices), "%d,1,%d", pick(0, 2), pick(2, 5));
         form == 1 ? setenv("SCONV_PIECE_SPLIT", slices, 1) : unsetenv("SCONV_PIECE_SPLIT");
-        form == 2 && G::BM != 32 ? setenv("SCONV_PIECE_SRC", "0", 1) : unsetenv("SCONV_PIECE_SRC");
+        form == 2 && G::BM != 32 && !pairs ? setenv("SCONV_PIECE_SRC", "0", 1) : unsetenv("SCONV_PIECE_SRC");
         EXPECT(sconv_env_refresh() == SCONV_OK, "%s", name);
         const size_t room = form || pick(0, 1) ? plan_workspace_bytes(p, G::POOL) / (form ? 1 : (size_t)pick(1, 20)) : 0;
         split_scratch_given(room ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, room, true);
@@ -182,7 +185,18 @@ static void plans(const char* name, Plan (*plan)(const Problem&, bool, bool), in
         HOLDS(pl.piece_bytes + (size_t)pl.ntail * (pl.ntail ? c.nss : 0) * G::BM * G::BN * 4 <= ws);
         HOLDS(c.whole + pl.ntail == c.ntiles * c.strips * c.kblocks * p.G && (!pl.ntail || (c.nss > 1 && c.nss <= c.nch)));
         HOLDS(c.nch * 16 * CS >= p.Cg && c.kblocks * G::BM >= p.Kg && (c.nch - 1) * 16 * CS < p.Cg);
-        HOLDS((pl.src == SRC_FP32) <= (p.wprep != nullptr));
+        HOLDS((pl.src == SRC_FP32) <= (p.wprep != nullptr) && (pl.src >= SRC_PAIRS) == pairs);
+        if (pairs) {
+            // fragments of 2048 bytes, a word for every filter behind them, and from the next 256 bytes on the pieces that the other chunks may read
+            const size_t fragments = (size_t)p.G * c.kb32 * c.nch * 9, exponents = (size_t)p.G * c.kb32 * 32, both = pair_bytes(p.G, c.kb32, c.nch);
+            HOLDS(both % 256 == 0 && fragments * 2048 + exponents * 4 <= both && c.kb32 * 32 >= c.kblocks * G::BM);
+            HOLDS(pl.lds_bytes >= 2 * (size_t)pair_buffer);
+            HOLDS(pl.piece_bytes == both + (pl.rest == SRC_PIECES ? fragments * 3072 : 0));
+            HOLDS(pl.rest == (p.wprep ? SRC_FP32 : pl.rest == SRC_PIECES ? SRC_PIECES : SRC_RAW));
+            if (p.wprep) HOLDS(c.kb32 == (p.Kg + 127) / 128 * 4 && p.Cg % 16 == 0);
+            HOLDS(fragments / p.G / c.kb32 * 4 * 3072 < (size_t)1 << 31 && (size_t)p.L * 4 <= 128 * 1024);   // a block's offsets, a filter in LDS
+            ++rests[pl.rest];
+        }
         if (pl.src == SRC_PIECES) HOLDS(pl.piece_bytes == (size_t)p.G * c.kb32 * c.nch * CS * T * 3072 && c.kb32 * 32 >= c.kblocks * G::BM);
         if (pl.src == SRC_FP32) HOLDS(c.kb32 * 32 >= c.kblocks * G::BM && p.Cg % (16 * CS) == 0);
         split += pl.ntail > 0;
@@ -244,7 +258,21 @@ static void plans(const char* name, Plan (*plan)(const Problem&, bool, bool), in
     unsetenv("SCONV_PIECE_SPLIT");
     unsetenv("SCONV_PIECE_SRC");
     EXPECT(sconv_env_refresh() == SCONV_OK && walked >= 40 && split >= 10, "%s: %d plans, %d with split tiles", name, walked, split);
-    if (G::BM != 32) EXPECT(in_pieces >= 10, "%s: %d plans with pieces of the filters", name, in_pieces);
+    if (G::BM != 32 && !pairs) EXPECT(in_pieces >= 10, "%s: %d plans with pieces of the filters", name, in_pieces);
+    if (pairs) EXPECT(rests[SRC_PIECES] >= 5 && rests[SRC_RAW] >= 3 && rests[SRC_FP32] >= 5, "%s: pieces %d, prepared %d, as stored %d", name, rests[0], rests[1], rests[2]);
+}
+
+// The forms with pairs: as above, and what a wavefront writes of a chunk in LDS stays in its buffer.
+template <class G>
+static void pair_plans(const char* name)
+{
+    if constexpr (G::PAIRS) {
+        constexpr int plane = G::PXMAX * 16;
+        for (int unit = 0; unit < G::XU * G::NW; ++unit)
+            EXPECT(unit % 2 * 2 * plane + (unit / 2 * 64 + 63) * 16 + plane + 16 <= 2 * 2 * plane, "%s: unit %d", name, unit);
+        EXPECT(2 * 2 * plane + 64 + G::NW * 8 <= G::PAIR_BUF && G::NW * 4 <= 64 && G::NW == 4, "%s: words and ranges of the wavefronts", name);
+        plans<G>(name, plan_pairs<G>, G::CS, G::PXMAX, 2 * G::SPARE, 2, G::PAIR_BUF);
+    }
 }
 
 int main()
@@ -253,7 +281,9 @@ int main()
     plans_are_kept();
 #define WALK_PIECE(NAME, ...)                          \
     raw_reads<PGeom<__VA_ARGS__>>(NAME);               \
-    plans<PGeom<__VA_ARGS__>>(NAME, plan_geom<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::CS, PGeom<__VA_ARGS__>::PXMAX, 0, 2);
+    plans<PGeom<__VA_ARGS__>>(NAME, plan_geom<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::CS, PGeom<__VA_ARGS__>::PXMAX, \
+                              2 * PGeom<__VA_ARGS__>::SPARE, 2);                        \
+    pair_plans<PGeom<__VA_ARGS__>>(NAME "/pairs");
 #define WALK_TAPS(NAME, ...) \
     plans<TGeom<__VA_ARGS__>>(NAME, plan_taps<TGeom<__VA_ARGS__>>, TGeom<__VA_ARGS__>::CS, TGeom<__VA_ARGS__>::PXMAX, TGeom<__VA_ARGS__>::FB, 1);
     PIECE_GEOMETRIES(WALK_PIECE, WALK_TAPS)
