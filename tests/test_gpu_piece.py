@@ -573,3 +573,26 @@ def test_pairs_are_no_further_from_64_bit_sums_than_what_they_replace(device, mo
     other = error()
     print(f"{mine:.3e} against {other:.3e}")
     assert mine <= 1.05 * other
+
+
+@pytest.mark.parametrize("shp,z", [((7, 262, 58, 58, 48, 3, 3, 1, 1, 1, None), 0.68), ((7, 656, 37, 27, 96, 3, 3, 1, 0, 1, None), 0.9),
+                                   ((8, 661, 24, 14, 127, 3, 3, 1, 1, 1, None), 0.84)])
+def test_pairs_leave_the_taps_kernel_where_it_is_closer(device, monkeypatch, shp, z):
+    """Layers that the taps kernel served as fast as three pieces do: what runs now is no further from 64-bit sums; seeds move either by a
+    twentieth."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(426, *shp[:10], None, z)
+    xd, wd = to_dev(x), to_dev(w)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    ref = (wd.double().reshape(K, -1) @ torch.nn.functional.unfold(xd[:1].double(), 3, padding=pad)[0]).reshape(1, K, H + 2 * pad - 2, -1)
+
+    def error():
+        y = sconv.sconv_forward(xd, wd, stride, pad, groups, zero_ratio=z if C == 262 else None, ws=ws)[:1].double()
+        return float((y - ref).norm() / ref.norm())
+    for name in ("SCONV_VARIANT", "SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
+        monkeypatch.delenv(name, raising=False)
+    mine = error()
+    _pin(monkeypatch, "t3x64", None, None)
+    other = error()
+    print(f"{mine:.3e} against {other:.3e}")
+    assert mine <= 1.05 * other
