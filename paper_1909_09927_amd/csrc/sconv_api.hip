@@ -396,10 +396,11 @@ static double family_time(const Problem& p, bool pooled, Variant v)
     // filters, took 277 / 131 us at 60 / 90 % zeros on the vector kernel against 91, 96 -> 416 @44x44 at batch 5 123 / 71 against 52, 576 -> 448 in
     // 4 groups @57x57 at batch 5 205 / 129 against 120.  Of 180 random layers at 60, 90 and 95 % zeros 40 move, 1.6 / 1.2 / 1.1 times as fast.  Not
     // below 32 channels a group (64 -> 576 in 4 groups @38x38, pooled: 21.6 against 23.2 at 90 %), not without a workspace and a ratio (448 -> 92 in 4
-    // groups @41x41 57.6 against 66.4 at 95 %), on quad3x3 from half a block on (64 -> 192 in 4 groups @57x57 54 against 58).
+    // groups @41x41 57.6 against 66.4 at 95 %) nor in the shortest launches without a ratio (128 -> 128 in 4 groups @14x14 at batch 7, prepared, 13.5
+    // against 16.1 at 78 %; with one, 192 -> 168 in 4 groups @19x19 at batch 1 18.2 against 13.7 at 46 %), on quad3x3 from half a block on (64 -> 192 in 4 groups @57x57 54 against 58).
     const double spare_k = (double)((p.Kg + 63) / 64 * 64) / p.Kg;
     const int cols = pooled ? p.PW * 2 : p.OW;
-    const bool fits_hold = p.Cg < 32 || (!can_split && !p.wprep && p.zhint < 0.0f);
+    const bool fits_hold = p.Cg < 32 || (p.zhint < 0.0f && (gf < 0.12 || (!can_split && !p.wprep)));
     const double spare = fits_hold ? 1.0 : spare_k * fmin(1.15, (double)((cols + 6) / 7 * 7) / cols);
     switch (v) {
     case V_TAP: {
@@ -450,6 +451,8 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     if (dense_gflop(p, pooled) < 0.03) return false;
     double c = piece_cost(p, pooled);
     if (c < 0.0) return false;
+    // (one chunk: what a tile stores is more than its model counts; 10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the piece kernel)
+    if (v == V_GEN && p.Cg <= 16) c *= piece_margin(p, pooled);
     if (v == V_PW) c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
     if (c < family_time(p, pooled, v)) return true;
     if (v != V_TAP || p.zhint >= 0.0f) return false;
