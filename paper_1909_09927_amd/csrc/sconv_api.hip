@@ -451,16 +451,16 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     if (dense_gflop(p, pooled) < 0.03) return false;
     double c = piece_cost(p, pooled);
     if (c < 0.0) return false;
-    // (one chunk: what a tile stores is more than its model counts; 10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the piece kernel)
-    if (v == V_GEN && p.Cg <= 16) c *= piece_margin(p, pooled);
     if (v == V_PW) c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
-    if (c < family_time(p, pooled, v)) return true;
+    const double other = family_time(p, pooled, v);
+    // (one chunk: what a tile stores is more than its model counts; 10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the piece kernel)
+    if (c < other) return v != V_GEN || p.Cg > 16 || c * piece_margin(p, pooled) < other;
     if (v != V_TAP || p.zhint >= 0.0f) return false;
     // Without a ratio, on tiles that are full.  A plan with sums apart has to be ahead by 4 % there, on prepared filters by 2 %: what that leaves to the
     // vector kernel is won and lost (512 @28x28 at batch 16, prepared, 243 against 284 us at 90 % zeros, 215 against 278 at 95, 413 against 299 at
     // 70; 128 @56x56 at batch 8 52 against 48, 49 against 47, 73 against 50).
-    const double gf = dense_gflop(p, pooled);
-    return c * piece_margin(p, pooled) < 14.0 + 4.6 * gf + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+    const double gf = dense_gflop(p, pooled), full = 14.0 + 4.6 * gf + (p.wprep || gf < 2.0 ? 0.0 : 8.0);
+    return c < full && c * piece_margin(p, pooled) < full;
 }
 
 // The plan that the model of family v makes, by name, where the family has one; with the workspace that is selected.
