@@ -1165,27 +1165,29 @@ __global__ __launch_bounds__(64) void piece_filters_kernel(Problem p, int kb32, 
 // every filter's scale (kUnpaired: not to be held in pairs).  Filters past the group and channels past Cg are zero.
 // Where `pieces` is given, the three pieces there besides, as piece_filters_kernel writes them: what a launch reads where pairs do not do (from
 // the filters as stored it took a third longer: 256 @56x56 at batch 32 with eight weights of 1e-20 729 us, now 517).
-// A workgroup takes one filter through LDS: its range, then its pairs, 16 bytes a lane at a filter's place in the fragments; neighbouring
-// filters go to one XCD, whose L2 puts the lines together.  Bound by the two trips to memory: 512 x 512 x 9 9.5 us (11.4 with a wavefront per
-// filter; three pieces of it, by piece_filters_kernel, 14.7).
-__global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, int nch16, const float* __restrict__ w, u4* __restrict__ out,
-                                                          u4* __restrict__ pieces)
+// A workgroup takes FW neighbouring filters through LDS: their ranges, then their pairs, 16 bytes a lane at a filter's place in the fragments; the
+// filters' places are side by side, and those of other workgroups on the same XCD, whose L2 puts the lines together.  Bound by the stores: 512 x 512
+// x 9, pairs alone / with pieces, 9.0 / 14.9 us with one filter a workgroup, 7.4 / 11.7 with two, 8.3 / 12.1 with four (half the chip), 768 x 768
+// 26.0, 18.4, 15.8 with pieces, 256 x 256 7.2, 6.7, 7.2; three pieces of 512 x 512 by piece_filters_kernel 14.7.
+template <int FW>
+__global__ __launch_bounds__(256 * FW) void piece_pairs_kernel(Problem p, int kb32, int nch16, const float* __restrict__ w, u4* __restrict__ out,
+                                                               u4* __restrict__ pieces)
 {
     extern __shared__ float f[];
-    __shared__ uint2 part[4];
+    __shared__ uint2 part[4 * FW];
     const int tid = threadIdx.x, g = blockIdx.y, L = p.L;
-    const int k = (blockIdx.x & 7) * (kb32 * 4) + (blockIdx.x >> 3);
-    const bool real = k < p.Kg;
+    const int k0 = ((blockIdx.x & 7) * (kb32 * 4 / FW) + (blockIdx.x >> 3)) * FW;
     Range rg;
-    if (real) {
-        const float* src = w + ((size_t)g * p.Kg + k) * L;
-        for (int o0 = tid; o0 < L; o0 += 16 * 256) {
+    if (k0 + (tid >> 8) < p.Kg) {
+        const float* src = w + ((size_t)g * p.Kg + k0 + (tid >> 8)) * L;
+        float* dst = f + (tid >> 8) * L;
+        for (int o0 = tid & 255; o0 < L; o0 += 16 * 256) {
             float v[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) v[j] = src[min(o0 + j * 256, L - 1)];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                f[min(o0 + j * 256, L - 1)] = v[j];
+                dst[min(o0 + j * 256, L - 1)] = v[j];
                 if (j & 1) rg.add(v[j - 1], v[j]);
             }
         }
@@ -1193,21 +1195,23 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
     const uint2 of = rg.of_wave();
     if ((tid & 63) == 63) part[tid >> 6] = of;
     __syncthreads();
-    const unsigned hi = __builtin_amdgcn_readfirstlane(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)));
-    const unsigned lo = __builtin_amdgcn_readfirstlane(min(min(part[0].y, part[1].y), min(part[2].y, part[3].y)));
+    const int fw = tid % FW, k = k0 + fw;
+    const uint2* r = part + 4 * fw;
+    const unsigned hi = max(max(r[0].x, r[1].x), max(r[2].x, r[3].x)), lo = min(min(r[0].y, r[1].y), min(r[2].y, r[3].y));
     const int sg = pair_exponent(hi);
-    const float up = power_of_two(sg), up2 = power_of_two(sg + 12);
+    const float up = power_of_two(sg);
+    const bool real = k < p.Kg;
     const size_t blk = ((size_t)g * kb32 + (k >> 5)) * nch16 * 9;
     u4* dst = out + blk * 128 + (k & 31);
     u4* dst3 = pieces + blk * 192 + (k & 31);
-    for (int it = tid; it < nch16 * 18; it += 256) {
+    for (int it = tid / FW; it < nch16 * 18; it += 256) {
         const int t = it % 9, hc = it / 9;          // 8 channels of one tap
         u4 q[2], q3[3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = hc * 8 + 2 * i;
-            const float a = real && c < p.Cg ? f[c * 9 + t] : 0.0f, b = real && c + 1 < p.Cg ? f[c * 9 + 9 + t] : 0.0f;
-            pair2(a, b, up, up2, up, up2, i, q);
+            const float a = real && c < p.Cg ? f[fw * L + c * 9 + t] : 0.0f, b = real && c + 1 < p.Cg ? f[fw * L + c * 9 + 9 + t] : 0.0f;
+            pair2(a * up, b * up, 1.0f, 4096.0f, 1.0f, 4096.0f, i, q);
             if (pieces) split2(a, b, kUp, kUp, i, q3);
         }
         const size_t at = (size_t)(hc >> 1) * 9 + t;
@@ -1221,7 +1225,7 @@ __global__ __launch_bounds__(256) void piece_pairs_kernel(Problem p, int kb32, i
         d[128] = q3[2];
     }
     int* exponents = reinterpret_cast<int*>(out + (size_t)p.G * kb32 * nch16 * 9 * 128) + (size_t)g * kb32 * 32;
-    if (tid == 0) exponents[k] = PairLimits(sg).hold(hi, lo) ? sg : kUnpaired;
+    if (tid < FW) exponents[k] = PairLimits(sg).hold(hi, lo) ? sg : kUnpaired;
 }
 
 struct Plan {
@@ -1488,6 +1492,21 @@ int launch_src(const Plan& pl, const Problem& p, const float* x, const float* w,
     return launch_status();
 }
 
+template <int FW>
+int launch_pairs(const Problem& p, const PieceCfg& cfg, const float* w, u4* pairs, u4* pieces, hipStream_t stream)
+{
+    const size_t rows = (size_t)p.L * 4 * FW;
+    static size_t opted = 0;
+    if (rows > opted) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(piece_pairs_kernel<FW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows) != hipSuccess)
+            return SCONV_ELAUNCH;
+        opted = rows;
+    }
+    hipLaunchKernelGGL(piece_pairs_kernel<FW>, dim3((unsigned)cfg.kb32 * 32 / FW, (unsigned)p.G), dim3(256 * FW), rows, stream, p, cfg.kb32, cfg.nch, w,
+                       pairs, pieces);
+    return launch_status();
+}
+
 template <class G>
 int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t stream)
 {
@@ -1506,16 +1525,9 @@ int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, c
         rc = launch_src<G, SRC_PIECES>(pl, p, x, w, ws, parts, y, stream);
     } else if (pl.src >= SRC_PAIRS) {
         if constexpr (G::PAIRS) {
-            const size_t row = (size_t)p.L * 4;
-            static size_t opted = 0;
-            if (row > opted) {
-                if (hipFuncSetAttribute(reinterpret_cast<const void*>(piece_pairs_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)row) != hipSuccess)
-                    return SCONV_ELAUNCH;
-                opted = row;
-            }
-            hipLaunchKernelGGL(piece_pairs_kernel, dim3((unsigned)pl.cfg.kb32 * 32, (unsigned)p.G), dim3(256), row, stream, p, pl.cfg.kb32, pl.cfg.nch, w,
-                               reinterpret_cast<u4*>(ws), pl.rest == SRC_PIECES ? reinterpret_cast<u4*>(ws + pair_bytes(p.G, pl.cfg.kb32, pl.cfg.nch)) : nullptr);
-            rc = launch_status();
+            u4* const pairs = reinterpret_cast<u4*>(ws);
+            u4* const pieces = pl.rest == SRC_PIECES ? reinterpret_cast<u4*>(ws + pair_bytes(p.G, pl.cfg.kb32, pl.cfg.nch)) : nullptr;
+            rc = p.L <= 16 * 1024 ? launch_pairs<2>(p, pl.cfg, w, pairs, pieces, stream) : launch_pairs<1>(p, pl.cfg, w, pairs, pieces, stream);   // (by LDS)
             if (rc) return rc;
             const bool kept = pl.src == SRC_PAIRS_KEPT;
             auto launch = pl.rest == SRC_FP32 ? (kept ? launch_src<G, SRC_FP32, SRC_PAIRS_KEPT> : launch_src<G, SRC_FP32, SRC_PAIRS>)
