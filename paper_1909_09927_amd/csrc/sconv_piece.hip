@@ -1655,16 +1655,17 @@ bool apart_of(const Choice& c) { return c.cand->apart(c.plan.src); }
 // family's kernel, `other` microseconds (negative: not known), where that is faster -, or -1.  Relative error against 64-bit sums (1e-7; the
 // same at 40 - 90 % zeros within a tenth): pairs 1.2 at 64 and 128 channels, 1.35 at 256, 1.5 at 512; kept 1.1 - 1.2 at any number.  Against three pieces in
 // one chain, 1.7 - 2.0, either is closer; against sums apart, 0.65 at 64 channels to 1.17 at 512 (less where tiles are split), kept ones from
-// 512 on while most tiles are whole; against the taps kernel neither (656 -> 96 @37x27 0.84 against 1.08, 661 -> 127 @24x14 0.93 against 1.15); against the other families where piece_close has it that three pieces in one chain are no further off
+// 512 on while most tiles are whole; against the taps kernel kept ones there too, where a reported ratio is 50 % at most (512 / 640 channels @14x14, taps against
+// kept, 1.20 / 1.28 against 1.16 / 1.21 at 50 % zeros, 1.02 / 1.09 against 1.12 / 1.20 at 70, 0.79 / 0.82 against 1.02 / 1.10 at 90); against the other families where piece_close has it that three pieces in one chain are no further off
 // than they, and from 512 channels on (vector kernel, split, 1.6 / 1.3 / 1.05 at 50 / 70 / 85 % zeros).
 // A call without a zero ratio whose family is the vector kernel's stays as it was (see piece_first).
 int pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double other, bool close)
 {
     if (other == 0.0) return -1;
     if (three && (other < 0.0 || three->cost < other)) {
-        if (taps) return -1;
         if (!apart) return p.Cg < 512 ? SRC_PAIRS : SRC_PAIRS_KEPT;
-        return p.Cg >= 512 && three->cfg.whole >= three->ntail ? SRC_PAIRS_KEPT : -1;
+        const bool level = p.Cg >= 512 && three->cfg.whole >= three->ntail;
+        return level && (!taps || (p.zhint >= 0.0f && p.zhint <= 0.5f)) ? SRC_PAIRS_KEPT : -1;
     }
     return !close || p.Cg >= 512 ? SRC_PAIRS_KEPT : -1;
 }
