@@ -534,6 +534,26 @@ def test_tiles_go_on_from_three_pieces(device, monkeypatch, what, split, pool, p
     assert np.linalg.norm(got - ref) <= 2e-7 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("what", ["integers", "plain", "element", "filter"])
+@pytest.mark.parametrize("shp,split", [((1, 1840, 5, 5, 130, 3, 3, 1, 1, 1, None), "0,1,1"), ((1, 64, 13, 21, 40, 3, 3, 1, 2, 1, None), "0,1,2")])
+def test_pairs_without_room_for_pieces(device, monkeypatch, shp, split, what, src):
+    """Pairs alone fill the workspace, so what they do not hold is summed from the filters as stored; 1840 channels: one filter in LDS, not two."""
+    _, x, w = workloads.make_random_case(427, *shp[:10], None, 0.6, what == "integers")
+    x, w = x.copy(), w.copy()
+    if what == "element":
+        x[0, 40, 2, 3] = 2.0 ** -30
+    elif what == "filter":
+        w[17, 20, 1, 1] = 1e-20
+    got = _pairs_call(monkeypatch, "a128x64", split, src, shp, x, w)
+    ref, scale = _reference(shp, x, w)
+    if what == "integers":
+        assert np.array_equal(got, ref)
+    else:
+        assert (np.abs(got - ref) <= (shp[1] * 9 + 6) * 2.0 ** -24 * scale).all()
+        assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
+
+
 def _pairs_rows(monkeypatch, shp, x, w):
     """The window-row kernel, which skips zeros of the map."""
     for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
