@@ -109,10 +109,14 @@ int sconv_encode(const sconv_desc_t* desc, int fmt, const float* x_dev, float* v
  * plain or pooled over 2x2 windows, where the input positions of its tiles fit (strided 3x3 mostly, strided 1x1, 5x5 and 7x7 on small
  * maps only).  Its time does not depend on the zeros, the vector kernel's does: it takes 3x3 layers of that family over where a reported
  * ratio makes it the faster one, and without one where it is no slower at 90 % zeros.  It multiplies the zeros of a tile (a result that
- * is not finite is summed again with every zero element skipped).
+ * is not finite is summed again with every zero element skipped).  3x3 launches with a workspace may take two fp16 values per
+ * fp32 value and three products instead (plan names with "-f16"), where their sums are measured no further from 64-bit sums than
+ * those of the plan they replace: 1.1e-7 to 1.5e-7 of the result at 40 - 90 % zeros, every single product within 2^-21 of
+ * its value (pieces: 2^-24; the sums' own roundings come on top of either).  Elements and weights that fp16 pairs do not hold so
+ * closely - 2^27 below the largest of their 16 channels of a tile, or of their filter - are summed from pieces, in the same launch.
  * A workspace (lent with sconv_set_workspace, or passed to the ..._ws forms) is used three ways.
- * (3) The piece kernel keeps its pieces of the filters there when there is room, and the partial sums of tiles that would
- * not fill a last round of workgroups.
+ * (3) The piece kernel keeps its pieces (and pairs) of the filters there when there is room, and the partial sums of tiles that
+ * would not fill a last round of workgroups.
  * (1) Launches too small to fill the chip - fewer than 128 workgroups ("tap3x3" and "gen": deep layers
  * at batch 1), "tap3x3" launches of up to 768 workgroups that walk 256 or more channels, 100-400 tiles of
  * "quad3x3" on a map 28 or more wide - are split along the channels over up to 16 workgroups per tile;

@@ -26,7 +26,7 @@ __device__ __forceinline__ int rank_from(int base, unsigned long long mask)
 __device__ __forceinline__ uint2 pair_of(float v, int col) { return make_uint2(__builtin_bit_cast(unsigned, v), (unsigned)col); }
 
 // Bound by the instructions of this walk (a row per wavefront, 12 - 14 wavefronts a compute unit on the benchmark's layers), so: offsets carried
-// along instead of multiplied out, four groups of columns read before the first is ranked, two instructions for a rank.  512 @28x28 24.2 -> 21.3 us,
+// along instead of multiplied out, several groups of columns read before the first is ranked (four, two where they are staged), two instructions for a rank.  512 @28x28 24.2 -> 21.3 us,
 // 256 @56x56 23.9 -> 22.5, 1x1 512 @14x14 at batch 4 20.5 -> 16.7, 256 @60x60 at batch 8 31.3 -> 29.5, stride 2 128 @64x64 14.5 -> 14.1.
 // 64 columns of a row: their nonzeros go into the row's ring, and a run of 64 pairs leaves it when there are as many.  (One LDS write and
 // one read for both halves of a pair.)

@@ -41,11 +41,12 @@
 // taps ahead (no LDS, no barrier): from pieces that a kernel writes into the workspace first, from prepared filters, or
 // from the filters as stored.  MT = 1, NT = 4 gives an instruction stream of 216 matrix instructions to 108 LDS reads and
 // 27 loads per chunk; two workgroups a compute unit keep the matrix pipe busy 67 % of the time at 1.9 GHz, 220 - 240 TFLOP/s
-// dense-equivalent on 512 channels @28x28 at batch 62 (quad3x3: 120).
+// dense-equivalent on 512 channels @28x28 at batch 62 (quad3x3: 120).  Two are what all geometries have a compute unit but those that cut stored
+// filters.
 //
 // Tiles that do not fill a last round of workgroups are split along the channels (split tiles: partial sums into the
-// workspace, piece_sum_kernel adds them): 784 tiles of 256 @56x56 at batch 8 on 768 places run as 768 whole ones and 16 in
-// 16 slices each, 153 us against 189.
+// workspace, piece_sum_kernel adds them): the 784 tiles of 256 @56x56 at batch 8 run as 768 whole ones, three to a compute unit, and 16 in 16
+// slices each (six products: 153 us against 189 with all of them whole).
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -220,8 +221,8 @@ __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast
 // The sums of one tile from fp16 pairs: v = p0 + 2^-12 p1, three products p0q0, p0q1, p1q0 (the fourth is 2^-22 of the product at most) instead of
 // six, two thirds of the LDS and filter traffic.  Bound by the chip's power like the six products (1.9 - 2.1 GHz; a third LDS buffer with one
 // barrier a chunk, loads two taps ahead, a second set of map registers and a third fewer vector instructions all measured within 3 %), of
-// which three take two thirds of the time: 256 @56x56 at batch 8 151 -> 105 us, 512 @28x28 at batch 8 with prepared filters 160 -> 112, at
-// batch 62 955 -> 720 (1.0 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
+// which three take two thirds of the time: 256 @56x56 at batch 8 149 -> 100 us, 512 @28x28 at batch 8 with prepared filters 159 -> 104, at
+// batch 62 937 -> 659 (1.04 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
 // The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
 // stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter such a
 // weight - about one of 4 x 10^7 normally distributed values -, the tile is summed from three pieces from there on: returned is the first chunk that
