@@ -430,18 +430,37 @@ static double family_time(const Problem& p, bool pooled, Variant v)
 // it is 0.5 - 0.9.
 // *family_us: what the kernel it takes over from would take; negative: not known (a pinned variant), zero: no plan of
 // fewer products may take its place (the vector kernel without a ratio, and quad3x3 from 92 % zeros on, whose error falls with the products left).
-bool piece_close(const Problem& p, bool pooled, double* family_us)
+// *pairs_to: the zero ratio up to which fp16 pairs are no further from 64-bit sums than that kernel (above 1: also where the ratio is not known;
+// negative: none).  Relative error at 70 / 80 / 88 / 95 % zeros, 1e-7, against 1.2 / 1.15 / 1.1 / 1.0 of pairs at any number of channels: gen and
+// wide3x3 1.8 / 1.5 / 1.2 / 0.86 at 144 channels, 2.3 / 1.9 / 1.5 / 1.05 at 256; quad3x3 at 256 channels 1.06 at 95 %; the vector kernel 1.09 at 90 and
+// 0.86 at 95 there, 1.13 at 95 and 512.  Kernels that split a tile's channels are closer: gen in launches of fewer than 128 tiles 1.1 / 0.95 / 0.84 / 0.72 at 144
+// channels, 1.3 / 1.13 / 0.97 / 0.78 at 256; quad3x3 at 256 channels 1.15 / 0.97 / 0.79 from 80 % on; the vector kernel at 512 1.0 at 88 %.
+bool piece_close(const Problem& p, bool pooled, double* family_us, float* pairs_to)
 {
     const bool have_ws = split_scratch_possible(nullptr);
     const Variant v = choose(p, pooled, have_ws, nullptr, p.zhint);
     const bool keeps = (v == V_TAP && p.zhint < 0.0f) || (v == V_QUAD && p.zhint >= 0.92f);
     *family_us = v == V_ROWS || v == V_PIECE || env_value("SCONV_VARIANT") ? -1.0 : keeps ? 0.0 : family_time(p, pooled, v);
+    const float any = 2.0f, none = -1.0f;
+    const long long windows = pooled ? (long long)p.N * p.PH * p.PW * 4 : (long long)p.N * p.OH * p.OW;
     switch (v) {
     case V_WIDE:
-    case V_GEN: return p.Cg < 128;
-    case V_QUAD: return p.Cg < 256;
-    case V_TAP: return p.Cg < 256 || (have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768);
-    default: return false;
+    case V_GEN: {
+        const bool split = v == V_GEN && have_ws && (windows + 63) / 64 * ((p.Kg + 63) / 64) * p.G < 128;
+        *pairs_to = p.Cg < 128 ? none : p.Cg < 256 ? (split ? none : 0.88f) : split ? 0.75f : any;
+        return p.Cg < 128;
+    }
+    case V_QUAD:
+        *pairs_to = p.Cg < 256 ? none : have_ws && small_quad_split(p, pooled, nullptr) ? 0.78f : any;
+        return p.Cg < 256;
+    case V_TAP: {
+        const bool split = have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768;
+        *pairs_to = p.Cg >= 512 ? (split ? 0.8f : any) : p.Cg >= 256 && !split ? 0.92f : none;
+        return p.Cg < 256 || split;
+    }
+    default:
+        *pairs_to = p.Cg >= 512 ? any : none;
+        return false;
     }
 }
 

@@ -91,7 +91,7 @@ double piece_margin(const Problem& p, bool pooled);
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                  hipStream_t stream);
 // whether such a plan must keep the small products apart, so that no result is further from 64-bit sums than the other kernels'
-bool piece_close(const Problem& p, bool pooled, double* family_us);
+bool piece_close(const Problem& p, bool pooled, double* family_us, float* pairs_to);
 // the piece plan by name: "geometry/form of the filters", and "/whole tiles+split tiles x slices" where it has split ones
 bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size);
 

@@ -1657,10 +1657,10 @@ bool apart_of(const Choice& c) { return c.cand->apart(c.plan.src); }
 // same at 40 - 90 % zeros within a tenth): pairs 1.2 at 64 and 128 channels, 1.35 at 256, 1.5 at 512; kept 1.1 - 1.2 at any number.  Against three pieces in
 // one chain, 1.7 - 2.0, either is closer; against sums apart, 0.65 at 64 channels to 1.17 at 512 (less where tiles are split), kept ones from
 // 512 on while most tiles are whole; against the taps kernel kept ones there too, where a reported ratio is 50 % at most (512 / 640 channels @14x14, taps against
-// kept, 1.20 / 1.28 against 1.16 / 1.21 at 50 % zeros, 1.02 / 1.09 against 1.12 / 1.20 at 70, 0.79 / 0.82 against 1.02 / 1.10 at 90); against the other families where piece_close has it that three pieces in one chain are no further off
-// than they, and from 512 channels on (vector kernel, split, 1.6 / 1.3 / 1.05 at 50 / 70 / 85 % zeros).
+// kept, 1.20 / 1.28 against 1.16 / 1.21 at 50 % zeros, 1.02 / 1.09 against 1.12 / 1.20 at 70, 0.79 / 0.82 against 1.02 / 1.10 at 90); against the other
+// families up to the zero ratio that piece_close gives, kept ones.
 // A call without a zero ratio whose family is the vector kernel's stays as it was (see piece_first).
-int pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double other, bool close)
+int pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double other, float pairs_to)
 {
     if (other == 0.0) return -1;
     if (three && (other < 0.0 || three->cost < other)) {
@@ -1668,7 +1668,7 @@ int pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double
         const bool level = p.Cg >= 512 && three->cfg.whole >= three->ntail;
         return level && (!taps || (p.zhint >= 0.0f && p.zhint <= 0.5f)) ? SRC_PAIRS_KEPT : -1;
     }
-    return !close || p.Cg >= 512 ? SRC_PAIRS_KEPT : -1;
+    return pairs_to > 1.0f || (p.zhint >= 0.0f && p.zhint <= pairs_to) ? SRC_PAIRS_KEPT : -1;
 }
 
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
@@ -1695,7 +1695,8 @@ const Choice& choose_plan(const Problem& p, bool pooled)
     const PlanPin* tuned = current_pin();
     const char* pin = pinned_geom("SCONV_PIECE_GEOM");
     double other = -1.0;
-    const bool close = piece_close(p, pooled, &other) && !pin;
+    float pairs_to = -1.0f;
+    const bool close = piece_close(p, pooled, &other, &pairs_to) && !pin;
     if (pin) other = -1.0;
     auto walk = [&](Choice& out) {
         out = Choice();
@@ -1705,14 +1706,14 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             Plan pl = c.plan(p, pooled, close);
             if (pl.cost < 0.0) continue;
             // (the taps kernel, which has no pairs and is the closest: where it is level too)
-            if (!out.cand || pl.cost < out.plan.cost * (out.cand->pairs && !c.pairs ? 1.01 : 1.0)) {
+            if (!out.cand || pl.cost < out.plan.cost * (out.cand->pairs && !c.pairs ? 1.05 : 1.0)) {
                 out.cand = &c;
                 out.plan = pl;
             }
         }
         // the same with pairs, where it is no further from 64-bit sums
         const bool pinned_pairs = env_value("SCONV_PIECE_SRC") && atoi(env_value("SCONV_PIECE_SRC")) >= SRC_PAIRS;
-        const int form = pinned_pairs ? atoi(env_value("SCONV_PIECE_SRC")) : pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), out.cand && !out.cand->pairs, other, close);
+        const int form = pinned_pairs ? atoi(env_value("SCONV_PIECE_SRC")) : pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), out.cand && !out.cand->pairs, other, pairs_to);
         if (form < 0) return;
         for (const Candidate& c : kCandidates) {
             if (!c.pairs || (pin && strcmp(pin, c.name) != 0)) continue;
