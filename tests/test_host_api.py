@@ -216,6 +216,15 @@ def test_pairs_stand_against_a_family_as_far_as_they_are_no_further_off(shp, poo
     assert ("-f16" in name) == pairs, name
 
 
+@pytest.mark.parametrize("shp,groups,z,prepared,plan", [
+    ((12, 96, 56, 56, 96, 3, 3, 1, 1), 1, None, False, "piece/model:s128x64/pieces"), ((13, 320, 24, 24, 128, 3, 3, 1, 1), 1, None, False, "piece/model:s128x64/pieces"),
+    ((3, 466, 19, 49, 352, 3, 3, 1, 1), 2, 0.91, False, "piece/model:t3x64/stored"), ((1, 320, 56, 56, 320, 3, 3, 1, 1), 1, None, False, "piece/model:t3x64/stored")])
+def test_plans_that_the_model_puts_level(shp, groups, z, prepared, plan):
+    """Geometries level with the taps kernel: it, where they are one chain; they, where their small products are apart."""
+    d = sconv.make_desc(*shp, groups=groups, relu=True, zero_ratio=z, prepared=prepared)
+    assert sconv.sconv_launch_name(d, False, sconv.sconv_workspace_size(d)).startswith(plan)
+
+
 @pytest.mark.parametrize("pinned_first", [True, False])
 def test_a_pinned_variant_leaves_other_calls_plans_alone(monkeypatch, pinned_first):
     """With the piece kernel pinned a layer takes pairs that it does not take on its own; either plan is kept for its own calls only."""
