@@ -396,12 +396,13 @@ static double family_time(const Problem& p, bool pooled, Variant v)
     // filters, took 277 / 131 us at 60 / 90 % zeros on the vector kernel against 91, 96 -> 416 @44x44 at batch 5 123 / 71 against 52, 576 -> 448 in
     // 4 groups @57x57 at batch 5 205 / 129 against 120.  Of 180 random layers at 60, 90 and 95 % zeros 40 move, 1.6 / 1.2 / 1.1 times as fast.  Not
     // below 32 channels a group (64 -> 576 in 4 groups @38x38, pooled: 21.6 against 23.2 at 90 %; 48 in launches so short that their channels would have to be
-    // split: 128 -> 192 in 4 groups @33x33 at batch 1, prepared, 12.1 against 15.7, and 384 -> 128 in 8 groups 20.5 against 15.1), not without a workspace and a ratio (448 -> 92 in 4
+    // split: 128 -> 192 in 4 groups @33x33 at batch 1, prepared, 12.1 against 15.7, and 384 -> 128 in 8 groups 20.5 against 15.1; not where the empty part makes them long: 32 -> 16 @29x29 at
+    // batch 22 29.9 against 16.2, 32 -> 16 @34x34 at batch 15 23.9 against 15.3), not without a workspace and a ratio (448 -> 92 in 4
     // groups @41x41 57.6 against 66.4 at 95 %) nor in the shortest launches without a ratio (128 -> 128 in 4 groups @14x14 at batch 7, prepared, 13.5
     // against 16.1 at 78 %; with one, 192 -> 168 in 4 groups @19x19 at batch 1 18.2 against 13.7 at 46 %), on quad3x3 from half a block on (64 -> 192 in 4 groups @57x57 54 against 58).
     const double spare_k = (double)((p.Kg + 63) / 64 * 64) / p.Kg;
     const int cols = pooled ? p.PW * 2 : p.OW;
-    const bool fits_hold = p.Cg < (gf < 0.2 ? 48 : 32) || (p.zhint < 0.0f && (gf < 0.12 || (!can_split && !p.wprep)));
+    const bool fits_hold = p.Cg < (gf < 0.2 && gf * spare_k < 0.3 ? 48 : 32) || (p.zhint < 0.0f && (gf < 0.12 || (!can_split && !p.wprep)));
     const double spare = fits_hold ? 1.0 : spare_k * fmin(1.15, (double)((cols + 6) / 7 * 7) / cols);
     switch (v) {
     case V_TAP: {
@@ -474,10 +475,8 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     if (v == V_PW) c += 0.15e-6 * 4.0 * p.N * p.K * (double)p.OH * p.OW;
     const double other = family_time(p, pooled, v);
     if (c < other) {
-        // One chunk: a tile's loads and stores are more than its model counts.  10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the
-        // piece kernel; 16 -> 64 @56x56 at batch 32, prepared, 28.7 on quad3x3, 31.2; 16 -> 32 @112x112 at batch 64 150 and 170, what its blocks leave empty counted.
-        if (p.Cg > 16 || (v != V_GEN && v != V_QUAD)) return true;
-        return c * piece_margin(p, pooled) < (v == V_GEN ? other : 8.0 + dense_gflop(p, pooled) * (p.zhint >= 0.92f ? 5.0 : 8.3));
+        // (one chunk: what a tile stores is more than its model counts; 10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the piece kernel)
+        return v != V_GEN || p.Cg > 16 || c * piece_margin(p, pooled) < other;
     }
     if (v != V_TAP || p.zhint >= 0.0f) return false;
     // Without a ratio, on tiles that are full.  A plan with sums apart has to be ahead by 4 % there, on prepared filters by 2 %: what that leaves to the
