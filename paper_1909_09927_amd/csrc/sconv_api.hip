@@ -436,7 +436,9 @@ static double family_time(const Problem& p, bool pooled, Variant v)
 // negative: none).  Relative error at 70 / 80 / 88 / 95 % zeros, 1e-7, against 1.2 / 1.15 / 1.1 / 1.0 of pairs at any number of channels: gen and
 // wide3x3 1.8 / 1.5 / 1.2 / 0.86 at 144 channels, 2.3 / 1.9 / 1.5 / 1.05 at 256; quad3x3 at 256 channels 1.06 at 95 %; the vector kernel 1.09 at 90 and
 // 0.86 at 95 there, 1.13 at 95 and 512.  Kernels that split a tile's channels are closer: gen in launches of fewer than 128 tiles 1.1 / 0.95 / 0.84 / 0.72 at 144
-// channels, 1.3 / 1.13 / 0.97 / 0.78 at 256; quad3x3 at 256 channels 1.15 / 0.97 / 0.79 from 80 % on; the vector kernel at 512 1.0 at 88 %.
+// channels, 1.3 / 1.13 / 0.97 / 0.78 at 256; quad3x3 at 256 channels 1.15 / 0.97 / 0.79 from 80 % on; the vector kernel at 512 1.0 at 88 %
+// with tiles in four slices, not in two or none (704 -> 512 @35x62 1.49 against 1.09 at 85 %, 95 us against 72; 608 -> 512 @13x13 at batch 17, prepared, 1.96
+// against 1.11 at 83 %, 123 against 79; 688 -> 564 @31x31 at batch 3, pooled, 1.56 against 0.86 at 86 %, 185 against 91).
 bool piece_close(const Problem& p, bool pooled, double* family_us, float* pairs_to)
 {
     const bool have_ws = split_scratch_possible(nullptr);
@@ -457,7 +459,10 @@ bool piece_close(const Problem& p, bool pooled, double* family_us, float* pairs_
         return p.Cg < 256;
     case V_TAP: {
         const bool split = have_ws && (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 127) / 128) * p.N * p.G <= 768;
-        *pairs_to = p.Cg >= 512 ? (split ? 0.8f : any) : p.Cg >= 256 && !split ? 0.92f : none;
+        // (four slices of a tile's channels and more; two; none)
+        const long long tiles = (long long)((p.OH + 4) / 5) * ((p.OW + 6) / 7) * ((p.Kg + 63) / 64) * p.N * p.G;
+        const float slices_to = !have_ws || tiles > 768 ? any : tiles < 128 || (tiles <= 384 && !pooled && !p.wprep) ? 0.8f : 0.92f;
+        *pairs_to = p.Cg >= 512 ? slices_to : p.Cg >= 256 && !split ? 0.92f : none;
         return p.Cg < 256 || split;
     }
     default:
