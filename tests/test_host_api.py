@@ -209,6 +209,9 @@ def test_short_calls_without_a_ratio_that_the_piece_kernel_loses(shp, groups, po
     ((8, 512, 14, 14, 512, 3, 3, 1, 1), None, 0.88, False), ((16, 256, 56, 56, 256, 3, 3, 1, 1), None, 0.9, True),
     ((2, 624, 37, 37, 480, 3, 3, 1, 1), None, 0.87, True), ((3, 688, 31, 31, 564, 3, 3, 1, 1), (2, 2, 2), 0.86, True),
     ((1, 704, 35, 62, 512, 3, 3, 1, 1), None, 0.85, True), ((4, 752, 20, 29, 128, 3, 3, 1, 1), None, 0.89, False),
+    ((19, 208, 11, 11, 592, 3, 3, 1, 1), None, None, True), ((18, 160, 25, 7, 512, 3, 3, 1, 1), None, None, False),
+    ((27, 176, 23, 23, 110, 3, 3, 1, 0), None, 0.89, True), ((3, 477, 37, 37, 80, 3, 3, 1, 1), (2, 2, 2), 0.86, True),
+    ((3, 318, 22, 19, 176, 3, 3, 1, 1), (2, 2, 2), None, False), ((3, 688, 17, 45, 269, 3, 3, 1, 1), None, None, True),
     ((13, 144, 29, 12, 320, 3, 3, 1, 1), None, None, False)])
 def test_pairs_stand_against_a_family_as_far_as_they_are_no_further_off(shp, pool, z, pairs):
     """Split launches and few channels: the family's kernel is closer to 64-bit sums on sparse maps (quad3x3, split, 0.79e-7 at 95 % zeros against
