@@ -1706,8 +1706,9 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             Plan pl = c.plan(p, pooled, close);
             if (pl.cost < 0.0) continue;
             // The taps kernel, which has no pairs and is the closest, also where it is level with a plan in one chain (466 -> 352 in 2 groups @19x49 at
-            // batch 3 modelled 49.7 and 48.9 us, 0.70e-7 and 1.7e-7), and then at the other's time against other families.
-            if (!out.cand || pl.cost < out.plan.cost * (!c.pairs && !apart_of(out) ? 1.02 : 1.0)) {
+            // batch 3 modelled 49.7 and 48.9 us, 0.70e-7 and 1.7e-7), and then at the other's time against other families.  Not over filters as stored: their
+            // one chain ran such layers before (368 -> 368 in 2 groups @31x31 at batch 9 152 us, the taps kernel 209; 388 -> 368 @28x28 at batch 11 162 and 224).
+            if (!out.cand || pl.cost < out.plan.cost * (!c.pairs && !apart_of(out) && out.plan.src != SRC_RAW ? 1.02 : 1.0)) {
                 const double least = out.cand && out.plan.cost < pl.cost ? out.plan.cost : pl.cost;
                 out.cand = &c;
                 out.plan = pl;

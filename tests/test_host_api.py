@@ -235,6 +235,13 @@ def test_plans_that_the_model_puts_level(shp, groups, z, prepared, plan):
     assert sconv.sconv_launch_name(d, False, sconv.sconv_workspace_size(d)).startswith(plan)
 
 
+@pytest.mark.parametrize("shp,groups,z", [((9, 736, 14, 31, 736, 3, 3, 1, 1), 2, 0.43), ((11, 388, 28, 28, 368, 3, 3, 1, 0), 1, None), ((7, 160, 30, 30, 544, 3, 3, 1, 0), 1, None)])
+def test_filters_as_stored_stay_in_one_chain_where_the_taps_kernel_is_level(shp, groups, z):
+    """Without a workspace (152, 162 and 77 us; on the taps kernel 209, 224 and 94)."""
+    d = sconv.make_desc(*shp, groups=groups, relu=True, zero_ratio=z)
+    assert sconv.sconv_launch_name(d, False, 0).startswith("piece/model:a128x128/stored")
+
+
 @pytest.mark.parametrize("pinned_first", [True, False])
 def test_a_pinned_variant_leaves_other_calls_plans_alone(monkeypatch, pinned_first):
     """With the piece kernel pinned a layer takes pairs that it does not take on its own; either plan is kept for its own calls only."""
