@@ -435,7 +435,7 @@ static double family_time(const Problem& p, bool pooled, Variant v)
 // *pairs_to: the zero ratio up to which fp16 pairs are no further from 64-bit sums than that kernel (above 1: also where the ratio is not known;
 // negative: none).  Relative error at 70 / 80 / 88 / 95 % zeros, 1e-7, against 1.2 / 1.15 / 1.1 / 1.0 of pairs at any number of channels: gen and
 // wide3x3 1.8 / 1.5 / 1.2 / 0.86 at 144 channels, 2.3 / 1.9 / 1.5 / 1.05 at 256, and at 95 % 0.93 at 184, 0.95 at 192, 0.93 at 208 (pairs 0.92, 0.92, 0.90; pooled
-// pairs 0.72 - 0.83 at any number, those kernels 0.74 - 0.89; 208 -> 592 in 1 group @11x11 at batch 19 78 us against 46 at 67 %); quad3x3 at 256 channels 1.06 at 95 %; the vector kernel 1.09 at 90 and
+// pairs 0.72 - 0.83 at any number, those kernels 0.72 - 0.79 up to 168 and 0.79 - 0.89 from 176 on; 208 -> 592 in 1 group @11x11 at batch 19 78 us against 46 at 67 %); quad3x3 at 256 channels 1.06 at 95 %; the vector kernel 1.09 at 90 and
 // 0.86 at 95 there, 1.13 at 95 and 512.  Kernels that split a tile's channels are closer: gen in launches of fewer than 128 tiles 1.1 / 0.95 / 0.84 / 0.72 at 144
 // channels, 1.3 / 1.13 / 0.97 / 0.78 at 256, 1.02 (pairs 0.95) at 477 and 86 %, 0.86 (0.85) at 746 and 95 %; quad3x3 at 256 channels 1.15 / 0.97 / 0.79 from 80 % on, at 688 as pairs at 95 % (1.0) and 1.25 (1.06) at 90; the vector kernel at 512 1.0 at 88 %
 // with tiles in four slices, not in two or none (704 -> 512 @35x62 1.49 against 1.09 at 85 %, 95 us against 72; 608 -> 512 @13x13 at batch 17, prepared, 1.96
@@ -453,7 +453,7 @@ bool piece_close(const Problem& p, bool pooled, double* family_us, float* pairs_
     case V_GEN: {
         const bool split = v == V_GEN && have_ws && (windows + 63) / 64 * ((p.Kg + 63) / 64) * p.G < 128;
         if (split) *pairs_to = p.Cg < 256 ? none : p.Cg < 448 ? 0.75f : p.Cg < 704 ? 0.86f : any;
-        else *pairs_to = p.Cg < 128 ? none : p.Cg < 184 ? 0.92f : any;
+        else *pairs_to = p.Cg < 128 ? none : p.Cg < (pooled ? 176 : 184) ? 0.92f : any;
         return p.Cg < 128;
     }
     case V_QUAD:

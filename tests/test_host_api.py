@@ -211,6 +211,7 @@ def test_short_calls_without_a_ratio_that_the_piece_kernel_loses(shp, groups, po
     ((1, 704, 35, 62, 512, 3, 3, 1, 1), None, 0.85, True), ((4, 752, 20, 29, 128, 3, 3, 1, 1), None, 0.89, False),
     ((19, 208, 11, 11, 592, 3, 3, 1, 1), None, None, True), ((18, 160, 25, 7, 512, 3, 3, 1, 1), None, None, False),
     ((27, 176, 23, 23, 110, 3, 3, 1, 0), None, 0.89, True), ((3, 477, 37, 37, 80, 3, 3, 1, 1), (2, 2, 2), 0.86, True),
+    ((10, 176, 41, 41, 64, 3, 3, 1, 0), (2, 2, 2), None, True), ((6, 144, 46, 56, 16, 3, 3, 1, 0), (2, 2, 2), None, False),
     ((3, 318, 22, 19, 176, 3, 3, 1, 1), (2, 2, 2), None, False), ((3, 688, 17, 45, 269, 3, 3, 1, 1), None, None, True),
     ((13, 144, 29, 12, 320, 3, 3, 1, 1), None, None, False)])
 def test_pairs_stand_against_a_family_as_far_as_they_are_no_further_off(shp, pool, z, pairs):
