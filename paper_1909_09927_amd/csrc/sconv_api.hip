@@ -483,7 +483,10 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
     const double other = family_time(p, pooled, v);
     if (c < other) {
         // (one chunk: what a tile stores is more than its model counts; 10 -> 464 @58x58 at batch 11, modelled level, 53.1 on gen, 73.7 on the piece kernel)
-        return v != V_GEN || p.Cg > 16 || c * piece_margin(p, pooled) < other;
+        // (not where filters as stored, whose model holds, are ahead: 15 -> 74 @57x57 at batch 21 30.8 us and 0.56e-7, on gen 41 and 1.5e-7)
+        if (v != V_GEN || p.Cg > 16 || c * piece_margin(p, pooled) < other) return true;
+        const double stored = piece_stored_cost(p, pooled);
+        return stored >= 0.0 && stored < other;
     }
     if (v != V_TAP || p.zhint >= 0.0f) return false;
     // Without a ratio, on tiles that are full.  A plan with sums apart has to be ahead by 4 % there, on prepared filters by 2 %: what that leaves to the

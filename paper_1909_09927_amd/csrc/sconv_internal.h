@@ -88,6 +88,8 @@ bool piece_supported(const Problem& p, bool pooled);
 double piece_cost(const Problem& p, bool pooled);
 // by how much such a plan has to be ahead of the vector kernel where the zero ratio is not known
 double piece_margin(const Problem& p, bool pooled);
+// modelled microseconds of the cheapest plan on filters as stored, negative where there is none
+double piece_stored_cost(const Problem& p, bool pooled);
 int launch_piece(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                  hipStream_t stream);
 // whether such a plan must keep the small products apart, so that no result is further from 64-bit sums than the other kernels'

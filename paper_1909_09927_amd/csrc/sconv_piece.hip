@@ -1231,6 +1231,7 @@ __global__ __launch_bounds__(256 * FW) void piece_pairs_kernel(Problem p, int kb
 
 struct Plan {
     double cost = -1.0;   // modelled microseconds; negative = not applicable
+    double stored = -1.0; // those of the cheapest split on filters as stored
     PieceCfg cfg;
     size_t lds_bytes = 0, piece_bytes = 0;
     int src = SRC_RAW, ntail = 0;
@@ -1368,6 +1369,7 @@ void consider(Plan& pl, long long tiles, long long round, int NW, double tc, dou
             const double resident = (double)(whole + tail * s) / 256.0;
             double cost = fixed + load * (resident * NW <= (lone > 1.0 ? 6.0 : 8.0) ? lone : 1.0);
             if (tail) cost += 3.0 + 2.0 * (double)(tail * s) * tile_bytes / 6e6;
+            if (src == SRC_RAW && (pl.stored < 0.0 || cost < pl.stored)) pl.stored = cost;
             if (pl.cost >= 0.0 && cost >= pl.cost) continue;
             pl.cost = cost;
             pl.src = src;
@@ -1647,6 +1649,7 @@ namespace {
 struct Choice {
     const Candidate* cand = nullptr;
     Plan plan;
+    double stored = -1.0;   // modelled microseconds on filters as stored, negative: no such plan
 };
 
 // Whether a plan keeps the small products' sums apart.
@@ -1705,6 +1708,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             if (pin && strcmp(pin, c.name) != 0) continue;
             Plan pl = c.plan(p, pooled, close);
             if (pl.cost < 0.0) continue;
+            if (pl.stored >= 0.0 && (out.stored < 0.0 || pl.stored < out.stored)) out.stored = pl.stored;
             // The taps kernel, which has no pairs and is the closest, also where it is level with a plan in one chain (466 -> 352 in 2 groups @19x49 at
             // batch 3 modelled 49.7 and 48.9 us, 0.70e-7 and 1.7e-7), and then at the other's time against other families.  Not over filters as stored: their
             // one chain ran such layers before (368 -> 368 in 2 groups @31x31 at batch 9 152 us, the taps kernel 209; 388 -> 368 @28x28 at batch 11 162 and 224).
@@ -1769,6 +1773,8 @@ double piece_margin(const Problem& p, bool pooled)
     const Choice& c = choose_plan(p, pooled);
     return !c.cand || !apart_of(c) || c.plan.src == SRC_RAW ? 1.0 : c.plan.src == SRC_FP32 ? 1.02 : 1.04;
 }
+
+double piece_stored_cost(const Problem& p, bool pooled) { return choose_plan(p, pooled).stored; }
 
 bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
 {

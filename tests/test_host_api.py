@@ -243,6 +243,13 @@ def test_filters_as_stored_stay_in_one_chain_where_the_taps_kernel_is_level(shp,
     assert sconv.sconv_launch_name(d, False, 0).startswith("piece/model:a128x128/stored")
 
 
+@pytest.mark.parametrize("shp,z", [((21, 15, 57, 57, 74, 3, 3, 1, 0), None), ((24, 11, 19, 19, 736, 3, 3, 1, 1), 0.68), ((12, 11, 49, 49, 224, 3, 3, 1, 1), None)])
+def test_one_chunk_stays_on_the_piece_kernel_where_filters_as_stored_are_ahead(shp, z):
+    """31, 32 and 32 us at 0.56e-7, 0.41e-7 and 0.36e-7 from 64-bit sums; on gen 41, 39 and 38 at 1.5, 1.0 and 0.8."""
+    d = sconv.make_desc(*shp, groups=1, relu=True, zero_ratio=z)
+    assert sconv.sconv_launch_name(d, False, sconv.sconv_workspace_size(d)).startswith("piece/")
+
+
 @pytest.mark.parametrize("pinned_first", [True, False])
 def test_a_pinned_variant_leaves_other_calls_plans_alone(monkeypatch, pinned_first):
     """With the piece kernel pinned a layer takes pairs that it does not take on its own; either plan is kept for its own calls only."""
