@@ -46,8 +46,8 @@ MFMA_VARIANTS = ("quad3x3", "quad1x1", "wide3x3", "gen", "piece")
 
 def piece_peak_tf(plan: str) -> float:
     """Piece kernel: the 16-bit matrix pipe's dense peak (published) over the products an fp32 one takes there - six of bf16 pieces, three of
-    fp16 pairs.  A tuned plan names its geometry only: the two that have the form with pairs are priced as if they ran it."""
-    pairs = "-f16" in plan or plan.startswith(("piece/a128x64/", "piece/u128x64/"))
+    fp16 pairs.  A tuned plan names its geometry only: those that have the form with pairs are priced as if they ran it."""
+    pairs = "-f16" in plan or plan.startswith(tuple(f"piece/{g}/" for g in ("a128x64", "u128x64", "a128x64x2", "u128x64x2")))
     return 2500.0 / (3 if pairs else 6)
 
 

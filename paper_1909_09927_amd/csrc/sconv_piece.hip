@@ -68,6 +68,26 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
+// Division by a number that is known before the launch, of numbers below 2^30: with 2^l >= d (l >= 2) and m = ceil(2^(30+l) / d), m d exceeds 2^(30+l) by
+// less than 2^l, so n m / 2^(30+l) exceeds n / d by less than 1 / d.  A wavefront issues an instruction every eight clocks, and a division by a
+// register's value is some 35 of them: with the dozen that place a workgroup's tile and the dozen that place its results, and results stored one by one
+// behind their conditions and biases (18 000 clocks, now 5 000), a launch of one chunk took 17 us, now 10.
+struct FastDiv {
+    unsigned m, s;       // (m == 0: by one)
+    void by(int d)
+    {
+        unsigned l = 2;
+        while ((1 << l) < d) ++l;
+        s = l - 2;
+        m = d == 1 ? 0 : (unsigned)(((1ull << (30 + l)) + d - 1) / d);
+    }
+    __host__ __device__ __forceinline__ int of(int n) const
+    {
+        const unsigned q = (unsigned)(((unsigned long long)(unsigned)n * m) >> 32) >> s;
+        return m ? (int)q : n;
+    }
+};
+
 struct PieceCfg {
     int nrun;        // window rows of one column strip: N*OH*TW, or N*PH*TW*4 in PECR order
     int ntiles;      // tiles of BN window rows per strip
@@ -75,18 +95,35 @@ struct PieceCfg {
     int kblocks;     // filter blocks of BM filters per group
     int kb32;        // 32-filter blocks per group in the prepared layout
     int nch;         // staged chunks of 16*CS channels
-    int whole;       // tiles run by one workgroup; the others are split along the channels over nss workgroups
+    int whole;       // tiles run by one workgroup; the others, `tail` of them, are split along the channels over nss workgroups each
     int nss;
+    int tail;
     int T, S;        // taps, kernel width
     int px, cgb;     // staged positions, bytes of one 8-channel group
     int flat;        // 1x1 / stride 1: a map is one row of H*W positions
+    FastDiv by_kblocks, by_strips, by_ntiles, by_TW, by_rows, by_pitch, by_HP, by_quads;   // rows of (pooled) results of an image; quads of a tile's row
+    void prepare(const Problem& p, bool pooled, int BN)
+    {
+        by_quads.by(BN / 4);
+        by_kblocks.by(kblocks);
+        by_strips.by(strips);
+        by_ntiles.by(ntiles);
+        by_TW.by(TW);
+        by_rows.by(pooled ? p.PH : flat ? 1 : p.OH);
+        by_pitch.by((pooled ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + p.S);
+        by_HP.by((flat ? 1 : p.H) + p.pad);
+    }
 };
 
-// Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums); the same
-// with the running sums' rounding errors kept
-enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3, SRC_PAIRS_KEPT = 4 };
+// Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums)
+enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3 };
 
 constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
+
+template <int V>
+struct Const {
+    static constexpr int value = V;
+};
 
 constexpr int kUnpaired = -0x40000000;   // in the place of a filter's exponent: no pairs of it
 
@@ -138,7 +175,7 @@ struct PGeom {
     // launches of the benchmark layers; s128x64 on filters as stored: 512 @28x28 at batch 8 218 us)
     static constexpr double tc(int src, int taps)
     {
-        if (src >= SRC_PAIRS) return src == SRC_PAIRS ? 1.72 : 1.82;
+        if (src == SRC_PAIRS) return 1.57;
         const double wide = XU > 3 ? 0.12 : 0.0;   // (four staging units: 512 @28x28 at batch 8 158 us against 151 with three or two)
         return (MT * NT * NW == 16 ? (src == SRC_PIECES ? 4.7 : src == SRC_FP32 ? 4.9 : 5.3)
                                    : (src == SRC_PIECES ? 2.48 + wide : src == SRC_FP32 ? 2.7 + wide : APART_ && T_ == 9 ? 3.45 : 3.7) * (MT * NT * NW) / 8.0) *
@@ -152,9 +189,11 @@ struct PGeom {
     static constexpr int SPARE = 1280;          // bytes of a chunk's LDS that lanes without a position write to (64 * 16 + 32)
     static constexpr int VW = T == 9 ? 3 : 1;    // taps fetched at once from filters as stored
     // sums of their own for the five small products (see the top)
-    static constexpr bool apart(int src) { return APART_ || (NT == 2 && (src == SRC_FP32 || src >= SRC_PAIRS)); }
-    static constexpr bool PAIRS = T == 9 && MT == 1 && NT == 2 && WM == 4 && XU == 2 && APART_ == POOL;   // has the form with pairs (a128x64, u128x64)
-    static constexpr int PAIR_BUF = 2 * 2 * PXMAX * 16 + 256;   // LDS of one chunk as pairs, and the ranges of the wavefronts
+    static constexpr bool apart(int src) { return APART_ || (NT == 2 && (src == SRC_FP32 || src == SRC_PAIRS)); }
+    // two tiles of 128 filters x 64 windows side by side, eight wavefronts, one workgroup a compute unit: see pair_sums
+    static constexpr bool BLOCK = T == 9 && NW == 8;
+    static constexpr bool PAIRS = T == 9 && MT == 1 && NT == 2 && WM == 4 && XU * WN == 2 && APART_ == POOL;   // has the form with pairs (a128x64, u128x64, the blocks)
+    static constexpr int PAIR_BUF = 2 * 2 * PXMAX * 16 + 256;   // LDS of one chunk as pairs, and a third of flags, ranges (from 64) and exponents (the last 512 bytes)
 };
 
 // Two fp32 values times up as pairs of fp16 values: v up = p0 + 2^-12 p1, p0 of 11 bits, p1 of 11 and a sign - all but the last bit of every
@@ -219,84 +258,108 @@ struct PairLimits {
 __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast(float, (unsigned)(e + 127) << 23); }
 
 // The sums of one tile from fp16 pairs: v = p0 + 2^-12 p1, three products p0q0, p0q1, p1q0 (the fourth is 2^-22 of the product at most) instead of
-// six, two thirds of the LDS and filter traffic.  Bound by the chip's power like the six products (1.9 - 2.1 GHz; a third LDS buffer with one
-// barrier a chunk, loads two taps ahead, a second set of map registers and a third fewer vector instructions all measured within 3 %), of
-// which three take two thirds of the time: 256 @56x56 at batch 8 149 -> 100 us, 512 @28x28 at batch 8 with prepared filters 159 -> 104, at
-// batch 62 937 -> 659 (1.04 PFLOP/s of fp16 products; the pipe alone runs at 1.9 on such data).
+// six, two thirds of the LDS and filter traffic.  Bound by the chip's power where every unit has work (1.6 - 1.9 GHz), otherwise by what a wavefront
+// issues between two matrix instructions: one instruction every eight clocks, so two wavefronts a SIMD have about seven each for the 32 clocks of one.
+// Hence six a product instead of nine: the compensation carried in the sums (below), an element cut in three instructions with no wait between them,
+// a flag that is written only when a scale has to move, one wait for the loads of a unit, two chunks a turn of the loop (no moves at its end).  And what
+// a product needs is asked for two taps ahead (p0) and one (p1), across the chunk's end too: a chunk has one barrier, six taps before the next one's
+// first staging, and three buffers, so that nobody waits in it for what was just asked for.  512 @28x28 at batch 62: 688 -> 618 us.
+// Blocks (PGeom::BLOCK, 128 filters x 128 windows, eight wavefronts) read the filters once for two wavefronts - on different SIMDs, side by side: the
+// second finds them in the L1 (L2 reads 61 -> 39 million; on the same SIMD they drift apart and it does not) - and stage a quarter less of the map:
+// 568 us, 1.21 PFLOP/s of fp16 products at 1.9 GHz, 51 clocks an instruction; without filter loads, map loads, bank conflicts and folding 46.
+// Measured and dropped: 64 x 64 a wavefront, one to a SIMD (667 us: half of what fits a matrix instruction's time can be issued there), wavefront priorities by progress (level).
 // The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
 // stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter such a
 // weight - about one of 4 x 10^7 normally distributed values -, the tile is summed from three pieces from there on: returned is the first chunk that
 // is not in the sums, `sigma` is their scale.  So every single product is within 2^-21 of its value, whatever the others in its window.  No map
-// and no filters take much longer than on pieces alone: 256 @56x56 at batch 32 347 us (pieces 493), with 64 elements of the map 2^-30 of its
-// largest 366, with every chunk or every block of filters out of range 535 and 517.
-// The sums of a chunk start from zero (p0q0); the small products' run through, 2^12 times their size, and with KEPT take the rounding error of
-// every addition to the running sums along (4 % of the time; error at 512 channels 1.5e-7 -> 1.07e-7).
-// Filters: a ring of nine fragments, eight taps ahead, for which half the registers of three pieces would not do.
-template <class G, bool KEPT, class Fetch>
+// and no filters take much longer than on pieces alone.
+// The sums of nine taps (p0q0) are added to the running ones once a chunk, those of the second block of windows four taps after the first's; the rounding error of
+// that addition stays where the next nine taps start (error at 512 channels 1.5e-7 without, 1.07e-7 with it).  The small products' sums run through, 2^12 times their size.
+// Filters: a ring of nine fragments, eight taps ahead (six with two staging units, for their registers).
+template <class G, class Fetch, class Exponents, class Paired>
 __device__ __forceinline__ int pair_sums(const Problem& p, const int (&pos)[G::NT], int pitch, int chb, int che, int wave, int lane,
-                                         unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, v16f (&acc)[1][G::NT], int& sigma)
+                                         unsigned char* lds, Fetch fetch_x, __amdgpu_buffer_rsrc_t wres, Exponents fetch_exponents, Paired paired,
+                                         v16f (&acc)[1][G::NT], int& sigma)
 {
-    constexpr int NT = G::NT, XU = G::XU, NW = G::NW, D = 8;
-    constexpr int PLANE = G::PXMAX * 16, CGB = 2 * PLANE, BUF = G::PAIR_BUF;
-    static_assert(G::T == 9 && G::MT == 1 && NT == 2 && G::CS == 1, "3x3, one block of filters by two of windows");
+    constexpr int NT = G::NT, XU = G::XU, NW = G::NW, D = XU == 2 ? 6 : 8;   // (taps of filters ahead: the second staging unit's registers)
+    constexpr int PLANE = G::PXMAX * 16, CGB = 2 * PLANE, BUF = 2 * CGB;
+    static_assert(G::T == 9 && G::MT == 1 && NT == 2 && XU * NW == 8 && G::CS == 1, "3x3, one block of filters by two of windows");
     const int half = lane >> 5;
     int lb[NT], xst[XU];
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb) lb[nb] = pos[nb] * 16 + half * CGB;
 #pragma unroll
-    for (int u = 0; u < XU; ++u) xst[u] = (u * NW + wave) % 2 * CGB + ((u * NW + wave) / 2 * 64 + lane) * 16;
+    for (int u = 0; u < XU; ++u) xst[u] = wave % 2 * CGB + ((u * NW + wave) / 2 * 64 + lane) * 16;   // (all units of a wavefront are of one channel group)
 
     float xr[XU][8];
     u4 ap[9][2];
-    auto fetch_a = [&](int ch, int t) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            ap[t][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16 + q * 1024, (ch * 9 + t) * 2048, 0));
+    auto fetch_a = [&](int ch, int t, int q) {
+        ap[t][q] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16 + q * 1024, (ch * 9 + t) * 2048, 0));
     };
-    // The scale.  In the rule every wavefront finds its share of the next chunk within the limits of the scale there is, and says so (one word
-    // each).  Where one does not, all exchange their ranges: a scale that holds the chunk, or none (false).
+    // The scale.  In the rule every wavefront finds its share of the next chunk within the limits of the scale there is.  Where one does not, it
+    // says so (a word for every other chunk), and all exchange their ranges: a scale that holds the chunk, or none (false).
     PairLimits lim(0);
     Range rg;
+    auto flag = [&](int parity) -> unsigned& { return *reinterpret_cast<unsigned*>(lds + 3 * BUF + parity * 4); };
     auto say = [&](int parity) {
-        const bool out = __any(!lim.hold(__builtin_bit_cast(unsigned, rg.hi), rg.lo));
+        if (__ballot(__builtin_bit_cast(unsigned, rg.hi) >= lim.hi) | __ballot(rg.lo < lim.lo)) flag(parity) = 1;
         rg = Range();
-        *reinterpret_cast<unsigned*>(lds + parity * BUF + 2 * CGB + wave * 4) = out;
     };
-    auto new_scale = [&](int parity, int& to) {
+    auto new_scale = [&](int& to, bool begin = false) {
         Range all;
 #pragma unroll
         for (int u = 0; u < XU; ++u)
 #pragma unroll
             for (int j = 0; j < 8; j += 2) all.add(xr[u][j], xr[u][j + 1]);
         const uint2 of = all.of_wave();
-        if (lane == 0) *reinterpret_cast<uint2*>(lds + parity * BUF + 2 * CGB + 64 + wave * 8) = of;
+        if (lane == 0) *reinterpret_cast<uint2*>(lds + 3 * BUF + 64 + wave * 8) = of;
+        if (begin && wave == 0) flag(0) = flag(1) = 0;
         __syncthreads();
-        const u4* s = reinterpret_cast<const u4*>(lds + parity * BUF + 2 * CGB + 64);
-        const u4 a = s[0], b = s[1];
-        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(a[0], a[2]), max(b[0], b[2])));
-        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)min(min(a[1], a[3]), min(b[1], b[3])));
+        const u4* s = reinterpret_cast<const u4*>(lds + 3 * BUF + 64);
+        unsigned h = 0, l = 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < NW / 2; ++i) {
+            h = max(h, max(s[i][0], s[i][2]));
+            l = min(l, min(s[i][1], s[i][3]));
+        }
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)h), lo = (unsigned)__builtin_amdgcn_readfirstlane((int)l);
         to = pair_exponent(hi);
         lim = PairLimits(to);
         return lim.hold(hi, lo);
     };
+    // Staging of one unit in nine parts: its channels cut two by two (p0 of a pair beside p1 of the one before, which waits for its p0), written,
+    // and those of the chunk after the next fetched two by two.  up: 2^sigma
     u4 xf[2];
-    // staging of one unit in six parts, as in piece_kernel; up: bits of 2^sigma
-    auto stage = [&](int u, int part, unsigned char* buf, int ch, int after, unsigned up) {
+    float a2, b2;
+    auto second = [&](int i) {
+        asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(xf[1][i]) : "v"(xf[0][i]), "s"(-4096.0f), "v"(a2));
+        asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(xf[1][i]) : "v"(xf[0][i]), "s"(-4096.0f), "v"(b2));
+    };
+    auto stage = [&](int u, int part, unsigned char* buf, int after, float up, float up2) {
         if (part < 4) {
-            const int left = p.Cg - (ch * 16 + (u * NW + wave) % 2 * 8) - 2 * part;
-            const unsigned ua = left > 0 ? up : 0, ub = left > 1 ? up : 0, ua2 = left > 0 ? up + (12u << 23) : 0, ub2 = left > 1 ? up + (12u << 23) : 0;
-            pair2(xr[u][2 * part], xr[u][2 * part + 1], __builtin_bit_cast(float, ua), __builtin_bit_cast(float, ua2), __builtin_bit_cast(float, ub),
-                  __builtin_bit_cast(float, ub2), part, xf);
+            const float a = xr[u][2 * part], b = xr[u][2 * part + 1];
+            unsigned h;
+            asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "=v"(h) : "v"(a), "s"(up));
+            if (part) second(part - 1);
+            asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "+v"(h) : "v"(b), "s"(up));
+            xf[0][part] = h;
+            a2 = a * up2;
+            b2 = b * up2;
         } else if (part == 4) {
+            second(3);
             *reinterpret_cast<u4*>(buf + xst[u]) = xf[0];
             *reinterpret_cast<u4*>(buf + xst[u] + PLANE) = xf[1];
         } else {
-            fetch_x(xr[u], u, after);
+            fetch_x(xr[u], u, after, (8 - part) * 2, 2);   // (the first pair comes last: one wait for all)
         }
     };
-    auto range_of = [&](int u) {
+    // channels past the group's last one count as zeros
+    auto clear = [&](int ch) {
+        const int left = p.Cg - (ch * 16 + wave % 2 * 8);
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) rg.add(xr[u][j], xr[u][j + 1]);
+        for (int u = 0; u < XU; ++u)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xr[u][j] = left > j ? xr[u][j] : 0.0f;
     };
 
     const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
@@ -304,111 +367,146 @@ __device__ __forceinline__ int pair_sums(const Problem& p, const int (&pos)[G::N
     float run[NT][16];
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb) {
-        accl[nb] = zero;
+        tmp[nb] = accl[nb] = zero;
 #pragma unroll
         for (int v = 0; v < 16; ++v) run[nb][v] = 0.0f;
     }
     u4 b0[3][NT], b1[2][NT];             // windows: p0 two taps ahead, p1 one
-    auto load_b = [&](u4& to, const unsigned char* buf, int e, int n, int q) {
-        to = *reinterpret_cast<const u4*>(buf + e / 3 * pitch * 16 + lb[n] + e % 3 * 16 + q * PLANE);
+    auto load_b = [&](const unsigned char* buf, int e, int n, int q) {
+        (q ? b1[e & 1][n] : b0[e % 3][n]) = *reinterpret_cast<const u4*>(buf + e / 3 * pitch * 16 + lb[n] + e % 3 * 16 + q * PLANE);
     };
+    // p0q0 first and last in turn: between the last product of a block before its sums are folded and the first one after lie eight others
+    constexpr int NM = 3 * NT;               // matrix instructions of a tap
     auto product = [&](int e, int m) {
-        const int c = m / NT, n = m % NT;      // p0q0, then p1q0 and p0q1
+        const int c = (m / NT + e % 2) % 3, n = m % NT;      // p0q0, p1q0, p0q1
         v16f& d = c ? accl[n] : tmp[n];
         d = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, ap[e][c == 1 ? 1 : 0]), __builtin_bit_cast(h8, c == 2 ? b1[e & 1][n] : b0[e % 3][n]),
-                                                   e == 0 && !c ? zero : d, 0, 0, 0);
+                                                   d, 0, 0, 0);
     };
 
+    // (both chunks of the map that are needed before the first product, and the filters, are asked for before any is waited for)
+    float xs[XU][8];
+    const int nx1 = min(chb + 1, che - 1);
 #pragma unroll
-    for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb);
+    for (int u = 0; u < XU; ++u) fetch_x(xr[u], u, chb, 0, 8);
+    fetch_exponents();
 #pragma unroll
-    for (int t = 0; t < D; ++t) fetch_a(chb, t);
-    if (!new_scale(0, sigma)) return chb;
+    for (int u = 0; u < XU; ++u) fetch_x(xs[u], u, nx1, 0, 8);
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+        fetch_a(chb, t, 1);
+        fetch_a(chb, t, 0);
+    }
+    if (!paired() || !new_scale(sigma, true)) return chb;
     const int first = sigma;             // (the running sums follow the scale: from 2^60 off the first one on their bits would not fit fp32's range)
+    if ((chb + 1) * 16 > p.Cg) clear(chb);
 #pragma unroll
     for (int u = 0; u < XU; ++u)
 #pragma unroll
-        for (int part = 0; part < 6; ++part) stage(u, part, lds, chb, min(chb + 1, che - 1), (unsigned)(sigma + 127) << 23);
+        for (int part = 0; part < 5; ++part) stage(u, part, lds, nx1, power_of_two(sigma), power_of_two(sigma + 12));
 #pragma unroll
-    for (int u = 0; u < XU; ++u) range_of(u);
+    for (int u = 0; u < XU; ++u)
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            xr[u][j] = xs[u][j];
+            xr[u][j + 1] = xs[u][j + 1];
+            rg.add(xr[u][j], xr[u][j + 1]);
+        }
     say(1);
     __syncthreads();
-
-    // a quarter of the chunk's sums to the running sums (times by: the step from the scale of the chunk before); with KEPT tmp becomes what
-    // the addition lost
-    float by = 1.0f;
-    auto fold = [&](int part) {
 #pragma unroll
-        for (int v = part % 2 * 8; v < part % 2 * 8 + 8; ++v) {
-            const float t = tmp[part / 2][v], a = run[part / 2][v], sum = __builtin_fmaf(a, by, t);
-            run[part / 2][v] = sum;
-            if (KEPT) tmp[part / 2][v] = t - __builtin_fmaf(-by, a, sum);
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) load_b(lds, e, n, 0);
+    unsigned said = flag(1);             // (asked for behind a barrier, needed two taps later)
+
+    float by = 1.0f;                     // the step from the running sums' scale to that of the others
+    // Some of a block's sums to the running ones; what the addition lost is where the next sums start
+    auto fold = [&](int n, int from, int to) {
+#pragma unroll
+        for (int v = from; v < to; ++v) {
+            const float t = tmp[n][v], a = run[n][v], sum = __builtin_fmaf(a, by, t);
+            run[n][v] = sum;
+            tmp[n][v] = t - __builtin_fmaf(a, -by, sum);
         }
     };
-    constexpr int NM = 3 * NT;               // matrix instructions of a tap
-    static_assert(XU == 2 && NT == 2, "the places of a chunk's work between its matrix instructions");
-    int end = che;
-    for (int ch = chb; ch < end; ++ch) {
-        const int par = (ch - chb) & 1, nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1);
-        const unsigned char* buf = lds + par * BUF;
-        unsigned char* nbuf = lds + (par ^ 1) * BUF;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) load_b(b0[0][n], buf, 0, n, 0);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) load_b(b1[0][n], buf, 0, n, 1);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) load_b(b0[1][n], buf, 1, n, 0);
-        const u4 said = *reinterpret_cast<const u4*>(nbuf + 2 * CGB);
+    int end = che, at = 0;
+    auto chunk = [&](int ch, auto parity) {
+        constexpr int par = decltype(parity)::value;
+        const int nx = min(ch + 1, che - 1), nx2 = min(ch + 2, che - 1), to = at == 2 * BUF ? 0 : at + BUF;
+        const unsigned char* buf = lds + at;
+        unsigned char* nbuf = lds + to;
+        at = to;
         int next = sigma;
-        unsigned up = (unsigned)(sigma + 127) << 23;
+        if (__builtin_amdgcn_readfirstlane((int)said)) {
+            if (!new_scale(next) || next > first + 60 || next < first - 60) {
+                next = sigma;
+                end = ch + 1;            // (what is staged of the next chunk is not read)
+            }
+            if (wave == 0) flag(par ^ 1) = 0;   // (all have read it: there is a barrier in new_scale)
+        }
+        if ((nx + 1) * 16 > p.Cg) clear(nx);
+        const float up = power_of_two(next), up2 = power_of_two(next + 12);
 #pragma unroll
         for (int e = 0; e < 9; ++e) {
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 product(e, m);
                 __builtin_amdgcn_sched_barrier(0);
-                if (m < NT && e < 7) load_b(b0[(e + 2) % 3][m], buf, e + 2, m, 0);
-                if (m >= NT && m < 2 * NT && e < 8) load_b(b1[(e + 1) & 1][m - NT], buf, e + 1, m - NT, 1);
-                if (m == NM - 1) fetch_a(e == 0 ? ch : nx, e == 0 ? 8 : e - 1);
-                const int at = e * NM + m - NM;
-                if (at >= 0 && at < XU * 6) stage(at / 6, at % 6, nbuf, nx, nx2, up);
-                if (e == 7 && m % 3 == 0) range_of(m / 3);
-                if (e == 8 && m == 0) say(par);
-                if (e == 8 && m >= 2) fold(m - 2);
+                // windows; those of the next chunk behind the barrier
+                if (e == 0 && m < 2) load_b(buf, 0, m, 1);
+                if (e == 0 && m >= 4) load_b(buf, 1, m - 4, 1);
+                if (e > 0 && e < 8 && m < 2) load_b(buf, e + 1, m, 1);
+                if (m >= 2 && m < 4) load_b(e < 7 ? buf : nbuf, (e + 2) % 9, m - 2, 0);
+                if (m >= 4) fetch_a(e + D < 9 ? ch : nx, (e + D) % 9, (e + D) % 9 % 2 ? m - 4 : 5 - m);
+                // the next chunk
+                const int item = e * NM + m - 2;
+                if (item >= 0 && item < 9 * XU) stage(item / 9, item % 9, nbuf, nx2, up, up2);
+                if (e == 5 && m >= 6 - 4 * XU) {
+                    const int k = XU == 1 ? m - 2 : m;
+                    rg.add(xr[k / 4][k % 4 * 2], xr[k / 4][k % 4 * 2 + 1]);
+                }
+                if (XU == 2 && e == 6 && m < 2) rg.add(xr[XU - 1][m * 2 + 4], xr[XU - 1][m * 2 + 5]);
+                if (e == 6 && m == 2) say(par);
+                // block 0 between taps 2 and 3, block 1 between 6 and 7
+                const int k = (e - 2) % 4 * NM + m - 3;
+                if (e >= 2 && k >= 0 && k < 7) fold((e - 2) / 4, k * 16 / 7, (k + 1) * 16 / 7);
                 __builtin_amdgcn_sched_barrier(0);
-                if (e == 0 && m == NM - 1 && __builtin_amdgcn_readfirstlane((int)(said[0] | said[1] | said[2] | said[3]))) {
-                    if (!new_scale(par ^ 1, next) || next > first + 60 || next < first - 60) {
-                        next = sigma;
-                        end = ch + 1;    // (what is staged of the next chunk is not read)
-                    }
-                    up = (unsigned)(next + 127) << 23;
+                if (e == 6 && m == NM - 1) {
+                    __syncthreads();
+                    said = flag(par);
                 }
             }
         }
-        if (KEPT)
-#pragma unroll
-            for (int nb = 0; nb < NT; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) accl[nb][v] = __builtin_fmaf(tmp[nb][v], 4096.0f, accl[nb][v]);
         by = power_of_two(next - sigma);
         if (next != sigma) {
 #pragma unroll
-            for (int nb = 0; nb < NT; ++nb) accl[nb] *= by;
+            for (int nb = 0; nb < NT; ++nb) {
+                accl[nb] *= by;
+                tmp[nb] *= by;
+            }
             sigma = next;
         }
-        __syncthreads();
+    };
+    // (two chunks a turn: the buffers are known, and the running sums are back in their registers)
+    for (int ch = chb;;) {
+        chunk(ch, Const<0>());
+        if (++ch >= end) break;
+        chunk(ch, Const<1>());
+        if (++ch >= end) break;
     }
+    __syncthreads();
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + accl[nb][v] * 0x1p-12f;   // (the last chunk is staged twice, so its scale may have moved on)
+        for (int v = 0; v < 16; ++v) acc[0][nb][v] = run[nb][v] * by + (tmp[nb][v] + accl[nb][v] * 0x1p-12f);
     return end;
 }
 
 // Bytes of the pairs of all filters and their exponents; behind them the pieces.
 __host__ __device__ inline size_t pair_bytes(int G, int kb32, int nch16) { return ((size_t)G * kb32 * ((size_t)nch16 * 9 * 2048 + 128) + 255) / 256 * 256; }
 
-// FORM: SRC_PAIRS or SRC_PAIRS_KEPT (SRC: the filters' form where pairs do not do), or 0
+// FORM: SRC_PAIRS (SRC: the filters' form where pairs do not do), or 0
 template <class G, int SRC, int FORM>
 __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
                                                               const float* __restrict__ w, const void* __restrict__ wp,
@@ -418,33 +516,38 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     constexpr int MT = G::MT, NT = G::NT, CS = G::CS, CG = G::CG, NW = G::NW, XU = G::XU, AR = G::AR;
     const int PX = cfg.px, CGB = cfg.cgb;
     constexpr int T = G::T, S = T == 9 ? 3 : 1;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % G::WM, wn = wave / G::WM;
-    const int half = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (eight wavefronts: those that read the same filters are on different SIMDs and run side by side, so that the second finds them in the L1)
+    const int wm = G::NW == 8 ? wave / G::WN : wave % G::WM, wn = G::NW == 8 ? wave % G::WN : wave / G::WM;
 
-    // workgroup -> (tile, slice); ids are dealt to the eight XCDs in turn, every XCD gets a contiguous range
+    // workgroup -> tiles and chunks of them; ids are dealt to the eight XCDs in turn, every XCD gets a contiguous range
     const int whole = cfg.whole, nb_all = gridDim.x;
     const bool split = (int)blockIdx.x >= whole;
-    int b = split ? blockIdx.x - whole : blockIdx.x, ss = 0;
+    int first = split ? blockIdx.x - whole : blockIdx.x;
     {
         const int cnt = split ? nb_all - whole : whole;
-        const int n8 = cnt >> 3, rem = cnt & 7, xcd = b & 7, i = b >> 3;
-        b = xcd * n8 + min(xcd, rem) + i;
+        const int n8 = cnt >> 3, rem = cnt & 7, xcd = first & 7, i = first >> 3;
+        first = xcd * n8 + min(xcd, rem) + i;
     }
-    int ptile = 0;                       // number of the tile among the split ones
-    if (split) {
-        const int ns = (nb_all - whole) / cfg.nss;
-        ss = b / ns;
-        ptile = b - ss * ns;
-        b = whole + ptile;
+
+    const int ss = split ? first / cfg.tail : 0, b = split ? whole + first - ss * cfg.tail : first;
+    float* const part = split ? parts + (size_t)first * (G::BM * G::BN) : nullptr;   // where a split tile's sums go
+    const int chb = split ? cfg.nch * ss / cfg.nss : 0, che = split ? cfg.nch * (ss + 1) / cfg.nss : cfg.nch;
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    int kb, strip, tile, g;
+    if (G::BLOCK) {                      // (an XCD's workgroups share the filters of few blocks)
+        const int b1 = cfg.by_strips.of(b), b2 = cfg.by_ntiles.of(b1);
+        strip = b - b1 * cfg.strips;
+        tile = b1 - b2 * cfg.ntiles;
+        g = cfg.by_kblocks.of(b2);
+        kb = b2 - g * cfg.kblocks;
+    } else {
+        const int b1 = cfg.by_kblocks.of(b), b2 = cfg.by_strips.of(b1);
+        kb = b - b1 * cfg.kblocks;
+        strip = b1 - b2 * cfg.strips;
+        g = cfg.by_ntiles.of(b2);
+        tile = b2 - g * cfg.ntiles;
     }
-    const int kb = b % cfg.kblocks;
-    b /= cfg.kblocks;
-    const int strip = b % cfg.strips;
-    b /= cfg.strips;
-    const int tile = b % cfg.ntiles;
-    const int g = b / cfg.ntiles;
 
     const int iH = cfg.flat ? 1 : p.H, iW = cfg.flat ? p.H * p.W : p.W;
     const int oH = cfg.flat ? 1 : p.OH, oW = cfg.flat ? p.OH * p.OW : p.OW;
@@ -453,13 +556,15 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     const int pitch = (G::POOL ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + S;
     const int pcols = G::POOL ? p.PW : oW, prows = G::POOL ? p.PH : oH;
     const int plane = prows * pcols;                // stored results per image and filter
-    // window row P of the strip -> image, output row and column (of the convolution; columns counted from the strip's first)
+    // window row P of the strip -> image, row and column of its (pooled) result, the column counted from the strip's first; of its convolution
+    auto place = [&](int P, int& n, int& row, int& c) {
+        const int pp = G::POOL ? P >> 2 : P, q = cfg.by_TW.of(pp);
+        c = pp - q * TW;
+        n = cfg.by_rows.of(q);
+        row = q - n * prows;
+    };
     auto window = [&](int P, int& n, int& oh, int& ow) {
-        const int pp = G::POOL ? P >> 2 : P;
-        const int q = pp / TW;
-        ow = pp - q * TW;
-        n = q / prows;
-        oh = q - n * prows;
+        place(P, n, oh, ow);
         if (G::POOL) {
             oh = p.ps * oh + ((P & 3) >> 1);
             ow = p.ps * ow + (P & 1);
@@ -486,8 +591,8 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
         const int id = u * NW + wave, cgi = id % CG, q = id / CG * 64 + lane;
-        const int row = q / pitch, cw = q - row * pitch + w0;
-        const int sr = r0 + row, n = sr / HP, h = sr - n * HP - p.pad;
+        const int row = cfg.by_pitch.of(q), cw = q - row * pitch + w0;
+        const int sr = r0 + row, n = cfg.by_HP.of(sr), h = sr - n * HP - p.pad;
         const bool ok = q < PX && n < p.N && h >= 0 && h < iH && cw >= 0 && cw < iW;
         xvo[u] = ok ? 4u * (unsigned)((n - n0) * p.C * HW + h * iW + cw) : 0x80000000u;
         xst[u] = q < PX ? cgi * CGB + q * 48 : CG * CGB + lane * 16;   // (lanes past the tile's positions write where nobody reads)
@@ -496,44 +601,55 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     const size_t xleft = ((size_t)p.N * p.C * HW - ((size_t)n0 * p.C + (size_t)g * p.Cg) * HW) * 4;
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xb), 0, (int)min(xleft, (size_t)0x7ffffffc), 0x00020000);
-    auto fetch_x = [&](float (&to)[8], int u, int ch) {
+    auto fetch_x = [&](float (&to)[8], int u, int ch, int j0 = 0, int n = 8) {
         const int c0 = ch * CS * 16 + (u * NW + wave) % CG * 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = j0; j < j0 + n; ++j)
             to[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, (int)xvo[u], min(c0 + j, p.Cg - 1) * HW * 4, 0));
     };
-    const int chb = split ? cfg.nch * ss / cfg.nss : 0, che = split ? cfg.nch * (ss + 1) / cfg.nss : cfg.nch;
     const int kblk0 = kb * (G::BM / 32) + wm * MT;
     v16f acc[MT][NT];
 
     int from = chb;                      // the chunks from here on are summed from pieces
-    if constexpr (FORM >= SRC_PAIRS) {
+    if constexpr (FORM == SRC_PAIRS) {
         const size_t blk = (size_t)cfg.nch * T * 2048;
         // the filters' exponents (kUnpaired: a filter that pairs cannot hold)
         const int* sg = reinterpret_cast<const int*>((const char*)wp + (size_t)p.G * cfg.kb32 * blk) + ((size_t)g * cfg.kb32 + kb * (G::BM / 32)) * 32;
-        bool paired = true;
+        // (every wavefront looks at all of them, and they wait in LDS for the end)
+        int* const sgl = reinterpret_cast<int*>(lds + 3 * G::PAIR_BUF - 512);
+        int sgr[G::BM / 64];
+        auto fetch_exponents = [&] {
 #pragma unroll
-        for (int i = 0; i < G::BM; i += 64) paired &= !__any(sg[i + lane] == kUnpaired);
+            for (int i = 0; i < G::BM / 64; ++i) sgr[i] = sg[i * 64 + lane];
+        };
+        auto paired = [&] {
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < G::BM / 64; ++i) {
+                all &= !__any(sgr[i] == kUnpaired);
+                sgl[i * 64 + lane] = sgr[i];
+            }
+            return all;
+        };
         const __amdgpu_buffer_rsrc_t pres =
             __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
         int sigma = 0;
-        if (paired) from = pair_sums<G, FORM == SRC_PAIRS_KEPT>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, acc, sigma);
+        from = pair_sums<G>(p, pos, pitch, chb, che, wave, lane, lds, fetch_x, pres, fetch_exponents, paired, acc, sigma);
         // To the scale of sums of pieces, by the exponents' sum: map and filters both small (or large) make two factors whose product fp32
         // does not hold, where the sum times both is an ordinary number.
         if (from > chb) {
-            sg += wm * MT * 32 + 4 * half;
+            const int* e = sgl + wm * 32 + 4 * half;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int e = 48 - sigma - sg[8 * (v >> 2) + (v & 3)];
+            for (int v = 0; v < 16; ++v)
 #pragma unroll
-                for (int nb = 0; nb < NT; ++nb) acc[0][nb][v] = __builtin_amdgcn_ldexpf(acc[0][nb][v], e);
-            }
+                for (int nb = 0; nb < NT; ++nb) acc[0][nb][v] = __builtin_amdgcn_ldexpf(acc[0][nb][v], 48 - sigma - e[8 * (v >> 2) + (v & 3)]);
+            if (from < che) __syncthreads();   // (pieces are staged where the exponents are)
         } else {
             acc[0][0] = acc[0][1] = 0.0f;
             __syncthreads();             // (what pair_sums exchanged in LDS is overwritten)
         }
-        wp = SRC == SRC_FP32 ? (const void*)p.wprep : (const char*)wp + pair_bytes(p.G, cfg.kb32, cfg.nch);   // (unused as stored)
     }
+    const void* const wrest = FORM == 0 ? wp : SRC == SRC_FP32 ? (const void*)p.wprep : (const char*)wp + pair_bytes(p.G, cfg.kb32, cfg.nch);   // (unused as stored)
     if (FORM == 0 || from < che) {
         // staging of one unit in six parts: its channels cut two by two, written, and those of the chunk after the next fetched;
         // channels past the group's last one count as zeros
@@ -561,11 +677,11 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         int wvo[SRC == SRC_RAW ? MT : 1];
         if (SRC == SRC_PIECES) {
             const size_t blk = (size_t)cfg.nch * CS * T * 3072;
-            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
+            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wrest + ((size_t)g * cfg.kb32 + kblk0) * blk), 0, 0x7ffffffc, 0x00020000);
             wvo[0] = lane * 16;
         } else if (SRC == SRC_FP32) {
             const size_t blk = (size_t)p.Cg * T * 256;
-            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wp + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
+            wres = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)wrest + ((size_t)g * (cfg.kb32 >> 1) + (kblk0 >> 1)) * blk), 0, 0x7ffffffc, 0x00020000);
             wvo[0] = half * 8 * T * 256 + (kblk0 & 1) * 128 + col * 4;
         } else {
             // filters as stored; a filter past the group's last one re-reads the last
@@ -762,27 +878,40 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
     }
 
     // epilogue
-    float* part = split ? parts + ((size_t)ss * ((nb_all - whole) / cfg.nss) + ptile) * (G::BM * G::BN) : nullptr;
     const int c_lo = chb * CS * 16, c_hi = min(che * CS * 16, p.Cg);
+    auto there = [&](int nb, int& P, int& n, int& row, int& wcol) {   // a window's result, and whether there is such a one
+        P = tile * G::BN + (wn * NT + nb) * 32 + col;
+        place(min(P, cfg.nrun - 1), n, row, wcol);
+        wcol += strip * TW;
+        return P < cfg.nrun && wcol < pcols;
+    };
+    // sums out of the pieces' range: x times 0 is NaN where x is Inf or NaN
+    float lost = 0.0f;
 #pragma unroll
-    for (int nb = 0; nb < NT; ++nb) {
-        const int P = tile * G::BN + (wn * NT + nb) * 32 + col;
-        int n, oh, ow;
-        window(min(P, cfg.nrun - 1), n, oh, ow);
-        ow += strip * TW * (G::POOL ? p.ps : 1);
-        const int wcol = G::POOL ? (ow - (P & 1)) / p.ps : ow;
-        const bool pos_ok = P < cfg.nrun && wcol < pcols;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            const int k0 = kb * G::BM + (wm * MT + i) * 32 + 4 * half;   // filter of element v: k0 + 8*(v/4) + v%4
-            bool bad = false;
+        for (int nb = 0; nb < NT; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
-                bad |= pos_ok && k0 + 8 * (v >> 2) + (v & 3) < p.Kg && not_finite(r);
-                acc[i][nb][v] = r * kDown;
-            }
-            if (__any(bad)) {
+            for (int v = 0; v < 16; ++v) lost = __builtin_fmaf(acc[i][nb][v], 0.0f, lost);
+    const bool again = __any(lost != 0.0f);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int nb = 0; nb < NT; ++nb) {
+            unsigned bad = 0;
+            if (again)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float r = acc[i][nb][v];   // (a copy: the cast of a vector element reads element 0)
+                    bad |= not_finite(r);
+                }
+            acc[i][nb] *= kDown;
+            if (again && __any(bad)) {
+                int P, n, oh, ow, row, wcol;
+                there(nb, P, n, row, wcol);
+                oh = G::POOL ? row * p.ps + ((P & 3) >> 1) : row;
+                ow = G::POOL ? wcol * p.ps + (P & 1) : wcol;
+                const int k0 = kb * G::BM + (wm * MT + i) * 32 + 4 * half;   // filter of element v: k0 + 8*(v/4) + v%4
                 float* sc = reinterpret_cast<float*>(lds) + wave * 1024 + lane;
                 for (int v = 0; v < 16; ++v) {
                     const int kk = min(k0 + 8 * (v >> 2) + (v & 3), p.Kg - 1);
@@ -800,37 +929,72 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][nb][v] = sc[v * 64];
             }
-            if (split) {
-                float* d = part + ((wm * MT + i) * 32 + 4 * half) * G::BN + (wn * NT + nb) * 32 + col;
+        }
+    if (part) {
+        float* const d = part + (wm * MT * 32 + 4 * half) * G::BN + wn * NT * 32 + col;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + (v & 3)) * G::BN] = acc[i][nb][v];
-            } else if (!G::POOL) {
-                const size_t o0 = ((size_t)n * p.K + (size_t)g * p.Kg + k0) * plane + oh * oW + ow;
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NT; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) d[(i * 32 + 8 * (v >> 2) + (v & 3)) * G::BN + nb * 32] = acc[i][nb][v];
+        return;
+    }
+    // (all biases are on their way before the first is needed)
+    float bias[MT][16];
+    auto filter = [&](int i, int v) { return kb * G::BM + (wm * MT + i) * 32 + 4 * half + 8 * (v >> 2) + (v & 3); };
+    const bool full = (kb + 1) * G::BM <= p.Kg;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bias[i][v] = 0.0f;
+    if (p.bias)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bias[i][v] = p.bias[(size_t)g * p.Kg + min(filter(i, v), p.Kg - 1)];
+#pragma unroll
+    for (int nb = 0; nb < NT; ++nb) {
+        int P, n, row, wcol;
+        const bool ok = there(nb, P, n, row, wcol);
+        float* const o = y + ((size_t)n * p.K + (size_t)g * p.Kg) * plane + row * pcols + wcol;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            if (!G::POOL) {
+                float r[16];
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int dk = 8 * (v >> 2) + (v & 3);
-                    if (!pos_ok || k0 + dk >= p.Kg) continue;
-                    float r = acc[i][nb][v] + bias_of(p, (size_t)g * p.Kg + k0 + dk);
-                    if (p.relu) r = fmaxf(r, 0.0f);
-                    y[o0 + (size_t)dk * plane] = r;
+                    r[v] = acc[i][nb][v] + bias[i][v];
+                    if (p.relu) r[v] = fmaxf(r[v], 0.0f);
+                }
+                float* const ok0 = o + (size_t)filter(i, 0) * plane;
+                if (full) {
+                    if (ok)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) ok0[(size_t)(8 * (v >> 2) + (v & 3)) * plane] = r[v];
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        if (ok && filter(i, v) < p.Kg) ok0[(size_t)(8 * (v >> 2) + (v & 3)) * plane] = r[v];
                 }
             } else {
                 // the four results of a pooling window lie in four neighbouring lanes; lane e of them keeps filter v = e
-                const int e = lane & 3, wrow = (oh - (e >> 1)) / p.ps;
+                const int e = lane & 3;
 #pragma unroll
                 for (int vq = 0; vq < 4; ++vq) {
-                    float r = 0.0f;
+                    float r = 0.0f, b = 0.0f;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         float m = acc[i][nb][vq * 4 + v];
                         m = fmaxf(m, __shfl_xor(m, 1));
                         m = fmaxf(m, __shfl_xor(m, 2));
-                        if (v == e) r = m;
+                        if (v == e) {
+                            r = m;
+                            b = bias[i][vq * 4 + v];
+                        }
                     }
-                    const int kk = k0 + 8 * vq + e;
-                    if (!pos_ok || kk >= p.Kg) continue;
-                    r = fmaxf(r + bias_of(p, (size_t)g * p.Kg + kk), 0.0f);
-                    y[((size_t)n * p.K + (size_t)g * p.Kg + kk) * plane + wrow * p.PW + wcol] = r;
+                    const int kk = filter(i, vq * 4) + e;
+                    if (ok && kk < p.Kg) o[(size_t)kk * plane] = fmaxf(r + b, 0.0f);
                 }
             }
         }
@@ -888,30 +1052,26 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
         const int n8 = cnt >> 3, rem = cnt & 7, xcd = b & 7, i = b >> 3;
         b = xcd * n8 + min(xcd, rem) + i;
     }
-    const int ns = split ? (nb_all - whole) / cfg.nss : 1;
-    int ptile = 0;
+    const int ns = cfg.tail, ptile0 = b;
     if (split) {
         ss = b / ns;
-        ptile = b - ss * ns;
-        b = whole + ptile;
+        b = whole + b - ss * ns;
     }
-    const int kb = b % cfg.kblocks;
-    b /= cfg.kblocks;
-    const int strip = b % cfg.strips;
-    b /= cfg.strips;
-    const int tile = b % cfg.ntiles;
-    const int g = b / cfg.ntiles;
+    const int b1 = cfg.by_kblocks.of(b), b2 = cfg.by_strips.of(b1), g = cfg.by_ntiles.of(b2);
+    const int kb = b - b1 * cfg.kblocks, strip = b1 - b2 * cfg.strips, tile = b2 - g * cfg.ntiles;
 
     const int TW = cfg.TW, HW = p.H * p.W, HP = p.H + p.pad;
     const int pitch = (G::POOL ? (TW - 1) * p.ps + 1 : TW - 1) * p.stride + S;
     const int pcols = G::POOL ? p.PW : p.OW, prows = G::POOL ? p.PH : p.OH;
     const int plane = prows * pcols;
-    auto window = [&](int P, int& n, int& oh, int& ow) {   // as in piece_kernel
-        const int pp = G::POOL ? P >> 2 : P;
-        const int q = pp / TW;
-        ow = pp - q * TW;
-        n = q / prows;
-        oh = q - n * prows;
+    auto place = [&](int P, int& n, int& row, int& c) {    // as in piece_kernel
+        const int pp = G::POOL ? P >> 2 : P, q = cfg.by_TW.of(pp);
+        c = pp - q * TW;
+        n = cfg.by_rows.of(q);
+        row = q - n * prows;
+    };
+    auto window = [&](int P, int& n, int& oh, int& ow) {
+        place(P, n, oh, ow);
         if (G::POOL) {
             oh = p.ps * oh + ((P & 3) >> 1);
             ow = p.ps * ow + (P & 1);
@@ -934,8 +1094,8 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
         const int id = u * NW + wave, cgi = id % CG, q = id / CG * 64 + lane;
-        const int row = q / pitch, cw = q - row * pitch + w0;
-        const int sr = r0 + row, n = sr / HP, h = sr - n * HP - p.pad;
+        const int row = cfg.by_pitch.of(q), cw = q - row * pitch + w0;
+        const int sr = r0 + row, n = cfg.by_HP.of(sr), h = sr - n * HP - p.pad;
         const bool ok = q < PX && n < p.N && h >= 0 && h < p.H && cw >= 0 && cw < p.W;
         xvo[u] = ok ? 4u * (unsigned)((n - n0) * p.C * HW + h * p.W + cw) : 0x80000000u;
         xst[u] = q < PX ? cgi * CGB + q * 48 : -1;
@@ -1040,7 +1200,7 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
 
     // the wavefronts' sums, 32 windows at a time: element v of lane l = filter 8 (v / 4) + v % 4 + 4 (l / 32), window l % 32
     const int c_lo = chb * CS * 16, c_hi = min(che * CS * 16, p.Cg);
-    float* part = split ? parts + ((size_t)ss * ns + ptile) * (G::BM * G::BN) : nullptr;
+    float* part = split ? parts + (size_t)ptile0 * (G::BM * G::BN) : nullptr;
 #pragma unroll
     for (int nb = 0; nb < NT; ++nb) {
         if (nb) __syncthreads();
@@ -1048,10 +1208,10 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
         for (int v = 0; v < 16; ++v) fl[(wave * 16 + v) * 64 + lane] = acc[nb][v] + accl[nb][v];
         __syncthreads();
         const int P = tile * G::BN + nb * 32 + col;
-        int n, oh, ow;
-        window(min(P, cfg.nrun - 1), n, oh, ow);
-        ow += strip * TW * (G::POOL ? p.ps : 1);
-        const int wcol = G::POOL ? (ow - (P & 1)) / p.ps : ow, wrow = G::POOL ? (oh - ((P & 3) >> 1)) / p.ps : oh;
+        int n, wrow, wcol;
+        place(min(P, cfg.nrun - 1), n, wrow, wcol);
+        wcol += strip * TW;
+        const int oh = G::POOL ? wrow * p.ps + ((P & 3) >> 1) : wrow, ow = G::POOL ? wcol * p.ps + (P & 1) : wcol;
         const bool pos_ok = P < cfg.nrun && wcol < pcols;
 #pragma unroll
         for (int i = 0; i < 16 / NW; ++i) {
@@ -1094,21 +1254,16 @@ __global__ __launch_bounds__(G::NW * 64, 2) void piece_taps_kernel(Problem p, Pi
 // is added, where one thread per result waited for each: 512 @14x14 at batch 8, 100 tiles x 5 slices 7.2 -> 5.7 us, 512 @7x7 at batch 1,
 // 16 x 16 slices of 32 x 64 6.4 -> 4.1, 256 @56x56 16 x 16 6.2 -> 4.6.
 template <bool POOL>
-__global__ __launch_bounds__(256) void piece_sum_kernel(Problem p, PieceCfg cfg, int BM, int BN, int ns, const float* __restrict__ parts,
+__global__ __launch_bounds__(256) void piece_sum_kernel(Problem p, PieceCfg cfg, int BM, int BN, const float* __restrict__ parts,
                                                         float* __restrict__ y)
 {
     const int per_row = BN / 4;
-    const int e = blockIdx.x * 256 + threadIdx.x, kr = e / per_row, c = e - kr * per_row;
-    int b = cfg.whole + blockIdx.y;
-    const int kb = b % cfg.kblocks;
-    b /= cfg.kblocks;
-    const int strip = b % cfg.strips;
-    b /= cfg.strips;
-    const int tile = b % cfg.ntiles;
-    const int g = b / cfg.ntiles;
+    const int e = blockIdx.x * 256 + threadIdx.x, kr = cfg.by_quads.of(e), c = e - kr * per_row;
+    const int b = cfg.whole + blockIdx.y, b1 = cfg.by_kblocks.of(b), b2 = cfg.by_strips.of(b1), g = cfg.by_ntiles.of(b2);
+    const int kb = b - b1 * cfg.kblocks, strip = b1 - b2 * cfg.strips, tile = b2 - g * cfg.ntiles;
     const int k = kb * BM + kr;
     if (kr >= BM || k >= p.Kg || tile * BN + c * 4 >= cfg.nrun) return;
-    const size_t tsz = (size_t)BM * BN, step = (size_t)ns * tsz;
+    const size_t tsz = (size_t)BM * BN, step = (size_t)cfg.tail * tsz;
     const float* src = parts + (size_t)blockIdx.y * tsz + (size_t)kr * BN + c * 4;
     f4 r = *reinterpret_cast<const f4*>(src);
     int s = 1;
@@ -1133,7 +1288,7 @@ __global__ __launch_bounds__(256) void piece_sum_kernel(Problem p, PieceCfg cfg,
 #pragma unroll
     for (int i = 0; i < (POOL ? 1 : 4); ++i) {
         const int P = POOL ? tile * BN / 4 + c : tile * BN + c * 4 + i;
-        const int q = P / cfg.TW, n = q / prows, wrow = q - n * prows, wcol = strip * cfg.TW + P - q * cfg.TW;
+        const int q = cfg.by_TW.of(P), n = cfg.by_rows.of(q), wrow = q - n * prows, wcol = strip * cfg.TW + P - q * cfg.TW;
         if (P >= cfg.nrun / (POOL ? 4 : 1) || wcol >= pcols) continue;
         float v = r[i] + bias;
         if (p.relu) v = fmaxf(v, 0.0f);
@@ -1378,9 +1533,30 @@ void consider(Plan& pl, long long tiles, long long round, int NW, double tc, dou
             c.kb32 = kb32;
             c.whole = (int)whole;
             c.nss = s;
+            c.tail = (int)tail;
         }
         if (pin_nss) break;
     }
+}
+
+// The same for blocks, one workgroup to a compute unit: whole tiles only, in rounds of 256.  A chunk takes 1.5 us where few units have a tile, at 2.3 GHz,
+// and 2.9 where all have, at the clock that the chip's power leaves (196 tiles of 8, 16, 32 chunks 32.4, 51.7, 90.7 us with the filters' pairs, 248 of
+// 32 103.9, 392 of 16 100.6, 784 of 16 192); for the same reason sharing the tiles of a last round evenly among all units won 4 % at best (392 of
+// 16: 96.7) and lost where less than a round was shared (196 of 32: 98).
+void consider_blocks(Plan& pl, long long tiles, double fixed, size_t pb, int kb32, size_t ws)
+{
+    PieceCfg& c = pl.cfg;
+    if (pb > ws || (!current_pin() && env_value("SCONV_PIECE_SPLIT"))) return;   // (a decomposition of its own)
+    const long long rounds = (tiles + 255) / 256;
+    const double last = (double)(tiles - (rounds - 1) * 256) / 256.0;
+    pl.cost = fixed + (double)(rounds - 1) * (c.nch * 2.88 + 5.0) + c.nch * (1.5 + 1.38 * last);
+    pl.src = SRC_PAIRS;
+    pl.piece_bytes = pb;
+    pl.ntail = 0;
+    c.kb32 = kb32;
+    c.whole = (int)tiles;
+    c.nss = 1;
+    c.tail = 0;
 }
 
 // The tiles of a geometry, without a form of the filters (cost < 0); their number, 0 where it has none.
@@ -1400,7 +1576,7 @@ long long plan_tiles(const Problem& p, bool pooled, Plan& pl)
     c.cgb = (c.px * 48 + 255) / 256 * 256;
     pl.lds_bytes = 2 * ((size_t)G::CG * c.cgb + G::SPARE);
     if (pl.lds_bytes < (size_t)G::NW * 4096) pl.lds_bytes = (size_t)G::NW * 4096;
-    if (G::PAIRS && pl.lds_bytes < 2 * (size_t)G::PAIR_BUF) pl.lds_bytes = 2 * (size_t)G::PAIR_BUF;
+    if (G::PAIRS && pl.lds_bytes < 3 * (size_t)G::PAIR_BUF) pl.lds_bytes = 3 * (size_t)G::PAIR_BUF;
     if (pl.lds_bytes > 160 * 1024) return 0;
     // images a tile can touch, and the byte offsets of their elements
     const long long run_img = (long long)(pooled ? p.PH : c.flat ? 1 : p.OH) * c.TW * (pooled ? 4 : 1);
@@ -1418,6 +1594,7 @@ template <class G>
 Plan plan_geom(const Problem& p, bool pooled, bool close)
 {
     Plan pl;
+    if (G::BLOCK) return pl;             // (pairs only)
     const long long tiles = plan_tiles<G>(p, pooled, pl);
     if (!tiles) return pl;
     const PieceCfg& c = pl.cfg;
@@ -1446,15 +1623,14 @@ Plan plan_geom(const Problem& p, bool pooled, bool close)
     return pl;
 }
 
-// The form with pairs of geometries that have it (kept: with the running sums' rounding errors).
+// The form with pairs of geometries that have it.
 template <class G>
-Plan plan_pairs(const Problem& p, bool pooled, bool kept)
+Plan plan_pairs(const Problem& p, bool pooled, bool)
 {
     Plan pl;
     if constexpr (G::PAIRS) {
-        const int src = kept ? SRC_PAIRS_KEPT : SRC_PAIRS;
         const char* pin_src = env_value("SCONV_PIECE_SRC");
-        if (pin_src && atoi(pin_src) != src) return pl;
+        if (pin_src && atoi(pin_src) < SRC_PAIRS) return pl;
         const long long tiles = plan_tiles<G>(p, pooled, pl);
         if (!tiles) return pl;
         const int kb32 = pl.cfg.kblocks * (G::BM / 32);
@@ -1469,8 +1645,10 @@ Plan plan_pairs(const Problem& p, bool pooled, bool kept)
             Plan q = empty;
             const size_t pb = pair_bytes(p.G, kb32, pl.cfg.nch) + room[i];
             if (pb > ws) continue;
-            consider(q, tiles, 256LL * occupancy_limit<G>(src, q.lds_bytes), G::NW, G::tc(src, 9), 1.25, 11.0 + 2e-6 * p.K * p.L, src, pb, kb32, ws,
-                     (size_t)G::BM * G::BN * 4, true);
+            const double fixed = 11.0 + 2e-6 * p.K * p.L;
+            if (G::BLOCK) consider_blocks(q, tiles, fixed, pb, kb32, ws);
+            else consider(q, tiles, 256LL * occupancy_limit<G>(SRC_PAIRS, q.lds_bytes), G::NW, G::tc(SRC_PAIRS, 9), 1.25, fixed, SRC_PAIRS, pb, kb32, ws,
+                          (size_t)G::BM * G::BN * 4, true);
             q.rest = rest[i];
             if (q.cost >= 0.0 && (pl.cost < 0.0 || q.cost < 0.9 * pl.cost)) pl = q;
         }
@@ -1490,8 +1668,10 @@ int launch_src(const Plan& pl, const Problem& p, const float* x, const float* w,
             return SCONV_ELAUNCH;
         opted = pl.lds_bytes;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.cfg.whole + pl.ntail * pl.cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, pl.cfg, x, w,
-                       wp, parts, y);
+    PieceCfg cfg = pl.cfg;
+    cfg.prepare(p, G::POOL, G::BN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.cfg.whole + pl.ntail * pl.cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, cfg, x,
+                       w, wp, parts, y);
     return launch_status();
 }
 
@@ -1511,42 +1691,47 @@ int launch_pairs(const Problem& p, const PieceCfg& cfg, const float* w, u4* pair
 }
 
 template <class G>
+int launch_sum(const Plan& pl, const Problem& p, const float* parts, float* y, hipStream_t stream)
+{
+    PieceCfg cfg = pl.cfg;
+    cfg.prepare(p, G::POOL, G::BN);
+    hipLaunchKernelGGL(piece_sum_kernel<G::POOL>, dim3((unsigned)((G::BM * G::BN / 4 + 255) / 256), (unsigned)pl.ntail), dim3(256), 0, stream, p, cfg,
+                       G::BM, G::BN, parts, y);
+    return launch_status();
+}
+
+template <class G>
 int launch_plan(const Plan& pl, const Problem& p, bool pooled, const float* x, const float* w, float* y, hipStream_t stream)
 {
     char* ws = reinterpret_cast<char*>(split_scratch(stream));
     float* parts = pl.ntail ? reinterpret_cast<float*>(ws + pl.piece_bytes) : nullptr;
-    int rc;
-    if (pl.src == SRC_FP32) {
-        if constexpr (G::T == 9) rc = launch_src<G, SRC_FP32>(pl, p, x, w, p.wprep, parts, y, stream);
-        else return SCONV_EUNSUPPORTED;
-    } else if (pl.src == SRC_PIECES) {
-        const int nch16 = pl.cfg.nch * G::CS, T = pl.cfg.T;
-        hipLaunchKernelGGL(piece_filters_kernel, dim3((unsigned)(nch16 * T), (unsigned)pl.cfg.kb32, (unsigned)p.G), dim3(64), 0, stream, p,
-                           pl.cfg.kb32, nch16, T, w, reinterpret_cast<u4*>(ws));
-        rc = launch_status();
-        if (rc) return rc;
-        rc = launch_src<G, SRC_PIECES>(pl, p, x, w, ws, parts, y, stream);
-    } else if (pl.src >= SRC_PAIRS) {
+    int rc = SCONV_EUNSUPPORTED;
+    if (pl.src == SRC_PAIRS) {
         if constexpr (G::PAIRS) {
             u4* const pairs = reinterpret_cast<u4*>(ws);
             u4* const pieces = pl.rest == SRC_PIECES ? reinterpret_cast<u4*>(ws + pair_bytes(p.G, pl.cfg.kb32, pl.cfg.nch)) : nullptr;
             rc = p.L <= 16 * 1024 ? launch_pairs<2>(p, pl.cfg, w, pairs, pieces, stream) : launch_pairs<1>(p, pl.cfg, w, pairs, pieces, stream);   // (by LDS)
             if (rc) return rc;
-            const bool kept = pl.src == SRC_PAIRS_KEPT;
-            auto launch = pl.rest == SRC_FP32 ? (kept ? launch_src<G, SRC_FP32, SRC_PAIRS_KEPT> : launch_src<G, SRC_FP32, SRC_PAIRS>)
-                          : pl.rest == SRC_PIECES ? (kept ? launch_src<G, SRC_PIECES, SRC_PAIRS_KEPT> : launch_src<G, SRC_PIECES, SRC_PAIRS>)
-                                                  : (kept ? launch_src<G, SRC_RAW, SRC_PAIRS_KEPT> : launch_src<G, SRC_RAW, SRC_PAIRS>);
+            auto launch = pl.rest == SRC_FP32     ? launch_src<G, SRC_FP32, SRC_PAIRS>
+                          : pl.rest == SRC_PIECES ? launch_src<G, SRC_PIECES, SRC_PAIRS>
+                                                  : launch_src<G, SRC_RAW, SRC_PAIRS>;
             rc = launch(pl, p, x, w, ws, parts, y, stream);
-        } else {
-            return SCONV_EUNSUPPORTED;
         }
-    } else {
-        rc = launch_src<G, SRC_RAW>(pl, p, x, w, nullptr, parts, y, stream);
+    } else if constexpr (!G::BLOCK) {
+        if (pl.src == SRC_FP32) {
+            if constexpr (G::T == 9) rc = launch_src<G, SRC_FP32>(pl, p, x, w, p.wprep, parts, y, stream);
+        } else if (pl.src == SRC_PIECES) {
+            const int nch16 = pl.cfg.nch * G::CS, T = pl.cfg.T;
+            hipLaunchKernelGGL(piece_filters_kernel, dim3((unsigned)(nch16 * T), (unsigned)pl.cfg.kb32, (unsigned)p.G), dim3(64), 0, stream, p,
+                               pl.cfg.kb32, nch16, T, w, reinterpret_cast<u4*>(ws));
+            rc = launch_status();
+            if (rc) return rc;
+            rc = launch_src<G, SRC_PIECES>(pl, p, x, w, ws, parts, y, stream);
+        } else {
+            rc = launch_src<G, SRC_RAW>(pl, p, x, w, nullptr, parts, y, stream);
+        }
     }
-    if (rc || !pl.ntail) return rc;
-    hipLaunchKernelGGL(piece_sum_kernel<G::POOL>, dim3((unsigned)((G::BM * G::BN / 4 + 255) / 256), (unsigned)pl.ntail), dim3(256), 0, stream,
-                       p, pl.cfg, G::BM, G::BN, pl.ntail, parts, y);
-    return launch_status();
+    return rc || !pl.ntail ? rc : launch_sum<G>(pl, p, parts, y, stream);
 }
 
 template <class G>
@@ -1588,12 +1773,11 @@ int launch_taps(const Plan& pl, const Problem& p, bool, const float* x, const fl
         opted = pl.lds_bytes;
     }
     float* parts = pl.ntail ? split_scratch(stream) : nullptr;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(pl.cfg.whole + pl.ntail * pl.cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, pl.cfg, x, w, parts, y);
+    PieceCfg cfg = pl.cfg;
+    cfg.prepare(p, G::POOL, G::BN);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(cfg.whole + cfg.tail * cfg.nss)), dim3(G::NW * 64), pl.lds_bytes, stream, p, cfg, x, w, parts, y);
     const int rc = launch_status();
-    if (rc || !pl.ntail) return rc;
-    hipLaunchKernelGGL(piece_sum_kernel<G::POOL>, dim3((unsigned)((G::BM * G::BN / 4 + 255) / 256), (unsigned)pl.ntail), dim3(256), 0, stream,
-                       p, pl.cfg, G::BM, G::BN, pl.ntail, parts, y);
-    return launch_status();
+    return rc || !pl.ntail ? rc : launch_sum<G>(pl, p, parts, y, stream);
 }
 
 struct Candidate {
@@ -1606,7 +1790,7 @@ struct Candidate {
 
 bool always_apart(int) { return true; }
 
-// The geometries, for the table below and for the test that walks their plans.
+// The geometries, for the table below and for the test that walks their plans; the blocks.
 #define PIECE_GEOMETRIES(CAND, TAPS) \
     /* 32-filter and 32-window blocks of a wavefront, wavefronts along filters and windows, taps, 16-channel groups per chunk, pooled, */ \
     /* staging units, wavefronts per SIMD, small products apart */ \
@@ -1629,9 +1813,12 @@ bool always_apart(int) { return true; }
     TAPS("t7x96", 49, 1, 3, false, 2) \
     TAPS("tp5x128", 25, 1, 4, true, 2) \
     TAPS("tp7x96", 49, 1, 3, true, 2)
+#define PIECE_BLOCKS(CAND) \
+    CAND("a128x64x2", 1, 2, 4, 2, 9, 1, false, 1, 2, false) /* two tiles of a128x64 side by side */ \
+    CAND("u128x64x2", 1, 2, 4, 2, 9, 1, true, 1, 2, true)
 #define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, plan_pairs<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::apart},
 #define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, nullptr, launch_taps<TGeom<__VA_ARGS__>>, always_apart},
-const Candidate kCandidates[] = {PIECE_GEOMETRIES(CAND, TAPS)};
+const Candidate kCandidates[] = {PIECE_GEOMETRIES(CAND, TAPS) PIECE_BLOCKS(CAND)};
 
 }  // namespace
 
@@ -1655,23 +1842,21 @@ struct Choice {
 // Whether a plan keeps the small products' sums apart.
 bool apart_of(const Choice& c) { return c.cand->apart(c.plan.src); }
 
-// The form with pairs that may take the place of what a launch takes without them - the plan `three` (its sums apart or not), or its
-// family's kernel, `other` microseconds (negative: not known), where that is faster -, or -1.  Relative error against 64-bit sums (1e-7; the
-// same at 40 - 90 % zeros within a tenth): pairs 1.2 at 64 and 128 channels, 1.35 at 256, 1.5 at 512; kept 1.1 - 1.2 at any number.  Against three pieces in
-// one chain, 1.7 - 2.0, either is closer; against sums apart, 0.65 at 64 channels to 1.17 at 512 (less where tiles are split), kept ones from
-// 512 on while most tiles are whole; against the taps kernel kept ones there too, where a reported ratio is 50 % at most (512 / 640 channels @14x14, taps against
-// kept, 1.20 / 1.28 against 1.16 / 1.21 at 50 % zeros, 1.02 / 1.09 against 1.12 / 1.20 at 70, 0.79 / 0.82 against 1.02 / 1.10 at 90); against the other
-// families up to the zero ratio that piece_close gives, kept ones.
+// Whether pairs may take the place of what a launch takes without them - the plan `three` (its sums apart or not), or its family's kernel, `other`
+// microseconds (negative: not known), where that is faster.  Relative error against 64-bit sums (1e-7; the same at 40 - 90 % zeros within a tenth): pairs
+// 1.05 - 1.2 at any number of channels.  Against three pieces in one chain, 1.7 - 2.0, they are closer; against sums apart, 0.65 at 64 channels to 1.17 at
+// 512 (less where tiles are split), from 512 on while most tiles are whole; against the taps kernel there too, where a reported ratio is 50 % at
+// most (512 / 640 channels @14x14, taps against pairs, 1.20 / 1.28 against 1.16 / 1.21 at 50 % zeros, 1.02 / 1.09 against 1.12 / 1.20 at 70, 0.79 / 0.82
+// against 1.02 / 1.10 at 90); against the other families up to the zero ratio that piece_close gives.
 // A call without a zero ratio whose family is the vector kernel's stays as it was (see piece_first).
-int pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double other, float pairs_to)
+bool pairs_for(const Problem& p, const Plan* three, bool apart, bool taps, double other, float pairs_to)
 {
-    if (other == 0.0) return -1;
+    if (other == 0.0) return false;
     if (three && (other < 0.0 || three->cost < other)) {
-        if (!apart) return p.Cg < 512 ? SRC_PAIRS : SRC_PAIRS_KEPT;
         const bool level = p.Cg >= 512 && three->cfg.whole >= three->ntail;
-        return level && (!taps || (p.zhint >= 0.0f && p.zhint <= 0.5f)) ? SRC_PAIRS_KEPT : -1;
+        return !apart || (level && (!taps || (p.zhint >= 0.0f && p.zhint <= 0.5f)));
     }
-    return pairs_to > 1.0f || (p.zhint >= 0.0f && p.zhint <= pairs_to) ? SRC_PAIRS_KEPT : -1;
+    return pairs_to > 1.0f || (p.zhint >= 0.0f && p.zhint <= pairs_to);
 }
 
 // The cheapest plan by the model.  Walking the candidates takes 2 to 80 us by shape, as long as a small kernel runs, so plans are
@@ -1721,11 +1906,10 @@ const Choice& choose_plan(const Problem& p, bool pooled)
         }
         // the same with pairs, where it is no further from 64-bit sums
         const bool pinned_pairs = env_value("SCONV_PIECE_SRC") && atoi(env_value("SCONV_PIECE_SRC")) >= SRC_PAIRS;
-        const int form = pinned_pairs ? atoi(env_value("SCONV_PIECE_SRC")) : pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), out.cand && !out.cand->pairs, other, pairs_to);
-        if (form < 0) return;
+        if (!pinned_pairs && !pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), out.cand && !out.cand->pairs, other, pairs_to)) return;
         for (const Candidate& c : kCandidates) {
             if (!c.pairs || (pin && strcmp(pin, c.name) != 0)) continue;
-            Plan pl = c.pairs(p, pooled, form == SRC_PAIRS_KEPT);
+            Plan pl = c.pairs(p, pooled, true);
             if (pl.cost < 0.0 || (out.cand && pl.cost >= out.plan.cost)) continue;
             out.cand = &c;
             out.plan = pl;
@@ -1781,8 +1965,11 @@ bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
     const Choice& c = choose_plan(p, pooled);
     if (!c.cand) return false;
     // (pairs are cut from the filters as stored in prepared calls too)
-    const char* const forms[] = {"pieces", "prepared", "stored", p.wprep ? "prepared-f16" : "pieces-f16", p.wprep ? "prepared-f16k" : "pieces-f16k"};
-    if (c.plan.ntail)
+    const char* const forms[] = {"pieces", "prepared", "stored", p.wprep ? "prepared-f16k" : "pieces-f16k"};
+    const size_t n = strlen(c.cand->name);
+    if (!strcmp(c.cand->name + n - 2, "x2"))   // (a block: its tiles' geometry)
+        snprintf(out, out_size, "%.*s/%s/x2", (int)n - 2, c.cand->name, forms[c.plan.src]);
+    else if (c.plan.ntail)
         snprintf(out, out_size, "%s/%s/%d+%dx%d", c.cand->name, forms[c.plan.src], c.plan.cfg.whole, c.plan.ntail, c.plan.cfg.nss);
     else
         snprintf(out, out_size, "%s/%s", c.cand->name, forms[c.plan.src]);

@@ -275,8 +275,84 @@ static void pair_plans(const char* name)
     }
 }
 
+// The blocks: whole tiles only; every result computed once, from what is staged, in the LDS and the workspace there are.
+template <class G>
+static void block_plans(const char* name)
+{
+    constexpr int plane = G::PXMAX * 16;
+    EXPECT(G::BLOCK && G::PAIRS && G::NW == 8 && G::XU == 1 && G::PXMAX == 256, "%s: one staging unit a wavefront", name);
+    for (int unit = 0; unit < G::NW; ++unit)
+        EXPECT(unit % 2 * 2 * plane + (unit / 2 * 64 + 63) * 16 + plane + 16 <= 2 * 2 * plane, "%s: unit %d", name, unit);
+    // three buffers; flags, ranges from 64 on, and in the last 512 bytes the exponents of 128 filters
+    EXPECT(3 * 2 * 2 * plane + 64 + G::NW * 8 <= 3 * G::PAIR_BUF - 512 && G::BM * 4 <= 512, "%s: what the wavefronts tell each other", name);
+    int walked = 0, rests[3] = {0, 0, 0};
+    for (int tries = 0; tries < 40000 && walked < 80; ++tries) {
+        Problem p;
+        if (!random_problem(9, G::POOL, &p)) continue;
+        static const float some = 0.0f;
+        const bool prepares = tap_supported(p, G::POOL) && p.stride == 1;
+        if (walked % 4 == 3 && !prepares) continue;
+        p.wprep = walked % 4 == 3 ? &some : nullptr;
+        const size_t room = plan_workspace_bytes(p, G::POOL) / (walked % 2 ? 1 : (size_t)pick(1, 4));
+        split_scratch_given(room ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, room, true);
+        split_scratch_select(nullptr);
+        const Plan pl = plan_pairs<G>(p, G::POOL, true);
+        const size_t ws = usable_workspace(p, G::POOL);
+        split_scratch_given(nullptr, 0, false);
+        EXPECT(plan_geom<G>(p, G::POOL, false).cost < 0.0, "%s: pairs only", name);
+        if (pl.cost < 0.0) continue;
+        ++walked;
+        const PieceCfg& c = pl.cfg;
+        const int prows = G::POOL ? p.PH : p.OH, pcols = G::POOL ? p.PW : p.OW, HP = p.H + p.pad;
+        const int pitch = (G::POOL ? (c.TW - 1) * p.ps + 1 : c.TW - 1) * p.stride + 3;
+        HOLDS(pl.src == SRC_PAIRS && pl.ntail == 0 && c.tail == 0 && c.whole == c.ntiles * c.strips * c.kblocks * p.G);
+        HOLDS(c.px <= G::PXMAX && pl.lds_bytes >= 3 * (size_t)G::PAIR_BUF && pl.lds_bytes <= 160 * 1024 && pl.piece_bytes <= ws);
+        HOLDS((size_t)2 * (2 * c.cgb + G::SPARE) <= pl.lds_bytes && c.px * 48 <= c.cgb);   // what goes on from pieces
+        const size_t fragments = (size_t)p.G * c.kb32 * c.nch * 9;
+        HOLDS(pl.piece_bytes == pair_bytes(p.G, c.kb32, c.nch) + (pl.rest == SRC_PIECES ? fragments * 3072 : 0));
+        HOLDS(c.kb32 * 32 >= c.kblocks * 128 && (!p.wprep || c.kb32 == (p.Kg + 127) / 128 * 4) && c.nch * 16 >= p.Cg && (c.nch - 1) * 16 < p.Cg);
+        ++rests[pl.rest];
+        std::vector<unsigned char> seen((size_t)p.N * prows * pcols, 0);
+        for (int tile = 0; tile < c.ntiles; ++tile)
+            for (int strip = 0; strip < c.strips; ++strip) {
+                int r0 = 0;
+                for (int i = 0; i < 128 && tile * 128 + i < c.nrun; ++i) {
+                    const int P = tile * 128 + i, pp = G::POOL ? P >> 2 : P, q = pp / c.TW, n = q / prows, row = q - n * prows, wcol = pp - q * c.TW;
+                    const int oh = G::POOL ? row * p.ps + ((P & 3) >> 1) : row, ow = G::POOL ? wcol * p.ps + (P & 1) : wcol;
+                    if (i == 0) r0 = n * HP + oh * p.stride;
+                    const int first = (n * HP + oh * p.stride - r0) * pitch + ow * p.stride, last = first + 2 * pitch + 2;
+                    HOLDS(first >= 0 && last < c.px);
+                    if (n < p.N && wcol + strip * c.TW < pcols) ++seen[((size_t)n * prows + row) * pcols + wcol + strip * c.TW];
+                }
+            }
+        for (size_t i = 0; i < seen.size(); ++i)
+            if (seen[i] != (G::POOL ? 4 : 1)) {
+                HOLDS(false);
+                break;
+            }
+    }
+    EXPECT(walked >= 60 && rests[SRC_PIECES] >= 5 && rests[SRC_RAW] >= 3 && rests[SRC_FP32] >= 5, "%s: %d plans, pieces %d, stored %d, prepared %d", name, walked,
+           rests[SRC_PIECES], rests[SRC_RAW], rests[SRC_FP32]);
+}
+
+// Division by multiplication: every divisor's multiples and their neighbours below 2^30, and some numbers between.
+static void divisions()
+{
+    for (int i = 0; i < 4000; ++i) {
+        const int d = i < 1000 ? i + 1 : pick_log(1, (1 << 30) - 1.0);
+        FastDiv by;
+        by.by(d);
+        for (int j = 0; j < 50; ++j) {
+            const int n = j < 20 ? pick_log(1, (1 << 30) - 1.0) - 1 : (int)((long long)d * pick(0, ((1 << 30) - 1) / d)) - j % 2;
+            if (n >= 0) EXPECT(by.of(n) == n / d, "%d / %d", n, d);
+        }
+        EXPECT(by.of((1 << 30) - 1) == ((1 << 30) - 1) / d && by.of(0) == 0, "%d", d);
+    }
+}
+
 int main()
 {
+    divisions();
     strips_are_the_best_of_all(4000);
     plans_are_kept();
 #define WALK_PIECE(NAME, ...)                          \
@@ -287,6 +363,8 @@ int main()
 #define WALK_TAPS(NAME, ...) \
     plans<TGeom<__VA_ARGS__>>(NAME, plan_taps<TGeom<__VA_ARGS__>>, TGeom<__VA_ARGS__>::CS, TGeom<__VA_ARGS__>::PXMAX, TGeom<__VA_ARGS__>::FB, 1);
     PIECE_GEOMETRIES(WALK_PIECE, WALK_TAPS)
+#define WALK_BLOCK(NAME, ...) block_plans<PGeom<__VA_ARGS__>>(NAME);
+    PIECE_BLOCKS(WALK_BLOCK)
     if (failures) {
         fprintf(stderr, "%d expectation(s) failed\n", failures);
         return 1;

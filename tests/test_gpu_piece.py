@@ -554,6 +554,48 @@ def test_pairs_without_room_for_pieces(device, monkeypatch, shp, split, what, sr
         assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("what", ["integers", "plain", "bias", "scales", "element", "filter"])
+@pytest.mark.parametrize("geom,shp", [
+    ("a128x64x2", (1, 16, 8, 16, 128, 3, 3, 1, 1, 1, None)),      # one tile, one chunk
+    ("a128x64x2", (3, 48, 14, 13, 129, 3, 3, 1, 1, 1, None)),     # one filter in the last block, the last tile ragged, three chunks
+    ("a128x64x2", (2, 96, 9, 57, 192, 3, 3, 1, 1, 2, None)),      # grouped, half a filter block, column strips
+    ("a128x64x2", (1, 112, 28, 28, 40, 3, 3, 1, 1, 1, None)),     # 28 columns: as many positions as are staged
+    ("u128x64x2", (2, 64, 13, 15, 130, 3, 3, 1, 1, 1, (2, 2, 2))),
+])
+def test_blocks(device, monkeypatch, geom, shp, what, prepared):
+    """128 filters x 128 windows: edges of tiles, filters and chunks; scales that move, what pairs do not hold; within the bound of test_pairs."""
+    N, C, H, W, K, R, S, stride, pad, groups, pool = shp
+    _, x, w = workloads.make_random_case(428, *shp[:10], None, 0.6, what == "integers")
+    x, w = x.copy(), w.copy()
+    if what == "scales":
+        x = np.ldexp(x, (np.arange(C) // 16 * 11 - 33).astype(int)[None, :, None, None]).astype(np.float32)
+    elif what == "element":
+        x[0, C - 1, 2, 3] = 2.0 ** -30
+    elif what == "filter":
+        w[K // 2, 3, 1, 1] = 1e-20
+    xd, wd = to_dev(x), to_dev(w)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    _pin(monkeypatch, geom, None, "3")
+    name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool, True, prepared=prepared), pool is not None, ws.numel())
+    assert name == f"piece/model:{geom[:-2]}/{'prepared' if prepared else 'pieces'}-f16k/x2"
+    b = np.random.default_rng(9).normal(size=K).astype(np.float32) if what == "bias" and prepared else None
+    kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd, groups), bias=to_dev(b) if b is not None else None) if prepared else dict(ws=ws)
+    got = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw) if pool
+           else sconv.sconv_forward(xd, wd, stride, pad, groups, relu=False, **kw)).cpu().numpy().astype(np.float64)
+    ref, scale = oracle.conv(x, w, stride, pad, groups, relu=False)
+    if b is not None:
+        ref, scale = ref + b.astype(np.float64)[None, :, None, None], scale + np.abs(b.astype(np.float64))[None, :, None, None]
+    if pool:
+        p = torch.nn.functional.max_pool2d
+        ref = p(torch.from_numpy(np.maximum(ref, 0.0)), pool[:2], pool[2]).numpy()
+        scale = p(torch.from_numpy(scale), pool[:2], pool[2]).numpy()
+    if what == "integers":
+        assert np.array_equal(got, ref)
+    else:
+        assert (np.abs(got - ref) <= (C // groups * 9 + 7) * 2.0 ** -24 * scale).all()
+
+
 def _pairs_rows(monkeypatch, shp, x, w):
     """The window-row kernel, which skips zeros of the map."""
     for name in ("SCONV_PIECE_GEOM", "SCONV_PIECE_SRC", "SCONV_PIECE_SPLIT"):
