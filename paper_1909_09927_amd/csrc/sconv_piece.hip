@@ -130,27 +130,42 @@ constexpr int kUnpaired = -0x40000000;   // in the place of a filter's exponent:
 // Whether a scaled sum is Inf or NaN.
 __device__ __forceinline__ bool not_finite(float r) { return (__builtin_bit_cast(unsigned, r) & 0x7fffffffu) >= 0x7f800000u; }
 
-// Eight fp32 values times 2^24 as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every
-// remainder is exact) for all values below 2^104.
+// Two fp32 values times up as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every remainder is exact) for all
+// values below 2^104 at up = 2^24.
+// DOT: a remainder is one dot product with (-1, 0) or (0, -1) where taking the piece apart and subtracting are two instructions, 9 for a pair of
+// values instead of 13; the same bits.  Where the compiler places the cuts and three wavefronts a SIMD fill the waits of its two-address form, that is
+// ahead (filters as stored: 896 channels in 7 groups @14x14 at batch 32 89.8 -> 87.8 us); between fenced matrix instructions it is not (128 @56x56
+// stride 2 48.8 -> 50.3, 5x5 48 -> 128 @7x7 12.55 -> 12.74), nor at two wavefronts a SIMD (92 -> 100).  A piece that is Inf makes the other value's
+// remainders NaN as well: their sums, over the same windows or the same filter, are NaN as they are, and are summed again.  The constants
+// come from registers: as an inline operand -1.0 stands in the upper half whatever was written.
+template <bool DOT = false>
 __device__ __forceinline__ void split2(float a, float b, float up_a, float up_b, int i, u4 (&out)[3])
 {
+    unsigned of_lo = 0x0000bf80u, of_hi = 0xbf800000u;
+    if (DOT) asm("" : "+s"(of_lo), "+s"(of_hi));
+    auto rest_a = [&](bf2 piece, float v) {
+        return DOT ? __builtin_amdgcn_fdot2_f32_bf16(piece, __builtin_bit_cast(bf2, of_lo), v, false)
+                   : v - __builtin_bit_cast(float, __builtin_bit_cast(unsigned, piece) << 16);
+    };
+    auto rest_b = [&](bf2 piece, float v) {
+        return DOT ? __builtin_amdgcn_fdot2_f32_bf16(piece, __builtin_bit_cast(bf2, of_hi), v, false)
+                   : v - __builtin_bit_cast(float, __builtin_bit_cast(unsigned, piece) & 0xffff0000u);
+    };
     a *= up_a;
     b *= up_b;
-    const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
-    const float ra = a - __builtin_bit_cast(float, h << 16);
-    const float rb = b - __builtin_bit_cast(float, h & 0xffff0000u);
-    const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
-    const float sa = ra - __builtin_bit_cast(float, m << 16);
-    const float sb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
-    out[0][i] = h;
-    out[1][i] = m;
-    out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){sa, sb}, bf2));
+    const bf2 h = __builtin_convertvector((f2){a, b}, bf2);
+    const float ra = rest_a(h, a), rb = rest_b(h, b);
+    const bf2 m = __builtin_convertvector((f2){ra, rb}, bf2);
+    out[0][i] = __builtin_bit_cast(unsigned, h);
+    out[1][i] = __builtin_bit_cast(unsigned, m);
+    out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){rest_a(m, ra), rest_b(m, rb)}, bf2));
 }
 
+template <bool DOT = false>
 __device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
 {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], kUp, kUp, i, out);
+    for (int i = 0; i < 4; ++i) split2<DOT>(v[2 * i], v[2 * i + 1], kUp, kUp, i, out);
 }
 
 // Filters read as stored: a lane's reads are at raw_base (its filter's row, its half of a fragment's 16 channels) plus raw_step,
@@ -193,6 +208,8 @@ struct PGeom {
     // two tiles of 128 filters x 64 windows side by side, eight wavefronts, one workgroup a compute unit: see pair_sums
     static constexpr bool BLOCK = T == 9 && NW == 8;
     static constexpr bool PAIRS = T == 9 && MT == 1 && NT == 2 && WM == 4 && XU * WN == 2 && APART_ == POOL;   // has the form with pairs (a128x64, u128x64, the blocks)
+    // one chain on filters as stored: 168 registers, three wavefronts a SIMD (896 channels in 7 groups @14x14 at batch 32 92.0 -> 89.8 us)
+    static constexpr bool three(int src, int form) { return T == 9 && src == SRC_RAW && form == 0 && XU == 2 && MT * NT * NW == 8 && !apart(src); }
     static constexpr int PAIR_BUF = 2 * 2 * PXMAX * 16 + 256;   // LDS of one chunk as pairs, and a third of flags, ranges (from 64) and exponents (the last 512 bytes)
 };
 
@@ -508,7 +525,7 @@ __host__ __device__ inline size_t pair_bytes(int G, int kb32, int nch16) { retur
 
 // FORM: SRC_PAIRS (SRC: the filters' form where pairs do not do), or 0
 template <class G, int SRC, int FORM>
-__global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
+__global__ __launch_bounds__(G::NW * 64, G::three(SRC, FORM) ? 3 : G::OCC) void piece_kernel(Problem p, PieceCfg cfg, const float* __restrict__ x,
                                                               const float* __restrict__ w, const void* __restrict__ wp,
                                                               float* __restrict__ parts, float* __restrict__ y)
 {
@@ -661,7 +678,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
         auto stage = [&](int u, int part, unsigned char* buf, int ch, int after) {
             if (part < 4) {
                 const int left = p.Cg - (ch * CS * 16 + (u * NW + wave) % CG * 8) - 2 * part;
-                split2(xr[u][2 * part], xr[u][2 * part + 1], left > 0 ? kUp : 0.0f, left > 1 ? kUp : 0.0f, part, xf);
+                split2<G::three(SRC, FORM)>(xr[u][2 * part], xr[u][2 * part + 1], left > 0 ? kUp : 0.0f, left > 1 ? kUp : 0.0f, part, xf);
             } else if (part == 4) {
                 u4* d = reinterpret_cast<u4*>(buf + xst[u]);
                 d[0] = xf[0];
@@ -775,7 +792,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                     float v[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) v[j] = ar[slot][i][j][e];
-                    split8(v, a[i]);
+                    split8<G::three(SRC, FORM)>(v, a[i]);
                 }
             }
         };
@@ -858,7 +875,7 @@ __global__ __launch_bounds__(G::NW * 64, G::OCC) void piece_kernel(Problem p, Pi
                                 if (nx * CS * 16 + (u * NW + wave) % CG * 8 + j >= p.Cg) xr[u][j] = 0.0f;
 #pragma unroll
                     for (int u = 0; u < XU; ++u) {
-                        split8(xr[u], xf);
+                        split8<G::three(SRC, FORM)>(xr[u], xf);
                         stage(u, 4, nbuf, nx, nx2);
                     }
                 }
