@@ -52,6 +52,10 @@ int launch_maxpool(const Problem& p, const float* conv, float* y, hipStream_t st
 int launch_rows(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                 hipStream_t stream);
 
+// 1x1 layers of few filters on large maps (sconv_stream.hip), in the place of launch_pointwise's kernel where the first tells so.
+bool stream_supported(const Problem& p, const float* x, const float* w, const float* y);
+int launch_stream(const Problem& p, const float* x, const float* w, float* y, hipStream_t stream);
+
 // Element-stationary 3x3 / stride 1 / pad 1 kernel.  tap_supported tells whether it covers p.
 bool tap_supported(const Problem& p, bool pooled);
 int launch_tap(const Problem& p, bool pooled, const float* x, const float* w, float* y,

@@ -53,20 +53,15 @@
 #include <string.h>
 
 #include "sconv_internal.h"
+#include "sconv_piece_split.h"
 
 namespace sconv {
 
 namespace {
 
 
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
 // Division by a number that is known before the launch, of numbers below 2^30: with 2^l >= d (l >= 2) and m = ceil(2^(30+l) / d), m d exceeds 2^(30+l) by
 // less than 2^l, so n m / 2^(30+l) exceeds n / d by less than 1 / d.  A wavefront issues an instruction every eight clocks, and a division by a
@@ -118,8 +113,6 @@ struct PieceCfg {
 // Filters: cut into three pieces in the workspace; as prepared by the caller; as stored; cut into pairs in the workspace (pair_sums)
 enum { SRC_PIECES = 0, SRC_FP32 = 1, SRC_RAW = 2, SRC_PAIRS = 3 };
 
-constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;   // scale of an operand before it is cut; of a sum, afterwards
-
 template <int V>
 struct Const {
     static constexpr int value = V;
@@ -129,44 +122,6 @@ constexpr int kUnpaired = -0x40000000;   // in the place of a filter's exponent:
 
 // Whether a scaled sum is Inf or NaN.
 __device__ __forceinline__ bool not_finite(float r) { return (__builtin_bit_cast(unsigned, r) & 0x7fffffffu) >= 0x7f800000u; }
-
-// Two fp32 values times up as three bf16 pieces each: v = p0 + p1 + p2 exactly (24 bits = 3 x 8, every remainder is exact) for all
-// values below 2^104 at up = 2^24.
-// DOT: a remainder is one dot product with (-1, 0) or (0, -1) where taking the piece apart and subtracting are two instructions, 9 for a pair of
-// values instead of 13; the same bits.  Where the compiler places the cuts and three wavefronts a SIMD fill the waits of its two-address form, that is
-// ahead (filters as stored: 896 channels in 7 groups @14x14 at batch 32 89.8 -> 87.8 us); between fenced matrix instructions it is not (128 @56x56
-// stride 2 48.8 -> 50.3, 5x5 48 -> 128 @7x7 12.55 -> 12.74), nor at two wavefronts a SIMD (92 -> 100).  A piece that is Inf makes the other value's
-// remainders NaN as well: their sums, over the same windows or the same filter, are NaN as they are, and are summed again.  The constants
-// come from registers: as an inline operand -1.0 stands in the upper half whatever was written.
-template <bool DOT = false>
-__device__ __forceinline__ void split2(float a, float b, float up_a, float up_b, int i, u4 (&out)[3])
-{
-    unsigned of_lo = 0x0000bf80u, of_hi = 0xbf800000u;
-    if (DOT) asm("" : "+s"(of_lo), "+s"(of_hi));
-    auto rest_a = [&](bf2 piece, float v) {
-        return DOT ? __builtin_amdgcn_fdot2_f32_bf16(piece, __builtin_bit_cast(bf2, of_lo), v, false)
-                   : v - __builtin_bit_cast(float, __builtin_bit_cast(unsigned, piece) << 16);
-    };
-    auto rest_b = [&](bf2 piece, float v) {
-        return DOT ? __builtin_amdgcn_fdot2_f32_bf16(piece, __builtin_bit_cast(bf2, of_hi), v, false)
-                   : v - __builtin_bit_cast(float, __builtin_bit_cast(unsigned, piece) & 0xffff0000u);
-    };
-    a *= up_a;
-    b *= up_b;
-    const bf2 h = __builtin_convertvector((f2){a, b}, bf2);
-    const float ra = rest_a(h, a), rb = rest_b(h, b);
-    const bf2 m = __builtin_convertvector((f2){ra, rb}, bf2);
-    out[0][i] = __builtin_bit_cast(unsigned, h);
-    out[1][i] = __builtin_bit_cast(unsigned, m);
-    out[2][i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){rest_a(m, ra), rest_b(m, rb)}, bf2));
-}
-
-template <bool DOT = false>
-__device__ __forceinline__ void split8(const float (&v)[8], u4 (&out)[3])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split2<DOT>(v[2 * i], v[2 * i + 1], kUp, kUp, i, out);
-}
 
 // Filters read as stored: a lane's reads are at raw_base (its filter's row, its half of a fragment's 16 channels) plus raw_step,
 // bytes from the block's first filter, all of it in the vector offset, which the buffer's bounds check covers (a scalar offset it

@@ -423,6 +423,9 @@ int launch_pointwise(const Problem& p, bool pooled, const float* x, const float*
                      hipStream_t stream)
 {
     if (!pw_supported(p, pooled)) return SCONV_EUNSUPPORTED;
+    int nwv = 0, ncs = 0;
+    pinned_split("SCONV_PW_SPLIT", &nwv, &ncs);
+    if (!pooled && !nwv && !pinned_geom("SCONV_PW_GEOM") && stream_supported(p, x, w, y)) return launch_stream(p, x, w, y, stream);
     return pooled ? launch_pw<true>(p, x, w, y, stream) : launch_pw<false>(p, x, w, y, stream);
 }
 

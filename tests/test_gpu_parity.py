@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads
 import paper_1909_09927_amd as sconv
 from parity import check_encode, check_forward, check_pool_forward, to_dev
@@ -778,6 +779,51 @@ PW_SHAPES = [
     (1, 192, 30, 58, 40, 1, 1, 1, 0, 1, (2, 2, 2)),     # pooled tiles with ragged columns
     (2, 64, 5, 8, 64, 1, 1, 1, 0, 1, (2, 2, 2)),        # odd height: last row unpooled
 ]
+
+
+STREAM_SHAPES = [
+    (24, 64, 40, 41, 32, 1, 1, 1, 0, 1, None),      # 615 blocks of 64 positions, 32 filters
+    (25, 832, 40, 40, 1, 1, 1, 1, 0, 1, None),      # one filter, the most channels whose pieces fit LDS
+    (31, 64, 40, 41, 33, 1, 1, 1, 0, 1, None),      # a ragged last block, one filter in the second block of 32
+    (31, 384, 40, 40, 64, 1, 1, 1, 0, 1, None),     # the most channels of 64 filters
+    (22, 64, 80, 80, 20, 1, 1, 1, 0, 1, None),      # 2200 blocks: some wavefronts take two
+    (32, 128, 40, 39, 80, 1, 1, 1, 0, 2, None),     # grouped
+    (52, 64, 40, 40, 70, 1, 1, 1, 0, 1, None),      # more than 64 filters: two passes over the map
+    (1020, 64, 7, 8, 48, 1, 1, 1, 0, 1, None),      # blocks that span images
+    (1030, 64, 7, 7, 48, 1, 1, 1, 0, 1, None),      # an odd plane: not this kernel's
+]
+
+
+@pytest.mark.parametrize("shp", STREAM_SHAPES)
+def test_pointwise_streamed(device, shp):
+    """1x1 layers of few filters on large maps (sconv_stream.hip): integers exactly, random values, a bias; an input and an output that
+    are not aligned to two positions take the other kernel; Inf and elements past the pieces' range spoil the sums they are in and no others."""
+    layer, x, w = _mk(197, shp, integer=True)
+    check_forward(layer, x, w, relu=False, integer_exact=True)
+    layer, x, w = _mk(198, shp)
+    check_forward(layer, x, w, relu=True)
+    K, groups = shp[4], shp[9]
+    bias = np.linspace(-1.0, 1.0, K).astype(np.float32)
+    xd, wd = to_dev(x), to_dev(w)
+    plain = sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False)
+    with_bias = sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False, bias=to_dev(bias))
+    assert torch.equal(with_bias, plain + to_dev(bias)[None, :, None, None])
+    shifted = torch.empty(xd.numel() + 1, device="cuda")[1:].view(xd.shape)
+    shifted.copy_(xd)
+    out = torch.empty(plain.numel() + 1, device="cuda")[1:].view(plain.shape)
+    scale = oracle.conv(x, w, 1, 0, groups, relu=False)[1]
+    for y in (sconv.sconv_forward(shifted, wd, 1, 0, groups, relu=False), sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False, out=out)):
+        assert ((y - plain).abs().cpu().numpy() <= 2e-6 * scale).all()   # (two roundings of 2^-24 of at most sqrt(832) running sums each)
+    spoiled = xd.clone()
+    spoiled[0, 1, 2, 3] = float("inf")
+    spoiled[-1, 2, 3, 4] = 2.0 ** 120
+    y = sconv.sconv_forward(spoiled, wd, 1, 0, groups, relu=False)
+    touched = torch.zeros_like(y, dtype=torch.bool)
+    touched[0, :K // groups, 2, 3] = touched[-1, :K // groups, 3, 4] = True
+    assert ((y - plain).abs()[~touched].cpu().numpy() <= 2e-6 * scale[~touched.cpu().numpy()]).all()
+    assert torch.isinf(y[0, :K // groups, 2, 3]).all()
+    want = plain[-1, :K // groups, 3, 4] + 2.0 ** 120 * wd[:K // groups, 2, 0, 0]
+    assert torch.allclose(y[-1, :K // groups, 3, 4], want, rtol=1e-6)
 
 
 @pytest.mark.parametrize("split", [None, "8,2", "16,4"])
