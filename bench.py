@@ -44,6 +44,11 @@ FP32_MFMA_PEAK_TF = 157.3    # dense fp32 matrix instructions, published
 MFMA_VARIANTS = ("quad3x3", "quad1x1", "wide3x3", "gen", "piece")
 
 
+def on_pieces(plan: str) -> bool:
+    """Whether a plan's products run on the 16-bit matrix pipe: the piece kernels, and the 1x1 kernel that streams the map."""
+    return plan.startswith("piece/") or ":stream" in plan
+
+
 def piece_peak_tf(plan: str) -> float:
     """Piece kernel: the 16-bit matrix pipe's dense peak (published) over the products an fp32 one takes there - six of bf16 pieces, three of
     fp16 pairs.  A tuned plan names its geometry only: those that have the form with pairs are priced as if they ran it."""
@@ -331,13 +336,13 @@ def layer_record(dl: DeviceLayer, work: dict, ms: float) -> dict:
     t = ms * 1e-3
     t_hbm = work["alg_bytes"] / (HBM_PEAK_GBS * 1e9)
     # the pipe the plan runs on (the fp32 matrix and vector peaks are the same figure), as in the headline's roofline
-    t_pipe = work["nz_flops"] / ((piece_peak_tf(dl.plan) if dl.variant == "piece" else FP32_VECTOR_PEAK_TF) * 1e12)
+    t_pipe = work["nz_flops"] / ((piece_peak_tf(dl.plan) if on_pieces(dl.plan) else FP32_VECTOR_PEAK_TF) * 1e12)
     # what the plan really issues: a kernel that tests groups of g elements multiplies every element of a
     # group that holds a nonzero (independent zeros: a share z^g of the groups is skipped); the forms without
     # any test (geometry names ending in d, "dense") issue everything - the dense fallback on the matrix pipe
     g = SKIP_GRANULE.get(dl.variant, 1)
     geom = dl.plan.split("/")[1] if "/" in dl.plan else ""
-    dense_form = dl.variant == "piece" or dl.variant in MFMA_VARIANTS and (geom == "dense" or (geom.endswith("d") and geom != "kept"))
+    dense_form = on_pieces(dl.plan) or dl.variant in MFMA_VARIANTS and (geom == "dense" or (geom.endswith("d") and geom != "kept"))
     z = work["zero_ratio"]
     skipped = 0.0 if dense_form else (z if g == 1 else z ** g)
     issued = work["dense_flops"] * (1.0 - skipped) if g > 1 or dense_form else work["nz_flops"]
@@ -491,7 +496,7 @@ def run_headline(args) -> None:
         ach = wk["nz_flops"] / t / 1e12
         if r["variant"] in MFMA_VARIANTS:
             # products go through the matrix pipe (fp32, or bf16 pieces); algorithmic flops = nonzero multiply-adds
-            peak = piece_peak_tf(r["plan"]) if r["variant"] == "piece" else FP32_MFMA_PEAK_TF
+            peak = piece_peak_tf(r["plan"]) if on_pieces(r["plan"]) else FP32_MFMA_PEAK_TF
             roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": round(peak, 1), "unit": "TFLOP/s",
                     "frac": round(ach / peak, 4), "traffic": None,
                     "issued_dense_equiv_TFLOPs": round(wk["dense_flops"] / t / 1e12, 2)}

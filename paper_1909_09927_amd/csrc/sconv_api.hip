@@ -500,6 +500,7 @@ static bool piece_first(const Problem& p, bool pooled, Variant v)
 static bool describe_model(Variant v, const Problem& p, bool pooled, hipStream_t s, char* out, size_t out_size)
 {
     if (v == V_TAP) return describe_tap(p, pooled, s, out, out_size);
+    if (v == V_PW) return describe_pointwise(p, pooled, out, out_size);
     return v == V_PIECE && describe_piece(p, pooled, out, out_size);
 }
 

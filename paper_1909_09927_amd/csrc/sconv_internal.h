@@ -55,6 +55,8 @@ int launch_rows(const Problem& p, bool pooled, const float* x, const float* w, f
 // 1x1 layers of few filters on large maps (sconv_stream.hip), in the place of launch_pointwise's kernel where the first tells so.
 bool stream_supported(const Problem& p, const float* x, const float* w, const float* y);
 int launch_stream(const Problem& p, const float* x, const float* w, float* y, hipStream_t stream);
+// "stream" where launch_pointwise's calls run there (on operands aligned for it); false: on its own kernel.
+bool describe_pointwise(const Problem& p, bool pooled, char* out, size_t out_size);
 
 // Element-stationary 3x3 / stride 1 / pad 1 kernel.  tap_supported tells whether it covers p.
 bool tap_supported(const Problem& p, bool pooled);

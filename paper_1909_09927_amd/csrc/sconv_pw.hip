@@ -419,13 +419,26 @@ bool pw_supported(const Problem& p, bool pooled)
 
 const char* const* pw_geoms() { return kPwGeoms; }
 
+// Whether a call without a pinned plan runs on stream_kernel.
+static bool streams(const Problem& p, bool pooled, const float* x, const float* w, const float* y)
+{
+    int nwv = 0, ncs = 0;
+    pinned_split("SCONV_PW_SPLIT", &nwv, &ncs);
+    return !pooled && !nwv && !pinned_geom("SCONV_PW_GEOM") && stream_supported(p, x, w, y);
+}
+
+bool describe_pointwise(const Problem& p, bool pooled, char* out, size_t out_size)
+{
+    if (!pw_supported(p, pooled) || !streams(p, pooled, nullptr, nullptr, nullptr)) return false;
+    snprintf(out, out_size, "stream");
+    return true;
+}
+
 int launch_pointwise(const Problem& p, bool pooled, const float* x, const float* w, float* y,
                      hipStream_t stream)
 {
     if (!pw_supported(p, pooled)) return SCONV_EUNSUPPORTED;
-    int nwv = 0, ncs = 0;
-    pinned_split("SCONV_PW_SPLIT", &nwv, &ncs);
-    if (!pooled && !nwv && !pinned_geom("SCONV_PW_GEOM") && stream_supported(p, x, w, y)) return launch_stream(p, x, w, y, stream);
+    if (streams(p, pooled, x, w, y)) return launch_stream(p, x, w, y, stream);
     return pooled ? launch_pw<true>(p, x, w, y, stream) : launch_pw<false>(p, x, w, y, stream);
 }
 

@@ -25,7 +25,6 @@ namespace sconv {
 
 namespace {
 
-constexpr int KB = 64;    // filters per workgroup
 constexpr int TP = 64;    // positions per block
 constexpr int NW = 8;     // wavefronts
 

@@ -805,6 +805,8 @@ def test_pointwise_streamed(device, shp):
     K, groups = shp[4], shp[9]
     bias = np.linspace(-1.0, 1.0, K).astype(np.float32)
     xd, wd = to_dev(x), to_dev(w)
+    name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, 1, 0, groups, None, False))
+    assert name == ("quad1x1/model" if shp[2] * shp[3] % 2 else "quad1x1/model:stream")
     plain = sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False)
     with_bias = sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False, bias=to_dev(bias))
     assert torch.equal(with_bias, plain + to_dev(bias)[None, :, None, None])
