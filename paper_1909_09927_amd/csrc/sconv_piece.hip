@@ -63,18 +63,18 @@ namespace {
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
-// Division by a number that is known before the launch, of numbers below 2^30: with 2^l >= d (l >= 2) and m = ceil(2^(30+l) / d), m d exceeds 2^(30+l) by
-// less than 2^l, so n m / 2^(30+l) exceeds n / d by less than 1 / d.  A wavefront issues an instruction every eight clocks, and a division by a
+// Division by a number that is known before the launch, of numbers below 2^31: with 2^l >= d > 2^(l-1) (l >= 1) and m = ceil(2^(31+l) / d), m is below 2^32
+// and m d exceeds 2^(31+l) by less than 2^l, so n m / 2^(31+l) exceeds n / d by less than 1 / d.  A wavefront issues an instruction every eight clocks, and a division by a
 // register's value is some 35 of them: with the dozen that place a workgroup's tile and the dozen that place its results, and results stored one by one
 // behind their conditions and biases (18 000 clocks, now 5 000), a launch of one chunk took 17 us, now 10.
 struct FastDiv {
     unsigned m, s;       // (m == 0: by one)
     void by(int d)
     {
-        unsigned l = 2;
-        while ((1 << l) < d) ++l;
-        s = l - 2;
-        m = d == 1 ? 0 : (unsigned)(((1ull << (30 + l)) + d - 1) / d);
+        unsigned l = 1;
+        while ((1u << l) < (unsigned)d) ++l;
+        s = l - 1;
+        m = d == 1 ? 0 : (unsigned)(((1ull << (31 + l)) + d - 1) / d);
     }
     __host__ __device__ __forceinline__ int of(int n) const
     {
@@ -1372,7 +1372,9 @@ bool shape_ok(const Problem& p, bool pooled)
     if (pooled && (p.ph != 2 || p.pw != 2)) return false;
     const long long npos = pooled ? (long long)p.N * p.PH * p.PW * 4 : (long long)p.N * p.OH * p.OW;
     if (npos >= (1LL << 30)) return false;
-    return true;
+    // rows of the padded batch are numbered from its first one, and a tile stages fewer than 4096 (715 827 883 images of 1x1, padded by 2, at stride 3
+    // have 2^31; a wrapped number reads as a row of the padding)
+    return (long long)p.N * (p.H + p.pad) + 4096 < (1LL << 31);
 }
 
 // Staged positions of a tile of BN windows of a strip TW columns wide: the largest over the tiles (a tile's rows depend

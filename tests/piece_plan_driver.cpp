@@ -335,24 +335,42 @@ static void block_plans(const char* name)
            rests[SRC_PIECES], rests[SRC_RAW], rests[SRC_FP32]);
 }
 
-// Division by multiplication: every divisor's multiples and their neighbours below 2^30, and some numbers between.
+// Division by multiplication: every divisor's multiples and their neighbours below 2^31, and some numbers between.
 static void divisions()
 {
+    const int most = 0x7fffffff;
     for (int i = 0; i < 4000; ++i) {
-        const int d = i < 1000 ? i + 1 : pick_log(1, (1 << 30) - 1.0);
+        const int d = i < 1000 ? i + 1 : pick_log(1, most - 1.0);
         FastDiv by;
         by.by(d);
         for (int j = 0; j < 50; ++j) {
-            const int n = j < 20 ? pick_log(1, (1 << 30) - 1.0) - 1 : (int)((long long)d * pick(0, ((1 << 30) - 1) / d)) - j % 2;
-            if (n >= 0) EXPECT(by.of(n) == n / d, "%d / %d", n, d);
+            const int n = j < 20 ? pick_log(1, most - 1.0) - 1 : (int)((long long)d * pick(0, most / d - 1)) + d - j % 2;
+            EXPECT(by.of(n) == n / d, "%d / %d", n, d);
         }
-        EXPECT(by.of((1 << 30) - 1) == ((1 << 30) - 1) / d && by.of(0) == 0, "%d", d);
+        const int top = most / d * d;
+        EXPECT(by.of(most) == most / d && by.of(top) == most / d && by.of(top - 1) == (top - 1) / d && by.of(0) == 0, "%d", d);
+    }
+    FastDiv by;
+    by.by(63);
+    EXPECT(by.of(1108378718) == 1108378718 / 63, "17593312 and 62 / 63");
+}
+
+// Padded rows of the whole batch are numbered in 32 bits: layers with more are not the piece kernels'.
+static void rows_are_numbered()
+{
+    for (int N : {(1 << 29), 715827000, 715828000, (1 << 30) - 1}) {
+        const sconv_desc_t d = {N, 1, 1, 1, 1, 3, 3, 3, 2, 1, 0, 0, 0, 0};   // one result of three padded rows an image
+        Problem p;
+        EXPECT(fill_problem(&d, false, &p) == SCONV_OK && p.OH == 1 && p.OW == 1, "%d images", N);
+        const bool numbered = (long long)N * (p.H + p.pad) + 4096 < (1LL << 31);   // (a tile starts at one and stages fewer than 4096 more)
+        EXPECT(shape_ok(p, false) == numbered, "%d images", N);
     }
 }
 
 int main()
 {
     divisions();
+    rows_are_numbered();
     strips_are_the_best_of_all(4000);
     plans_are_kept();
 #define WALK_PIECE(NAME, ...)                          \
