@@ -220,12 +220,20 @@ bool stream_supported(const Problem& p, const float* x, const float* w, const fl
     if ((long long)p.N * p.C * p.H * p.W >= (1LL << 30) || (long long)p.N * p.H * p.W >= (1LL << 30)) return false;
     const long long images = (TP + p.H * p.W - 1) / (p.H * p.W) + 1;
     if (images * p.C * p.H * p.W >= (1LL << 29)) return false;                                          // a block's byte offsets in 32 bits
-    // Cutting the filters and one block's walk take 8 us (32 filters, 64 channels) to 25 (64, 384) however few blocks there are, so a launch has to
-    // have enough of them.  quad1x1 / here, 64 - 384 channels at 392, 613, 784, 1568 blocks: 32 filters 1.02 - 1.26, 1.10 - 1.51, 1.10 - 1.52, 1.41 - 1.62 times
-    // as fast; 64 filters 0.89 - 0.94, 1.02 - 1.10 (0.88 at 686 and 64 channels), 1.09 - 1.30, 1.13 - 1.35; more than 64, where every 64 have the map
-    // read again, 0.58 - 0.80, 0.79 - 0.97, 0.85 - 1.13, 1.08 - 1.22 (from 1125 on 0.98 - 1.22).
-    const long long blocks = ((long long)p.N * p.H * p.W + TP - 1) / TP;
-    return blocks >= (p.Kg <= 32 ? 600 : p.Kg <= 64 ? 768 : 1300);
+    // A pass - 64 filters of a group, or a group of up to 32 - cuts its filters and has at most one block to a wavefront up to 2048 blocks, however few
+    // there are, and multiplies zeros, which quad1x1 skips where neighbouring channels have them together: a launch has to have enough blocks.  quad1x1 / here,
+    // 64 - 384 channels, at 65 % zeros and at 95 % in clusters: 32 filters at 628 blocks 1.08 - 1.61 and 1.04 - 1.12 times as fast; 64 filters at
+    // 784 - 1372 1.02 - 1.35 and 0.89 - 1.05, at 1500 - 1536 (95 %) 0.87 - 1.0, at 1568, where quad1x1 begins another round, 1.30 - 1.53 and 1.08 - 1.13; 80 - 128
+    // filters (two passes) at 1323 1.05 - 1.29 and 0.92 - 0.96, at 1666 1.15 - 1.46 and 1.00 - 1.12; 160 - 512 at 1323 0.99 - 1.27 and 0.83 - 0.91, at 1666 1.11 - 1.44 and
+    // 0.95 - 1.07; 768 at 1813 (95 %) 0.93 - 0.95, at 3136 1.33 - 1.44 and 1.08.  So where the ratio is not known, or high, the lines are where clusters are level.
+    // Clusters of 80 - 85 %: 64 filters at 784 - 1372 1.03 - 1.14 from 128 channels on (0.95 - 1.06 at 64); 80 - 128 at 1323 0.97 - 1.09; 160 - 768 at 1323 0.91 -
+    // 1.10, at 1421 0.95 and more; 1024 at 1519 0.95.  Groups at 57 % in clusters: 128 -> 32 in 2 at 637 blocks 12.1 / 14.1 us, 256 -> 64 in 4 at 931 29.9 / 34.2.
+    const long long blocks = ((long long)p.N * p.H * p.W + TP - 1) / TP, passes = (long long)p.G * ((p.Kg + 63) / 64);
+    const bool known = p.G == 1 && p.zhint >= 0.0f && p.zhint <= 0.8f;
+    if (passes == 1 && p.Kg <= 32) return blocks >= 600;
+    if (passes == 1) return blocks >= (known && p.Cg >= 128 ? 768 : 1537);
+    if (known) return blocks >= (passes == 2 ? 1300 : passes <= 8 ? 1450 : 1650);
+    return blocks >= (passes == 2 ? 1600 : passes <= 8 ? 1800 : 2000);
 }
 
 int launch_stream(const Problem& p, const float* x, const float* w, float* y, hipStream_t stream)

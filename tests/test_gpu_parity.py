@@ -784,13 +784,13 @@ PW_SHAPES = [
 STREAM_SHAPES = [
     (24, 64, 40, 41, 32, 1, 1, 1, 0, 1, None),      # 615 blocks of 64 positions, 32 filters
     (25, 832, 40, 40, 1, 1, 1, 1, 0, 1, None),      # one filter, the most channels whose pieces fit LDS
-    (31, 64, 40, 41, 33, 1, 1, 1, 0, 1, None),      # a ragged last block, one filter in the second block of 32
-    (31, 384, 40, 40, 64, 1, 1, 1, 0, 1, None),     # the most channels of 64 filters
+    (61, 64, 40, 41, 33, 1, 1, 1, 0, 1, None),      # a ragged last block, one filter in the second block of 32
+    (62, 384, 40, 40, 64, 1, 1, 1, 0, 1, None),     # the most channels of 64 filters, the fewest blocks
     (22, 64, 80, 80, 20, 1, 1, 1, 0, 1, None),      # 2200 blocks: some wavefronts take two
-    (32, 128, 40, 39, 80, 1, 1, 1, 0, 2, None),     # grouped
-    (52, 64, 40, 40, 70, 1, 1, 1, 0, 1, None),      # more than 64 filters: two passes over the map
-    (1020, 64, 7, 8, 48, 1, 1, 1, 0, 1, None),      # blocks that span images
-    (1030, 64, 7, 7, 48, 1, 1, 1, 0, 1, None),      # an odd plane: not this kernel's
+    (66, 128, 40, 39, 80, 1, 1, 1, 0, 2, None),     # grouped
+    (64, 64, 40, 40, 70, 1, 1, 1, 0, 1, None),      # more than 64 filters: two passes over the map
+    (1757, 64, 7, 8, 48, 1, 1, 1, 0, 1, None),      # blocks that span images
+    (2010, 64, 7, 7, 48, 1, 1, 1, 0, 1, None),      # an odd plane: not this kernel's
 ]
 
 

@@ -535,3 +535,32 @@ def test_dims_of_a_call_are_the_librarys():
             continue
         assert sconv._call_dims(d, N, C, H, W, K, R, S, stride, pad, groups, pool) == want
     assert 500 < refused < 3500   # both sides are met
+
+
+@pytest.mark.parametrize("shp,groups,ratio,streams", [
+    ((10, 64, 64, 62, 32), 1, None, True),       # 620 blocks of 64 positions, 32 filters: one pass over the map
+    ((9, 64, 64, 62, 32), 1, None, False),       # 558
+    ((13, 128, 56, 56, 32), 2, 0.57, False),     # groups are passes: 637 blocks, 14.1 us against quad1x1's 12.1
+    ((4, 256, 122, 122, 64), 4, None, False),    # 931 blocks, 34.2 against 29.9
+    ((38, 128, 56, 56, 32), 2, None, True),      # 1862
+    ((28, 128, 56, 56, 64), 1, None, False),     # 64 filters, 1372 blocks: 18.6 against 17.5 at 95 % zeros in clusters
+    ((28, 128, 56, 56, 64), 1, 0.7, True),       # 1.15 times as fast at 65 %
+    ((28, 64, 56, 56, 64), 1, 0.7, False),       # 64 channels: level
+    ((6, 64, 128, 128, 64), 1, None, False),     # 1536: 13.9 against 12.8 at 95 % in clusters
+    ((32, 256, 56, 56, 64), 1, None, True),      # 1568
+    ((27, 64, 56, 56, 512), 1, None, False),     # eight passes, 1323 blocks: 84.1 against 71.3 at 95 % in clusters, 84.9 against 79.5 at 95 %
+    ((27, 64, 56, 56, 512), 1, 0.65, False),
+    ((30, 64, 56, 56, 512), 1, 0.65, True),      # 1470
+    ((30, 64, 56, 56, 512), 1, 0.9, False),
+    ((31, 64, 56, 56, 1024), 1, 0.8, False),     # sixteen passes, 1519: 188.8 against 178.8 at 80 % in clusters
+    ((34, 64, 56, 56, 96), 1, None, True),       # two passes, 1666
+    ((34, 64, 56, 56, 160), 1, None, False),
+    ((38, 64, 56, 56, 512), 1, None, True),      # 1862
+    ((37, 64, 56, 56, 768), 1, None, False),     # twelve passes, 1813: 152.7 against 142.5
+    ((41, 64, 56, 56, 768), 1, None, True),      # 2009
+])
+def test_streamed_pointwise_layers(shp, groups, ratio, streams):
+    """1x1 layers are streamed only where that is ahead at any zero ratio the call can have."""
+    N, C, H, W, K = shp
+    d = sconv.make_desc(N, C, H, W, K, 1, 1, 1, 0, groups, relu=True, zero_ratio=ratio)
+    assert sconv.sconv_launch_name(d) == ("quad1x1/model:stream" if streams else "quad1x1/model")
