@@ -162,6 +162,7 @@ struct PGeom {
     static constexpr bool apart(int src) { return APART_ || (NT == 2 && (src == SRC_FP32 || src == SRC_PAIRS)); }
     // two tiles of 128 filters x 64 windows side by side, eight wavefronts, one workgroup a compute unit: see pair_sums
     static constexpr bool BLOCK = T == 9 && NW == 8;
+    static constexpr const char* tiles = !BLOCK ? nullptr : POOL ? "u128x64" : "a128x64";
     static constexpr bool PAIRS = T == 9 && MT == 1 && NT == 2 && WM == 4 && XU * WN == 2 && APART_ == POOL;   // has the form with pairs (a128x64, u128x64, the blocks)
     // one chain on filters as stored: 168 registers, three wavefronts a SIMD (896 channels in 7 groups @14x14 at batch 32 92.0 -> 89.8 us)
     static constexpr bool three(int src, int form) { return T == 9 && src == SRC_RAW && form == 0 && XU == 2 && MT * NT * NW == 8 && !apart(src); }
@@ -1760,6 +1761,7 @@ struct Candidate {
     Plan (*pairs)(const Problem&, bool, bool);
     int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
     bool (*apart)(int);
+    const char* tiles;   // a block's tiles; null: no block
 };
 
 bool always_apart(int) { return true; }
@@ -1790,8 +1792,8 @@ bool always_apart(int) { return true; }
 #define PIECE_BLOCKS(CAND) \
     CAND("a128x64x2", 1, 2, 4, 2, 9, 1, false, 1, 2, false) /* two tiles of a128x64 side by side */ \
     CAND("u128x64x2", 1, 2, 4, 2, 9, 1, true, 1, 2, true)
-#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, plan_pairs<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::apart},
-#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, nullptr, launch_taps<TGeom<__VA_ARGS__>>, always_apart},
+#define CAND(NAME, ...) {NAME, plan_geom<PGeom<__VA_ARGS__>>, plan_pairs<PGeom<__VA_ARGS__>>, launch_plan<PGeom<__VA_ARGS__>>, PGeom<__VA_ARGS__>::apart, PGeom<__VA_ARGS__>::tiles},
+#define TAPS(NAME, ...) {NAME, plan_taps<TGeom<__VA_ARGS__>>, nullptr, launch_taps<TGeom<__VA_ARGS__>>, always_apart, nullptr},
 const Candidate kCandidates[] = {PIECE_GEOMETRIES(CAND, TAPS) PIECE_BLOCKS(CAND)};
 
 }  // namespace
@@ -1815,6 +1817,11 @@ struct Choice {
 
 // Whether a plan keeps the small products' sums apart.
 bool apart_of(const Choice& c) { return c.cand->apart(c.plan.src); }
+
+// Whether the last round of a block's launch would leave three fifths of the compute units idle.  Its tiles one by one, two to a unit, fill twice as many:
+// of 290 layers on blocks, 21 with at most 102 in the last of up to three rounds took 0.78 - 0.98 of the blocks' time that way (median 0.91), where the model has them
+// level, and the others 0.89 and more (median 1.06); 11 with so many in the fourth 0.95 - 1.05.
+bool idle_end(const Plan& block) { return block.cfg.whole <= 3 * 256 && (block.cfg.whole - 1) % 256 < 102; }
 
 // Whether pairs may take the place of what a launch takes without them - the plan `three` (its sums apart or not), or its family's kernel, `other`
 // microseconds (negative: not known), where that is faster.  Relative error against 64-bit sums (1e-7; the same at 40 - 90 % zeros within a tenth): pairs
@@ -1888,6 +1895,18 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             out.cand = &c;
             out.plan = pl;
         }
+        if (out.cand && out.cand->tiles && !pin && idle_end(out.plan)) {
+            const double modelled = out.plan.cost;
+            for (const Candidate& c : kCandidates) {
+                if (strcmp(c.name, out.cand->tiles) != 0) continue;
+                const Plan pl = c.pairs(p, pooled, true);
+                if (pl.cost < 0.0) break;
+                out.cand = &c;
+                out.plan = pl;
+                out.plan.cost = modelled;
+                break;
+            }
+        }
     };
     if ((pin && !tuned) || env_value("SCONV_PIECE_SPLIT") || env_value("SCONV_PIECE_SRC")) {
         walk(pinned);
@@ -1940,9 +1959,8 @@ bool describe_piece(const Problem& p, bool pooled, char* out, size_t out_size)
     if (!c.cand) return false;
     // (pairs are cut from the filters as stored in prepared calls too)
     const char* const forms[] = {"pieces", "prepared", "stored", p.wprep ? "prepared-f16k" : "pieces-f16k"};
-    const size_t n = strlen(c.cand->name);
-    if (!strcmp(c.cand->name + n - 2, "x2"))   // (a block: its tiles' geometry)
-        snprintf(out, out_size, "%.*s/%s/x2", (int)n - 2, c.cand->name, forms[c.plan.src]);
+    if (c.cand->tiles)
+        snprintf(out, out_size, "%s/%s/x2", c.cand->tiles, forms[c.plan.src]);
     else if (c.plan.ntail)
         snprintf(out, out_size, "%s/%s/%d+%dx%d", c.cand->name, forms[c.plan.src], c.plan.cfg.whole, c.plan.ntail, c.plan.cfg.nss);
     else

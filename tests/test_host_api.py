@@ -564,3 +564,19 @@ def test_streamed_pointwise_layers(shp, groups, ratio, streams):
     N, C, H, W, K = shp
     d = sconv.make_desc(N, C, H, W, K, 1, 1, 1, 0, groups, relu=True, zero_ratio=ratio)
     assert sconv.sconv_launch_name(d) == ("quad1x1/model:stream" if streams else "quad1x1/model")
+
+
+@pytest.mark.parametrize("shp,groups,pool,ratio,block", [
+    ((3, 264, 44, 44, 256), 2, (2, 2, 2), 0.52, False),    # 92 blocks on 256 compute units: 29.8 us, its tiles 24.5
+    ((2, 670, 32, 32, 768), 2, None, None, False),         # 96: 54.9 and 45.4
+    ((15, 456, 36, 36, 288), 2, (2, 2, 2), 0.64, False),   # two rounds and 96: 128.1 and 114.6
+    ((13, 944, 19, 19, 32), 2, (2, 2, 2), None, False),    # 66: 68.1 and 53.4
+    ((8, 256, 56, 56, 256), 1, None, 0.6, True),           # a round and 136 of 392
+    ((24, 305, 116, 116, 80), 1, None, 0.64, True),        # many rounds
+])
+def test_blocks_fill_their_last_round(shp, groups, pool, ratio, block):
+    """Blocks of two tiles whose last round would leave most compute units idle run as the tiles they consist of."""
+    N, C, H, W, K = shp
+    d = sconv.make_desc(N, C, H, W, K, 3, 3, 1, 1, groups, pool, True, zero_ratio=ratio)
+    name = sconv.sconv_launch_name(d, pool is not None, sconv.sconv_workspace_size(d, pool is not None))
+    assert name.startswith("piece/model:" + ("u" if pool else "a") + "128x64/pieces-f16k") and name.endswith("/x2") == block, name
