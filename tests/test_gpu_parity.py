@@ -813,7 +813,8 @@ def test_pointwise_streamed(device, shp):
     shifted = torch.empty(xd.numel() + 1, device="cuda")[1:].view(xd.shape)
     shifted.copy_(xd)
     out = torch.empty(plain.numel() + 1, device="cuda")[1:].view(plain.shape)
-    scale = oracle.conv(x, w, 1, 0, groups, relu=False)[1]
+    ref, scale = oracle.conv(x, w, 1, 0, groups, relu=False)
+    assert np.linalg.norm(plain.cpu().numpy() - ref) <= 3e-7 * np.linalg.norm(ref)   # measured 0.4e-7 to 0.9e-7, 1.1e-7 on the other kernel
     for y in (sconv.sconv_forward(shifted, wd, 1, 0, groups, relu=False), sconv.sconv_forward(xd, wd, 1, 0, groups, relu=False, out=out)):
         assert ((y - plain).abs().cpu().numpy() <= 2e-6 * scale).all()   # (two roundings of 2^-24 of at most sqrt(832) running sums each)
     spoiled = xd.clone()
@@ -826,6 +827,41 @@ def test_pointwise_streamed(device, shp):
     assert torch.isinf(y[0, :K // groups, 2, 3]).all()
     want = plain[-1, :K // groups, 3, 4] + 2.0 ** 120 * wd[:K // groups, 2, 0, 0]
     assert torch.allclose(y[-1, :K // groups, 3, 4], want, rtol=1e-6)
+
+
+@pytest.mark.parametrize("bias,relu", [(False, False), (True, True)])
+@pytest.mark.parametrize("what", ["nan", "inf weight", "nan weight", "huge weight", "subnormal", "small weights"])
+@pytest.mark.parametrize("shp", [STREAM_SHAPES[0], STREAM_SHAPES[2], STREAM_SHAPES[5]])
+def test_pointwise_streamed_operands_of_any_size(device, monkeypatch, shp, what, bias, relu):
+    """What the pieces' range does not hold, in the map or in a filter that all wavefronts share: the same results are Inf or NaN as in the window-row
+    kernel, which skips zeros of the map, and all others are as close as fp32 sums are (two kernels, each off by C / groups roundings at most)."""
+    _, x, w = _mk(199, shp)
+    x, w = x.astype(np.float64), w.astype(np.float64)
+    N, C, H, W, K, groups = *shp[:5], shp[9]
+    if what == "nan":
+        x[N // 2, 5, 3, 4] = np.nan
+    elif what == "inf weight":
+        w[K - 1, 7] = np.inf
+    elif what == "nan weight":
+        w[0, 7] = np.nan
+    elif what == "huge weight":          # past what is cut into pieces; its sums are ordinary numbers
+        w[K // 2, 3] = 2.0 ** 110
+    elif what == "subnormal":
+        x, w = np.ldexp(x, -135), np.ldexp(w, 60)
+    else:
+        x, w = np.ldexp(x, 60), np.ldexp(w, -135)
+    xd, wd = to_dev(x.astype(np.float32)), to_dev(w.astype(np.float32))
+    kw = dict(relu=relu, bias=to_dev(np.linspace(-1.0, 1.0, K).astype(np.float32)) if bias else None)
+    assert sconv.sconv_launch_name(sconv.desc_for(xd, wd, 1, 0, groups, None, relu)) == "quad1x1/model:stream"
+    got = sconv.sconv_forward(xd, wd, 1, 0, groups, **kw)
+    monkeypatch.setenv("SCONV_VARIANT", "rows")
+    want = sconv.sconv_forward(xd, wd, 1, 0, groups, **kw)
+    finite = torch.isfinite(want)
+    assert torch.equal(torch.isfinite(got), finite) and torch.equal(got[~finite].nan_to_num(7.0), want[~finite].nan_to_num(7.0))
+    assert finite.all() == (what != "inf weight" and (relu or "nan" not in what))   # (ReLU of NaN is 0)
+    scale = sconv.sconv_forward(xd.nan_to_num(0.0).abs(), wd.nan_to_num(0.0, 0.0, 0.0).abs(), 1, 0, groups, **dict(kw, relu=False, bias=kw["bias"].abs() if bias else None))
+    bound = 2.0 * (C // groups + 4) * 2.0 ** -24 * scale + 8 * 2.0 ** -149
+    assert ((got - want).abs() <= bound)[finite].all()
 
 
 @pytest.mark.parametrize("split", [None, "8,2", "16,4"])

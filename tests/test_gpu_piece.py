@@ -1,6 +1,8 @@
 """The matrix kernel on bf16 pieces (SCONV_VARIANT=piece): every geometry at the edges of its tiles, whole and split
 along the channels, from every form of the filters; integer inputs exact, the others within the parity bar and as close
 to the 64-bit sums as an fp32 sum of the same length; non-finite and tiny values as the fp32 kernels treat them."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -368,14 +370,18 @@ PAIRS = [
 ]
 
 
-def _pairs_call(monkeypatch, geom, split, src, shp, x, w, relu=False, prepared=False):
+def _pairs_call(monkeypatch, geom, split, shp, x, w, relu=False, prepared=False):
+    """split "x2": blocks of two of the geometry's tiles."""
     N, C, H, W, K, R, S, stride, pad, groups, pool = shp
     xd, wd = to_dev(x), to_dev(w)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
-    _pin(monkeypatch, geom, split, src)
+    block = split == "x2"
+    _pin(monkeypatch, geom + "x2" if block else geom, None if block else split, "3")
     kw = dict(ws=ws, wprep=sconv.sconv_filter_prep(wd, groups)) if prepared else dict(ws=ws)
     name = sconv.sconv_launch_name(sconv.desc_for(xd, wd, stride, pad, groups, pool, True, prepared=prepared), pool is not None, ws.numel())
-    assert name.startswith(f"piece/model:{geom}/{'prepared' if prepared else 'pieces'}-f16{'k' if src == '4' else ''}")
+    slices = ("/x2" if block else r"(/\d+\+\d+x\d+)?" if split is None else "" if split.endswith(",1,1") else
+              r"/{}\+\d+x{}".format(*split.split(",")[::2]))
+    assert re.fullmatch(f"piece/model:{geom}/{'prepared' if prepared else 'pieces'}-f16k{slices}", name), name
     y = (sconv.sconv_pool_forward(xd, wd, pool, stride, pad, groups, **kw) if pool else sconv.sconv_forward(xd, wd, stride, pad, groups, relu, **kw))
     return y.cpu().numpy().astype(np.float64)
 
@@ -390,15 +396,14 @@ def _reference(shp, x, w):
     return ref, scale
 
 
-@pytest.mark.parametrize("src", ["3", "4"])     # pairs; pairs with the running sums' errors kept
-@pytest.mark.parametrize("geom,shp,split", PAIRS)
-def test_pairs(device, monkeypatch, geom, shp, split, src):
+@pytest.mark.parametrize("geom,shp,split", PAIRS + [(geom, shp, "x2") for geom, shp, _ in PAIRS])
+def test_pairs(device, monkeypatch, geom, shp, split):
     """Tile edges, remainders, splits: integers exact; the others within what fp32 sums of the same length may be off by, and within
     5e-7 in all (measured 1e-7 to 1.5e-7)."""
     N, C, H, W, K, R, S, stride, pad, groups, pool = shp
     for integer in (False, True):
         _, x, w = workloads.make_random_case(420, N, C, H, W, K, R, S, stride, pad, groups, pool, 0.6, integer)
-        got = _pairs_call(monkeypatch, geom, split, src, shp, x, w)
+        got = _pairs_call(monkeypatch, geom, split, shp, x, w)
         ref, scale = _reference(shp, x, w)
         if integer:
             assert np.array_equal(got, ref)
@@ -408,10 +413,10 @@ def test_pairs(device, monkeypatch, geom, shp, split, src):
             assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("split", [None, "x2"])
 @pytest.mark.parametrize("what", ["images", "channels up", "channels down", "late", "small among large", "subnormal", "huge", "small weights", "filters",
                                   "weight range", "inf", "nan", "inf weight"])
-def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src):
+def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, split):
     """The scale of a pair follows the chunks; what no scale holds is summed from three pieces: as close as ever, element by element."""
     shp = (6, 64, 6, 7, 140, 3, 3, 1, 1, 1, None)
     _, x, w = workloads.make_random_case(421, *shp[:10], None, 0.6)
@@ -446,7 +451,7 @@ def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src
     else:
         w[77, 3, 1, 1] = -np.inf
     x, w = x.astype(np.float32), w.astype(np.float32)
-    got = _pairs_call(monkeypatch, "a128x64", None, src, shp, x, w)
+    got = _pairs_call(monkeypatch, "a128x64", split, shp, x, w)
     bad = ~np.isfinite(_pairs_rows(monkeypatch, shp, x, w))
     xf, wf = np.where(np.isfinite(x), x, 0), np.where(np.isfinite(w), w, 0)
     ref, scale = _reference(shp, xf, wf)
@@ -454,10 +459,10 @@ def test_pairs_hold_maps_and_filters_of_any_range(device, monkeypatch, what, src
     assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[~bad].all()
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
-@pytest.mark.parametrize("split,pool", [("0,1,1", None), ("0,1,2", None), ("0,1,1", (2, 2, 2)), ("0,1,2", (2, 2, 2))])
+@pytest.mark.parametrize("split", ["0,1,1", "0,1,2", "x2"])
+@pytest.mark.parametrize("pool", [None, (2, 2, 2)])
 @pytest.mark.parametrize("up_x,up_w", [(-62, -62), (-76, -50), (-30, -96), (-99, -27), (55, 55), (104, 54), (54, 104)])
-def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch, up_x, up_w, split, pool, src):
+def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch, up_x, up_w, split, pool):
     """What undoes the two scales is far outside fp32's range where the results are ordinary numbers: sums of 2^-126 and more, windows of
     zeros, and, where the large elements overflow, the windows that hold small ones against small weights."""
     shp = (6, 64, 6, 7, 140, 3, 3, 1, 1, 1, pool)
@@ -470,7 +475,7 @@ def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch,
         w[:, 1::2] = np.ldexp(w[:, 1::2], -24)
         x, w = np.where(np.abs(x) < 2.0 ** -24.5, 0, x), np.where(np.abs(w) < 2.0 ** -28, 2.0 ** -28, w)
     x, w = np.ldexp(x, up_x).astype(np.float32), np.ldexp(w, up_w).astype(np.float32)
-    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, src, shp, x, w)
+    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, shp, x, w)
     ref, scale = _reference(shp, x, w)
     assert np.abs(ref).max() > 2.0 ** -126 and not ref[2 if pool else 3, :, 0 if pool else 3].any()
     fits = scale < 2.0 ** 126
@@ -478,24 +483,23 @@ def test_pairs_of_maps_and_filters_both_small_or_both_large(device, monkeypatch,
     assert (np.abs(got - ref) <= (64 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149)[fits].all()
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
-@pytest.mark.parametrize("split", ["0,1,1", "0,1,2"])
+@pytest.mark.parametrize("split", ["0,1,1", "0,1,2", "x2"])
 @pytest.mark.parametrize("step", [40, -40, 11, -11])
-def test_pairs_of_chunks_whose_scales_keep_moving(device, monkeypatch, step, split, src):
+def test_pairs_of_chunks_whose_scales_keep_moving(device, monkeypatch, step, split):
     """Chunks that are each 2^step of the one before: windows that hold elements of the first one only keep their sums."""
     shp = (6, 96, 6, 7, 140, 3, 3, 1, 1, 1, None)
     _, x, w = workloads.make_random_case(424, *shp[:10], None, 0.6)
     x[0, 16:] = 0
     x[3, :80] = 0
     x = np.ldexp(x, (np.arange(96) // 16 * step - 2.5 * step).astype(int)[None, :, None, None]).astype(np.float32)
-    got = _pairs_call(monkeypatch, "a128x64", split, src, shp, x, w)
+    got = _pairs_call(monkeypatch, "a128x64", split, shp, x, w)
     ref, scale = _reference(shp, x, w)
     assert (np.abs(got - ref) <= (96 * 9 + 6) * 2.0 ** -24 * scale + 4 * 2.0 ** -149).all()
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
+@pytest.mark.parametrize("split", [None, "x2"])
 @pytest.mark.parametrize("spread_x,spread_w", [(0, 0), (26, 0), (0, 26), (26, 26), (0, 29), (29, 0)])
-def test_pairs_hold_every_single_product(device, monkeypatch, spread_x, spread_w, src):
+def test_pairs_hold_every_single_product(device, monkeypatch, spread_x, spread_w, split):
     """One nonzero element a window, so nothing averages: its product with any weight, over the range that pairs hold (26 octaves) and just
     past it.  A value is held to 2^-23 of itself and the product left out is 2^-22; a fp32 rounding or two of the result besides."""
     shp = (2, 32, 12, 15, 140, 3, 3, 1, 1, 1, None)
@@ -505,17 +509,16 @@ def test_pairs_hold_every_single_product(device, monkeypatch, spread_x, spread_w
     c = rng.integers(0, 32, (2, 4, 5))
     x[at[0], c, at[1], at[2]] = rng.uniform(1, 2, c.shape) * np.exp2(-rng.integers(0, spread_x + 1, c.shape))
     x, w = x.astype(np.float32), w.astype(np.float32)
-    got = _pairs_call(monkeypatch, "a128x64", None, src, shp, x, w)
+    got = _pairs_call(monkeypatch, "a128x64", split, shp, x, w)
     ref, scale = _reference(shp, x, w)
     assert (scale > 0).all()
     assert (np.abs(got - ref) <= (2.0 ** -22 + 2 * 2.0 ** -23 + 2 * 2.0 ** -24) * scale).all()
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
 @pytest.mark.parametrize("prepared", [False, True])
-@pytest.mark.parametrize("split,pool", [("0,1,1", None), ("2,1,2", None), ("0,1,1", (2, 2, 2))])
+@pytest.mark.parametrize("split,pool", [("0,1,1", None), ("2,1,2", None), ("x2", None), ("0,1,1", (2, 2, 2)), ("x2", (2, 2, 2))])
 @pytest.mark.parametrize("what", [0, 1, 3, 5, "every", "filter", "filters"])
-def test_tiles_go_on_from_three_pieces(device, monkeypatch, what, split, pool, prepared, src):
+def test_tiles_go_on_from_three_pieces(device, monkeypatch, what, split, pool, prepared):
     """One element that pairs do not hold, in chunk `what` (or in every one): the chunks before it from pairs, it and those after it from
     three pieces, of either form of the filters.  A filter that pairs do not hold: its whole block from pieces."""
     shp = (4, 96, 6, 7, 140, 3, 3, 1, 1, 1, pool)
@@ -528,16 +531,16 @@ def test_tiles_go_on_from_three_pieces(device, monkeypatch, what, split, pool, p
     else:
         for c in range(96) if what == "every" else (16 * what + 3,):
             x[1, c, 2, 3] = 2.0 ** -30
-    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, src, shp, x, w, prepared=prepared)
+    got = _pairs_call(monkeypatch, "u128x64" if pool else "a128x64", split, shp, x, w, prepared=prepared)
     ref, scale = _reference(shp, x, w)
     assert (np.abs(got - ref) <= (96 * 9 + 6) * 2.0 ** -24 * scale).all()
     assert np.linalg.norm(got - ref) <= 2e-7 * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("src", ["3", "4"])
 @pytest.mark.parametrize("what", ["integers", "plain", "element", "filter"])
-@pytest.mark.parametrize("shp,split", [((1, 1840, 5, 5, 130, 3, 3, 1, 1, 1, None), "0,1,1"), ((1, 64, 13, 21, 40, 3, 3, 1, 2, 1, None), "0,1,2")])
-def test_pairs_without_room_for_pieces(device, monkeypatch, shp, split, what, src):
+@pytest.mark.parametrize("shp,split", [((1, 1840, 5, 5, 130, 3, 3, 1, 1, 1, None), "0,1,1"), ((1, 64, 13, 21, 40, 3, 3, 1, 2, 1, None), "0,1,2"),
+                                       ((1, 1840, 5, 5, 130, 3, 3, 1, 1, 1, None), "x2"), ((1, 64, 13, 21, 40, 3, 3, 1, 2, 1, None), "x2")])
+def test_pairs_without_room_for_pieces(device, monkeypatch, shp, split, what):
     """Pairs alone fill the workspace, so what they do not hold is summed from the filters as stored; 1840 channels: one filter in LDS, not two."""
     _, x, w = workloads.make_random_case(427, *shp[:10], None, 0.6, what == "integers")
     x, w = x.copy(), w.copy()
@@ -545,7 +548,7 @@ def test_pairs_without_room_for_pieces(device, monkeypatch, shp, split, what, sr
         x[0, 40, 2, 3] = 2.0 ** -30
     elif what == "filter":
         w[17, 20, 1, 1] = 1e-20
-    got = _pairs_call(monkeypatch, "a128x64", split, src, shp, x, w)
+    got = _pairs_call(monkeypatch, "a128x64", split, shp, x, w)
     ref, scale = _reference(shp, x, w)
     if what == "integers":
         assert np.array_equal(got, ref)
@@ -594,6 +597,7 @@ def test_blocks(device, monkeypatch, geom, shp, what, prepared):
         assert np.array_equal(got, ref)
     else:
         assert (np.abs(got - ref) <= (C // groups * 9 + 7) * 2.0 ** -24 * scale).all()
+        assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)   # as in test_pairs
 
 
 def _pairs_rows(monkeypatch, shp, x, w):
