@@ -1600,7 +1600,7 @@ Plan plan_geom(const Problem& p, bool pooled, bool close)
 
 // The form with pairs of geometries that have it.
 template <class G>
-Plan plan_pairs(const Problem& p, bool pooled, bool)
+Plan plan_pairs(const Problem& p, bool pooled)
 {
     Plan pl;
     if constexpr (G::PAIRS) {
@@ -1758,7 +1758,7 @@ int launch_taps(const Plan& pl, const Problem& p, bool, const float* x, const fl
 struct Candidate {
     const char* name;
     Plan (*plan)(const Problem&, bool, bool);
-    Plan (*pairs)(const Problem&, bool, bool);
+    Plan (*pairs)(const Problem&, bool);
     int (*launch)(const Plan&, const Problem&, bool, const float*, const float*, float*, hipStream_t);
     bool (*apart)(int);
     const char* tiles;   // a block's tiles; null: no block
@@ -1890,7 +1890,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
         if (!pinned_pairs && !pairs_for(p, out.cand ? &out.plan : nullptr, out.cand && apart_of(out), out.cand && !out.cand->pairs, other, pairs_to)) return;
         for (const Candidate& c : kCandidates) {
             if (!c.pairs || (pin && strcmp(pin, c.name) != 0)) continue;
-            Plan pl = c.pairs(p, pooled, true);
+            Plan pl = c.pairs(p, pooled);
             if (pl.cost < 0.0 || (out.cand && pl.cost >= out.plan.cost)) continue;
             out.cand = &c;
             out.plan = pl;
@@ -1899,7 +1899,7 @@ const Choice& choose_plan(const Problem& p, bool pooled)
             const double modelled = out.plan.cost;
             for (const Candidate& c : kCandidates) {
                 if (strcmp(c.name, out.cand->tiles) != 0) continue;
-                const Plan pl = c.pairs(p, pooled, true);
+                const Plan pl = c.pairs(p, pooled);
                 if (pl.cost < 0.0) break;
                 out.cand = &c;
                 out.plan = pl;

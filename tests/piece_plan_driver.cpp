@@ -271,7 +271,7 @@ static void pair_plans(const char* name)
         for (int unit = 0; unit < G::XU * G::NW; ++unit)
             EXPECT(unit % 2 * 2 * plane + (unit / 2 * 64 + 63) * 16 + plane + 16 <= 2 * 2 * plane, "%s: unit %d", name, unit);
         EXPECT(2 * 2 * plane + 64 + G::NW * 8 <= G::PAIR_BUF && G::NW * 4 <= 64 && G::NW == 4, "%s: words and ranges of the wavefronts", name);
-        plans<G>(name, plan_pairs<G>, G::CS, G::PXMAX, 2 * G::SPARE, 2, G::PAIR_BUF);
+        plans<G>(name, [](const Problem& p, bool pooled, bool) { return plan_pairs<G>(p, pooled); }, G::CS, G::PXMAX, 2 * G::SPARE, 2, G::PAIR_BUF);
     }
 }
 
@@ -296,7 +296,7 @@ static void block_plans(const char* name)
         const size_t room = plan_workspace_bytes(p, G::POOL) / (walked % 2 ? 1 : (size_t)pick(1, 4));
         split_scratch_given(room ? reinterpret_cast<void*>(uintptr_t(256)) : nullptr, room, true);
         split_scratch_select(nullptr);
-        const Plan pl = plan_pairs<G>(p, G::POOL, true);
+        const Plan pl = plan_pairs<G>(p, G::POOL);
         const size_t ws = usable_workspace(p, G::POOL);
         split_scratch_given(nullptr, 0, false);
         EXPECT(plan_geom<G>(p, G::POOL, false).cost < 0.0, "%s: pairs only", name);
