@@ -61,11 +61,13 @@ def piece_peak_tf(plan: str) -> float:
 # run measures - the line names its source, and prints null when the plan that ran is not in the table.
 MEASURED_TRAFFIC = {
     ("quad3x3/q32t7d/8x4", "vgg-256x56", 8): (54.8e6 + 25.9e6, "profiles/quad3x3_vgg-256x56_n8.txt"),
-    # the launches of a piece plan together: filters cut into pairs and pieces, the product kernel, the sum of its split tiles
-    **{(plan, "vgg-256x56", 8): (73.8e6 + 37.6e6, "profiles/piece_counters.txt")
-       for plan in ("piece/model:a128x64/pieces-f16/768+16x8/kept", "piece/model:a128x64/pieces-f16/768+16x8", "piece/a128x64/4x1")},
-    **{(plan, "vgg-512x28", 8): (147.6e6 + 50.7e6, "profiles/piece_counters.txt")
-       for plan in ("piece/model:a128x64/pieces-f16k/256+136x3/kept", "piece/model:a128x64/pieces-f16k/256+136x3", "piece/a128x64/4x1")},
+    # the launches of a piece plan together: filters cut into pairs and pieces, the product kernel, the sum of its split tiles.  (A tuned plan of blocks names
+    # all of it; one of single tiles leaves their split open.)
+    **{(plan, layer, 8): (read + written, "profiles/piece_counters.txt")
+       for layer, plans, read, written in (
+           ("vgg-256x56", ("model:a128x64/pieces-f16k/x2", "a128x64x2/4x1"), 81.8e6, 34.1e6), ("vgg-256x56", ("model:a128x64/pieces-f16k/768+16x8",), 72.8e6, 37.3e6),
+           ("vgg-512x28", ("model:a128x64/pieces-f16k/x2", "a128x64x2/4x1"), 83.9e6, 37.5e6), ("vgg-512x28", ("model:a128x64/pieces-f16k/256+136x3",), 148.8e6, 50.5e6))
+       for name in plans for plan in (f"piece/{name}", f"piece/{name}/kept")},
 }
 # elements per zero test of the kernels that skip whole groups (1: every zero element is skipped)
 SKIP_GRANULE = {"rows": 1, "tap3x3": 1, "quad3x3": 6, "quad1x1": 32, "wide3x3": 16, "gen": 16}

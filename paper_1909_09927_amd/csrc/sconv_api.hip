@@ -377,7 +377,7 @@ static Variant choose(const Problem& p, bool pooled, bool have_ws = false, PlanP
 // on), 75 (gen).  quad1x1: 6.6 + gf * 10.2, and what the piece kernel stores on top of its model at 0.15 us/MB, which 1x1 layers are too
 // short to hide (plain calls, quad1x1 / piece kernel: 512 -> 256 @28x28 at batch 16 43.9 / 35.3 us, 512 -> 2048 @7x7 at batch 32 51.1 /
 // 46.1, but 64 -> 256 @56x56 at batch 32 53.8 / 59.5, 1024 -> 256 @14x14 45.4 / 51.1, 256 -> 256 @28x28 at batch 8 17.0 / 18.6, 128 -> 256
-// 11.9 / 14.1).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
+// 11.9 / 14.1; where launch_pointwise streams the map, sconv_stream.hip, it takes 0.5 - 0.97 of the fit, which the choice does not know).  A launch of few tiles takes as long as one workgroup's walk over the channels where nothing
 // splits it: without a workspace 41 us for 256 channels on the vector kernel (23 on the taps kernel), 8 + 0.029 per column on
 // gen (48 channels of 5x5 43 us against 13, 64 of 7x7 98 against 25), 0.27 per channel on wide3x3.
 // Caller holds g_lock and has selected the stream's workspace.

@@ -238,8 +238,8 @@ __host__ __device__ inline float power_of_two(int e) { return __builtin_bit_cast
 // a product needs is asked for two taps ahead (p0) and one (p1), across the chunk's end too: a chunk has one barrier, six taps before the next one's
 // first staging, and three buffers, so that nobody waits in it for what was just asked for.  512 @28x28 at batch 62: 688 -> 618 us.
 // Blocks (PGeom::BLOCK, 128 filters x 128 windows, eight wavefronts) read the filters once for two wavefronts - on different SIMDs, side by side: the
-// second finds them in the L1 (L2 reads 61 -> 39 million; on the same SIMD they drift apart and it does not) - and stage a quarter less of the map:
-// 568 us, 1.21 PFLOP/s of fp16 products at 1.9 GHz, 51 clocks an instruction; without filter loads, map loads, bank conflicts and folding 46.
+// second finds them in the L1 (L2 reads 9.3 -> 5.1 million at batch 8; on the same SIMD they drift apart and it does not) - and stage a quarter less of the map:
+// 568 us, 1.21 PFLOP/s of fp16 products at 1.7 GHz, a matrix instruction of 32 clocks every 48 (profiles/piece_counters.txt).
 // Measured and dropped: 64 x 64 a wavefront, one to a SIMD (667 us: half of what fits a matrix instruction's time can be issued there), wavefront priorities by progress (level).
 // The map's pairs are scaled by a power of two, 2^sigma, that stays while the chunks' elements fit it (Range of what the workgroup
 // stages, one chunk ahead), the filters' by one per filter.  Where a chunk holds a nonzero element 2^27 below its largest, or a filter such a
